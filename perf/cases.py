@@ -1,0 +1,244 @@
+"""What the performance of this framework is measured on.
+
+A case is one call of a user's program: a decode step of a stack of layers, the compression of a prompt,
+a chunk of several queries, a stand-alone rebuild, a decode step with the swap loop. Sizes are those of the
+named workloads (kvr_synth.WORKLOADS) and tests, or generic ones between and around them. All of it goes
+through `LayerState` and the functions of `binding`.
+
+A decode step advances its state by one token. After `steps` tokens the state goes back to the compressed
+prompt, as in a server that answers one request after another over the same prompt; that is a few copies
+once every `steps` passes.
+"""
+import math
+
+import torch
+
+from paper_2512_17917_amd import binding as kvr
+from paper_2512_17917_amd.state import LayerState
+
+D = 128
+MAX_SWAPS = 4          # per unit and step, the swap loop's bound in the benchmark
+REPLACE_RATE = 1.1     # the paper's
+
+
+def _case(kind, context, batch, q_heads, kv_heads, *, budget=0.25, rows=3, layers=1, dtype="bf16", slack=0,
+          steps=128, n_q=1, side=True, name=None):
+    c = dict(kind=kind, context=context, batch=batch, q_heads=q_heads, kv_heads=kv_heads, budget=budget, rows=rows,
+             layers=layers, dtype=dtype, slack=slack, steps=steps, n_q=n_q, side=side)
+    return c if name is None else dict(c, name=name)
+
+
+def listed():
+    return [
+        # one short sequence, one head, float32: the smallest call there is, all latency
+        _case("decode", 2048, 1, 1, 1, budget=0.10, dtype="f32", name="decode-2k-f32"),
+        # a batch of summarisation-length prompts at a 10 % budget, one layer
+        _case("decode", 2048, 8, 32, 8, budget=0.10, name="decode-2k-b8"),
+        # full multi-head attention (one query head per kv head), ragged length, evictions in bulk (Slack)
+        _case("decode", 5003, 3, 32, 32, layers=4, slack=3, side=False, name="decode-5k-mha"),
+        # one long-document request: few units per layer, several layers
+        _case("decode", 32768, 1, 32, 8, layers=6, name="decode-32k-b1"),
+        # the throughput configuration: 16 long-document requests decoded together
+        _case("decode", 32768, 16, 32, 8, layers=3, name="decode-32k-b16"),
+        # 8 query heads per kv head, odd batch and length
+        _case("decode", 16411, 5, 64, 8, layers=2, name="decode-16k-gqa8"),
+        # the longest contexts: with the paper's three sketch rows, and with four
+        _case("decode", 131072, 2, 32, 8, layers=1, steps=64, name="decode-131k-r3"),
+        _case("decode", 131072, 4, 32, 8, layers=1, rows=4, steps=64, name="decode-131k-r4"),
+        # decode with the swap loop: a change of topic makes tokens in the sketch important again
+        _case("swap", 32768, 4, 32, 8, layers=1, steps=64, name="swap-32k-b4"),
+        # a prompt's cache compressed after its prefill (whose scores are given)
+        _case("compress", 32768, 8, 32, 8, name="compress-32k-b8"),
+        # a chunk of drafted tokens attends at once
+        _case("multi", 32768, 8, 32, 8, n_q=4, name="multi-32k-b8-q4"),
+        # all tokens in the sketch rebuilt into memory
+        _case("reconstruct", 32768, 4, 32, 8, name="reconstruct-32k-b4"),
+    ]
+
+
+def draw(rng):
+    kind = rng.choice(["decode", "decode", "decode", "decode", "swap", "compress", "multi", "reconstruct"])
+    context = int(math.exp(rng.uniform(math.log(700), math.log(131072))))
+    q_heads, kv_heads = rng.choice([(32, 8), (32, 8), (32, 32), (16, 8), (64, 8), (8, 2)])
+    g = q_heads // kv_heads
+    most = max(1, min(16, 2_000_000 // (context * kv_heads)))
+    batch = max(1, min(most, int(math.exp(rng.uniform(0, math.log(most + 1))))))
+    dtype = "f32" if kind in ("decode", "swap", "compress") and context < 8192 and rng.random() < 0.15 else "bf16"
+    rows = rng.choice([3, 3, 3, 4])
+    layers = rng.choice([1, 2]) if kind == "decode" and (g < 8 or rows == 3) else 1
+    return _case(kind, context, batch, q_heads, kv_heads, budget=rng.choice([0.10, 0.20, 0.25, 0.30]), rows=rows,
+                 layers=layers, dtype=dtype,
+                 slack=rng.choice([0, 0, 3]) if kind == "decode" else 0, steps=64,
+                 n_q=rng.choice([n for n in (2, 4, 8) if n * g <= 16]) if kind == "multi" else 1,
+                 side=rng.random() < 0.75)
+
+
+# ---------------------------------------------------------------------------
+def _sizes(c):
+    """(slots per sketch row, retained tokens, Recent, Candidate, Vague tokens): the split of the workloads."""
+    m = int(math.floor(c["budget"] * c["context"] + 1e-9))
+    w = max(1, (m // 10) // c["rows"])
+    kept = m - c["rows"] * w
+    return w, kept, kept // 2, kept - kept // 2, c["context"] - kept
+
+
+def _gen(seed, *ids):
+    s = seed
+    for i in ids:
+        s = (s * 1000003 + i + 1) % (1 << 62)
+    return torch.Generator(device="cuda").manual_seed(s)
+
+
+def _rows(c, g, n, needles, u, outliers):
+    """Keys and values [batch, kv heads, n, D]: normal, four channels eight times as large, some keys near u."""
+    dt = torch.float32 if c["dtype"] == "f32" else torch.bfloat16
+    shape = (c["batch"], c["kv_heads"], n, D)
+    k = torch.randn(shape, generator=g, device="cuda", dtype=dt)
+    v = torch.randn(shape, generator=g, device="cuda", dtype=dt)
+    k[..., outliers] *= 8
+    v[..., outliers] *= 8
+    if needles:
+        at = torch.randint(0, n, (needles,), generator=g, device="cuda")
+        e = torch.randn((c["batch"], c["kv_heads"], needles, D), generator=g, device="cuda")
+        e = torch.nn.functional.normalize(e, dim=-1)
+        k[:, :, at] = (math.sqrt(D) * (0.9 * u.unsqueeze(2) + math.sqrt(0.19) * e)).to(dt)
+    return k, v
+
+
+def _prompt(c, seed, layer):
+    """What a model's prefill leaves for one layer: keys, values, cumulative scores and the topic of the queries."""
+    g = _gen(seed, layer)
+    u = torch.randn((c["batch"], c["kv_heads"], D), generator=g, device="cuda")
+    u = torch.nn.functional.normalize(u, dim=-1)
+    outliers = torch.randperm(D, generator=g, device="cuda")[:4]
+    k, v = _rows(c, g, c["context"], 16, u, outliers)
+    # every query of the prompt and every head of the group left one unit of probability somewhere
+    scores = torch.randn((c["batch"], c["kv_heads"], c["context"]), generator=g, device="cuda").exp_()
+    scores *= c["q_heads"] // c["kv_heads"]
+    return g, u, outliers, k, v, scores
+
+
+def _queries(c, g, u, n):
+    """q [n, batch, q heads, D] near the topic."""
+    dt = torch.float32 if c["dtype"] == "f32" else torch.bfloat16
+    x = u.repeat_interleave(c["q_heads"] // c["kv_heads"], dim=1)
+    x = x + 0.3 * torch.randn((n, c["batch"], c["q_heads"], D), generator=g, device="cuda")
+    return (math.sqrt(D) * torch.nn.functional.normalize(x, dim=-1)).to(dt)
+
+
+def _desc(c, seed, layer):
+    w = _sizes(c)[0]
+    return kvr.make_desc(c["batch"], c["q_heads"], c["kv_heads"], c["rows"], w,
+                         torch.float32 if c["dtype"] == "f32" else torch.bfloat16, seed=seed * 64 + layer)
+
+
+_KEPT = ("k_ret", "v_ret", "ret_pos", "scores", "sketch_k", "sketch_v", "n_vague")
+
+
+def prepare(case, seed):
+    c = case
+    _, _, n_recent, n_cand, n_vague = _sizes(c)
+    s = {"kind": c["kind"], "steps": c["steps"], "t": 0, "layers": [], "tokens": []}
+    if c["kind"] == "compress":
+        g, u, _, k, v, scores = _prompt(c, seed, 0)
+        s.update(desc=_desc(c, seed, 0), k=k, v=v, q=_queries(c, g, u, 1)[0], scores=scores, n_recent=n_recent,
+                 n_cand=n_cand)
+        return s
+    side = kvr.SideStream() if c["side"] else None
+    n_ctx = torch.zeros(c["batch"], dtype=torch.int32, device="cuda")
+    ws_attend = ws_encode = None
+    for layer in range(c["layers"]):
+        g, u, outliers, k, v, scores = _prompt(c, seed, layer)
+        q = _queries(c, g, u, c["steps"])
+        ls, _ = LayerState.from_prefill(_desc(c, seed, layer), k, v, q[0], n_recent=n_recent, k_candidate=n_cand,
+                                        max_new_tokens=c["steps"], init_scores=scores, ws_attend=ws_attend,
+                                        ws_encode=ws_encode, n_ctx=n_ctx, slack=c["slack"], side=side)
+        ws_attend, ws_encode = ls.ws_attend, ls.ws_encode
+        del k, v
+        if c["kind"] == "swap":
+            # enough tokens of the sketch for a swap in every step have become the most important ones
+            at = torch.randperm(n_vague, generator=g, device="cuda")[:2 * MAX_SWAPS * c["steps"]]
+            pos = ls.vague_pos[:, :, at].long()
+            up = torch.rand(pos.shape, generator=g, device="cuda") + 2.0
+            ls.scores.scatter_(2, pos, up * ls.scores.amax(dim=2, keepdim=True))
+        s["layers"].append(ls)
+        if c["kind"] in ("decode", "swap"):
+            kn, vn = _rows(c, g, c["steps"], 0, u, outliers)
+            s["tokens"].append([x.contiguous() for x in (kn.permute(2, 0, 1, 3), vn.permute(2, 0, 1, 3), q)])
+    if c["kind"] in ("decode", "swap"):
+        s["n_ctx"] = n_ctx
+        s["prompt"] = [{f: getattr(ls, f).clone() for f in _KEPT} for ls in s["layers"]]
+        s["n_ctx0"], s["r_size0"] = n_ctx.clone(), s["layers"][0].r_size
+    ls = s["layers"][0]
+    if c["kind"] == "multi":
+        s["n_q"] = c["n_q"]
+        s["q"] = _queries(c, g, u, c["n_q"]).permute(1, 0, 2, 3).contiguous()
+        n = kvr.kvr_attend_multi_workspace_size(ls.desc, c["n_q"], ls.ret_cap, ls.vague_cap)
+        s["ws"] = torch.empty(max(n, 256), dtype=torch.uint8, device="cuda")
+    if c["kind"] == "reconstruct":
+        s["k_out"] = torch.zeros(c["batch"], c["kv_heads"], ls.vague_cap, D, dtype=ls.dtype, device="cuda")
+        s["v_out"] = torch.zeros_like(s["k_out"])
+    return s
+
+
+def _back_to_prompt(s):
+    for ls, kept in zip(s["layers"], s["prompt"]):
+        for f, x in kept.items():
+            getattr(ls, f).copy_(x)
+        ls.r_size = s["r_size0"]
+    s["n_ctx"].copy_(s["n_ctx0"])
+    s["t"] = 0
+
+
+def _whole(ls):
+    return [ls.out, ls.scores, ls.ret_pos, ls.vague_pos, ls.n_vague, ls.sketch_k, ls.sketch_v, ls.k_ret, ls.v_ret]
+
+
+def run(state):
+    s = state
+    if s["kind"] in ("decode", "swap"):
+        if s["t"] == s["steps"]:
+            _back_to_prompt(s)
+        t = s["t"]
+        s["t"] = t + 1
+        more = {"replace_rate": REPLACE_RATE, "max_swaps": MAX_SWAPS} if s["kind"] == "swap" else {}
+        s["n_ctx"].add_(1)
+        for ls, (kn, vn, q) in zip(s["layers"], s["tokens"]):
+            ls.decode_step(kn[t], vn[t], q[t], bump_n_ctx=False, **more)
+        return [_whole(ls) for ls in s["layers"]]
+    if s["kind"] == "compress":
+        ls, _ = LayerState.from_prefill(s["desc"], s["k"], s["v"], s["q"], n_recent=s["n_recent"],
+                                        k_candidate=s["n_cand"], max_new_tokens=s["steps"], init_scores=s["scores"])
+        return _whole(ls)[1:]
+    ls = s["layers"][0]
+    if s["kind"] == "multi":
+        return [ls.attend_multi(s["q"], s["n_q"], ws=s["ws"]), ls.scores]
+    kvr.kvr_reconstruct(ls.desc, ls.sketch_k, ls.sketch_v, ls.vague_pos, ls.n_vague, ls.vague_cap, s["k_out"],
+                        s["v_out"])
+    return [s["k_out"], s["v_out"]]
+
+
+def work(case):
+    """Per unit and layer: retained rows, the sketch, the list of the tokens in it and the cumulative scores (read and
+    written), q and the output; two products with every token's key and value per query."""
+    c = case
+    w, kept, _, _, vague = _sizes(c)
+    e = 4 if c["dtype"] == "f32" else 2
+    units, g, n = c["batch"] * c["kv_heads"], c["q_heads"] // c["kv_heads"], c["context"]
+    sketch = 2 * c["rows"] * w * D * e
+    if c["kind"] == "compress":      # every prompt row and score read, kept rows, scores, sketch and lists written
+        per = 2 * n * D * e + 2 * kept * D * e + sketch + 8 * n + 4 * n
+        return {"bytes": units * per, "flops": units * 2 * vague * c["rows"] * D}
+    if c["kind"] == "reconstruct":   # the sketch and the list read, rebuilt rows written
+        return {"bytes": units * (2 * vague * D * e + sketch + 4 * vague), "flops": units * 2 * vague * c["rows"] * D}
+    per = 2 * kept * D * e + sketch + 4 * vague + 8 * n + c["n_q"] * g * D * (e + 4)
+    return {"bytes": c["layers"] * units * per, "flops": c["layers"] * units * c["n_q"] * g * 4 * n * D}
+
+
+def tolerance(case):
+    """Lists, sketch and rows come out bit for bit. Outputs and scores are sums in float32 of float32 or bfloat16
+    products and of exponentials of such sums: against the same attention in float64 over the rebuilt rows the largest
+    relative error of any of these cases is 2.6e-6 and the largest single one 8.3e-5 of the root mean square."""
+    if case["kind"] in ("compress", "reconstruct"):
+        return "exact"
+    return {"rel": 1e-5, "max": 4e-4, "differ": 0.0}
