@@ -98,7 +98,7 @@ def _rows(c, g, n, needles, u, outliers):
     k[..., outliers] *= 8
     v[..., outliers] *= 8
     if needles:
-        at = torch.randint(0, n, (needles,), generator=g, device="cuda")
+        at = torch.randperm(n, generator=g, device="cuda")[:needles]
         e = torch.randn((c["batch"], c["kv_heads"], needles, D), generator=g, device="cuda")
         e = torch.nn.functional.normalize(e, dim=-1)
         k[:, :, at] = (math.sqrt(D) * (0.9 * u.unsqueeze(2) + math.sqrt(0.19) * e)).to(dt)
