@@ -11,6 +11,8 @@
  *   - Recent and Candidate, Algorithm 3, first line (R.Push of the new token)
  *                                            -> kvr_append
  *   - the three of a decode step in one launch -> kvr_step_update
+ *   - after a prompt's selection, the tokens that stay move into the retained slots
+ *                                            -> kvr_compact
  *   - Algorithm 3, second loop (a Vague token swaps places with the weakest
  *     Candidate: V.Max_Score, V.Query, V.Delete, V.Insert(C.Top_Pop()), C.Push)
  *                                            -> kvr_swap_back
@@ -250,6 +252,25 @@ int32_t kvr_encode(const kvr_desc* desc, const void* k_src, const void* v_src, i
                    const int32_t* src_slot, const int32_t* tok_pos, const int32_t* count, int32_t cap,
                    void* sketch_k, void* sketch_v, int32_t* out_bucket, uint8_t* out_sign,
                    void* ws, size_t ws_bytes, void* stream);
+
+/*
+ * After a prompt's selection: move the tokens that stayed out of the prompt's full
+ * cache into the (smaller) retained slots of the decode steps.  All slots of the
+ * source were occupied before kvr_select listed some of them in evict_slot and
+ * emptied them (src_pos = -1).  Per unit, the slots that stayed, in ascending order
+ * and at most max_keep of them, become slots 0, 1, ... of the destination with
+ * their positions; the destination slots after them become empty (ret_pos = -1)
+ * and their rows zero.  Source and destination must not overlap.
+ *   k_src, v_src  dev [B, Hkv, src_cap, D] storage type, read
+ *   src_pos       dev int32 [B, Hkv, src_cap], read
+ *   evict_slot    dev int32 [B, Hkv, evict_cap], read; ascending
+ *   n_evict       dev int32 [B, Hkv], read; negative = nothing was evicted
+ *   k_ret, v_ret  dev [B, Hkv, ret_cap, D], written (every row)
+ *   ret_pos       dev int32 [B, Hkv, ret_cap], written (every entry)
+ */
+int32_t kvr_compact(const kvr_desc* desc, const void* k_src, const void* v_src, const int32_t* src_pos,
+                    int32_t src_cap, const int32_t* evict_slot, const int32_t* n_evict, int32_t evict_cap,
+                    void* k_ret, void* v_ret, int32_t* ret_pos, int32_t ret_cap, int32_t max_keep, void* stream);
 
 /*
  * Algorithm 3 for one decode step, in one launch: exactly kvr_append, then

@@ -30,7 +30,7 @@ _ERR_NAMES = {-1: "KVR_ERR_INVALID_ARG", -2: "KVR_ERR_UNSUPPORTED",
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libkvr.so")
 
 EXPORTS = ["kvr_version", "kvr_last_hip_error", "kvr_recent_size", "kvr_hash_params_from_seed", "kvr_hash_host",
-           "kvr_workspace_size", "kvr_append", "kvr_select", "kvr_encode", "kvr_step_update",
+           "kvr_workspace_size", "kvr_append", "kvr_select", "kvr_encode", "kvr_compact", "kvr_step_update",
            "kvr_swap_back", "kvr_reconstruct", "kvr_attend_decode", "kvr_attend_decode_static",
            "kvr_attend_multi_workspace_size", "kvr_attend_multi"]
 KVR_STATIC_SCRATCH_BYTES = 80 << 20
@@ -138,6 +138,8 @@ def lib() -> C.CDLL:
                                  vp, sz, vp]
         L.kvr_encode.restype = i32
         L.kvr_encode.argtypes = [dp, vp, vp, i32, vp, vp, vp, i32, vp, vp, vp, vp, vp, sz, vp]
+        L.kvr_compact.restype = i32
+        L.kvr_compact.argtypes = [dp, vp, vp, vp, i32, vp, vp, i32, vp, vp, vp, i32, i32, vp]
         L.kvr_step_update.restype = i32
         L.kvr_step_update.argtypes = [dp, vp, vp, vp, vp, vp, vp, i32, vp, i64, i32, i32, vp, vp, vp, i32,
                                       vp, vp, i32, vp, vp, vp]
@@ -303,6 +305,18 @@ def kvr_encode(desc, k_src, v_src, src_rows, src_slot, tok_pos, count, cap, sket
         _ptr(out_bucket, torch.int32, U * cap * desc.r, "out_bucket", True),
         _ptr(out_sign, torch.uint8, U * cap, "out_sign", True), wp, wb, _stream())
     _check("kvr_encode", rc)
+
+
+def kvr_compact(desc, k_src, v_src, src_pos, src_cap, evict_slot, n_evict, evict_cap, k_ret, v_ret, ret_pos, ret_cap,
+                max_keep):
+    U, D, dt = desc.batch * desc.n_kv_heads, desc.head_dim, _torch_dtype(desc)
+    rc = lib().kvr_compact(
+        C.byref(desc), _ptr(k_src, dt, U * src_cap * D, "k_src"), _ptr(v_src, dt, U * src_cap * D, "v_src"),
+        _ptr(src_pos, torch.int32, U * src_cap, "src_pos"), src_cap,
+        _ptr(evict_slot, torch.int32, U * evict_cap, "evict_slot"), _ptr(n_evict, torch.int32, U, "n_evict"), evict_cap,
+        _ptr(k_ret, dt, U * ret_cap * D, "k_ret"), _ptr(v_ret, dt, U * ret_cap * D, "v_ret"),
+        _ptr(ret_pos, torch.int32, U * ret_cap, "ret_pos"), ret_cap, max_keep, _stream())
+    _check("kvr_compact", rc)
 
 
 def kvr_step_update(desc, k_new, v_new, n_ctx, k_ret, v_ret, ret_pos, ret_cap, scores, n_cap, n_recent,

@@ -199,6 +199,22 @@ int32_t kvr_encode(const kvr_desc* desc, const void* k_src, const void* v_src, i
                                    sketch_k, sketch_v, out_bucket, out_sign, ws, plan, (hipStream_t)stream));
 }
 
+int32_t kvr_compact(const kvr_desc* desc, const void* k_src, const void* v_src, const int32_t* src_pos,
+                    int32_t src_cap, const int32_t* evict_slot, const int32_t* n_evict, int32_t evict_cap,
+                    void* k_ret, void* v_ret, int32_t* ret_pos, int32_t ret_cap, int32_t max_keep, void* stream) {
+  kvr::DevDesc d;
+  const int32_t rc = check_desc(desc, d);
+  if (rc != KVR_OK) return rc;
+  if (!k_src || !v_src || !src_pos || !evict_slot || !n_evict || !k_ret || !v_ret || !ret_pos)
+    return KVR_ERR_INVALID_ARG;
+  if (!aligned16(k_src) || !aligned16(v_src) || !aligned16(k_ret) || !aligned16(v_ret)) return KVR_ERR_INVALID_ARG;
+  if (src_cap < 1 || src_cap > MAX_TOKENS || ret_cap < 1 || ret_cap > MAX_TOKENS || evict_cap < 1 ||
+      evict_cap > MAX_TOKENS || max_keep < 0)
+    return KVR_ERR_INVALID_ARG;
+  return finish(kvr::launch_compact(d, desc->dtype, k_src, v_src, src_pos, src_cap, evict_slot, n_evict, evict_cap,
+                                    k_ret, v_ret, ret_pos, ret_cap, max_keep, (hipStream_t)stream));
+}
+
 int32_t kvr_step_update(const kvr_desc* desc, const void* k_new, const void* v_new, const int32_t* n_ctx,
                         void* k_ret, void* v_ret, int32_t* ret_pos, int32_t ret_cap, const float* scores,
                         int64_t n_cap, int32_t n_recent, int32_t k_candidate, int32_t* evict_slot,

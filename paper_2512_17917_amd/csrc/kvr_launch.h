@@ -67,6 +67,11 @@ struct AttendArgs {
 hipError_t launch_attend_retained(const DevDesc& d, const AttendArgs& a, int n_rslices, int max_wgs,
                                   int reg_form, hipStream_t st);
 
+// kept rows of a prompt's cache into the small slot array
+hipError_t launch_compact(const DevDesc& d, int dtype, const void* k_src, const void* v_src, const int32_t* src_pos,
+                          int src_cap, const int32_t* evict_slot, const int32_t* n_evict, int evict_cap, void* k_ret,
+                          void* v_ret, int32_t* ret_pos, int ret_cap, int max_keep, hipStream_t st);
+
 struct EncodePlan {
   bool bulk;
   size_t off_bucket, off_order, off_start, total_bytes;

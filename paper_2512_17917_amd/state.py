@@ -1,7 +1,7 @@
 """Device buffers of one attention layer and the call sequence of a decode step.
 
-Plumbing only (allocation, slicing, one gather that compacts the prompt's kept
-rows): every arithmetic step is a call into libkvr through `binding`.
+Plumbing only (allocation and slicing): everything that touches tokens is a call
+into libkvr through `binding`.
 """
 from __future__ import annotations
 
@@ -10,15 +10,39 @@ import torch
 from . import binding as kvr
 
 
+def _zeros_together(dev, *shapes):
+    """Zero-filled tensors [(shape, dtype), ...] carved out of one allocation, each at a 256-byte
+    boundary: one fill launch for all of them."""
+    offs, n = [], 0
+    for shape, dt in shapes:
+        offs.append(n)
+        numel = 1
+        for x in shape:
+            numel *= x
+        n += (numel * dt.itemsize + 255) // 256 * 256
+    base = torch.zeros(n // 4, dtype=torch.int32, device=dev)
+    typed = {dt: base.view(dt) for dt in {dt for _, dt in shapes}}
+    out = []
+    for (shape, dt), off in zip(shapes, offs):
+        stride, strides = 1, []
+        for x in reversed(shape):
+            strides.append(stride)
+            stride *= x
+        out.append(typed[dt].as_strided(shape, strides[::-1], off // dt.itemsize))
+    return out
+
+
 class LayerState:
     """All per-unit buffers of one layer, unit-major [B, Hkv, ...]."""
 
     def __init__(self, desc, *, n_recent, k_candidate, ret_cap, vague_cap, n_cap, evict_cap=8,
-                 device="cuda", ws_attend=None, ws_encode=None, n_ctx=None, slack=0, side=None):
+                 device="cuda", ws_attend=None, ws_encode=None, n_ctx=None, slack=0, side=None, empty_slots=True):
         """n_recent, k_candidate: R.budget and C.budget of Algorithm 3; slack: its Slack (the
         Recent queue may outgrow its budget by that many tokens before slack + 1 of them leave at
         once; needs ret_cap >= n_recent + k_candidate + slack + 1 and evict_cap >= slack + 1);
-        side: a binding.SideStream lent to every attend call (None: kernels back to back)."""
+        side: a binding.SideStream lent to every attend call (None: kernels back to back);
+        empty_slots: start with every retained slot empty (False: the caller fills k_ret, v_ret and
+        ret_pos itself)."""
         self.desc = desc
         self.n_recent, self.k_candidate = int(n_recent), int(k_candidate)
         self.slack = int(slack)
@@ -30,21 +54,21 @@ class LayerState:
         dt = torch.float32 if desc.dtype == kvr.KVR_F32 else torch.bfloat16
         dev = torch.device(device)
         self.device, self.dtype = dev, dt
-        self.k_ret = torch.zeros(B, Hkv, self.ret_cap, D, dtype=dt, device=dev)
-        self.v_ret = torch.zeros(B, Hkv, self.ret_cap, D, dtype=dt, device=dev)
-        self.ret_pos = torch.full((B, Hkv, self.ret_cap), -1, dtype=torch.int32, device=dev)
-        self.scores = torch.zeros(B, Hkv, self.n_cap, dtype=torch.float32, device=dev)
-        self.sketch_k = torch.zeros(B, Hkv, desc.r, desc.w, D, dtype=dt, device=dev)
-        self.sketch_v = torch.zeros(B, Hkv, desc.r, desc.w, D, dtype=dt, device=dev)
-        self.vague_pos = torch.zeros(B, Hkv, self.vague_cap, dtype=torch.int32, device=dev)
-        self.n_vague = torch.zeros(B, Hkv, dtype=torch.int32, device=dev)
-        self.evict_slot = torch.zeros(B, Hkv, self.evict_cap, dtype=torch.int32, device=dev)
-        self.evict_pos = torch.zeros(B, Hkv, self.evict_cap, dtype=torch.int32, device=dev)
-        self.n_evict = torch.zeros(B, Hkv, dtype=torch.int32, device=dev)
+        slots = torch.zeros if empty_slots else torch.empty
+        self.k_ret = slots(B, Hkv, self.ret_cap, D, dtype=dt, device=dev)
+        self.v_ret = slots(B, Hkv, self.ret_cap, D, dtype=dt, device=dev)
+        self.ret_pos = torch.empty(B, Hkv, self.ret_cap, dtype=torch.int32, device=dev)
+        if empty_slots:
+            self.ret_pos.fill_(-1)
+        i32, f32 = torch.int32, torch.float32
+        (self.scores, self.sketch_k, self.sketch_v, self.vague_pos, self.n_vague, self.evict_slot, self.evict_pos,
+         self.n_evict, self.out) = _zeros_together(
+            dev, ((B, Hkv, self.n_cap), f32), ((B, Hkv, desc.r, desc.w, D), dt), ((B, Hkv, desc.r, desc.w, D), dt),
+            ((B, Hkv, self.vague_cap), i32), ((B, Hkv), i32), ((B, Hkv, self.evict_cap), i32),
+            ((B, Hkv, self.evict_cap), i32), ((B, Hkv), i32), ((B, Hq, D), f32))
         # several layers may share one n_ctx tensor and one workspace (calls on one
         # stream are ordered, and no workspace content outlives a call)
         self.n_ctx = torch.zeros(B, dtype=torch.int32, device=dev) if n_ctx is None else n_ctx
-        self.out = torch.zeros(B, Hq, D, dtype=torch.float32, device=dev)
         self.ws_attend = ws_attend if ws_attend is not None else kvr.alloc_workspace(
             desc, kvr.KVR_OP_ATTEND, self.ret_cap, self.vague_cap, dev)
         self.ws_encode = ws_encode if ws_encode is not None else kvr.alloc_workspace(
@@ -141,7 +165,7 @@ class LayerState:
         """Compress a prompt's KV cache K, V [B, Hkv, N, D]: cumulative scores are
         initialised with one dense attention pass of q0 (or taken from
         init_scores [B, Hkv, N]), the Recent and Candidate parts are kept raw and
-        compacted into ret_cap = n_recent + k_candidate + 1 slots, everything else
+        moved into ret_cap = n_recent + k_candidate + slack + 1 slots, everything else
         goes into the sketch.  Returns (state, info)."""
         B, Hkv, N, D = K.shape
         dev = K.device
@@ -154,7 +178,7 @@ class LayerState:
             evict_cap = max(8, slack + 1)
         st = cls(desc, n_recent=n_recent, k_candidate=k_candidate, ret_cap=ret_cap, vague_cap=vague_cap,
                  n_cap=n_cap, evict_cap=evict_cap, device=dev, ws_attend=ws_attend, ws_encode=ws_encode,
-                 n_ctx=n_ctx, slack=slack, side=side)
+                 n_ctx=n_ctx, slack=slack, side=side, empty_slots=False)
         st.n_ctx.fill_(N)
         # the whole prompt was pushed into the Recent queue
         st.r_size = kvr.kvr_recent_size(N, n_recent, slack)
@@ -169,8 +193,8 @@ class LayerState:
         # 2. partition: every prompt token sits in "slot = position" of the full cache
         full_pos = torch.arange(N, dtype=torch.int32, device=dev).expand(B, Hkv, N).contiguous()
         ev_cap = max(n_vague0, 1)
-        ev_slot = torch.zeros(B, Hkv, ev_cap, dtype=torch.int32, device=dev)
-        ev_pos = torch.zeros(B, Hkv, ev_cap, dtype=torch.int32, device=dev)
+        ev_slot = torch.empty(B, Hkv, ev_cap, dtype=torch.int32, device=dev)
+        ev_pos = torch.empty(B, Hkv, ev_cap, dtype=torch.int32, device=dev)
         ws = kvr.alloc_workspace(desc, kvr.KVR_OP_ENCODE, ev_cap, 0, dev)
         if timers is not None:       # (start, stop) torch events around select + bulk encode
             timers[0].record()
@@ -182,15 +206,8 @@ class LayerState:
         if timers is not None:
             timers[1].record()
         del ws
-        # 4. compact the kept rows (ascending slot order) into the small slot array
-        R = min(st.r_size + k_candidate, N)
-        kept_first = torch.sort((full_pos < 0).to(torch.int8), dim=2, stable=True).indices[:, :, :R]
-        n_kept = (full_pos >= 0).sum(dim=2)
-        st.k_ret[:, :, :R] = K.gather(2, kept_first.unsqueeze(-1).expand(-1, -1, -1, D))
-        st.v_ret[:, :, :R] = V.gather(2, kept_first.unsqueeze(-1).expand(-1, -1, -1, D))
-        rp = full_pos.gather(2, kept_first)
-        rp = torch.where(torch.arange(R, device=dev).view(1, 1, R) < n_kept.unsqueeze(-1), rp,
-                         torch.full_like(rp, -1))
-        st.ret_pos[:, :, :R] = rp
+        # 4. the kept rows move into the small slot array (ascending slot order)
+        kvr.kvr_compact(desc, K, V, full_pos, N, ev_slot, st.n_evict, ev_cap, st.k_ret, st.v_ret, st.ret_pos,
+                        ret_cap, min(st.r_size + k_candidate, N))
         info = {"evict_slot": ev_slot, "evict_pos": ev_pos, "n_evict": st.n_evict.clone()}
         return st, info
