@@ -1,4 +1,4 @@
-"""kvr_compact against plain indexing: ranges of 512 source slots and their edges, a last range without a kept
+"""kvr_compact against plain indexing: ranges of 256 source slots and their edges, a last range without a kept
 row, more kept rows than max_keep or than the destination holds, both storage types.  Copies: exact."""
 import pytest
 import torch
