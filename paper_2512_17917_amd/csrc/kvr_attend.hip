@@ -19,9 +19,6 @@ namespace kvr {
 
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-constexpr int STAGED_KMAX = 6;                    // wave-rounds (64 tokens) per wave, staged kernel
-constexpr int STAGED_LDS_LIMIT = 160 * 1024;      // LDS per workgroup on gfx950
-
 // Tokens per slice: about 1280 slices per launch (measured on the 32k workloads: fewer, larger slices leave
 // the merge kernel fewer partials to fold and cost the retained kernel nothing), in multiples of
 // 64 tokens, at least 128 when a unit has a long list (a workgroup of four waves with a single 16-token tile
@@ -48,22 +45,22 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
   // staged kernel: bf16, the paper's sign setting, G <= 4, r = 3 or 4, bucket fits 15 bits
   if (dtype == KVR_BF16 && d.sign_mask == 2 && d.G <= 4 && (d.r == 3 || d.r == 4) && d.w <= 32768 &&
       vague_cap >= 64) {
-    const int fixed = STAGED_KMAX * 512 * 8 + 8 * d.G * 64 * 4 + 1024 + d.G * 256;
+    const int fixed = staged_fixed_lds(d.G);
     int ch = 0;
     for (int c = 64; c >= 8; c >>= 1) {
-      if ((long long)d.r * d.w * c * 2 + 1024 + fixed <= STAGED_LDS_LIMIT) { ch = c; break; }
+      if (staged_chunk_fits(d.r, d.w, d.G, c)) { ch = c; break; }
     }
     if (ch) {
       const long long wr = (vague_cap + 63) / 64;          // wave-rounds to cover the list
       // Cost model: a workgroup that gives every wave rho rounds of 64 tokens takes
       // about (fixed + rho) round times (fixed part: staging the sketch chunks,
       // hashes, softmax, reductions: 2.8 rounds' worth for four 64-channel chunks,
-      // 7.5 for the sixteen 16-channel chunks of the four-row kernel, whose waves may
+      // 7.5 for the sixteen 16-channel chunks of that kernel, whose waves may
       // also take more rounds), and the launch runs ceil(workgroups / 256)
       // such workgroups one after another on each CU.
-      const bool r4 = staged_r4_applies(d);
-      const int kmax = r4 ? STAGED_R4_KMAX : STAGED_KMAX;
-      const double fixed_rounds = r4 ? 7.5 : 2.8;
+      const bool s16 = staged16_applies(d);
+      const int kmax = s16 ? STAGED16_KMAX : STAGED_KMAX;
+      const double fixed_rounds = s16 ? 7.5 : 2.8;
       double best = 1e30;
       int best_rho = 1, best_n = 1;
       for (int rho = 1; rho <= kmax; ++rho) {
@@ -511,7 +508,7 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
   // Not next to the four-row kernel either: its two waves per SIMD hold up to 2 x 238 of the 512
   // registers, so the retained kernel would only find room where a workgroup of it has just ended
   // (measured on the 131k workload: 571 us side by side, 511 us back to back).
-  const bool side = sd.stream != nullptr && plan.mfma_retained && plan.staged && big && !staged_r4_applies(d);
+  const bool side = sd.stream != nullptr && plan.mfma_retained && plan.staged && big && !(d.r == 4 && staged16_applies(d));
   if (side) {
     e = hipEventRecord(sd.fork, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(sd.stream, sd.fork, 0);
@@ -519,9 +516,9 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
       // From here on the side stream may hold work that writes the caller's workspace: whatever
       // fails below, `st` is made to wait for it before this call returns.
       // what the staged kernel's two waves leave of a SIMD's 512 registers: 128 next to the 64-channel
-      // kernel, 80 next to the widest general form
-      const bool s64 = d.r == 3 && plan.ch == 64 && 3 * d.w <= 1024;
-      const int reg_form = s64 ? 1 : ((d.G == 4 && plan.ch <= 16) ? 2 : 0);
+      // kernel and the three-row form of the 16-channel kernel (2 x 176), 80 next to the widest general form
+      const bool s64_16 = staged64_applies(d) || staged16_applies(d);
+      const int reg_form = s64_16 ? 1 : ((d.G == 4 && plan.ch <= 16) ? 2 : 0);
       e = launch_attend_retained(d, a, plan.n_rslices, cus, reg_form, sd.stream);
       const hipError_t ej = hipEventRecord(sd.join, sd.stream);
       if (e == hipSuccess && ej == hipSuccess) e = launch_attend_vague_staged(d, a, plan, st);

@@ -1,18 +1,24 @@
-// Staged attention kernel over the Vague list for r = 4 sketch rows (bf16 storage,
-// values signed only, G <= 4 query heads per kv head).  Same contract and the
-// same token -> wave mapping as the general staged kernel (kvr_attend_staged.hip),
-// which it replaces for four rows.
+// Staged attention kernel over the Vague list in chunks of 16 channels: four sketch
+// rows, or three whose sketch is too wide for the 64-channel kernel (bf16 storage,
+// values signed only, G <= 4 query heads per kv head).  Same contract and the same
+// token -> wave mapping as the general staged kernel (kvr_attend_staged.hip), which
+// takes what is wider still (more than 4096 rows in all).
 //
-// With four rows a kv head's sketch is large (the 131k-token workload: 4 x 819
-// slots of 256 bytes per tensor), so it goes through LDS in chunks of 16 channels
+// Such a sketch is large (131k tokens: 4 x 819 or 3 x 1092 slots of 256 bytes per
+// tensor), so it goes through LDS in chunks of 16 channels
 // (32 bytes per slot; eight chunks of the K sketch, then eight of the V sketch).
 // Inside a chunk the unit of work is a *half piece*: 4 channels = 8 bytes, which
 // is exactly the contraction length of v_mfma_f32_4x4x4.
 //
+// Bound by vector-ALU issue.  Three rows, one layer's decode step against the general kernel with float32
+// p.v: 131072 tokens, 16 units 452 -> 233 us, 8 units 263 -> 173 us; 70000 tokens, 24 units 235 -> 187 us;
+// 42000 tokens, 48 units 259 -> 205 us, 8 units 92 -> 92 us.  With three rows a wave holds 176 registers (four:
+// 240), which leaves room for the retained-slot kernel next to it.
+//
 //  * K phases: one lane = one token.  The 4 lanes of a block read the same half
 //    piece of their tokens' rows (neighbouring blocks take different half pieces,
-//    so the 16 lanes served together spread over the banks), the four-row median
-//    is taken on packed bf16 bits (median_dword<4>), and one matrix instruction per
+//    so the 16 lanes served together spread over the banks), the median is taken on
+//    packed bf16 bits, and one matrix instruction per
 //    half piece multiplies the block's 4 rebuilt tokens (A, one row per lane) with
 //    q (B, column j = head j): lane j receives the logits of the block's 4 tokens
 //    for head j -- already the layout the V phases want for their A operand, so the
@@ -35,29 +41,33 @@
 namespace kvr {
 namespace {
 
-constexpr int R4_CH = 16;                 // channels per chunk
-constexpr int R4_ROWB = 32;               // bytes per LDS row
-constexpr int R4_NHP = 4;                 // 8-byte half pieces per LDS row
-constexpr int R4_NCHUNK = D / R4_CH;      // chunks per tensor
-constexpr int R4_NROW = ST_WAVES * 4;     // 16-lane rows per workgroup
-constexpr int R4_KMAX = STAGED_R4_KMAX;   // wave-rounds (64 tokens) per wave
+constexpr int S16_CH = 16;                 // channels per chunk
+constexpr int S16_ROWB = 32;               // bytes per LDS row
+constexpr int S16_NHP = 4;                 // 8-byte half pieces per LDS row
+constexpr int S16_NCHUNK = D / S16_CH;      // chunks per tensor
+constexpr int S16_NROW = ST_WAVES * 4;     // 16-lane rows per workgroup
+constexpr int S16_KMAX = STAGED16_KMAX;   // wave-rounds (64 tokens) per wave
 
-struct Rows4 {
-  uint2 r0, r1, r2, r3;
+template <int R>
+struct Rows {
+  uint2 r[R];
 };
 
-__device__ __forceinline__ void load_rows4(Rows4& o, const unsigned char* s_sk, const int (&rb)[4], int co) {
-  o.r0 = *reinterpret_cast<const uint2*>(s_sk + rb[0] + co);
-  o.r1 = *reinterpret_cast<const uint2*>(s_sk + rb[1] + co);
-  o.r2 = *reinterpret_cast<const uint2*>(s_sk + rb[2] + co);
-  o.r3 = *reinterpret_cast<const uint2*>(s_sk + rb[3] + co);
+template <int R>
+__device__ __forceinline__ void load_rows(Rows<R>& o, const unsigned char* s_sk, const int (&rb)[R], int co) {
+#pragma unroll
+  for (int i = 0; i < R; ++i) o.r[i] = *reinterpret_cast<const uint2*>(s_sk + rb[i] + co);
 }
 
-template <int MODE>
-__device__ __forceinline__ uint2 median4(const Rows4& v) {
-  const uint32_t x[4] = {v.r0.x, v.r1.x, v.r2.x, v.r3.x};
-  const uint32_t y[4] = {v.r0.y, v.r1.y, v.r2.y, v.r3.y};
-  return make_uint2(median_dword<4>(x, MODE), median_dword<4>(y, MODE));
+template <int R, int MODE>
+__device__ __forceinline__ uint2 median_rows_of(const Rows<R>& v) {
+  if constexpr (R == 3) {
+    return med3_half_piece(v.r[0], v.r[1], v.r[2]);
+  } else {
+    const uint32_t x[4] = {v.r[0].x, v.r[1].x, v.r[2].x, v.r[3].x};
+    const uint32_t y[4] = {v.r[0].y, v.r[1].y, v.r[2].y, v.r[3].y};
+    return make_uint2(median_dword<4>(x, MODE), median_dword<4>(y, MODE));
+  }
 }
 
 // value of lane J of this lane's quad
@@ -70,68 +80,90 @@ __device__ __forceinline__ uint32_t quad_bcast(uint32_t v) {
 // pre-multiplied by the 32-byte row pitch: row 0 in x[5..16], row 1 in x[17..28],
 // row 2 in y[5..16], row 3 in y[17..28].  Bit 0 of x is a sign that is folded into
 // the token's weight; bit 30 of x, bit 31 of x, bit 31 of y and bit 30 of y say
-// whether rows 0, 1, 2, 3 are flipped before the median.  The mean of the two middle
-// values is an odd function of the four values, so there g_0 goes onto the weight
-// and the rows are flipped relative to row 0 (row 0 never is); the lower of the two
-// middle values is not odd, so there nothing is folded and every row is flipped by
-// its own sign.
-template <int MODE>
+// whether rows 0, 1, 2, 3 are flipped before the median.
+//
+// Four rows: the mean of the two middle values is an odd function of the four
+// values, so there g_0 goes onto the weight and the rows are flipped relative to
+// row 0 (row 0 never is); the lower of the two middle values is not odd, so there
+// nothing is folded and every row is flipped by its own sign.
+// Three rows: two of the three signs always agree; theirs goes onto the weight and
+// the row with the other sign, if there is one, is listed last (a median does not
+// care about the order), so that only "row 2" is ever flipped.
+template <int R, int MODE>
 __device__ __forceinline__ uint2 make_record(const DevDesc& d, int w, int J) {
-  const uint32_t r0 = (uint32_t)bucket_of(d, 0, J), r1 = (uint32_t)(w + bucket_of(d, 1, J)),
-                 r2 = (uint32_t)(2 * w + bucket_of(d, 2, J)), r3 = (uint32_t)(3 * w + bucket_of(d, 3, J));
-  const uint32_t s0 = sign_neg(d, 0, J) ? 1u : 0u, s1 = sign_neg(d, 1, J) ? 1u : 0u,
-                 s2 = sign_neg(d, 2, J) ? 1u : 0u, s3 = sign_neg(d, 3, J) ? 1u : 0u;
-  const uint32_t fold = (MODE == KVR_MEDIAN_MIDMEAN) ? s0 : 0u;
-  return make_uint2((r0 << 5) | (r1 << 17) | fold | ((s0 ^ fold) << 30) | ((s1 ^ fold) << 31),
-                    (r2 << 5) | (r3 << 17) | ((s2 ^ fold) << 31) | ((s3 ^ fold) << 30));
+  uint32_t r[R], s[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    r[i] = (uint32_t)(i * w + bucket_of(d, i, J));
+    s[i] = sign_neg(d, i, J) ? 1u : 0u;
+  }
+  if constexpr (R == 3) {
+    const uint32_t maj = (s[0] & s[1]) | (s[2] & (s[0] | s[1]));
+    const uint32_t flip = (s[0] ^ s[1]) | (s[0] ^ s[2]);
+    const bool last0 = (s[0] != maj), last1 = (s[1] != maj);
+    const uint32_t q0 = last0 ? r[2] : r[0];
+    const uint32_t q1 = last1 ? r[2] : r[1];
+    const uint32_t q2 = last0 ? r[0] : (last1 ? r[1] : r[2]);
+    return make_uint2((q0 << 5) | (q1 << 17) | maj, (q2 << 5) | (flip << 31));
+  } else {
+    const uint32_t fold = (MODE == KVR_MEDIAN_MIDMEAN) ? s[0] : 0u;
+    return make_uint2((r[0] << 5) | (r[1] << 17) | fold | ((s[0] ^ fold) << 30) | ((s[1] ^ fold) << 31),
+                      (r[2] << 5) | (r[3] << 17) | ((s[2] ^ fold) << 31) | ((s[3] ^ fold) << 30));
+  }
 }
-__device__ __forceinline__ void rec_offsets(uint2 rec, int (&rb)[4]) {
+template <int R>
+__device__ __forceinline__ void rec_offsets(uint2 rec, int (&rb)[R]) {
   rb[0] = (int)(rec.x & 0x1ffe0u);
   rb[1] = (int)((rec.x >> 12) & 0x1ffe0u);
   rb[2] = (int)(rec.y & 0x1ffe0u);
-  rb[3] = (int)((rec.y >> 12) & 0x1ffe0u);
+  if constexpr (R > 3) rb[3] = (int)((rec.y >> 12) & 0x1ffe0u);
 }
 
-// V phases: what a lane derives from its own token's record (row offsets and the
-// flip masks of rows 1..3); the other lanes of the quad fetch it with quad
-// broadcasts, so a record is taken apart once per quad.
+// first row that a V phase may have to flip
+template <int R, int MODE>
+__host__ __device__ constexpr int first_flip() {
+  return R == 3 ? 2 : (MODE == KVR_MEDIAN_MIDMEAN ? 1 : 0);
+}
+
+// V phases: what a lane derives from its own token's record (row offsets and flip
+// masks); the other lanes of the quad fetch it with quad broadcasts, so a record is
+// taken apart once per quad.
+template <int R>
 struct VOwn {
-  int o0, o1, o2, o3;
-  uint32_t f0, f1, f2, f3;
+  int o[R];
+  uint32_t f[R];
 };
-__device__ __forceinline__ VOwn v_own(uint2 rec) {
-  int rb[4];
-  rec_offsets(rec, rb);
-  return VOwn{rb[0], rb[1], rb[2], rb[3], (uint32_t)((int)(rec.x << 1) >> 31) & 0x80008000u,
-              (uint32_t)((int)rec.x >> 31) & 0x80008000u, (uint32_t)((int)rec.y >> 31) & 0x80008000u,
-              (uint32_t)((int)(rec.y << 1) >> 31) & 0x80008000u};
+template <int R>
+__device__ __forceinline__ VOwn<R> v_own(uint2 rec) {
+  VOwn<R> v;
+  rec_offsets<R>(rec, v.o);
+  v.f[0] = (uint32_t)((int)(rec.x << 1) >> 31) & 0x80008000u;
+  v.f[1] = (uint32_t)((int)rec.x >> 31) & 0x80008000u;
+  v.f[2] = (uint32_t)((int)rec.y >> 31) & 0x80008000u;
+  if constexpr (R > 3) v.f[3] = (uint32_t)((int)(rec.y << 1) >> 31) & 0x80008000u;
+  return v;
 }
+template <int R>
 struct VItem {
-  Rows4 rows;
-  uint32_t f0, f1, f2, f3;
+  Rows<R> rows;
+  uint32_t f[R];
 };
-template <int J, int MODE>
-__device__ __forceinline__ void v_fetch(VItem& o, const VOwn& own, const unsigned char* s_sk, int co) {
-  int rb[4];
-  rb[0] = (int)quad_bcast<J>((uint32_t)own.o0) + co;
-  rb[1] = (int)quad_bcast<J>((uint32_t)own.o1) + co;
-  rb[2] = (int)quad_bcast<J>((uint32_t)own.o2) + co;
-  rb[3] = (int)quad_bcast<J>((uint32_t)own.o3) + co;
-  o.f0 = (MODE == KVR_MEDIAN_MIDMEAN) ? 0u : quad_bcast<J>(own.f0);
-  o.f1 = quad_bcast<J>(own.f1);
-  o.f2 = quad_bcast<J>(own.f2);
-  o.f3 = quad_bcast<J>(own.f3);
-  load_rows4(o.rows, s_sk, rb, 0);
+template <int J, int R, int MODE>
+__device__ __forceinline__ void v_fetch(VItem<R>& o, const VOwn<R>& own, const unsigned char* s_sk, int co) {
+  int rb[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    rb[i] = (int)quad_bcast<J>((uint32_t)own.o[i]) + co;
+    o.f[i] = (i < first_flip<R, MODE>()) ? 0u : quad_bcast<J>(own.f[i]);
+  }
+  load_rows<R>(o.rows, s_sk, rb, 0);
 }
-template <int MODE>
-__device__ __forceinline__ uint2 v_median(const VItem& it) {
-  Rows4 x;
-  x.r0 = it.rows.r0;
-  if constexpr (MODE != KVR_MEDIAN_MIDMEAN) x.r0 = make_uint2(it.rows.r0.x ^ it.f0, it.rows.r0.y ^ it.f0);
-  x.r1 = make_uint2(it.rows.r1.x ^ it.f1, it.rows.r1.y ^ it.f1);
-  x.r2 = make_uint2(it.rows.r2.x ^ it.f2, it.rows.r2.y ^ it.f2);
-  x.r3 = make_uint2(it.rows.r3.x ^ it.f3, it.rows.r3.y ^ it.f3);
-  return median4<MODE>(x);
+template <int R, int MODE>
+__device__ __forceinline__ uint2 v_median(const VItem<R>& it) {
+  Rows<R> x = it.rows;
+#pragma unroll
+  for (int i = first_flip<R, MODE>(); i < R; ++i) x.r[i] = make_uint2(it.rows.r[i].x ^ it.f[i], it.rows.r[i].y ^ it.f[i]);
+  return median_rows_of<R, MODE>(x);
 }
 
 // acc[c] (4 head sums of channel c of the half piece) += weights (4 heads x 4 tokens,
@@ -174,30 +206,30 @@ __device__ __forceinline__ void take_turn(int t) {
 // offset co[j] of the row).  s[k][i]: logit of token i of this lane's quad in round
 // k, for head (lane mod 4).  Pipeline over the steps t = 4 k + j: rows of step t + 2
 // requested, median of step t + 1 formed, matrix instruction of step t issued.
-template <int NK, int MODE>
-__device__ __forceinline__ void k_pass(const unsigned char* s_sk, const uint2 (&info)[R4_KMAX],
-                                       const uint2 (&qx)[R4_NHP], const int (&co)[R4_NHP], int turn,
-                                       float (&s)[R4_KMAX][4]) {
-  Rows4 buf[3];                          // rows of step t live in buf[t % 3]
-  int rb[4];
-  rec_offsets(opaque(info[0]), rb);
-  load_rows4(buf[0], s_sk, rb, co[0]);
-  load_rows4(buf[1], s_sk, rb, co[1]);
+template <int NK, int R, int MODE>
+__device__ __forceinline__ void k_pass(const unsigned char* s_sk, const uint2 (&info)[S16_KMAX],
+                                       const uint2 (&qx)[S16_NHP], const int (&co)[S16_NHP], int turn,
+                                       float (&s)[S16_KMAX][4]) {
+  Rows<R> buf[3];                        // rows of step t live in buf[t % 3]
+  int rb[R];
+  rec_offsets<R>(opaque(info[0]), rb);
+  load_rows<R>(buf[0], s_sk, rb, co[0]);
+  load_rows<R>(buf[1], s_sk, rb, co[1]);
   uint2 m[2];                            // median of step t in m[t % 2]
-  m[0] = median4<MODE>(buf[0]);
+  m[0] = median_rows_of<R, MODE>(buf[0]);
 #pragma unroll
   for (int k = 0; k < NK; ++k) {
-    int rn[4] = {0, 0, 0, 0};
-    if (k + 1 < NK) rec_offsets(opaque(info[k + 1]), rn);
+    int rn[R] = {};
+    if (k + 1 < NK) rec_offsets<R>(opaque(info[k + 1]), rn);
     f32x4_t ax = {0.f, 0.f, 0.f, 0.f};
     take_turn(k + turn);
 #pragma unroll
-    for (int j = 0; j < R4_NHP; ++j) {
-      const int t = R4_NHP * k + j;
-      if (j + 2 < R4_NHP) load_rows4(buf[(t + 2) % 3], s_sk, rb, co[j + 2]);
-      else if (k + 1 < NK) load_rows4(buf[(t + 2) % 3], s_sk, rn, co[j + 2 - R4_NHP]);
+    for (int j = 0; j < S16_NHP; ++j) {
+      const int t = S16_NHP * k + j;
+      if (j + 2 < S16_NHP) load_rows<R>(buf[(t + 2) % 3], s_sk, rb, co[j + 2]);
+      else if (k + 1 < NK) load_rows<R>(buf[(t + 2) % 3], s_sk, rn, co[j + 2 - S16_NHP]);
       KVR_PIN();
-      if (j + 1 < R4_NHP || k + 1 < NK) m[(t + 1) & 1] = median4<MODE>(buf[(t + 1) % 3]);
+      if (j + 1 < S16_NHP || k + 1 < NK) m[(t + 1) & 1] = median_rows_of<R, MODE>(buf[(t + 1) % 3]);
       KVR_PIN();
       const uint2 mc = m[t & 1];
       ax = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(pack_k4(mc.x, mc.y), pack_k4(qx[j].x, qx[j].y), ax, 0, 0, 0);
@@ -206,40 +238,40 @@ __device__ __forceinline__ void k_pass(const unsigned char* s_sk, const uint2 (&
 #pragma unroll
     for (int i = 0; i < 4; ++i) s[k][i] += ax[i];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) rb[i] = rn[i];
+    for (int i = 0; i < R; ++i) rb[i] = rn[i];
   }
   __builtin_amdgcn_s_setprio(1);
 }
 
 // V pass over NK rounds of one chunk for the half piece at byte offset co of each
 // row: the quad's 4 tokens per round, same kind of pipeline.
-template <int NK, int MODE>
-__device__ __forceinline__ void v_pass(const unsigned char* s_sk, const uint2 (&info)[R4_KMAX],
-                                       const uint32_t (&W)[R4_KMAX][4], int co, int turn, f32x4_t (&acc)[4]) {
-  VItem buf[4];
-  VOwn own = v_own(info[0]);
-  v_fetch<0, MODE>(buf[0], own, s_sk, co);
-  v_fetch<1, MODE>(buf[1], own, s_sk, co);
+template <int NK, int R, int MODE>
+__device__ __forceinline__ void v_pass(const unsigned char* s_sk, const uint2 (&info)[S16_KMAX],
+                                       const uint32_t (&W)[S16_KMAX][4], int co, int turn, f32x4_t (&acc)[4]) {
+  VItem<R> buf[4];
+  VOwn<R> own = v_own<R>(info[0]);
+  v_fetch<0, R, MODE>(buf[0], own, s_sk, co);
+  v_fetch<1, R, MODE>(buf[1], own, s_sk, co);
 #pragma unroll
   for (int k = 0; k < NK; ++k) {
     uint2 med[4];
     take_turn(k + turn);
-    v_fetch<2, MODE>(buf[2], own, s_sk, co);
+    v_fetch<2, R, MODE>(buf[2], own, s_sk, co);
     KVR_PIN();
-    med[0] = v_median<MODE>(buf[0]);
+    med[0] = v_median<R, MODE>(buf[0]);
     KVR_PIN();
-    v_fetch<3, MODE>(buf[3], own, s_sk, co);
-    if (k + 1 < NK) own = v_own(info[k + 1]);
+    v_fetch<3, R, MODE>(buf[3], own, s_sk, co);
+    if (k + 1 < NK) own = v_own<R>(info[k + 1]);
     KVR_PIN();
-    med[1] = v_median<MODE>(buf[1]);
+    med[1] = v_median<R, MODE>(buf[1]);
     KVR_PIN();
-    if (k + 1 < NK) v_fetch<0, MODE>(buf[0], own, s_sk, co);
+    if (k + 1 < NK) v_fetch<0, R, MODE>(buf[0], own, s_sk, co);
     KVR_PIN();
-    med[2] = v_median<MODE>(buf[2]);
+    med[2] = v_median<R, MODE>(buf[2]);
     KVR_PIN();
-    if (k + 1 < NK) v_fetch<1, MODE>(buf[1], own, s_sk, co);
+    if (k + 1 < NK) v_fetch<1, R, MODE>(buf[1], own, s_sk, co);
     KVR_PIN();
-    med[3] = v_median<MODE>(buf[3]);
+    med[3] = v_median<R, MODE>(buf[3]);
     pv_half_piece(med, pack_k4(W[k][0], W[k][1]), pack_k4(W[k][2], W[k][3]), acc);
     KVR_PIN();
   }
@@ -264,21 +296,21 @@ __device__ __forceinline__ void v_pass(const unsigned char* s_sk, const uint2 (&
     case 13: { constexpr int NK = 13; CALL; } break; \
     default: break;              \
   }
-static_assert(STAGED_R4_KMAX <= 13, "KVR_DISPATCH_NK covers 1..13 rounds");
+static_assert(STAGED16_KMAX <= 13, "KVR_DISPATCH_NK covers 1..13 rounds");
 
 // LDS of a workgroup: one chunk, two sets of V partial sums [NROW][G][CH], wave statistics, q
-__host__ __device__ constexpr int chunk_bytes(int w) { return (4 * w * R4_ROWB + 1023) & ~1023; }
+__host__ __device__ constexpr int chunk_bytes(int r, int w) { return (r * w * S16_ROWB + 1023) & ~1023; }
 __host__ __device__ constexpr int stat_floats(int G) { return 3 * ST_WAVES * G; }
-__host__ __device__ constexpr size_t lds_need(int w, int G) {
-  return (size_t)chunk_bytes(w) + (size_t)2 * R4_NROW * G * R4_CH * 4 + (size_t)stat_floats(G) * 4 + (size_t)G * 256;
+__host__ __device__ constexpr size_t lds_need(int r, int w, int G) {
+  return (size_t)chunk_bytes(r, w) + (size_t)2 * S16_NROW * G * S16_CH * 4 + (size_t)stat_floats(G) * 4 + (size_t)G * 256;
 }
 
 }  // namespace
 
-template <int G, int MODE>
-__global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_r4_kernel(DevDesc d, AttendArgs a) {
+template <int G, int R, int MODE>
+__global__ __launch_bounds__(ST_THREADS) void attend_vague_staged16_kernel(DevDesc d, AttendArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int KMAX = R4_KMAX, CH = R4_CH;
+  constexpr int KMAX = S16_KMAX, CH = S16_CH;
 
   // XCD-aware mapping: workgroup ids are dealt round-robin to the 8 XCDs, so all
   // workgroups of a unit get ids that are equal modulo 8 (they share one L2).
@@ -292,10 +324,10 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_r4_kernel(DevD
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int b = unit / d.Hkv, hk = unit % d.Hkv;
   const int w = d.w;
-  const int cb = chunk_bytes(w);
+  const int cb = chunk_bytes(R, w);
   unsigned char* s_sk = smem;                                             // one 16-channel chunk
   float* s_part = reinterpret_cast<float*>(smem + cb);                    // [2][NROW][G][CH]
-  float* s_stat = s_part + 2 * R4_NROW * G * CH;                          // [8 waves][G] maxima, sums, factors
+  float* s_stat = s_part + 2 * S16_NROW * G * CH;                          // [8 waves][G] maxima, sums, factors
   uint2* s_q = reinterpret_cast<uint2*>(s_stat + stat_floats(G));         // [G][32] half pieces of q
 
   const int nv = clampi(a.n_vague[unit], 0, a.vague_cap);
@@ -307,10 +339,10 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_r4_kernel(DevD
   n_k = __builtin_amdgcn_readfirstlane(n_k);      // equal in all lanes of a wave; now the compiler knows
   const int turn = __builtin_amdgcn_readfirstlane(wave >> 2);   // waves i and i + 4 share a SIMD
 
-  const size_t sk_unit = (size_t)unit * 4 * w * D;      // elements
+  const size_t sk_unit = (size_t)unit * R * w * D;      // elements
   const unsigned char* skg = reinterpret_cast<const unsigned char*>((const bf16_t*)a.sk + sk_unit);
   const unsigned char* svg = reinterpret_cast<const unsigned char*>((const bf16_t*)a.sv + sk_unit);
-  const int n_pieces = 4 * w * (R4_ROWB / 16);          // 16-byte pieces of a chunk
+  const int n_pieces = R * w * (S16_ROWB / 16);          // 16-byte pieces of a chunk
 
   __builtin_amdgcn_s_setprio(1);
   // ---- loads first: Vague positions of this wave's tokens and q ---------------
@@ -329,13 +361,13 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_r4_kernel(DevD
   __builtin_amdgcn_s_waitcnt(0x0F70);
 
   // ---- the first K chunk is on its way while the hashes are computed ----------
-  stage_issue<R4_ROWB / 16, R4_ROWB>(skg, s_sk, n_pieces, 0, tid);
+  stage_issue<S16_ROWB / 16, S16_ROWB>(skg, s_sk, n_pieces, 0, tid);
 
   uint2 info[KMAX];
 #pragma unroll
   for (int k = 0; k < KMAX; ++k) {
     const int J = Jv[k];
-    info[k] = (J >= 0) ? make_record<MODE>(d, w, J) : make_uint2(0u, 0u);
+    info[k] = (J >= 0) ? make_record<R, MODE>(d, w, J) : make_uint2(0u, 0u);
   }
   if (tid < G * 16) reinterpret_cast<uint4*>(s_q)[tid] = qv;
 
@@ -348,23 +380,23 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_r4_kernel(DevD
     for (int i = 0; i < 4; ++i) s[k][i] = 0.f;
 
   const int sub = lane & 3, tl = lane >> 2;
-  for (int cc = 0; cc < R4_NCHUNK; ++cc) {
+  for (int cc = 0; cc < S16_NCHUNK; ++cc) {
     stage_wait();
     lds_barrier();                         // chunk cc is complete
     {
-      uint2 qx[R4_NHP];
-      int co[R4_NHP];
+      uint2 qx[S16_NHP];
+      int co[S16_NHP];
 #pragma unroll
-      for (int j = 0; j < R4_NHP; ++j) {
-        const int hp = (tl + j) & (R4_NHP - 1);       // the block's half piece at step j
+      for (int j = 0; j < S16_NHP; ++j) {
+        const int hp = (tl + j) & (S16_NHP - 1);       // the block's half piece at step j
         co[j] = hp * 8;
-        qx[j] = (sub < G) ? s_q[sub * 32 + cc * R4_NHP + hp] : make_uint2(0u, 0u);
+        qx[j] = (sub < G) ? s_q[sub * 32 + cc * S16_NHP + hp] : make_uint2(0u, 0u);
       }
-      KVR_DISPATCH_NK(n_k, (k_pass<NK, MODE>(s_sk, info, qx, co, turn, s)))
+      KVR_DISPATCH_NK(n_k, (k_pass<NK, R, MODE>(s_sk, info, qx, co, turn, s)))
     }
     lds_barrier();                         // every wave is done with chunk cc
-    if (cc + 1 < R4_NCHUNK) stage_issue<R4_ROWB / 16, R4_ROWB>(skg, s_sk, n_pieces, cc + 1, tid);
-    else stage_issue<R4_ROWB / 16, R4_ROWB>(svg, s_sk, n_pieces, 0, tid);       // the first V chunk, under the softmax
+    if (cc + 1 < S16_NCHUNK) stage_issue<S16_ROWB / 16, S16_ROWB>(skg, s_sk, n_pieces, cc + 1, tid);
+    else stage_issue<S16_ROWB / 16, S16_ROWB>(svg, s_sk, n_pieces, 0, tid);       // the first V chunk, under the softmax
   }
 
   // ---- softmax weights against the wave's own maximum ---------------------------
@@ -448,8 +480,8 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_r4_kernel(DevD
   // ---- V phases: weighted values ------------------------------------------------
   float* s_fw = s_stat + 2 * ST_WAVES * G;          // [8 waves][G]: exp(wave maximum - workgroup maximum)
   const int prow = wave * 4 + (lane >> 4);
-  static_assert(G * R4_CH <= ST_THREADS, "one output element per thread and chunk");
-  for (int cc = 0; cc < R4_NCHUNK; ++cc) {
+  static_assert(G * S16_CH <= ST_THREADS, "one output element per thread and chunk");
+  for (int cc = 0; cc < S16_NCHUNK; ++cc) {
     stage_wait();
     lds_barrier();             // V chunk cc complete; partial sums of chunk cc - 1 visible
     if (cc == 0) {
@@ -481,24 +513,24 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_r4_kernel(DevD
       }
     } else if (tid < G * CH) {
       // chunk cc - 1's output element: the NROW rows of partial sums that the barrier just published
-      const float* sp = s_part + ((cc - 1) & 1) * (R4_NROW * G * CH);
+      const float* sp = s_part + ((cc - 1) & 1) * (S16_NROW * G * CH);
       float v = 0.f;
 #pragma unroll
-      for (int pr = 0; pr < R4_NROW; ++pr) v += sp[pr * G * CH + tid];
+      for (int pr = 0; pr < S16_NROW; ++pr) v += sp[pr * G * CH + tid];
       a.part_o[part * G * D + (tid / CH) * D + (cc - 1) * CH + (tid % CH)] = v;
     }
     f32x4_t acc[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    KVR_DISPATCH_NK(n_k, (v_pass<NK, MODE>(s_sk, info, W, sub * 8, turn, acc)))
+    KVR_DISPATCH_NK(n_k, (v_pass<NK, R, MODE>(s_sk, info, W, sub * 8, turn, acc)))
     lds_barrier();                         // every wave is done with this V chunk
-    if (cc + 1 < R4_NCHUNK) stage_issue<R4_ROWB / 16, R4_ROWB>(svg, s_sk, n_pieces, cc + 1, tid);
+    if (cc + 1 < S16_NCHUNK) stage_issue<S16_ROWB / 16, S16_ROWB>(svg, s_sk, n_pieces, cc + 1, tid);
 
     // Reduction over the workgroup's tokens.  Lane (quad, sub) holds, per head, the 4
     // channels of half piece `sub` summed over the tokens of its quad; the four quads of
     // a 16-lane row are added with two DPP rotations, and the NROW rows meet in LDS.
     {
-      float* sp = s_part + (cc & 1) * (R4_NROW * G * CH);
+      float* sp = s_part + (cc & 1) * (S16_NROW * G * CH);
       float o[G][4];
 #pragma unroll
       for (int g = 0; g < G; ++g) {
@@ -515,17 +547,17 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_r4_kernel(DevD
   }
   lds_barrier();
   if (tid < G * CH) {
-    const float* sp = s_part + ((R4_NCHUNK - 1) & 1) * (R4_NROW * G * CH);
+    const float* sp = s_part + ((S16_NCHUNK - 1) & 1) * (S16_NROW * G * CH);
     float v = 0.f;
 #pragma unroll
-    for (int pr = 0; pr < R4_NROW; ++pr) v += sp[pr * G * CH + tid];
-    a.part_o[part * G * D + (tid / CH) * D + (R4_NCHUNK - 1) * CH + (tid % CH)] = v;
+    for (int pr = 0; pr < S16_NROW; ++pr) v += sp[pr * G * CH + tid];
+    a.part_o[part * G * D + (tid / CH) * D + (S16_NCHUNK - 1) * CH + (tid % CH)] = v;
   }
 }
 
-template <int G, int MODE>
-static hipError_t launch_r4(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan, hipStream_t st) {
-  auto kern = attend_vague_staged_r4_kernel<G, MODE>;
+template <int G, int R, int MODE>
+static hipError_t launch16(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan, hipStream_t st) {
+  auto kern = attend_vague_staged16_kernel<G, R, MODE>;
   static std::once_flag once;
   static hipError_t attr_rc = hipSuccess;
   std::call_once(once, [&]() {
@@ -535,27 +567,30 @@ static hipError_t launch_r4(const DevDesc& d, const AttendArgs& a, const AttendP
   if (attr_rc != hipSuccess) return attr_rc;
   const int units = d.B * d.Hkv;
   const int units_pad = (units + 7) / 8 * 8;
-  hipLaunchKernelGGL(kern, dim3(units_pad * plan.n_vslices), dim3(ST_THREADS), lds_need(d.w, G), st, d, a);
+  hipLaunchKernelGGL(kern, dim3(units_pad * plan.n_vslices), dim3(ST_THREADS), lds_need(R, d.w, G), st, d, a);
   return hipGetLastError();
 }
 
 template <int G>
-static hipError_t launch_r4_mode(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan, hipStream_t st) {
-  return d.median_mode == KVR_MEDIAN_LOWER ? launch_r4<G, KVR_MEDIAN_LOWER>(d, a, plan, st)
-                                           : launch_r4<G, KVR_MEDIAN_MIDMEAN>(d, a, plan, st);
+static hipError_t launch16_r(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan, hipStream_t st) {
+  if (d.r == 3) return launch16<G, 3, KVR_MEDIAN_MIDMEAN>(d, a, plan, st);      // one median, whatever the rule
+  return d.median_mode == KVR_MEDIAN_LOWER ? launch16<G, 4, KVR_MEDIAN_LOWER>(d, a, plan, st)
+                                           : launch16<G, 4, KVR_MEDIAN_MIDMEAN>(d, a, plan, st);
 }
 
-bool staged_r4_applies(const DevDesc& d) {
-  return d.r == 4 && 4 * d.w <= 4096 && d.G <= 4 && d.sign_mask == 2 && lds_need(d.w, d.G) <= (size_t)160 * 1024;
+bool staged16_applies(const DevDesc& d) {
+  if (staged64_applies(d)) return false;
+  return (d.r == 3 || d.r == 4) && d.r * d.w <= 4096 && d.G <= 4 && d.sign_mask == 2 &&
+         lds_need(d.r, d.w, d.G) <= (size_t)160 * 1024;
 }
 
-hipError_t launch_attend_vague_staged_r4(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
-                                         hipStream_t st) {
-  if (!staged_r4_applies(d) || plan.n_vslices < 1) return hipErrorInvalidValue;    // 12-bit LDS row indices, LDS size
+hipError_t launch_attend_vague_staged16(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
+                                        hipStream_t st) {
+  if (!staged16_applies(d) || plan.n_vslices < 1) return hipErrorInvalidValue;    // 12-bit LDS row indices, LDS size
   switch (d.G) {
-    case 1: return launch_r4_mode<1>(d, a, plan, st);
-    case 2: return launch_r4_mode<2>(d, a, plan, st);
-    case 4: return launch_r4_mode<4>(d, a, plan, st);
+    case 1: return launch16_r<1>(d, a, plan, st);
+    case 2: return launch16_r<2>(d, a, plan, st);
+    case 4: return launch16_r<4>(d, a, plan, st);
     default: return hipErrorInvalidValue;
   }
 }

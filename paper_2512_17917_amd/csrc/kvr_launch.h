@@ -120,14 +120,25 @@ hipError_t launch_attend_multi(const DevDesc& d, const AttendArgs& a, const int3
 // Staged kernel over the Vague list (bf16, values signed only, G <= 4, r in {3,4}).
 hipError_t launch_attend_vague_staged(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
                                       hipStream_t st);
-// Its specialisation for r = 4 (kvr_attend_staged_r4.hip; launch_attend_vague_staged forwards to it).  A wave
-// of that kernel takes up to STAGED_R4_KMAX rounds of 64 tokens (every workgroup stages the unit's whole
+// LDS of the staged kernel beside the sketch chunk: token records, output sums, statistics, q
+constexpr int STAGED_KMAX = 6;                    // wave-rounds (64 tokens) per wave
+constexpr int STAGED_LDS_LIMIT = 160 * 1024;      // LDS per workgroup on gfx950
+constexpr int staged_fixed_lds(int G) { return STAGED_KMAX * 512 * 8 + 8 * G * 64 * 4 + 1024 + G * 256; }
+constexpr bool staged_chunk_fits(int r, long long w, int G, int channels) {
+  return (long long)r * w * channels * 2 + 1024 + staged_fixed_lds(G) <= STAGED_LDS_LIMIT;
+}
+// Its specialisation for chunks of 16 channels (kvr_attend_staged16.hip; launch_attend_vague_staged forwards
+// to it): four rows, and three rows whose sketch is too wide for the 64-channel kernel.  A wave
+// of that kernel takes up to STAGED16_KMAX rounds of 64 tokens (every workgroup stages the unit's whole
 // sketch, sixteen chunks of it, so few large workgroups are better than many small ones).
-constexpr int STAGED_R4_KMAX = 13;
-bool staged_r4_applies(const DevDesc& d);
-hipError_t launch_attend_vague_staged_r4(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
+constexpr int STAGED16_KMAX = 13;
+bool staged16_applies(const DevDesc& d);
+hipError_t launch_attend_vague_staged16(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
                                          hipStream_t st);
-// Its specialisation for r = 3 and plan.ch = 64 (launch_attend_vague_staged forwards to it).
+// Its specialisation for r = 3 and 64-channel chunks (launch_attend_vague_staged forwards to it); 10-bit row indices.
+inline bool staged64_applies(const DevDesc& d) {
+  return d.r == 3 && d.G <= 4 && d.sign_mask == 2 && 3 * (long long)d.w <= 1024 && staged_chunk_fits(3, d.w, d.G, 64);
+}
 hipError_t launch_attend_vague_staged64(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
                                         hipStream_t st);
 

@@ -466,6 +466,19 @@ def test_attend_four_rows_many_rounds(kvr, G, mode):
                     check_units=set(lens))
 
 
+@pytest.mark.parametrize("G,w", [(1, 342), (2, 700), (4, 334), (4, 1365), (2, 1366)])
+def test_attend_three_rows_wide_sketch(kvr, G, w):
+    """Three rows too wide for 64-channel chunks: the 16-channel kernel, from the first width it takes to the
+    last (4095 rows in LDS), and the general kernel right behind it.  One workgroup per unit and up to 13
+    rounds of 64 tokens per wave, ragged ends, one token and none."""
+    B, Hkv, cap = 32, 8, 6656
+    lens = {(0, 0): 6656, (0, 1): 6593, (5, 3): 5000, (17, 6): 3300, (31, 7): 1, (31, 6): 0, (12, 0): 4161}
+    nv = [lens.get((u // Hkv, u % Hkv), 6656 - 64 * (u % 7)) for u in range(B * Hkv)]
+    rng = np.random.default_rng(67 + w)
+    say("attend three rows, wide sketch", G, w)
+    run_attend_case(kvr, rng, torch.bfloat16, B, Hkv * G, Hkv, 3, w, 70, nv, cap, check_units=set(lens))
+
+
 @pytest.mark.parametrize("G", [1, 2, 4])
 def test_attend_side_by_side(kvr, G):
     """Enough units and Vague tokens that the staged kernel fills the chip more than twice over: with a
