@@ -417,13 +417,21 @@ bool multi_staged_applies(const DevDesc& d, long long vague_cap) {
 
 int multi_staged_pad_tokens() { return MS_PAD_TOKENS; }
 
-// tokens per workgroup: a unit's list is cut for about one workgroup per CU in all, at least 256 tokens each
+// Tokens per workgroup, at least 256.  One workgroup (16 waves, the chunk in LDS) runs per CU, so a launch takes
+// ceil(workgroups / 256) turns of (fixed part + tokens of a workgroup); the fixed part (four chunk copies, the
+// reductions) costs about as much as 400 tokens.
 int multi_staged_part_tokens(long long vague_cap, long long units) {
-  long long parts = (256 + units - 1) / units;
-  if (parts < 1) parts = 1;
-  long long t = (vague_cap + parts - 1) / parts;
-  if (t < 256) t = 256;
-  return (int)((t + 15) / 16 * 16);
+  const long long n_max = 1024 / units + 1;
+  double best = 1e30;
+  long long best_t = vague_cap;
+  for (long long n = 1; n <= n_max; ++n) {
+    long long t = (vague_cap + n - 1) / n;
+    if (t < 256 && n > 1) break;
+    if (t < 256) t = 256;
+    const double cost = (double)((units * n + 255) / 256) * (400.0 + (double)t);
+    if (cost < best - 1e-9) { best = cost; best_t = t; }
+  }
+  return (int)((best_t + 15) / 16 * 16);
 }
 
 template <int NCOL>
