@@ -334,25 +334,44 @@ __global__ __launch_bounds__(256) void attend_combine_kernel(DevDesc d, AttendAr
     for (int u = 0; u < U; ++u) old[u] = (pos[u] >= 0) ? sc[pos[u]] : 0.f;
   }
 
-  // ---- global max and sum per head: wave w takes heads w, w + 4 ----------------
-  for (int g = wave; g < G; g += 4) {
-    float M = -__builtin_inff(), L = 0.f;
+  // ---- global max and sum per head: wave w takes heads w, w + 4, ...; their chains of loads, exponentials and
+  //      lane exchanges run side by side ---------------------------------------------------------------------
+  {
+    constexpr int NG = (G + 3) / 4;             // heads per wave
+    float M[NG], L[NG];
+#pragma unroll
+    for (int j = 0; j < NG; ++j) { M[j] = -__builtin_inff(); L[j] = 0.f; }
     for (int s = lane; s < a.n_slices; s += WAVE) {
-      const float ms = pml[(s * G + g) * 2], ls = pml[(s * G + g) * 2 + 1];
-      if (ls > 0.f) {
-        const float mn = fmaxf(M, ms);
-        L = L * expf(M - mn) + ls * expf(ms - mn);
-        M = mn;
+      float2 ml[NG];
+#pragma unroll
+      for (int j = 0; j < NG; ++j)
+        ml[j] = *reinterpret_cast<const float2*>(pml + (s * G + min(wave + 4 * j, G - 1)) * 2);
+#pragma unroll
+      for (int j = 0; j < NG; ++j) {
+        if (ml[j].y > 0.f) {
+          const float mn = fmaxf(M[j], ml[j].x);
+          L[j] = L[j] * expf(M[j] - mn) + ml[j].y * expf(ml[j].x - mn);
+          M[j] = mn;
+        }
       }
     }
     // the wave's maximum first (no exponentials), then one rescaling per lane and a plain sum
-    float Mw = M;
+    float Mw[NG], Lw[NG];
 #pragma unroll
-    for (int off = 1; off < WAVE; off <<= 1) Mw = fmaxf(Mw, __shfl_xor(Mw, off));
-    float Lw = (L > 0.f) ? L * expf(M - Mw) : 0.f;
+    for (int j = 0; j < NG; ++j) Mw[j] = M[j];
 #pragma unroll
-    for (int off = 1; off < WAVE; off <<= 1) Lw += __shfl_xor(Lw, off);
-    if (lane == 0) { sM[g] = Mw; sL[g] = Lw; }
+    for (int off = 1; off < WAVE; off <<= 1)
+#pragma unroll
+      for (int j = 0; j < NG; ++j) Mw[j] = fmaxf(Mw[j], __shfl_xor(Mw[j], off));
+#pragma unroll
+    for (int j = 0; j < NG; ++j) Lw[j] = (L[j] > 0.f) ? L[j] * expf(M[j] - Mw[j]) : 0.f;
+#pragma unroll
+    for (int off = 1; off < WAVE; off <<= 1)
+#pragma unroll
+      for (int j = 0; j < NG; ++j) Lw[j] += __shfl_xor(Lw[j], off);
+#pragma unroll
+    for (int j = 0; j < NG; ++j)
+      if (lane == 0 && wave + 4 * j < G) { sM[wave + 4 * j] = Mw[j]; sL[wave + 4 * j] = Lw[j]; }
   }
   __syncthreads();
 
@@ -394,12 +413,13 @@ __global__ __launch_bounds__(256) void attend_combine_kernel(DevDesc d, AttendAr
   //      of two): workgroup bx takes G*D/nb output elements, `tpe` threads per
   //      element, each summing every tpe-th slice with eight loads in flight.  A
   //      unit cut into many slices (few units, long lists) gets 16 threads per
-  //      element and up to 32 workgroups, so that a thread's walk over the slices
-  //      is one batch of loads; otherwise 4 threads and up to 8 workgroups. ----------
+  //      element, so that a thread's walk over the slices is one batch of loads;
+  //      otherwise 4 threads.  As many workgroups as the grid has and as there are
+  //      rounds of 256 / tpe elements: one round each at best. ----------
   const int tpe = (a.n_slices > 32) ? 16 : 4;
   const int epw = 256 / tpe;                  // output elements per workgroup and round
   int nb = 1;
-  while (nb * 2 <= 2 * tpe && nb * 2 <= (int)gridDim.x && G * D / (nb * 2) >= epw) nb *= 2;
+  while (nb * 2 <= (int)gridDim.x && G * D / (nb * 2) >= epw) nb *= 2;
   if ((int)blockIdx.x < nb) {
     __shared__ float sO[16][64];               // [slice share][output element of this round]
     const int per_wg = G * D / nb;             // a multiple of epw
