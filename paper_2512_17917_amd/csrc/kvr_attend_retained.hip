@@ -14,6 +14,11 @@
 // Online softmax per wave; the four waves of a workgroup are merged through LDS
 // into one partial per slice.
 //
+// Bound by HBM.  Alone, a wave requests the next tile's rows while it computes (168 registers keep three waves
+// per SIMD); the logits wait in LDS and leave together, 16 bytes a lane.  32 units x 29492 slots, 4 heads: 107 ->
+// 102 us = 4.7 TB/s (a large copy reaches 5.1); 40 units x 4104 slots, 8 heads: 32.4 -> 30.0 us.  Next to a staged kernel
+// there are no registers for it.
+//
 // A workgroup walks over (unit, slice) items with a grid stride, so the launch
 // can be as wide as the item count (stand-alone: many workgroups per CU hide the
 // HBM latency) or as narrow as one workgroup per CU (next to the staged kernel,
@@ -66,32 +71,50 @@ __device__ __forceinline__ uint4 stream_load16(const bf16_t* p) {
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-__device__ __forceinline__ void load_tile(RetTile& t, const bf16_t* __restrict__ kret,
-                                          const bf16_t* __restrict__ vret, const int32_t* __restrict__ rp,
-                                          int t0, int t_end, int ret_cap, int r16, int col) {
+__device__ __forceinline__ void load_k(RetTile& t, const bf16_t* __restrict__ kret, int t0, int ret_cap, int r16,
+                                       int col) {
   const int tk = min(t0 + col, ret_cap - 1);
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk)
     t.ka[kk] = stream_load16(kret + (size_t)tk * D + 32 * kk + 8 * r16);
+}
+__device__ __forceinline__ void load_pos_v(RetTile& t, const bf16_t* __restrict__ vret,
+                                           const int32_t* __restrict__ rp, int t0, int t_end, int ret_cap, int r16,
+                                           int col) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int tt = t0 + 4 * r16 + j;
-    const int tc = min(tt, ret_cap - 1);
+    const int x = rp ? rp[min(tt, ret_cap - 1)] : tt;
+    t.pos[j] = (tt < t_end) ? x : -1;
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int tc = min(t0 + 4 * r16 + j, ret_cap - 1);
     t.vv[j] = stream_load16(vret + (size_t)tc * D + 8 * col);
-    t.pos[j] = (tt < t_end) ? (rp ? rp[tc] : tt) : -1;
   }
 }
 
-template <int G>
-__device__ __forceinline__ void compute_tile(const RetTile& t, const uint4 (&qb)[4], float scale, int t0,
-                                             int t_end, int r16, int col, float* __restrict__ logits_unit,
-                                             float& m_run, float& l_run, float (&acc)[G][8]) {
+// One 16-token tile.  NEXT: the tile at t_next follows, and its K rows are requested as soon as this tile's are
+// consumed, its positions and V rows behind this tile's p.v, all into the same registers.  No global store may sit
+// between these loads (reads and writes complete in no common order, so a wait for a read with a write outstanding
+// is a wait for everything): the logits go to s_log.
+template <int G, bool NEXT>
+__device__ __forceinline__ void compute_tile(RetTile& t, const uint4 (&qb)[4], const bf16_t* __restrict__ kret,
+                                             const bf16_t* __restrict__ vret, const int32_t* __restrict__ rp,
+                                             float scale, int t0, int t_next, int t_end, int ret_cap, int r16, int col,
+                                             float* __restrict__ s_log, float& m_run, float& l_run,
+                                             float (&acc)[G][8]) {
   const float NEG_INF = -__builtin_inff();
   f32x4_t S = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk)
     S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, t.ka[kk]),
                                                 __builtin_bit_cast(bf16x8_t, qb[kk]), S, 0, 0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (NEXT) {
+    load_k(t, kret, t_next, ret_cap, r16, col);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   float s[4];
   bool invalid = false;
 #pragma unroll
@@ -100,12 +123,9 @@ __device__ __forceinline__ void compute_tile(const RetTile& t, const uint4 (&qb)
     s[i] = ok ? S[i] * scale : NEG_INF;
     invalid = invalid || t.pos[i] < 0;
   }
-  if (logits_unit != nullptr && col < G) {
+  if (col < G) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int tt = t0 + 4 * r16 + i;
-      if (tt < t_end) logits_unit[(size_t)tt * G + col] = s[i];
-    }
+    for (int i = 0; i < 4; ++i) s_log[(4 * r16 + i) * G + col] = s[i];
   }
   float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
   mx = fmaxf(mx, __shfl_xor(mx, 16));
@@ -136,10 +156,14 @@ __device__ __forceinline__ void compute_tile(const RetTile& t, const uint4 (&qb)
       for (int c = 0; c < 8; ++c) v[c] = dead ? 0.f : v[c];
     }
     AccStep<G, 0>::fma(acc, p[j], v);
+    if constexpr (NEXT) __builtin_amdgcn_sched_barrier(0);       // one row's floats at a time: registers
+  }
+  if constexpr (NEXT) {
+    load_pos_v(t, vret, rp, t_next, t_end, ret_cap, r16, col);
   }
 }
 
-template <int G>
+template <int G, bool AHEAD>
 __device__ __forceinline__ void attend_retained_body(const DevDesc& d, const AttendArgs& a, int n_rslices) {
   constexpr int NW = 4;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -147,7 +171,8 @@ __device__ __forceinline__ void attend_retained_body(const DevDesc& d, const Att
   const int tot_cap = a.ret_cap + a.vague_cap;
   const int n_items = d.B * d.Hkv * n_rslices;
   const float NEG_INF = -__builtin_inff();
-  __shared__ float s_acc[NW][G][D];
+  // logits of the slice while it is walked, then the waves' sums [NW][G][D]
+  extern __shared__ __align__(16) float s_dyn[];
   __shared__ float s_m[NW][G], s_l[NW][G];
 
   // Same issue priority as the lower of the two levels that the staged kernel's
@@ -163,6 +188,13 @@ __device__ __forceinline__ void attend_retained_body(const DevDesc& d, const Att
     const int32_t* rp = a.ret_pos ? a.ret_pos + (size_t)unit * a.ret_cap : nullptr;
     float* logits_unit = a.logits ? a.logits + (size_t)unit * tot_cap * G : nullptr;
 
+    const int n_tiles = (t_end > t_begin) ? (t_end - t_begin + 15) >> 4 : 0;
+    int ti = wave;
+    RetTile tile;
+    if (AHEAD && ti < n_tiles) {
+      load_k(tile, kret, t_begin + ti * 16, a.ret_cap, r16, col);
+      load_pos_v(tile, vret, rp, t_begin + ti * 16, t_end, a.ret_cap, r16, col);
+    }
     uint4 qb[4];
     {
       const bf16_t* q = (const bf16_t*)a.q + ((size_t)b * d.Hq + (size_t)hk * G + (col < G ? col : 0)) * D + 8 * r16;
@@ -179,11 +211,20 @@ __device__ __forceinline__ void attend_retained_body(const DevDesc& d, const Att
 #pragma unroll
       for (int c = 0; c < 8; ++c) acc[g][c] = 0.f;
 
-    const int n_tiles = (t_end > t_begin) ? (t_end - t_begin + 15) >> 4 : 0;
-    for (int ti = wave; ti < n_tiles; ti += NW) {
-      RetTile ta;
-      load_tile(ta, kret, vret, rp, t_begin + ti * 16, t_end, a.ret_cap, r16, col);
-      compute_tile<G>(ta, qb, d.scale, t_begin + ti * 16, t_end, r16, col, logits_unit, m_run, l_run, acc);
+    if constexpr (AHEAD) {
+      for (; ti + NW < n_tiles; ti += NW)
+        compute_tile<G, true>(tile, qb, kret, vret, rp, d.scale, t_begin + ti * 16, t_begin + (ti + NW) * 16, t_end,
+                              a.ret_cap, r16, col, s_dyn + ti * 16 * G, m_run, l_run, acc);
+      if (ti < n_tiles)
+        compute_tile<G, false>(tile, qb, kret, vret, rp, d.scale, t_begin + ti * 16, 0, t_end, a.ret_cap, r16, col,
+                               s_dyn + ti * 16 * G, m_run, l_run, acc);
+    } else {
+      for (; ti < n_tiles; ti += NW) {
+        load_k(tile, kret, t_begin + ti * 16, a.ret_cap, r16, col);
+        load_pos_v(tile, vret, rp, t_begin + ti * 16, t_end, a.ret_cap, r16, col);
+        compute_tile<G, false>(tile, qb, kret, vret, rp, d.scale, t_begin + ti * 16, 0, t_end, a.ret_cap, r16, col,
+                               s_dyn + ti * 16 * G, m_run, l_run, acc);
+      }
     }
 
     // the four 16-lane rows of the wave hold different tokens: add them
@@ -197,7 +238,19 @@ __device__ __forceinline__ void attend_retained_body(const DevDesc& d, const Att
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);
 
-    __syncthreads();             // the previous item's readers are done with the LDS arrays
+    __syncthreads();             // the slice's logits are complete
+    if (logits_unit != nullptr) {
+      const int n = (t_end - t_begin) * G;       // floats
+      float* dst = logits_unit + (size_t)t_begin * G;
+      if constexpr (G % 4 == 0) {
+        for (int i = threadIdx.x * 4; i < n; i += 1024)
+          *reinterpret_cast<float4*>(dst + i) = *reinterpret_cast<const float4*>(s_dyn + i);
+      } else {
+        for (int i = threadIdx.x; i < n; i += 256) dst[i] = s_dyn[i];
+      }
+    }
+    __syncthreads();             // everyone has read them: the sums may take their place
+    float (*s_acc)[G][D] = reinterpret_cast<float (*)[G][D]>(s_dyn);
     if (r16 == 0) {
 #pragma unroll
       for (int g = 0; g < G; ++g)
@@ -223,21 +276,22 @@ __device__ __forceinline__ void attend_retained_body(const DevDesc& d, const Att
       po[idx] = O;
       if (c == 0) { pml[g * 2] = M; pml[g * 2 + 1] = L; }
     }
+    __syncthreads();             // the next item writes its logits over the sums
   }
 }
 
-// Two kernels around the same body.  Alone, the kernel takes the registers it likes (135 for G = 4).  Next to
+// Two kernels around the same body.  Alone, the kernel may use what three waves per SIMD leave (one head: four).  Next to
 // the staged kernel it is capped at 124 + 4 accumulation registers (the attribute counts in units of two on
 // this target): 2 x 192 (two waves of the staged kernel, which then needs no spills) + 128 fill a SIMD's 512
 // registers exactly; the few spills of this kernel, which waits for HBM most of the time, cost nothing.
 template <int G>
-__global__ __launch_bounds__(256) void attend_retained_kernel(DevDesc d, AttendArgs a, int n_rslices) {
-  attend_retained_body<G>(d, a, n_rslices);
+__global__ __launch_bounds__(256, (G <= 1 ? 4 : G <= 4 ? 3 : 2)) void attend_retained_kernel(DevDesc d, AttendArgs a, int n_rslices) {
+  attend_retained_body<G, true>(d, a, n_rslices);
 }
 template <int G>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(62))) void attend_retained_shared_kernel(
     DevDesc d, AttendArgs a, int n_rslices) {
-  attend_retained_body<G>(d, a, n_rslices);
+  attend_retained_body<G, false>(d, a, n_rslices);
 }
 
 // Third form, 76 + 4 registers: what two waves of the general staged kernel with 16- or 8-channel chunks and
@@ -246,7 +300,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(62))) void atte
 template <int G>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(38))) void attend_retained_tight_kernel(
     DevDesc d, AttendArgs a, int n_rslices) {
-  attend_retained_body<G>(d, a, n_rslices);
+  attend_retained_body<G, false>(d, a, n_rslices);
 }
 
 hipError_t launch_attend_retained(const DevDesc& d, const AttendArgs& a, int n_rslices, int max_wgs,
@@ -255,24 +309,25 @@ hipError_t launch_attend_retained(const DevDesc& d, const AttendArgs& a, int n_r
   if (max_wgs > 0 && n_wgs > max_wgs) n_wgs = max_wgs;
   if (n_wgs < 1) return hipSuccess;
   const dim3 grid(n_wgs), block(256);
+  const size_t lds = (size_t)d.G * 4 * std::max(4 * D, (a.slice_tokens + 15) / 16 * 16);   // <= 32 KB (1024 tokens, G = 8)
   if (reg_form == 2 && d.G == 4) {      // next to the general staged kernel in its widest form
-    hipLaunchKernelGGL(attend_retained_tight_kernel<4>, grid, block, 0, st, d, a, n_rslices);
+    hipLaunchKernelGGL(attend_retained_tight_kernel<4>, grid, block, lds, st, d, a, n_rslices);
     return hipGetLastError();
   }
   if (reg_form == 1) {                  // next to the 64-channel staged kernel
     switch (d.G) {
-      case 1: hipLaunchKernelGGL(attend_retained_shared_kernel<1>, grid, block, 0, st, d, a, n_rslices); break;
-      case 2: hipLaunchKernelGGL(attend_retained_shared_kernel<2>, grid, block, 0, st, d, a, n_rslices); break;
-      case 4: hipLaunchKernelGGL(attend_retained_shared_kernel<4>, grid, block, 0, st, d, a, n_rslices); break;
+      case 1: hipLaunchKernelGGL(attend_retained_shared_kernel<1>, grid, block, lds, st, d, a, n_rslices); break;
+      case 2: hipLaunchKernelGGL(attend_retained_shared_kernel<2>, grid, block, lds, st, d, a, n_rslices); break;
+      case 4: hipLaunchKernelGGL(attend_retained_shared_kernel<4>, grid, block, lds, st, d, a, n_rslices); break;
       default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
   }
   switch (d.G) {
-    case 1: hipLaunchKernelGGL(attend_retained_kernel<1>, grid, block, 0, st, d, a, n_rslices); break;
-    case 2: hipLaunchKernelGGL(attend_retained_kernel<2>, grid, block, 0, st, d, a, n_rslices); break;
-    case 4: hipLaunchKernelGGL(attend_retained_kernel<4>, grid, block, 0, st, d, a, n_rslices); break;
-    case 8: hipLaunchKernelGGL(attend_retained_kernel<8>, grid, block, 0, st, d, a, n_rslices); break;
+    case 1: hipLaunchKernelGGL(attend_retained_kernel<1>, grid, block, lds, st, d, a, n_rslices); break;
+    case 2: hipLaunchKernelGGL(attend_retained_kernel<2>, grid, block, lds, st, d, a, n_rslices); break;
+    case 4: hipLaunchKernelGGL(attend_retained_kernel<4>, grid, block, lds, st, d, a, n_rslices); break;
+    case 8: hipLaunchKernelGGL(attend_retained_kernel<8>, grid, block, lds, st, d, a, n_rslices); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
