@@ -15,6 +15,8 @@
 // kvr_attend_staged.hip.
 #include "kvr_launch.h"
 
+#include <algorithm>
+
 namespace kvr {
 
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -278,12 +280,52 @@ __global__ __launch_bounds__(256) void attend_main_kernel(DevDesc d, AttendArgs 
 // ---------------------------------------------------------------------------
 
 template <int G>
-__global__ __launch_bounds__(256) void attend_combine_kernel(DevDesc d, AttendArgs a) {
+__global__ __launch_bounds__(256, (G <= 2 ? 8 : G <= 4 ? 7 : G == 8 ? 5 : 4)) void attend_combine_kernel(DevDesc d, AttendArgs a) {
   const int unit = blockIdx.y;
   const int b = unit / d.Hkv, hk = unit % d.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   __shared__ float sM[G], sL[G];
   const float* pml = a.part_ml + (size_t)unit * a.n_slices * G * 2;
+
+  // ---- the unit's output: spread over the first nb workgroups of the unit (a power
+  //      of two): workgroup bx takes G*D/nb output elements in rounds of 256/tpe, `tpe`
+  //      threads per element, each summing every tpe-th slice with eight loads in
+  //      flight.  tpe is the one of 4, 8, 16 that takes the fewest batches of loads, rounds
+  //      x batches per round, on the grid there is.  The first batch is requested here,
+  //      ahead of the statistics.  Against 4 or 16 threads by the slice count alone, at most 8 or 32 workgroups and
+  //      no look-ahead, us: 8 units, 83 slices 10.1 -> 8.8; 64 units, 12 slices, 3 workgroups per unit 9.6 -> 7.4;
+  //      40 units, 35 slices, 8 heads 18.7 -> 15.0; 16 units, 93 slices 22 -> 20. ----------
+  int tpe = 4, best = 1 << 30;
+#pragma unroll
+  for (int c = 4; c <= 16; c *= 2) {
+    int n = 1;
+    while (n * 2 <= (int)gridDim.x && G * D / (n * 2) >= 256 / c) n *= 2;
+    const int cost = (G * D / n) / (256 / c) * ((a.n_slices + 8 * c - 1) / (8 * c));
+    if (cost < best) { best = cost; tpe = c; }
+  }
+  const int epw = 256 / tpe;                  // output elements per workgroup and round
+  int nb = 1;
+  while (nb * 2 <= (int)gridDim.x && G * D / (nb * 2) >= epw) nb *= 2;
+  const bool do_out = (int)blockIdx.x < nb;
+  const int per_wg = G * D / nb;              // a multiple of epw
+  const int el = tid % epw, sq = tid / epw;
+  const float* po = a.part_o + (size_t)unit * a.n_slices * G * D;
+  float bv[8];
+  float2 bm[8];                               // (maximum, sum) of the slice
+  auto load_batch = [&](int idx, int s0) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int s_ = s0 + tpe * j;
+      bv[j] = 0.f;
+      bm[j] = make_float2(0.f, 0.f);
+      if (s_ < a.n_slices) {
+        bv[j] = po[(size_t)s_ * G * D + idx];
+        bm[j] = *reinterpret_cast<const float2*>(pml + (s_ * G + idx / D) * 2);
+      }
+    }
+  };
+  constexpr bool EARLY = G < 16;              // 16 columns: the logits take the registers (four waves per SIMD)
+  if (EARLY && do_out) load_batch(blockIdx.x * per_wg + el, sq);
 
   // ---- score pass, first half: everything that does not depend on the global
   //      statistics is requested before they are formed (token positions, the
@@ -377,17 +419,20 @@ __global__ __launch_bounds__(256) void attend_combine_kernel(DevDesc d, AttendAr
 
   // ---- score pass, second half ----------------------------------------------------
   if (do_scores) {
-    float invL[G], M[G];
+    float acc[U];
 #pragma unroll
-    for (int g = 0; g < G; ++g) { M[g] = sM[g]; invL[g] = sL[g] > 0.f ? 1.f / sL[g] : 0.f; }
+    for (int u = 0; u < U; ++u) acc[u] = 0.f;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      float acc = 0.f;
+    for (int g = 0; g < G; ++g) {
+      const float M = sM[g], L = sL[g];
+      const float invL = L > 0.f ? 1.f / L : 0.f;
 #pragma unroll
-      for (int g = 0; g < G; ++g)
-        if (x[u][g] != -__builtin_inff()) acc += __expf(x[u][g] - M[g]) * invL[g];
-      if (pos[u] >= 0) sc[pos[u]] = old[u] + acc;
+      for (int u = 0; u < U; ++u)
+        if (x[u][g] != -__builtin_inff()) acc[u] += __expf(x[u][g] - M) * invL;
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (pos[u] >= 0) sc[pos[u]] = old[u] + acc[u];
     // tokens beyond the launch width (the dispatch covers every token with one
     // round; this loop only runs if a caller launches a narrower grid)
     for (int base = (blockIdx.x + gridDim.x) * 256 * U; base < total; base += gridDim.x * 256 * U) {
@@ -400,63 +445,35 @@ __global__ __launch_bounds__(256) void attend_combine_kernel(DevDesc d, AttendAr
         else ps = a.vague_pos[(size_t)unit * a.vague_cap + (t - a.ret_cap)];
         if (ps < 0 || ps >= a.n_cap) continue;
         const float* lg = a.logits + ((size_t)unit * tot_cap + t) * G;
-        float acc = 0.f;
+        float p = 0.f;
 #pragma unroll
         for (int g = 0; g < G; ++g)
-          if (lg[g] != -__builtin_inff()) acc += __expf(lg[g] - M[g]) * invL[g];
-        sc[ps] += acc;
+          if (lg[g] != -__builtin_inff()) p += __expf(lg[g] - sM[g]) * (sL[g] > 0.f ? 1.f / sL[g] : 0.f);
+        sc[ps] += p;
       }
     }
   }
 
-  // ---- the unit's output: spread over the first nb workgroups of the unit (a power
-  //      of two): workgroup bx takes G*D/nb output elements, `tpe` threads per
-  //      element, each summing every tpe-th slice with eight loads in flight.  A
-  //      unit cut into many slices (few units, long lists) gets 16 threads per
-  //      element, so that a thread's walk over the slices is one batch of loads;
-  //      otherwise 4 threads.  As many workgroups as the grid has and as there are
-  //      rounds of 256 / tpe elements: one round each at best. ----------
-  const int tpe = (a.n_slices > 32) ? 16 : 4;
-  const int epw = 256 / tpe;                  // output elements per workgroup and round
-  int nb = 1;
-  while (nb * 2 <= (int)gridDim.x && G * D / (nb * 2) >= epw) nb *= 2;
-  if ((int)blockIdx.x < nb) {
-    __shared__ float sO[16][64];               // [slice share][output element of this round]
-    const int per_wg = G * D / nb;             // a multiple of epw
-    const float* po = a.part_o + (size_t)unit * a.n_slices * G * D;
+  // ---- the output elements ------------------------------------------------------------
+  if (do_out) {
+    __shared__ float sO[256];                  // [slice share][output element of this round]
     for (int o0 = 0; o0 < per_wg; o0 += epw) {
-      const int el = tid % epw, sq = tid / epw;
       const int idx = blockIdx.x * per_wg + o0 + el;
       const int g = idx / D;
       const float M = sM[g];
       float o = 0.f;
       for (int s0 = sq; s0 < a.n_slices; s0 += tpe * 8) {
-        float v[8], wgt[8];
+        if (!EARLY || o0 != 0 || s0 != sq) load_batch(idx, s0);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int s_ = s0 + tpe * j;
-          v[j] = 0.f;
-          wgt[j] = 0.f;
-          if (s_ < a.n_slices) {
-            v[j] = po[(size_t)s_ * G * D + idx];
-            const float ms = pml[(s_ * G + g) * 2], ls = pml[(s_ * G + g) * 2 + 1];
-            wgt[j] = (ls > 0.f) ? expf(ms - M) : 0.f;
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) o = fmaf(v[j], wgt[j], o);
+        for (int j = 0; j < 8; ++j) o = fmaf(bv[j], (bm[j].y > 0.f) ? expf(bm[j].x - M) : 0.f, o);
       }
       __syncthreads();                         // previous round's readers are done with sO
-      sO[sq][el] = o;
+      sO[sq * epw + el] = o;
       __syncthreads();
       if (sq == 0) {
         float tot = 0.f;
-        if (tpe == 4) {
-          tot = (sO[0][el] + sO[1][el]) + (sO[2][el] + sO[3][el]);
-        } else {
-#pragma unroll
-          for (int k = 0; k < 16; k += 4) tot += (sO[k][el] + sO[k + 1][el]) + (sO[k + 2][el] + sO[k + 3][el]);
-        }
+        for (int k = 0; k < tpe; k += 4)
+          tot += (sO[k * epw + el] + sO[(k + 1) * epw + el]) + (sO[(k + 2) * epw + el] + sO[(k + 3) * epw + el]);
         const float L = sL[g];
         // column g of the partials = (query tq, head gh of the group); out is [B, n_q, Hq, D]
         const int tq = g / d.G, gh = g % d.G;
@@ -489,6 +506,9 @@ hipError_t launch_attend_combine(const DevDesc& d, const AttendArgs& a, int n_co
   const int units = d.B * d.Hkv;
   const long long tot_cap = (long long)a.ret_cap + a.vague_cap;
   int cx = (int)((tot_cap + 1023) / 1024);
+  // few tokens and few units: workgroups for the output alone, 64 elements each, as long as the chip has room
+  const int want = std::min(n_cols * D / 64, 512 / units);
+  if (cx < want) cx = want;
   if (cx < 1) cx = 1;
   const dim3 grid(cx, units), block(256);
   switch (n_cols) {

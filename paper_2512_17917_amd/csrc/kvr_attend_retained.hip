@@ -25,6 +25,8 @@
 // whose registers and LDS leave room for exactly that).
 #include "kvr_launch.h"
 
+#include <algorithm>
+
 namespace kvr {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
