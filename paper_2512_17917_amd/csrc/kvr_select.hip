@@ -9,12 +9,17 @@
 // keys.  Two ways to find the cut:
 //   - n_e small (the decode steady state evicts one token per unit per step):
 //     n_e rounds of a block-wide minimum over keys above the previous minimum;
-//   - otherwise an 8-pass radix select of the k-th largest key on LDS histograms
-//     whose 256 bins are scanned by 256 threads.
+//   - otherwise a radix select of the k-th largest key, eleven bits per pass on an LDS
+//     histogram with two bins per thread; it stops at the digit where a bin is taken whole
+//     (two or three passes unless scores are equal; a digit narrower than the exponent would
+//     put most of a prompt's scores into a handful of bins).
 // Up to 8192 slots the keys are computed once and stay in registers (8 per
 // thread); larger slot arrays (a whole prompt) recompute them from memory in
-// every pass.  The evicted slots are emitted in ascending slot order with a
-// ballot / prefix-sum compaction.
+// every pass.  The evicted slots are emitted in ascending slot order: ballots count
+// per wave and chunk of 1024 slots, one scan over up to 128 chunks places them.
+// Bound by one workgroup's chain of memory round trips and passes (one CU per unit).  Against eight passes
+// of eight bits, two dependent loads per slot and three barriers per chunk, us: 64 units x 32768 slots 88 -> 66;
+// 8 units 85 -> 55; 16 units x 131072 slots 526 -> 219; 16 units' fused update, 29493 slots 29 -> 26.
 //
 // kvr_step_update runs append -> select -> encode (small regime) of a unit in
 // one workgroup (slot arrays up to 32768 entries: 8 or 32 slots per thread), one launch instead of three; the steps communicate through the
@@ -30,8 +35,27 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(
     int ret_cap, const int32_t* __restrict__ n_ctx, int n_recent, int k_cand,
     int32_t* __restrict__ evict_slot, int32_t* __restrict__ evict_pos, int32_t* __restrict__ n_evict,
     int evict_cap, int32_t* __restrict__ vague_pos, int32_t* __restrict__ n_vague, int vague_cap) {
-  select_body<REG, KPT>(d, blockIdx.x, scores, n_cap, ret_pos, ret_cap, n_ctx, n_recent, k_cand, evict_slot,
-                   evict_pos, n_evict, evict_cap, vague_pos, n_vague, vague_cap);
+  if constexpr (REG) {
+    // all positions of a thread, then all scores: two rounds of loads instead of two per slot
+    const int32_t* rp = ret_pos + (size_t)blockIdx.x * ret_cap;
+    const float* sc = scores + (size_t)blockIdx.x * n_cap;
+    const int recent_from = n_ctx[blockIdx.x / d.Hkv] - n_recent;
+    int pre[KPT];
+    float pre_sc[KPT];
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+      const int s = j * SEL_THREADS + threadIdx.x;
+      pre[j] = (s < ret_cap) ? rp[s] : -1;
+    }
+#pragma unroll
+    for (int j = 0; j < KPT; ++j)
+      pre_sc[j] = (pre[j] >= 0 && pre[j] < recent_from && pre[j] < n_cap) ? sc[pre[j]] : 0.f;
+    select_body<REG, KPT>(d, blockIdx.x, scores, n_cap, ret_pos, ret_cap, n_ctx, n_recent, k_cand, evict_slot,
+                          evict_pos, n_evict, evict_cap, vague_pos, n_vague, vague_cap, pre, pre_sc);
+  } else {
+    select_body<REG, KPT>(d, blockIdx.x, scores, n_cap, ret_pos, ret_cap, n_ctx, n_recent, k_cand, evict_slot,
+                          evict_pos, n_evict, evict_cap, vague_pos, n_vague, vague_cap);
+  }
 }
 
 hipError_t launch_select(const DevDesc& d, const float* scores, long long n_cap, int32_t* ret_pos,

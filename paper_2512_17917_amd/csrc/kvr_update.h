@@ -18,14 +18,19 @@ constexpr int SEL_REG_SLOTS = SEL_THREADS * SEL_KPT;
 constexpr int SEL_SMALL = 8;                     // up to this many evictions: repeated minimum
 constexpr unsigned long long KEY_NONE = ~0ull;   // not a valid key (it would be a NaN score at position 0)
 constexpr int ENC_SMALL_CAP = 64;
+constexpr int SEL_DIGIT = 11;                    // bits per radix pass
+constexpr int SEL_BINS = 1 << SEL_DIGIT;         // two per thread
+constexpr int SEL_PLACE_CHUNKS = 128;            // chunks of SEL_THREADS slots that are emitted together
 
 struct SelShared {
-  unsigned hist[256];
+  union {
+    unsigned hist[SEL_BINS];                       // radix select
+    int place[SEL_PLACE_CHUNKS * SEL_WAVES];       // emission: evictions per (chunk, wave), then where each starts
+  };
   unsigned long long wmin[SEL_WAVES];
   unsigned long long prefix;
   int wsum[SEL_WAVES];
-  int wscan[4];
-  int krem, cnt, base;
+  int krem, cnt, whole;
   int nlist, list[SEL_SMALL];        // small eviction counts: the evicted slots, in any order
 };
 
@@ -188,32 +193,45 @@ __device__ __forceinline__ unsigned long long block_min(unsigned long long v, Se
   return r;
 }
 
-// 256 bins, scanned from the top: pick the bin where the running count reaches
-// krem; updates sh.krem and ors the digit into sh.prefix.  All threads call it.
-__device__ __forceinline__ void pick_digit(SelShared& sh, int byte) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int c = 0, incl = 0;
-  if (tid < 256) {
-    c = (int)sh.hist[255 - tid];
-    incl = c;
+// Inclusive scan of one value per thread over the workgroup; total (may be null): the sum.  The caller's barrier
+// must separate two calls.
+__device__ __forceinline__ int block_scan(int v, SelShared& sh, int* total = nullptr) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int incl = v;
 #pragma unroll
-    for (int off = 1; off < WAVE; off <<= 1) {
-      const int y = __shfl_up(incl, off);
-      if (lane >= off) incl += y;
-    }
-    if (lane == WAVE - 1) sh.wscan[wave] = incl;
+  for (int off = 1; off < WAVE; off <<= 1) {
+    const int y = __shfl_up(incl, off);
+    if (lane >= off) incl += y;
   }
+  if (lane == WAVE - 1) sh.wsum[wave] = incl;
   __syncthreads();
-  if (tid < 256) {
-    int before = 0;
+  int before = 0, tot = 0;
 #pragma unroll
-    for (int w_ = 0; w_ < 4; ++w_) before += (w_ < wave) ? sh.wscan[w_] : 0;
-    incl += before;
-    const int krem = sh.krem;
-    if (incl >= krem && incl - c < krem) {          // exactly one thread
-      sh.krem = krem - (incl - c);
-      sh.prefix |= (unsigned long long)(255 - tid) << (8 * byte);
-    }
+  for (int w_ = 0; w_ < SEL_WAVES; ++w_) {
+    const int c = sh.wsum[w_];
+    before += (w_ < wave) ? c : 0;
+    tot += c;
+  }
+  if (total) *total = tot;
+  return incl + before;
+}
+
+// The bins, scanned from the top: pick the one where the running count reaches
+// krem; updates sh.krem, ors the digit into sh.prefix and says in sh.whole whether
+// all keys of that bin are among the krem.  All threads call it, two bins each.
+__device__ __forceinline__ void pick_digit(SelShared& sh, int shift) {
+  static_assert(SEL_BINS == 2 * SEL_THREADS, "two bins per thread");
+  const int hi_bin = SEL_BINS - 1 - 2 * (int)threadIdx.x;
+  const int a = (int)sh.hist[hi_bin], b = (int)sh.hist[hi_bin - 1];
+  const int krem = sh.krem;
+  const int incl = block_scan(a + b, sh);            // its barrier: everyone has read krem
+  const int excl = incl - a - b;
+  if (excl < krem && krem <= incl) {                 // exactly one thread
+    const bool first = krem <= excl + a;
+    const int left = first ? krem - excl : krem - excl - a;
+    sh.krem = left;
+    sh.whole = left == (first ? a : b);
+    sh.prefix |= (unsigned long long)(first ? hi_bin : hi_bin - 1) << shift;
   }
   __syncthreads();
 }
@@ -247,16 +265,35 @@ __device__ __forceinline__ void select_body(
   // keys of this thread's slots: slot = j * SEL_THREADS + tid
   unsigned long long rkey[REG ? KPT : 1];
   const int n_chunks = (ret_cap + SEL_THREADS - 1) / SEL_THREADS;
-  auto get_key = [&](int j, unsigned long long& key) -> bool {
+  // f(chunk, eligible, key) for the chunks [jb, je) in order, the same ones in all threads; without registers the
+  // positions, then the scores of eight chunks are requested together
+  auto for_keys = [&](int jb, int je, auto&& f) {
     if constexpr (REG) {
-      key = rkey[j];
-      return key != KEY_NONE;
+#pragma unroll
+      for (int j = 0; j < KPT; ++j) f(j, rkey[j] != KEY_NONE, rkey[j]);
     } else {
-      return slot_key(rp, sc, j * SEL_THREADS + tid, ret_cap, recent_from, n_cap, key);
+      for (int j0 = jb; j0 < je; j0 += 8) {
+        int p8[8];
+        float s8[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int slot = (j0 + u) * SEL_THREADS + tid;
+          p8[u] = (j0 + u < je && slot < ret_cap) ? rp[slot] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          s8[u] = (p8[u] >= 0 && p8[u] < recent_from && p8[u] < n_cap) ? sc[p8[u]] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          unsigned long long key = KEY_NONE;
+          const bool ok = pos_key_val(p8[u], s8[u], (j0 + u) * SEL_THREADS + tid, ret_cap, recent_from, n_cap, key);
+          if (j0 + u < je) f(j0 + u, ok, key);
+        }
+      }
     }
   };
 
-  if (tid == 0) { sh.cnt = 0; sh.base = 0; sh.prefix = 0ull; sh.krem = k_cand; sh.nlist = 0; }
+  if (tid == 0) { sh.cnt = 0; sh.prefix = 0ull; sh.krem = k_cand; sh.nlist = 0; }
   __syncthreads();
   {
     int c = 0;
@@ -271,10 +308,7 @@ __device__ __forceinline__ void select_body(
         c += ok ? 1 : 0;
       }
     } else {
-      for (int j = 0; j < n_chunks; ++j) {
-        unsigned long long key;
-        c += get_key(j, key) ? 1 : 0;
-      }
+      for_keys(0, n_chunks, [&](int, bool ok, unsigned long long) { c += ok ? 1 : 0; });
     }
     if (c) atomicAdd(&sh.cnt, c);
   }
@@ -315,22 +349,22 @@ __device__ __forceinline__ void select_body(
     }
     cut = last;
   } else {
-    for (int byte = 7; byte >= 0; --byte) {
-      if (tid < 256) sh.hist[tid] = 0u;
+    // the pass stops where a bin is taken whole: with distinct scores after two or three digits, and no later than
+    // the last bit, since all keys are distinct
+    for (int shift = 64 - SEL_DIGIT, known = 64; ;
+         known = shift, shift = shift > SEL_DIGIT ? shift - SEL_DIGIT : 0) {     // bits from `known` up are decided
+      for (int i = tid; i < SEL_BINS; i += SEL_THREADS) sh.hist[i] = 0u;
       __syncthreads();
       const unsigned long long prefix = sh.prefix;
-#pragma unroll
-      for (int j = 0; j < (REG ? KPT : n_chunks); ++j) {
-        unsigned long long key;
-        if (get_key(j, key)) {
-          const bool match = (byte == 7) || ((key >> (8 * (byte + 1))) == (prefix >> (8 * (byte + 1))));
-          if (match) atomicAdd(&sh.hist[(unsigned)(key >> (8 * byte)) & 255u], 1u);
-        }
-      }
+      for_keys(0, n_chunks, [&](int, bool ok, unsigned long long key) {
+        const bool match = known >= 64 || (key >> known) == (prefix >> known);
+        if (ok && match) atomicAdd(&sh.hist[(unsigned)(key >> shift) & (SEL_BINS - 1)], 1u);
+      });
       __syncthreads();
-      pick_digit(sh, byte);
+      pick_digit(sh, shift);
+      if (sh.whole || shift == 0) break;             // uniform: read behind pick_digit's barrier
     }
-    cut = sh.prefix - 1;       // prefix = the k-th largest key; it stays
+    cut = sh.prefix - 1;       // the k largest keys are those from the prefix up; they stay
   }
 
   if (REG && n_e <= SEL_SMALL) {
@@ -364,37 +398,39 @@ __device__ __forceinline__ void select_body(
     return;
   }
 
-#pragma unroll
-  for (int j = 0; j < (REG ? KPT : n_chunks); ++j) {
-    if (REG && j >= n_chunks) break;
-    const int slot = j * SEL_THREADS + tid;
-    unsigned long long key = 0;
-    bool flag = get_key(j, key);
-    flag = flag && key <= cut;
-    const unsigned long long bal = __ballot(flag);
-    const int in_wave = __popcll(bal & ((1ull << lane) - 1ull));
-    if (lane == 0) sh.wsum[wave] = __popcll(bal);
+  // Ascending slot order = (chunk, wave, lane) order: count the evictions of every wave and chunk, scan, place.
+  static_assert(SEL_PLACE_CHUNKS * SEL_WAVES == 2 * SEL_THREADS, "two counters per thread");
+  int base = 0;
+  for (int c0 = 0; c0 < n_chunks; c0 += SEL_PLACE_CHUNKS) {
+    const int c1 = min(c0 + SEL_PLACE_CHUNKS, n_chunks);
+    const int n_cnt = (REG ? KPT : c1 - c0) * SEL_WAVES;
+    __syncthreads();                                 // nobody reads hist / the previous places any more
+    for_keys(c0, c1, [&](int j, bool ok, unsigned long long key) {
+      const unsigned long long bal = __ballot(ok && key <= cut);
+      if (lane == 0) sh.place[(j - c0) * SEL_WAVES + wave] = __popcll(bal);
+    });
     __syncthreads();
-    int before = 0, tot = 0;
-#pragma unroll
-    for (int w_ = 0; w_ < SEL_WAVES; ++w_) {
-      const int c = sh.wsum[w_];
-      before += (w_ < wave) ? c : 0;
-      tot += c;
-    }
-    const int base = sh.base;
-    if (flag) {
-      const int idx = base + before + in_wave;      // < n_e <= evict_cap
-      const int pos = key_pos(key);
-      evict_slot[(size_t)unit * evict_cap + idx] = slot;
-      evict_pos[(size_t)unit * evict_cap + idx] = pos;
-      if (ho && idx < ENC_SMALL_CAP) { ho->slot[idx] = slot; ho->pos[idx] = pos; }
-      rp[slot] = -1;
-      if (vague_pos && n_vague) vague_pos[(size_t)unit * vague_cap + nv_old + idx] = pos;
-    }
+    const int a = (2 * tid < n_cnt) ? sh.place[2 * tid] : 0, b_ = (2 * tid + 1 < n_cnt) ? sh.place[2 * tid + 1] : 0;
+    int total;
+    const int excl = base + block_scan(a + b_, sh, &total) - a - b_;
+    if (2 * tid < n_cnt) sh.place[2 * tid] = excl;
+    if (2 * tid + 1 < n_cnt) sh.place[2 * tid + 1] = excl + a;
     __syncthreads();
-    if (tid == 0) sh.base = base + tot;
-    __syncthreads();
+    for_keys(c0, c1, [&](int j, bool ok, unsigned long long key) {
+      const bool flag = ok && key <= cut;
+      const unsigned long long bal = __ballot(flag);
+      if (flag) {
+        const int slot = j * SEL_THREADS + tid;
+        const int idx = sh.place[(j - c0) * SEL_WAVES + wave] + __popcll(bal & ((1ull << lane) - 1ull));   // < n_e
+        const int pos = key_pos(key);
+        evict_slot[(size_t)unit * evict_cap + idx] = slot;
+        evict_pos[(size_t)unit * evict_cap + idx] = pos;
+        if (ho && idx < ENC_SMALL_CAP) { ho->slot[idx] = slot; ho->pos[idx] = pos; }
+        rp[slot] = -1;
+        if (vague_pos && n_vague) vague_pos[(size_t)unit * vague_cap + nv_old + idx] = pos;
+      }
+    });
+    base += total;
   }
   if (tid == 0) {
     n_evict[unit] = n_e;

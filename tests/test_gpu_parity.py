@@ -284,6 +284,18 @@ def test_select_bit_exact(kvr):
     run_select_case(kvr, rng, 1, 1, 33000, 33100, [33000], 3000, 9000, 33000, 33000, 32500, 0, score_levels=500)
 
 
+@pytest.mark.parametrize("slots,levels", [(8193, 1), (3000, 1), (32768, 3), (32769, None), (131072 + 70, 9),
+                                           (32768, None)])
+def test_select_radix_digits(kvr, slots, levels):
+    """The radix pass over all digits (one score for all: only the position's last bits decide), over a few
+    (distinct scores), and the emission behind it at the edges of its chunks: keys in registers up to the last
+    slot, one slot more, and more than 128 chunks of 1024 slots."""
+    rng = np.random.default_rng(77 + slots)
+    say("select radix digits", slots, levels)
+    more = {} if levels is None else {"score_levels": levels}
+    run_select_case(kvr, rng, 1, 2, slots, slots + 100, [slots], slots // 9, slots // 7, slots, slots, slots - 30, 2, **more)
+
+
 # ----------------------------------------------------------------------------- append
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_append(kvr, dtype):
