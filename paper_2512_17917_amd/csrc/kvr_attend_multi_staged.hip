@@ -419,9 +419,11 @@ int multi_staged_pad_tokens() { return MS_PAD_TOKENS; }
 
 // Tokens per workgroup, at least 256.  One workgroup (16 waves, the chunk in LDS) runs per CU, so a launch takes
 // ceil(workgroups / 256) turns of (fixed part + tokens of a workgroup); the fixed part (four chunk copies, the
-// reductions) costs about as much as 400 tokens.
+// reductions) costs about as much as 400 tokens.  At most as many parts as give every CU a workgroup, rounded up:
+// more would only grow the workspace.  40 units x 12706 tokens, 8 columns: 7 parts (280 workgroups, the last 24 on
+// a turn of their own) 82 us, 6 parts 49 us.
 int multi_staged_part_tokens(long long vague_cap, long long units) {
-  const long long n_max = 1024 / units + 1;
+  const long long n_max = (256 + units - 1) / units;
   double best = 1e30;
   long long best_t = vague_cap;
   for (long long n = 1; n <= n_max; ++n) {
