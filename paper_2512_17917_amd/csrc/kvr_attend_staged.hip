@@ -1,5 +1,6 @@
 // Staged attention kernel for the Vague index list (bf16 storage, values signed
-// only, G <= 4 query heads per kv head, r = 3 or 4 sketch rows).
+// only, G <= 4 query heads per kv head, r = 3 or 4 sketch rows) whose sketch is
+// wider than the 16-channel kernel takes (more than 4096 rows in all).
 //
 // Rebuilding a Vague token needs r rows of the K sketch and r rows of the V
 // sketch (Algorithm 2); with tens of thousands of Vague tokens per unit the
@@ -17,11 +18,10 @@
 //     each of its r rows starting at piece (lane mod CH/8), so that at any
 //     moment 8 neighbouring lanes read 8 different 16-byte bank groups; q is
 //     kept in registers in the same rotated order.  No cross-lane reduction.
-//   V phases: CH/16 lanes share one token (two pieces = 16 channels each) and
-//     accumulate p * v in registers across all of the wave's tokens; the
-//     token's weights come from their owner lane by a lane permute.  Lanes of
-//     odd token groups take their two pieces in the opposite order, so that 8
-//     neighbouring lanes (two tokens) again cover 8 different bank groups.
+//   V phases: the same lane rebuilds its token's CH channels and accumulates p * v in
+//     registers across all of the wave's tokens; odd lanes take the two pieces of a row
+//     in the opposite order, so that 8 neighbouring lanes again cover different bank
+//     groups.
 // Per-channel median of three on packed bf16: v_med3_f16 on the raw bit
 // patterns (both formats are sign-magnitude with the exponent above the
 // mantissa, so the order of finite values is the same; zeros of either sign
@@ -39,10 +39,10 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_kernel(DevDesc
   constexpr int NC = CH / 8;                 // 16-byte pieces per LDS row
   constexpr int NPH = D / CH;                // phases per tensor
   constexpr int ROWB = CH * 2;               // bytes per LDS row
-  constexpr int ROWB_LOG2 = (CH == 64) ? 7 : (CH == 32) ? 6 : (CH == 16) ? 5 : 4;
+  constexpr int ROWB_LOG2 = (CH == 16) ? 5 : 4;
   constexpr int PPL = (NC >= 2) ? 2 : 1;     // V phase: pieces per lane
   constexpr int LPT = NC / PPL;              // V phase: lanes per token
-  constexpr int TPW = WAVE / LPT;            // V phase: tokens per wave-iteration
+  static_assert(CH <= 16 && LPT == 1, "one lane per token in both phases");
   constexpr int VCH = PPL * 8;               // V phase: channels per lane
 
   // XCD-aware mapping: workgroup ids are dealt round-robin to the 8 XCDs, so all
@@ -60,7 +60,6 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_kernel(DevDesc
   // chunk buffer; it doubles as reduction scratch [32 rows][G][CH] floats
   const int sk_bytes = max((R * w * ROWB + 1023) & ~1023, 32 * G * CH * 4);
   unsigned char* s_sk = smem;
-  uint2* s_info = reinterpret_cast<uint2*>(smem + sk_bytes);
   float* s_red = reinterpret_cast<float*>(smem + sk_bytes + ST_KMAX * ST_THREADS * 8);   // [8][G][CH]
   float* s_stat = s_red + ST_WAVES * G * 64;                                               // [8][G] x 2
   uint4* s_q = reinterpret_cast<uint4*>(smem + sk_bytes + ST_KMAX * ST_THREADS * 8 + ST_WAVES * G * 64 * 4 + 1024);
@@ -104,7 +103,6 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_kernel(DevDesc
       vmask |= 1u << k;
     }
     info[k] = pk;
-    s_info[(k * ST_WAVES + wave) * 64 + lane] = pk;
   }
   asm volatile("" ::"v"(touched));       // the touch load has no other use: keep it
   if (tid < G * 16) {
@@ -128,24 +126,20 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_kernel(DevDesc
     lds_barrier();
     stage_chunk<NC, ROWB>(skg, s_sk, n_pieces, cc, tid);
     lds_barrier();
-    // the pieces of a row are taken in two halves so that only half of q (in
-    // this lane's rotated order) has to sit in registers at a time
-    constexpr int JH = (NC >= 8) ? NC / 2 : NC;
+    {
+      uint4 qreg[NC][G];
 #pragma unroll
-    for (int j0 = 0; j0 < NC; j0 += JH) {
-      uint4 qreg[JH][G];
+      for (int j = 0; j < NC; ++j)
 #pragma unroll
-      for (int j = 0; j < JH; ++j)
-#pragma unroll
-        for (int g = 0; g < G; ++g) qreg[j][g] = s_q[g * 16 + cc * NC + ((lane + j0 + j) & (NC - 1))];
+        for (int g = 0; g < G; ++g) qreg[j][g] = s_q[g * 16 + cc * NC + ((lane + j) & (NC - 1))];
 #pragma unroll
       for (int k = 0; k < ST_KMAX; ++k) {
         if (k < n_k) {
           int rb[R];
           row_offsets<R>(info[k], rb, ROWB_LOG2);
 #pragma unroll
-          for (int j = 0; j < JH; ++j) {
-            const int co = ((lane + j0 + j) & (NC - 1)) * 16;
+          for (int j = 0; j < NC; ++j) {
+            const int co = ((lane + j) & (NC - 1)) * 16;
             uint4 row[R];
 #pragma unroll
             for (int i = 0; i < R; ++i) row[i] = *reinterpret_cast<const uint4*>(s_sk + rb[i] + co);
@@ -245,34 +239,14 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_kernel(DevDesc
     for (int g = 0; g < G; ++g)
 #pragma unroll
       for (int c = 0; c < VCH; ++c) acc[g][c] = 0.f;
-    // With 4 lanes per token (CH = 64) the 4 lanes of a token group are one block
-    // of v_mfma_f32_4x4x4 (16 blocks): the group's 4 tokens of a round are the
-    // contraction index, lane `sub` supplies the weights of head `sub` (A) and
-    // one channel of the rebuilt values (B), and keeps that channel's 4 head
-    // sums (D).  The weights go in as bf16 hi + lo (two MFMAs), which carries 16
-    // mantissa bits; the values are bf16 already.  This replaces the float32
-    // multiply-adds of the vector ALUs, which are this kernel's bottleneck.
-    constexpr bool V_MFMA = (LPT == 4 && PPL == 2);
-    f32x4_t accm[V_MFMA ? 2 : 1][V_MFMA ? 8 : 1];
-    if constexpr (V_MFMA) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) accm[h][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
 #pragma unroll
     for (int k = 0; k < ST_KMAX; ++k) {
       if (k < n_k) {
-        uint4 med[V_MFMA ? 2 : 1][V_MFMA ? 4 : 1];
-        float psel[V_MFMA ? 4 : 1];
-#pragma unroll
-        for (int j8 = 0; j8 < LPT; ++j8) {
-          const int owner = j8 * TPW + tl;
-          // one lane per token: the lane is its own owner
-          const uint2 inf = (LPT == 1) ? info[k] : s_info[(k * ST_WAVES + wave) * 64 + owner];
+        {
+          const uint2 inf = info[k];
           float pg[G];
 #pragma unroll
-          for (int g = 0; g < G; ++g) pg[g] = (LPT == 1) ? s[k][g] : __shfl(s[k][g], owner);
+          for (int g = 0; g < G; ++g) pg[g] = s[k][g];
           int rb[R];
           row_offsets<R>(inf, rb, ROWB_LOG2);
           uint32_t fm[R];
@@ -290,13 +264,6 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_kernel(DevDesc
             fm[2] = info_neg<2>(inf) ? 0x80008000u : 0u;
             if constexpr (R > 3) fm[3] = info_neg<3>(inf) ? 0x80008000u : 0u;
           }
-          if constexpr (V_MFMA) {
-            float ph = pg[0];
-            if constexpr (G > 1) ph = (sub == 1) ? pg[1] : ph;
-            if constexpr (G > 2) ph = (sub == 2) ? pg[2] : ph;
-            if constexpr (G > 3) ph = (sub == 3) ? pg[3] : ph;
-            psel[j8] = (sub < G) ? ph : 0.f;
-          }
 #pragma unroll
           for (int h = 0; h < PPL; ++h) {
             const int co = (h == 0 ? pa : pb) * 16;
@@ -307,9 +274,7 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_kernel(DevDesc
               if (!(R == 3 && i == 0)) row[i] = xor4(row[i], fm[i]);
             }
             const uint4 m = median_piece<R>(row, MODE);
-            if constexpr (V_MFMA) {
-              med[h][j8] = m;
-            } else {
+            {
               const float v[8] = {bf_lo(m.x), bf_hi(m.x), bf_lo(m.y), bf_hi(m.y),
                                   bf_lo(m.z), bf_hi(m.z), bf_lo(m.w), bf_hi(m.w)};
 #pragma unroll
@@ -319,34 +284,7 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_kernel(DevDesc
             }
           }
         }
-        if constexpr (V_MFMA) {
-          // A: this lane's head, 4 tokens, as bf16 hi and lo parts
-          uint32_t hb[4], lb[4];
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const uint32_t pb_ = __float_as_uint(psel[t]);
-            hb[t] = pb_ & 0xffff0000u;
-            lb[t] = __float_as_uint(psel[t] - __uint_as_float(hb[t]));
-          }
-          const short4_t a_hi = pack_k4(pair_hi(hb[0], hb[1]), pair_hi(hb[2], hb[3]));
-          const short4_t a_lo = pack_k4(pair_hi(lb[0], lb[1]), pair_hi(lb[2], lb[3]));
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            pv_mfma<0>(med[h], a_hi, a_lo, accm[h]);
-            pv_mfma<1>(med[h], a_hi, a_lo, accm[h]);
-            pv_mfma<2>(med[h], a_hi, a_lo, accm[h]);
-            pv_mfma<3>(med[h], a_hi, a_lo, accm[h]);
-          }
-        }
       }
-    }
-    if constexpr (V_MFMA) {
-#pragma unroll
-      for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int c = 0; c < 8; ++c) acc[g][h * 8 + c] = accm[h][c][g];
     }
     // odd token groups hold their two pieces swapped: put them in piece order
     if constexpr (PPL == 2) {
@@ -411,8 +349,6 @@ static hipError_t launch_one(const DevDesc& d, const AttendArgs& a, const Attend
 template <int G, int R, int MODE>
 static hipError_t launch_ch(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan, hipStream_t st) {
   switch (plan.ch) {
-    case 64: return launch_one<G, R, 64, MODE>(d, a, plan, st);
-    case 32: return launch_one<G, R, 32, MODE>(d, a, plan, st);
     case 16: return launch_one<G, R, 16, MODE>(d, a, plan, st);
     case 8: return launch_one<G, R, 8, MODE>(d, a, plan, st);
     default: return hipErrorInvalidValue;

@@ -132,24 +132,6 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ short4_t pack_k4(uint32_t k01, uint32_t k23) {
   return __builtin_bit_cast(short4_t, make_uint2(k01, k23));
 }
-template <int DW>
-__device__ __forceinline__ uint32_t dword_of(const uint4& v) {
-  return DW == 0 ? v.x : DW == 1 ? v.y : DW == 2 ? v.z : v.w;
-}
-
-// One dword position (two channels) of a piece, for the 4 tokens of a block:
-// acc[2 DW] and acc[2 DW + 1] (4 head sums each) += weights x values.
-template <int DW>
-__device__ __forceinline__ void pv_mfma(const uint4 (&med)[4], short4_t a_hi, short4_t a_lo, f32x4_t (&acc)[8]) {
-  const uint32_t t0 = dword_of<DW>(med[0]), t1 = dword_of<DW>(med[1]);
-  const uint32_t t2 = dword_of<DW>(med[2]), t3 = dword_of<DW>(med[3]);
-  const short4_t b_even = pack_k4(pair_lo(t0, t1), pair_lo(t2, t3));
-  const short4_t b_odd = pack_k4(pair_hi(t0, t1), pair_hi(t2, t3));
-  acc[2 * DW] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_hi, b_even, acc[2 * DW], 0, 0, 0);
-  acc[2 * DW] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_lo, b_even, acc[2 * DW], 0, 0, 0);
-  acc[2 * DW + 1] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_hi, b_odd, acc[2 * DW + 1], 0, 0, 0);
-  acc[2 * DW + 1] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_lo, b_odd, acc[2 * DW + 1], 0, 0, 0);
-}
 
 // Workgroup barrier for data exchanged through LDS only: waits for this wave's
 // LDS traffic, not for its outstanding global stores (which __syncthreads would).
