@@ -10,10 +10,13 @@
 // Inside a chunk the unit of work is a *half piece*: 4 channels = 8 bytes, which
 // is exactly the contraction length of v_mfma_f32_4x4x4.
 //
-// Bound by vector-ALU issue.  Three rows, one layer's decode step against the general kernel with float32
-// p.v: 131072 tokens, 16 units 452 -> 233 us, 8 units 263 -> 173 us; 70000 tokens, 24 units 235 -> 187 us;
-// 42000 tokens, 48 units 259 -> 205 us, 8 units 92 -> 92 us.  With three rows a wave holds 176 registers (four:
+// Three rows, one layer's decode step against the general kernel with float32
+// p.v: 131072 tokens, 16 units 452 -> 235 us, 8 units 263 -> 175 us; 70000 tokens, 24 units 235 -> 189 us;
+// 42000 tokens, 48 units 259 -> 207 us, 8 units 92 -> 92 us.  With three rows a wave holds 192 registers (four:
 // 240), which leaves room for the retained-slot kernel next to it.
+// Error of a call's output against float64, relative in the 2-norm, three rows: 1.6e-7 (200 tokens) .. 3.0e-7 (101580), as
+// with the general kernel's float32 multiply-adds (1.7e-7 .. 3.2e-7); weights as two bf16 parts: 8e-6 .. 1.1e-5, three
+// parts cost 1 % of the time.  Four rows: two parts, 7e-6 .. 1.1e-5.
 //
 //  * K phases: one lane = one token.  The 4 lanes of a block read the same half
 //    piece of their tokens' rows (neighbouring blocks take different half pieces,
@@ -29,7 +32,7 @@
 //    function of the four values) g_0 is folded into the token's weight and the
 //    other rows are flipped relative to row 0; with the lower-middle rule every row
 //    is flipped by its own sign.  p.v on the same matrix instruction with the 4
-//    tokens as the contraction index; weights as bf16 hi + lo.
+//    tokens as the contraction index; weights as two or three bf16 parts.
 //  * Every loop over LDS reads is a pinned software pipeline (rows of the step
 //    after next requested, medians of the next step formed, matrix instruction of
 //    this step issued): two waves per SIMD cannot hide LDS latency for each other.
@@ -166,18 +169,28 @@ __device__ __forceinline__ uint2 v_median(const VItem<R>& it) {
   return median_rows_of<R, MODE>(x);
 }
 
-// acc[c] (4 head sums of channel c of the half piece) += weights (4 heads x 4 tokens,
-// bf16 hi + lo) x values (4 tokens x 4 channels)
-__device__ __forceinline__ void pv_half_piece(const uint2 (&med)[4], short4_t a_hi, short4_t a_lo, f32x4_t (&acc)[4]) {
+// A weight goes into the matrix instruction as a sum of bf16 parts, each the upper half of what the parts before it
+// leave.  Three rows: three parts, which hold all 24 bits of the float32 weight, as the float32 multiply-adds of the
+// general kernel do.  Four rows: two parts (16 bits).
+template <int R>
+__host__ __device__ constexpr int weight_parts() {
+  return R == 3 ? 3 : 2;
+}
+
+// acc[c] (4 head sums of channel c of the half piece) += weights (4 heads x 4 tokens, packed parts W: two dwords
+// each, largest first) x values (4 tokens x 4 channels)
+template <int NP>
+__device__ __forceinline__ void pv_half_piece(const uint2 (&med)[4], const uint32_t (&W)[2 * NP], f32x4_t (&acc)[4]) {
   short4_t b[4];
   b[0] = pack_k4(pair_lo(med[0].x, med[1].x), pair_lo(med[2].x, med[3].x));
   b[1] = pack_k4(pair_hi(med[0].x, med[1].x), pair_hi(med[2].x, med[3].x));
   b[2] = pack_k4(pair_lo(med[0].y, med[1].y), pair_lo(med[2].y, med[3].y));
   b[3] = pack_k4(pair_hi(med[0].y, med[1].y), pair_hi(med[2].y, med[3].y));
 #pragma unroll
-  for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_hi, b[c], acc[c], 0, 0, 0);
+  for (int p = 0; p < NP; ++p)
 #pragma unroll
-  for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_lo, b[c], acc[c], 0, 0, 0);
+    for (int c = 0; c < 4; ++c)
+      acc[c] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(pack_k4(W[2 * p], W[2 * p + 1]), b[c], acc[c], 0, 0, 0);
 }
 
 // The same value, but the compiler can no longer tell: whatever is derived from
@@ -247,7 +260,8 @@ __device__ __forceinline__ void k_pass(const unsigned char* s_sk, const uint2 (&
 // row: the quad's 4 tokens per round, same kind of pipeline.
 template <int NK, int R, int MODE>
 __device__ __forceinline__ void v_pass(const unsigned char* s_sk, const uint2 (&info)[S16_KMAX],
-                                       const uint32_t (&W)[S16_KMAX][4], int co, int turn, f32x4_t (&acc)[4]) {
+                                       const uint32_t (&W)[S16_KMAX][2 * weight_parts<R>()], int co, int turn,
+                                       f32x4_t (&acc)[4]) {
   VItem<R> buf[4];
   VOwn<R> own = v_own<R>(info[0]);
   v_fetch<0, R, MODE>(buf[0], own, s_sk, co);
@@ -272,7 +286,7 @@ __device__ __forceinline__ void v_pass(const unsigned char* s_sk, const uint2 (&
     if (k + 1 < NK) v_fetch<1, R, MODE>(buf[1], own, s_sk, co);
     KVR_PIN();
     med[3] = v_median<R, MODE>(buf[3]);
-    pv_half_piece(med, pack_k4(W[k][0], W[k][1]), pack_k4(W[k][2], W[k][3]), acc);
+    pv_half_piece<weight_parts<R>()>(med, W[k], acc);
     KVR_PIN();
   }
   __builtin_amdgcn_s_setprio(1);
@@ -453,28 +467,38 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged16_kernel(DevDe
   // ---- weights into matrix-core operand form ----------------------------------
   // The A operand of the V phases is, per lane, the weights of head `sub` for the
   // quad's 4 tokens: what the lane holds already.  The sign g_0 of each token (bit 0
-  // of its record, which lives in the lane that owns the token) is folded in, the
-  // weight is split into bf16 hi + lo (16 mantissa bits together), and the two
-  // halves are packed as the two A operands of a round.
-  uint32_t W[KMAX][4];
+  // of its record, which lives in the lane that owns the token) is folded in, and the
+  // weight's bf16 parts are packed as the A operands of a round.
+  // Three rows: odd quads take the negative weights, and their sums are negated back when quads are added.  The matrix
+  // instruction cuts the smaller addends off towards minus infinity where it aligns them; the same small loss at every
+  // token would grow with the list (101580 tokens, error against float64 4.0e-7 of the result), in opposite senses it
+  // cancels.
+  constexpr int NP = weight_parts<R>();
+  const uint32_t neg_quad = (R == 3) ? (uint32_t)(lane & 4) << 29 : 0u;
+  uint32_t W[KMAX][2 * NP];
 #pragma unroll
   for (int k = 0; k < KMAX; ++k) {
-    W[k][0] = W[k][1] = W[k][2] = W[k][3] = 0u;
+#pragma unroll
+    for (int p = 0; p < 2 * NP; ++p) W[k][p] = 0u;
     if (k >= n_k) continue;
     const uint32_t rx = info[k].x;
     const uint32_t sg[4] = {quad_bcast<0>(rx) << 31, quad_bcast<1>(rx) << 31, quad_bcast<2>(rx) << 31,
                             quad_bcast<3>(rx) << 31};
-    uint32_t hb[4], lb[4];
+    float rest[4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const float pt = head_ok ? __uint_as_float(__float_as_uint(s[k][t]) ^ sg[t]) : 0.f;
-      hb[t] = __float_as_uint(pt) & 0xffff0000u;
-      lb[t] = __float_as_uint(pt - __uint_as_float(hb[t]));
+    for (int t = 0; t < 4; ++t)
+      rest[t] = head_ok ? __uint_as_float(__float_as_uint(s[k][t]) ^ (sg[t] ^ neg_quad)) : 0.f;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      uint32_t part[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        part[t] = __float_as_uint(rest[t]) & 0xffff0000u;
+        rest[t] -= __uint_as_float(part[t]);                // exact
+      }
+      W[k][2 * p] = pair_hi(part[0], part[1]);
+      W[k][2 * p + 1] = pair_hi(part[2], part[3]);
     }
-    W[k][0] = pair_hi(hb[0], hb[1]);
-    W[k][1] = pair_hi(hb[2], hb[3]);
-    W[k][2] = pair_hi(lb[0], lb[1]);
-    W[k][3] = pair_hi(lb[2], lb[3]);
   }
 
   // ---- V phases: weighted values ------------------------------------------------
@@ -532,11 +556,17 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged16_kernel(DevDe
     {
       float* sp = s_part + (cc & 1) * (S16_NROW * G * CH);
       float o[G][4];
+      // odd quads hold the negative sums (formed here anew: in a register through the V passes it would not fit)
+      const uint32_t neg_back = (R == 3) ? (opaque(make_uint2((uint32_t)lane, 0u)).x & 4u) << 29 : 0u;
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const float f = s_fw[wave * G + g];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) o[g][c] = row_sum<4>(acc[c][g]) * f;
+        for (int c = 0; c < 4; ++c) {
+          float x = acc[c][g];
+          if constexpr (R == 3) x = __uint_as_float(__float_as_uint(x) ^ neg_back);
+          o[g][c] = row_sum<4>(x) * f;
+        }
       }
       if ((lane & 15) < 4) {
 #pragma unroll

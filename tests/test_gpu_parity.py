@@ -491,6 +491,39 @@ def test_attend_three_rows_wide_sketch(kvr, G, w):
     run_attend_case(kvr, rng, torch.bfloat16, B, Hkv * G, Hkv, 3, w, 70, nv, cap, check_units=set(lens))
 
 
+@pytest.mark.parametrize("G,r,w", [(1, 3, 345), (2, 3, 700), (4, 3, 334), (4, 3, 1365), (4, 3, 1366), (2, 4, 1030)])
+def test_attend_wide_sketch_weights_keep_float32(kvr, G, r, w):
+    """Sketches too wide for 64-channel chunks (three rows: the 16-channel kernel; wider still, three or four rows: the
+    general kernel), next to nothing retained: the probabilities that multiply the rebuilt values carry float32's 24
+    bits.  Against float64: a logit of up to ~8 in float32 is off by a few 2^-22, so is its exponential, and the errors
+    of different tokens are independent: 2^-20 of the result in the 2-norm, 2^-21 along the result (where a weight cut
+    off at 16 bits shows as a loss of 2^-17, the same sign for every token)."""
+    say("attend wide sketch, float32 weights", G, r, w)
+    rng = np.random.default_rng(83 + w)
+    dtype, Hkv, n, D = torch.bfloat16, 2, 1500, 128
+    d = kvr.make_desc(1, Hkv * G, Hkv, r, w, dtype, seed=77)
+    SK = U.rand_storage(rng, (1, Hkv, r, w, D), dtype, 1.5)
+    SV = O.to_storage(rng.standard_normal((1, Hkv, r, w, D)) + 1.0, "bf16")
+    K, V = U.rand_storage(rng, (1, Hkv, 4, D), dtype), U.rand_storage(rng, (1, Hkv, 4, D), dtype)
+    q = U.rand_storage(rng, (1, Hkv * G, D), dtype, 0.7)
+    pos = rng.permutation(n + 4).astype(np.int32)
+    dev = lambda x: torch.as_tensor(np.tile(x, (1, Hkv, 1))).cuda()
+    out = torch.zeros(1, Hkv * G, D, device="cuda")
+    ws = kvr.alloc_workspace(d, kvr.KVR_OP_ATTEND, 4, n)
+    kvr.kvr_attend_decode(d, U.to_dev(q, dtype), U.to_dev(K, dtype), U.to_dev(V, dtype), dev(pos[n:]), 4,
+                          U.to_dev(SK, dtype), U.to_dev(SV, dtype), dev(pos[:n]),
+                          torch.full((1, Hkv), n, dtype=torch.int32, device="cuda"), n, out, None, n + 4, ws)
+    got, want = out.cpu().double().numpy()[0], []
+    for h in range(Hkv):
+        kh, vh = O.query(SK[0, h], SV[0, h], kvr.desc_hash_params(d), pos[:n], storage="bf16")
+        x = q[0, h * G:(h + 1) * G] @ np.concatenate([kh, K[0, h]]).T * float(d.softmax_scale)
+        p = np.exp(x - x.max(axis=1, keepdims=True))
+        want.append(p / p.sum(axis=1, keepdims=True) @ np.concatenate([vh, V[0, h]]))
+    want = np.concatenate(want)
+    assert np.linalg.norm(got - want) <= 2.0 ** -20 * np.linalg.norm(want), np.linalg.norm(got - want) / np.linalg.norm(want)
+    assert abs(((got - want) * want).sum()) <= 2.0 ** -21 * (want * want).sum()
+
+
 @pytest.mark.parametrize("G", [1, 2, 4])
 def test_attend_side_by_side(kvr, G):
     """Enough units and Vague tokens that the staged kernel fills the chip more than twice over: with a
