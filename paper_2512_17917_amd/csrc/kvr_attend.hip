@@ -81,7 +81,7 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
       size_t buf = align_up((size_t)d.r * d.w * ch * 2, 1024);
       const size_t red = (size_t)32 * d.G * ch * 4;
       if (buf < red) buf = red;
-      p.lds_bytes = (int)buf + fixed;
+      p.lds_bytes = s16 ? staged16_lds(d) : (int)buf + fixed;
     }
   }
   p.mfma_retained = (dtype == KVR_BF16);
@@ -125,6 +125,12 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
   }
   p.total_bytes = off;
   return p;
+}
+
+bool attend_side_fits(const DevDesc& d, const AttendPlan& p) {
+  constexpr int UNIT = 1280;                   // LDS is handed out in these
+  const int ret = retained_lds(d.G, p.rslice_tokens, true) + 2 * 4 * d.G * (int)sizeof(float);   // + statistics
+  return (p.lds_bytes + UNIT - 1) / UNIT + (ret + UNIT - 1) / UNIT <= STAGED_LDS_LIMIT / UNIT;
 }
 
 // ---------------------------------------------------------------------------
@@ -548,7 +554,10 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
   // Not next to the four-row kernel either: its two waves per SIMD hold up to 2 x 238 of the 512
   // registers, so the retained kernel would only find room where a workgroup of it has just ended
   // (measured on the 131k workload: 571 us side by side, 511 us back to back).
-  const bool side = sd.stream != nullptr && plan.mfma_retained && plan.staged && big && !(d.r == 4 && staged16_applies(d));
+  // And only where LDS holds both: 16 x 8 units, four heads, 312 slots per row 352 us a call against 417 back to back,
+  // 313 slots 483 against 420 (forked all the same, the retained kernel has the chip to itself with a workgroup per CU).
+  const bool side = sd.stream != nullptr && plan.mfma_retained && plan.staged && big &&
+                    !(d.r == 4 && staged16_applies(d)) && attend_side_fits(d, plan);
   if (side) {
     e = hipEventRecord(sd.fork, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(sd.stream, sd.fork, 0);

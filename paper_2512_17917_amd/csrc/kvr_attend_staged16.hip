@@ -315,9 +315,6 @@ static_assert(STAGED16_KMAX <= 13, "KVR_DISPATCH_NK covers 1..13 rounds");
 // LDS of a workgroup: one chunk, two sets of V partial sums [NROW][G][CH], wave statistics, q
 __host__ __device__ constexpr int chunk_bytes(int r, int w) { return (r * w * S16_ROWB + 1023) & ~1023; }
 __host__ __device__ constexpr int stat_floats(int G) { return 3 * ST_WAVES * G; }
-__host__ __device__ constexpr size_t lds_need(int r, int w, int G) {
-  return (size_t)chunk_bytes(r, w) + (size_t)2 * S16_NROW * G * S16_CH * 4 + (size_t)stat_floats(G) * 4 + (size_t)G * 256;
-}
 
 }  // namespace
 
@@ -597,7 +594,7 @@ static hipError_t launch16(const DevDesc& d, const AttendArgs& a, const AttendPl
   if (attr_rc != hipSuccess) return attr_rc;
   const int units = d.B * d.Hkv;
   const int units_pad = (units + 7) / 8 * 8;
-  hipLaunchKernelGGL(kern, dim3(units_pad * plan.n_vslices), dim3(ST_THREADS), lds_need(R, d.w, G), st, d, a);
+  hipLaunchKernelGGL(kern, dim3(units_pad * plan.n_vslices), dim3(ST_THREADS), staged16_lds(d), st, d, a);
   return hipGetLastError();
 }
 
@@ -608,10 +605,14 @@ static hipError_t launch16_r(const DevDesc& d, const AttendArgs& a, const Attend
                                            : launch16<G, 4, KVR_MEDIAN_MIDMEAN>(d, a, plan, st);
 }
 
+int staged16_lds(const DevDesc& d) {
+  return chunk_bytes(d.r, d.w) + 2 * S16_NROW * d.G * S16_CH * 4 + stat_floats(d.G) * 4 + d.G * 256;
+}
+
 bool staged16_applies(const DevDesc& d) {
   if (staged64_applies(d)) return false;
   return (d.r == 3 || d.r == 4) && d.r * d.w <= 4096 && d.G <= 4 && d.sign_mask == 2 &&
-         lds_need(d.r, d.w, d.G) <= (size_t)160 * 1024;
+         staged16_lds(d) <= STAGED_LDS_LIMIT;
 }
 
 hipError_t launch_attend_vague_staged16(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,

@@ -27,6 +27,8 @@ struct AttendPlan {
   size_t off_part_o, off_part_ml, off_logits, off_rec, off_partial, total_bytes;
 };
 AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long vague_cap);
+// a workgroup of the staged kernel and one of the retained kernel's capped forms find room in one CU's LDS
+bool attend_side_fits(const DevDesc& d, const AttendPlan& p);
 
 struct AttendArgs {
   const void* q;
@@ -64,6 +66,13 @@ struct AttendArgs {
 // max_wgs > 0 caps the launch width (the workgroups then walk the items with a grid stride).
 // reg_form: 0 = the kernel takes the registers it likes; 1 = capped at 128 (it shares the SIMDs with the
 // 64-channel staged kernel); 2 = capped at 80 (with the general staged kernel's widest form; G = 4 only).
+// Dynamic LDS of a workgroup: the sums of its four waves, and alone, in the same place, the logits of its slice.  Next to
+// a staged kernel the sums alone: LDS of a CU holds both kernels' workgroups up to the widest sketch it can (128 units, 300
+// slots per row, slices of 832 tokens: a call takes 346 us, with 16 bytes of LDS per token of the slice 437).
+constexpr int retained_lds(int G, int slice_tokens, bool next_to_staged) {
+  const int sums = 4 * D, logits = (slice_tokens + 15) / 16 * 16;
+  return G * 4 * (next_to_staged || sums > logits ? sums : logits);          // <= 32 KB (1024 tokens, G = 8)
+}
 hipError_t launch_attend_retained(const DevDesc& d, const AttendArgs& a, int n_rslices, int max_wgs,
                                   int reg_form, hipStream_t st);
 
@@ -133,6 +142,7 @@ constexpr bool staged_chunk_fits(int r, long long w, int G, int channels) {
 // sketch, sixteen chunks of it, so few large workgroups are better than many small ones).
 constexpr int STAGED16_KMAX = 13;
 bool staged16_applies(const DevDesc& d);
+int staged16_lds(const DevDesc& d);               // bytes of a workgroup
 hipError_t launch_attend_vague_staged16(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
                                          hipStream_t st);
 // Its specialisation for r = 3 and 64-channel chunks (launch_attend_vague_staged forwards to it); 10-bit row indices.
