@@ -31,6 +31,8 @@
 // random slots then spread over all bank groups instead of two.
 #include "kvr_staged.h"
 
+#include <algorithm>
+
 namespace kvr {
 
 typedef __bf16 bf16x8ms_t __attribute__((ext_vector_type(8)));
@@ -417,23 +419,16 @@ bool multi_staged_applies(const DevDesc& d, long long vague_cap) {
 
 int multi_staged_pad_tokens() { return MS_PAD_TOKENS; }
 
-// Tokens per workgroup, at least 256.  One workgroup (16 waves, the chunk in LDS) runs per CU, so a launch takes
-// ceil(workgroups / 256) turns of (fixed part + tokens of a workgroup); the fixed part (four chunk copies, the
-// reductions) costs about as much as 400 tokens.  At most as many parts as give every CU a workgroup, rounded up:
-// more would only grow the workspace.  40 units x 12706 tokens, 8 columns: 7 parts (280 workgroups, the last 24 on
-// a turn of their own) 82 us, 6 parts 49 us.
+// Tokens per workgroup, at least 256 (below, its fixed part is nearly all there is).  One workgroup (16 waves, the chunk in
+// LDS) runs per CU, so a launch takes ceil(workgroups / 256) turns of (fixed part + tokens of a workgroup), and a unit gets
+// as many parts as one turn holds: with n parts on one turn, n + 1 on two cost 2 (fixed + tokens / (n + 1)), never less
+// than fixed + tokens / n.  40 units x 12706 tokens, 8 columns: 7 parts (280 workgroups, the last 24 on a turn of their own)
+// 82 us, 6 parts 49 us.  A turn of 256 workgroups, 8 columns, 273 slots per row: 34.7 us at 1024 tokens each, 87.5 at 4096.
 int multi_staged_part_tokens(long long vague_cap, long long units) {
-  const long long n_max = (256 + units - 1) / units;
-  double best = 1e30;
-  long long best_t = vague_cap;
-  for (long long n = 1; n <= n_max; ++n) {
-    long long t = (vague_cap + n - 1) / n;
-    if (t < 256 && n > 1) break;
-    if (t < 256) t = 256;
-    const double cost = (double)((units * n + 255) / 256) * (400.0 + (double)t);
-    if (cost < best - 1e-9) { best = cost; best_t = t; }
-  }
-  return (int)((best_t + 15) / 16 * 16);
+  const long long turn = units < 256 ? 256 / units : 1;
+  const long long n = std::max(1ll, std::min(turn, (vague_cap + 255) / 256));
+  const long long t = std::max(256ll, (vague_cap + n - 1) / n);
+  return (int)((t + 15) / 16 * 16);
 }
 
 template <int NCOL>

@@ -48,3 +48,14 @@ def test_retained_kernel_fits_next_to_a_staged_one(plan, units):
         ok, staged, ret, _ = plan(case(4, w))[0]
         assert ok == fits and (staged + ret + 128 <= 160 * 1024) == bool(fits), (w, staged, ret)
     assert all(p[0] for p in plan(*[case(1, w) for w in (300, 341, 342, 1365)]))
+
+
+@pytest.mark.parametrize("units", [1, 3, 8, 40, 128, 129, 200, 256, 300])
+def test_streamed_list_takes_one_turn_of_the_chip(plan, units):
+    """Eight heads: as many parts as fit 256 workgroups, none below 256 tokens, none missing."""
+    for vague in (64, 256, 257, 511, 1000, 5003, 25395, 130000):
+        parts = plan((units, 8, 3, 60, 187, vague))[0][3]
+        most = max(1, min(256 // units, -(-vague // 256)))
+        assert 1 <= parts <= most and (parts == 1 or units * parts <= 256)
+        tokens = -(-max(256, -(-vague // most)) // 16) * 16
+        assert parts == -(-vague // tokens)
