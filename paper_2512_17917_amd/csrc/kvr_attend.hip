@@ -59,7 +59,10 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
       // hashes, softmax, reductions: 2.8 rounds' worth for four 64-channel chunks,
       // 7.5 for the sixteen 16-channel chunks of that kernel, whose waves may
       // also take more rounds), and the launch runs ceil(workgroups / 256)
-      // such workgroups one after another on each CU.
+      // such workgroups one after another on each CU.  Measured on one turn of the 16-channel kernel: four rows 4.6 (w =
+      // 600) .. 5.9 (819) rounds of 11 us; three rows 4.8 (w = 350), 7.7 (700), 11.5 (1092) rounds of 6 us.  With three rows
+      // the counts chosen with 7.5 cost at most 4 % more than those chosen with each width's own figure (99 of 100
+      // sizes: the same counts).
       const bool s16 = staged16_applies(d);
       const int kmax = s16 ? STAGED16_KMAX : STAGED_KMAX;
       const double fixed_rounds = s16 ? 7.5 : 2.8;
