@@ -10,25 +10,10 @@ import torch
 from . import binding as kvr
 
 
-def _zeros_together(dev, *shapes):
-    """Zero-filled tensors [(shape, dtype), ...] carved out of one allocation, each at a 256-byte
-    boundary: one fill launch for all of them."""
-    offs, n = [], 0
-    for shape, dt in shapes:
-        offs.append(n)
-        numel = 1
-        for x in shape:
-            numel *= x
-        n += (numel * dt.itemsize + 255) // 256 * 256
-    base = torch.zeros(n // 4, dtype=torch.int32, device=dev)
-    typed = {dt: base.view(dt) for dt in {dt for _, dt in shapes}}
-    out = []
-    for (shape, dt), off in zip(shapes, offs):
-        stride, strides = 1, []
-        for x in reversed(shape):
-            strides.append(stride)
-            stride *= x
-        out.append(typed[dt].as_strided(shape, strides[::-1], off // dt.itemsize))
+def _zeros(dev, *shapes):
+    """Zero-filled tensors [(shape, dtype), ...], each with a storage of its own, filled by one launch."""
+    out = [torch.empty(shape, dtype=dt, device=dev) for shape, dt in shapes]
+    torch._foreach_zero_([x.view(torch.int32) for x in out if x.numel()])
     return out
 
 
@@ -62,7 +47,7 @@ class LayerState:
             self.ret_pos.fill_(-1)
         i32, f32 = torch.int32, torch.float32
         (self.scores, self.sketch_k, self.sketch_v, self.vague_pos, self.n_vague, self.evict_slot, self.evict_pos,
-         self.n_evict, self.out) = _zeros_together(
+         self.n_evict, self.out) = _zeros(
             dev, ((B, Hkv, self.n_cap), f32), ((B, Hkv, desc.r, desc.w, D), dt), ((B, Hkv, desc.r, desc.w, D), dt),
             ((B, Hkv, self.vague_cap), i32), ((B, Hkv), i32), ((B, Hkv, self.evict_cap), i32),
             ((B, Hkv, self.evict_cap), i32), ((B, Hkv), i32), ((B, Hq, D), f32))
@@ -193,8 +178,11 @@ class LayerState:
         # 2. partition: every prompt token sits in "slot = position" of the full cache
         full_pos = torch.arange(N, dtype=torch.int32, device=dev).expand(B, Hkv, N).contiguous()
         ev_cap = max(n_vague0, 1)
-        ev_slot = torch.empty(B, Hkv, ev_cap, dtype=torch.int32, device=dev)
-        ev_pos = torch.empty(B, Hkv, ev_cap, dtype=torch.int32, device=dev)
+        lists = ((B, Hkv, ev_cap), torch.int32), ((B, Hkv, ev_cap), torch.int32)
+        if n_vague0 > 0 and st.r_size == n_recent:       # exactly n_vague0 tokens leave every unit: no entry stays unwritten
+            ev_slot, ev_pos = (torch.empty(shape, dtype=dt, device=dev) for shape, dt in lists)
+        else:
+            ev_slot, ev_pos = _zeros(dev, *lists)
         ws = kvr.alloc_workspace(desc, kvr.KVR_OP_ENCODE, ev_cap, 0, dev)
         if timers is not None:       # (start, stop) torch events around select + bulk encode
             timers[0].record()
