@@ -13,8 +13,6 @@ namespace kvr {
 
 constexpr int SEL_THREADS = 1024;
 constexpr int SEL_WAVES = SEL_THREADS / WAVE;
-constexpr int SEL_KPT = 8;                       // keys per thread held in registers
-constexpr int SEL_REG_SLOTS = SEL_THREADS * SEL_KPT;
 constexpr int SEL_SMALL = 8;                     // up to this many evictions: repeated minimum
 constexpr unsigned long long KEY_NONE = ~0ull;   // not a valid key (it would be a NaN score at position 0)
 constexpr int ENC_SMALL_CAP = 64;
@@ -132,37 +130,12 @@ __device__ __forceinline__ int append_body_pre(const DevDesc& d, int unit, const
 // ---------------------------------------------------------------------------
 // select
 // ---------------------------------------------------------------------------
-// key of a slot whose position is already known
-__device__ __forceinline__ bool pos_key(int pos, const float* __restrict__ sc, int slot, int ret_cap,
-                                        int recent_from, long long n_cap, unsigned long long& key) {
-  if (slot >= ret_cap) return false;
-  if (pos < 0 || pos >= recent_from || pos >= n_cap) return false;
-  uint32_t b = __float_as_uint(sc[pos]);
-  if (b == 0x80000000u) b = 0u;                                   // -0 ranks as +0
-  const uint32_t mono = b ^ ((b >> 31) ? 0xffffffffu : 0x80000000u);
-  key = ((unsigned long long)mono << 32) | (uint32_t)(~(uint32_t)pos);
-  return true;
-}
-
-// the same with the token's score already in a register (scv = scores[pos], read only if pos is eligible)
-__device__ __forceinline__ bool pos_key_val(int pos, float scv, int slot, int ret_cap, int recent_from,
-                                            long long n_cap, unsigned long long& key) {
+// key of a slot from its position and the token's score there (scv is read only if the position is eligible)
+__device__ __forceinline__ bool pos_key(int pos, float scv, int slot, int ret_cap, int recent_from, long long n_cap,
+                                        unsigned long long& key) {
   if (slot >= ret_cap) return false;
   if (pos < 0 || pos >= recent_from || pos >= n_cap) return false;
   uint32_t b = __float_as_uint(scv);
-  if (b == 0x80000000u) b = 0u;                                   // -0 ranks as +0
-  const uint32_t mono = b ^ ((b >> 31) ? 0xffffffffu : 0x80000000u);
-  key = ((unsigned long long)mono << 32) | (uint32_t)(~(uint32_t)pos);
-  return true;
-}
-
-__device__ __forceinline__ bool slot_key(const int32_t* __restrict__ rp, const float* __restrict__ sc,
-                                         int slot, int ret_cap, int recent_from, long long n_cap,
-                                         unsigned long long& key) {
-  if (slot >= ret_cap) return false;
-  const int pos = rp[slot];
-  if (pos < 0 || pos >= recent_from || pos >= n_cap) return false;
-  uint32_t b = __float_as_uint(sc[pos]);
   if (b == 0x80000000u) b = 0u;                                   // -0 ranks as +0
   const uint32_t mono = b ^ ((b >> 31) ? 0xffffffffu : 0x80000000u);
   key = ((unsigned long long)mono << 32) | (uint32_t)(~(uint32_t)pos);
@@ -240,13 +213,12 @@ __device__ __forceinline__ void pick_digit(SelShared& sh, int shift) {
 // in registers (KPT per thread: 8 for the retained slots of a decode step, 32 for
 // a 32k prompt).  Writes the eviction lists, frees the slots, appends to the Vague
 // list, sets n_evict (negative = needed count on overflow, nothing evicted).
-// pre (REG only, may be null): positions of this thread's slots, read by the caller
-// ahead of time.  The fused update kernel reads them before it appends the new
-// token: while that token is Recent it ranks like an empty slot, so the stale
-// value serves; with an empty Recent window the kernel patches the one entry.
-// pre_sc (with pre, may be null): the scores at those positions, gathered by the
-// caller ahead of time (valid where the position is eligible).
-template <bool REG, int KPT = SEL_KPT>
+// pre, pre_sc (REG only): positions of this thread's slots and the scores at those
+// positions (valid where the position is eligible), read by the caller ahead of time.
+// The fused update kernel reads them before it appends the new token: while that token
+// is Recent it ranks like an empty slot, so the stale value serves; with an empty Recent
+// window the kernel patches the one entry.
+template <bool REG, int KPT>
 __device__ __forceinline__ void select_body(
     const DevDesc& d, int unit, const float* __restrict__ scores, long long n_cap,
     int32_t* __restrict__ ret_pos, int ret_cap, const int32_t* __restrict__ n_ctx, int n_recent, int k_cand,
@@ -286,7 +258,7 @@ __device__ __forceinline__ void select_body(
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           unsigned long long key = KEY_NONE;
-          const bool ok = pos_key_val(p8[u], s8[u], (j0 + u) * SEL_THREADS + tid, ret_cap, recent_from, n_cap, key);
+          const bool ok = pos_key(p8[u], s8[u], (j0 + u) * SEL_THREADS + tid, ret_cap, recent_from, n_cap, key);
           if (j0 + u < je) f(j0 + u, ok, key);
         }
       }
@@ -301,9 +273,7 @@ __device__ __forceinline__ void select_body(
 #pragma unroll
       for (int j = 0; j < KPT; ++j) {
         unsigned long long key = KEY_NONE;
-        const bool ok = pre_sc ? pos_key_val(pre[j], pre_sc[j], j * SEL_THREADS + tid, ret_cap, recent_from, n_cap, key)
-                        : pre  ? pos_key(pre[j], sc, j * SEL_THREADS + tid, ret_cap, recent_from, n_cap, key)
-                               : slot_key(rp, sc, j * SEL_THREADS + tid, ret_cap, recent_from, n_cap, key);
+        const bool ok = pos_key(pre[j], pre_sc[j], j * SEL_THREADS + tid, ret_cap, recent_from, n_cap, key);
         rkey[j] = ok ? key : KEY_NONE;
         c += ok ? 1 : 0;
       }
