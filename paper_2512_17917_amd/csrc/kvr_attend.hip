@@ -47,12 +47,21 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
   // staged kernel: bf16, the paper's sign setting, G <= 4, r = 3 or 4, bucket fits 15 bits
   if (dtype == KVR_BF16 && d.sign_mask == 2 && d.G <= 4 && (d.r == 3 || d.r == 4) && d.w <= 32768 &&
       vague_cap >= 64) {
-    const int fixed = staged_fixed_lds(d.G);
-    int ch = 0;
-    for (int c = 64; c >= 8; c >>= 1) {
-      if (staged_chunk_fits(d.r, d.w, d.G, c)) { ch = c; break; }
-    }
-    if (ch) {
+    const bool s64 = staged64_applies(d), s16 = staged16_applies(d);
+    p.lds_bytes = s64 ? staged64_lds(d.w, d.G) : s16 ? staged16_lds(d) : 0;
+    p.ch = s64 ? 64 : s16 ? 16 : 0;
+    // The general kernel: 16 channels where they fit (four heads: 5056 rows), else 8, up to 8000 rows: a chunk then passes
+    // through LDS 32 times for fewer and fewer tokens per row, and the gather of the generic kernel is no slower.
+    // 16 units, 31 tokens per row, us with 8 channels / by the gather: four rows, four heads 7000 rows 924 / 995, 8000
+    // 1030 / 1076, 9000 1165 / 1150; one head 6000 560 / 665, 7000 865 / 714; three rows, four heads 5100 483 / 502,
+    // 6000 558 / 534, 7000 867 / 723 (three rows, and one head, lose from a narrower sketch on than the line says).
+    // 16 against 8 channels: 32 units of 139000 tokens, 4500 rows, 1360 -> 946 us a call.
+    for (int c = 16; c >= 8 && p.ch == 0; c >>= 1)
+      if (staged_lds(d.r * d.w, d.G, c) <= STAGED_LDS_LIMIT && (c == 16 || d.r * d.w <= 8000)) {
+        p.ch = c;
+        p.lds_bytes = staged_lds(d.r * d.w, d.G, c);
+      }
+    if (p.ch) {
       const long long wr = (vague_cap + 63) / 64;          // wave-rounds to cover the list
       // Cost model: a workgroup that gives every wave rho rounds of 64 tokens takes
       // about (fixed + rho) round times (fixed part: staging the sketch chunks,
@@ -63,28 +72,19 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
       // 600) .. 5.9 (819) rounds of 11 us; three rows 4.8 (w = 350), 7.7 (700), 11.5 (1092) rounds of 6 us.  With three rows
       // the counts chosen with 7.5 cost at most 4 % more than those chosen with each width's own figure (99 of 100
       // sizes: the same counts).
-      const bool s16 = staged16_applies(d);
       const int kmax = s16 ? STAGED16_KMAX : STAGED_KMAX;
       const double fixed_rounds = s16 ? 7.5 : 2.8;
       double best = 1e30;
-      int best_rho = 1, best_n = 1;
+      int best_n = 1;
       for (int rho = 1; rho <= kmax; ++rho) {
         const long long n = (wr + 8 * rho - 1) / (8 * rho);
         const long long rho_eff = (wr + 8 * n - 1) / (8 * n);      // rounds the busiest wave really gets
         const long long waves_of_wgs = (units * n + 255) / 256;
         const double cost = (double)waves_of_wgs * (fixed_rounds + (double)rho_eff);
-        if (cost < best - 1e-9) { best = cost; best_rho = rho; best_n = (int)n; }
+        if (cost < best - 1e-9) { best = cost; best_n = (int)n; }
       }
-      (void)best_rho;
       p.staged = true;
-      p.ch = ch;
       p.n_vslices = best_n;
-      // the chunk buffer doubles as reduction scratch [32 rows][G][ch] floats
-      // and is padded to whole kilobytes (a wave stages 1 KB at a time)
-      size_t buf = align_up((size_t)d.r * d.w * ch * 2, 1024);
-      const size_t red = (size_t)32 * d.G * ch * 4;
-      if (buf < red) buf = red;
-      p.lds_bytes = s16 ? staged16_lds(d) : (int)buf + fixed;
     }
   }
   p.mfma_retained = (dtype == KVR_BF16);

@@ -57,13 +57,10 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged_kernel(DevDesc
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int b = unit / d.Hkv, hk = unit % d.Hkv;
   const int w = d.w;
-  // chunk buffer; it doubles as reduction scratch [32 rows][G][CH] floats
-  const int sk_bytes = max((R * w * ROWB + 1023) & ~1023, 32 * G * CH * 4);
+  const int sk_bytes = staged_chunk_lds(R * w, G, CH);
   unsigned char* s_sk = smem;
-  float* s_red = reinterpret_cast<float*>(smem + sk_bytes + ST_KMAX * ST_THREADS * 8);   // [8][G][CH]
-  float* s_stat = s_red + ST_WAVES * G * 64;                                               // [8][G] x 2
-  uint4* s_q = reinterpret_cast<uint4*>(smem + sk_bytes + ST_KMAX * ST_THREADS * 8 + ST_WAVES * G * 64 * 4 + 1024);
-
+  float* s_stat = reinterpret_cast<float*>(smem + sk_bytes);                               // [32 rows][G] x 2
+  uint4* s_q = reinterpret_cast<uint4*>(smem + sk_bytes + staged_stat_lds(G));
   const int nv = clampi(a.n_vague[unit], 0, a.vague_cap);
   const int rounds_total = (nv + 63) >> 6;
   const int NWT = a.n_vslices * ST_WAVES;

@@ -626,11 +626,7 @@ static hipError_t launch64(const DevDesc& d, const AttendArgs& a, const AttendPl
 
 hipError_t launch_attend_vague_staged64(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
                                         hipStream_t st) {
-  if (d.r != 3 || plan.ch != 64 || 3 * d.w > 1024) return hipErrorInvalidValue;   // 10-bit LDS row indices
-  // LDS: chunk + [32][G][64] floats + statistics + q; the plan reserves at least that
-  const size_t need = (((size_t)3 * d.w * 128 + 1023) & ~(size_t)1023) + (size_t)32 * d.G * 64 * 4 +
-                      (size_t)2 * 32 * d.G * 4 + (size_t)d.G * 256;
-  if (need > (size_t)plan.lds_bytes) return hipErrorInvalidValue;
+  if (!staged64_applies(d) || plan.lds_bytes < staged64_lds(d.w, d.G)) return hipErrorInvalidValue;
   switch (d.G) {
     case 1: return launch64<1>(d, a, plan, st);
     case 2: return launch64<2>(d, a, plan, st);

@@ -129,12 +129,17 @@ hipError_t launch_attend_multi(const DevDesc& d, const AttendArgs& a, const int3
 // Staged kernel over the Vague list (bf16, values signed only, G <= 4, r in {3,4}).
 hipError_t launch_attend_vague_staged(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
                                       hipStream_t st);
-// LDS of the staged kernel beside the sketch chunk: token records, output sums, statistics, q
+// LDS per workgroup (bytes): the sketch chunk in whole kilobytes (a wave copies 1 KB at a time; it doubles as the reduction
+// scratch [32 rows][G][channels] floats), wave statistics [2][32 rows][G] and q [G][16 pieces]
 constexpr int STAGED_KMAX = 6;                    // wave-rounds (64 tokens) per wave
 constexpr int STAGED_LDS_LIMIT = 160 * 1024;      // LDS per workgroup on gfx950
-constexpr int staged_fixed_lds(int G) { return STAGED_KMAX * 512 * 8 + 8 * G * 64 * 4 + 1024 + G * 256; }
-constexpr bool staged_chunk_fits(int r, long long w, int G, int channels) {
-  return (long long)r * w * channels * 2 + 1024 + staged_fixed_lds(G) <= STAGED_LDS_LIMIT;
+__host__ __device__ constexpr int staged_chunk_lds(int rows, int G, int channels) {
+  const int chunk = (rows * channels * 2 + 1023) & ~1023, scratch = 32 * G * channels * 4;
+  return chunk > scratch ? chunk : scratch;
+}
+__host__ __device__ constexpr int staged_stat_lds(int G) { return 2 * 32 * G * 4; }
+constexpr int staged_lds(int rows, int G, int channels) {
+  return staged_chunk_lds(rows, G, channels) + staged_stat_lds(G) + G * 256;
 }
 // Its specialisation for chunks of 16 channels (kvr_attend_staged16.hip; launch_attend_vague_staged forwards
 // to it): four rows, and three rows whose sketch is too wide for the 64-channel kernel.  A wave
@@ -146,9 +151,15 @@ int staged16_lds(const DevDesc& d);               // bytes of a workgroup
 hipError_t launch_attend_vague_staged16(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
                                          hipStream_t st);
 // Its specialisation for r = 3 and 64-channel chunks (launch_attend_vague_staged forwards to it); 10-bit row indices.
-inline bool staged64_applies(const DevDesc& d) {
-  return d.r == 3 && d.G <= 4 && d.sign_mask == 2 && 3 * (long long)d.w <= 1024 && staged_chunk_fits(3, d.w, d.G, 64);
+// Its chunk stays whole through the V phases, so the reduction scratch is a place of its own.
+constexpr int staged64_lds(int w, int G) {
+  return ((3 * w * 128 + 1023) & ~1023) + 32 * G * 64 * 4 + staged_stat_lds(G) + G * 256;
 }
+// Range: with four heads what LDS holds (less the last kilobyte: w <= 333), with fewer what ten bits hold (w <= 341).
+inline bool staged64_applies(const DevDesc& d) {
+  return d.r == 3 && d.G <= 4 && d.sign_mask == 2 && 3 * d.w <= (d.G == 4 ? 1000 : 1024);
+}
+static_assert(staged64_lds(1000 / 3, 4) <= STAGED_LDS_LIMIT && staged64_lds(1024 / 3, 2) <= STAGED_LDS_LIMIT, "LDS");
 hipError_t launch_attend_vague_staged64(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
                                         hipStream_t st);
 

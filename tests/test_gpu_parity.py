@@ -491,6 +491,20 @@ def test_attend_three_rows_wide_sketch(kvr, G, w):
     run_attend_case(kvr, rng, torch.bfloat16, B, Hkv * G, Hkv, 3, w, 70, nv, cap, check_units=set(lens))
 
 
+@pytest.mark.parametrize("G,r,w,mode", [(4, 3, 1685, 0), (4, 3, 1686, 0), (4, 4, 1264, 1), (4, 4, 1265, 0),
+                                        (2, 4, 1100, 0), (2, 4, 1100, 1), (1, 4, 2000, 1), (1, 3, 1400, 0), (4, 3, 2667, 0)])
+def test_attend_widest_sketches(kvr, G, r, w, mode):
+    """More than 4096 sketch rows: the general staged kernel, in chunks of 16 channels up to the last width they fit
+    and of 8 behind it, three and four rows under both median rules; the gather behind its last width.  Several workgroups per unit, three rounds per
+    wave, ragged ends, one token and none."""
+    B, Hkv, cap = 4, 8, 9000
+    lens = {(0, 0): 9000, (1, 5): 4161, (3, 7): 1, (3, 6): 0}
+    nv = [lens.get((u // Hkv, u % Hkv), 9000 - 640 * (u % 7)) for u in range(B * Hkv)]
+    rng = np.random.default_rng(71 + w)
+    say("attend widest sketches", G, r, w, mode)
+    run_attend_case(kvr, rng, torch.bfloat16, B, Hkv * G, Hkv, r, w, 70, nv, cap, mode=mode, check_units=set(lens))
+
+
 @pytest.mark.parametrize("G,r,w", [(1, 3, 345), (2, 3, 700), (4, 3, 334), (4, 3, 1365), (4, 3, 1366), (2, 4, 1030)])
 def test_attend_wide_sketch_weights_keep_float32(kvr, G, r, w):
     """Sketches too wide for 64-channel chunks (three rows: the 16-channel kernel; wider still, three or four rows: the

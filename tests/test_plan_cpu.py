@@ -10,15 +10,15 @@ PROBE = r"""
 #include <cstdio>
 #include "kvr_launch.h"
 // per input line: units heads rows slots retained vague -> side-by-side fits, LDS of the staged and the retained kernel,
-// parts of a streamed list
+// parts of the Vague list, channels per phase of the staged kernel (0: the list is not staged)
 int main() {
   int units, G, r, w, ret, vague;
   while (std::scanf("%d %d %d %d %d %d", &units, &G, &r, &w, &ret, &vague) == 6) {
     kvr::DevDesc d = {};
     d.B = 1; d.Hkv = units; d.Hq = units * G; d.G = G; d.r = r; d.w = w; d.sign_mask = 2;
     const kvr::AttendPlan p = kvr::attend_plan(d, KVR_BF16, ret, vague);
-    std::printf("%d %d %d %d\n", (int)kvr::attend_side_fits(d, p), p.lds_bytes,
-                kvr::retained_lds(G, p.rslice_tokens, true), p.streamed ? p.n_vslices : 0);
+    std::printf("%d %d %d %d %d\n", (int)kvr::attend_side_fits(d, p), p.lds_bytes,
+                kvr::retained_lds(G, p.rslice_tokens, true), p.n_vslices, p.staged ? p.ch : 0);
   }
 }
 """
@@ -45,7 +45,7 @@ def test_retained_kernel_fits_next_to_a_staged_one(plan, units):
     (120 KB of chunk + 34 KB + 8.1 KB), and beside the three-row 16-channel kernel at every width it takes."""
     case = lambda G, w: (units, G, 3, w, 27 * w, 93 * w)
     for w, fits in [(6, 1), (273, 1), (291, 1), (300, 1), (312, 1), (313, 0), (333, 0), (334, 1), (700, 1), (1365, 1)]:
-        ok, staged, ret, _ = plan(case(4, w))[0]
+        ok, staged, ret = plan(case(4, w))[0][:3]
         assert ok == fits and (staged + ret + 128 <= 160 * 1024) == bool(fits), (w, staged, ret)
     assert all(p[0] for p in plan(*[case(1, w) for w in (300, 341, 342, 1365)]))
 
@@ -59,3 +59,17 @@ def test_streamed_list_takes_one_turn_of_the_chip(plan, units):
         assert 1 <= parts <= most and (parts == 1 or units * parts <= 256)
         tokens = -(-max(256, -(-vague // most)) // 16) * 16
         assert parts == -(-vague // tokens)
+
+
+@pytest.mark.parametrize("G,r,edges", [(4, 3, [(333, 64), (334, 16), (1365, 16), (1366, 16), (1685, 16), (1686, 8), (2666, 8), (2667, 0)]),
+                                       (4, 4, [(1, 16), (1024, 16), (1025, 16), (1264, 16), (1265, 8), (2000, 8), (2001, 0)]),
+                                       (2, 3, [(341, 64), (342, 16)]),
+                                       (1, 4, [(1272, 16), (1273, 8), (2000, 8), (2001, 0)])])
+def test_channels_per_phase(plan, G, r, edges):
+    """The widest chunk whose LDS (chunk, statistics, q and nothing else) fits a workgroup's 160 KB; 8 channels up to
+    8000 rows."""
+    for w, ch in edges:
+        p = plan((16, G, r, w, 1000, 9000))[0]
+        assert p[4] == ch and p[1] <= 160 * 1024, (w, p)
+        if ch and r * w > 4096:
+            assert p[1] == -(-r * w * ch * 2 // 1024) * 1024 + 2 * 32 * G * 4 + G * 256
