@@ -131,6 +131,15 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
 }
 
 bool attend_side_fits(const DevDesc& d, const AttendPlan& p) {
+  if (!p.staged || !p.mfma_retained) return false;
+  // Registers: two waves of the staged kernel and one of the retained kernel's capped form (128) share a SIMD's 512.  The
+  // 64-channel kernel takes 192, the 16-channel kernel 192 with three rows and 238 with four, the general kernel up to 192
+  // but for four rows and four heads.  Where they do not fit, the retained kernel only finds room where a workgroup has just
+  // ended: 131072 tokens, four rows 571 us side by side, 511 back to back; 4400 rows in four, four heads 1105 and 1087.
+  // Where they do: three rows of 1092 slots, 64 units 792 against 910 us, 1500 slots (general kernel), 32 units 907 / 947.
+  if (d.r != 3 && (staged16_applies(d) || d.G == 4)) return false;
+  // LDS: 16 x 8 units, four heads, 312 slots per row 352 us a call against 417 back to back, 313 slots 483 against 420
+  // (forked all the same, the retained kernel has the chip to itself with a workgroup per CU).
   constexpr int UNIT = 1280;                   // LDS is handed out in these
   const int ret = retained_lds(d.G, p.rslice_tokens, true) + 2 * 4 * d.G * (int)sizeof(float);   // + statistics
   return (p.lds_bytes + UNIT - 1) / UNIT + (ret + UNIT - 1) / UNIT <= STAGED_LDS_LIMIT / UNIT;
@@ -554,24 +563,15 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
   // off with a launch as wide as its item count than with one workgroup per CU.
   const int cus = cu_count();
   const bool big = (long long)units * plan.n_vslices >= 2ll * cus;
-  // Not next to the four-row kernel either: its two waves per SIMD hold up to 2 x 238 of the 512
-  // registers, so the retained kernel would only find room where a workgroup of it has just ended
-  // (measured on the 131k workload: 571 us side by side, 511 us back to back).
-  // And only where LDS holds both: 16 x 8 units, four heads, 312 slots per row 352 us a call against 417 back to back,
-  // 313 slots 483 against 420 (forked all the same, the retained kernel has the chip to itself with a workgroup per CU).
-  const bool side = sd.stream != nullptr && plan.mfma_retained && plan.staged && big &&
-                    !(d.r == 4 && staged16_applies(d)) && attend_side_fits(d, plan);
+  // And only where a CU holds a workgroup of each.
+  const bool side = sd.stream != nullptr && big && attend_side_fits(d, plan);
   if (side) {
     e = hipEventRecord(sd.fork, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(sd.stream, sd.fork, 0);
     if (e == hipSuccess) {
       // From here on the side stream may hold work that writes the caller's workspace: whatever
       // fails below, `st` is made to wait for it before this call returns.
-      // what the staged kernel's two waves leave of a SIMD's 512 registers: 128 next to the 64-channel
-      // kernel and the three-row form of the 16-channel kernel (2 x 176), 80 next to the widest general form
-      const bool s64_16 = staged64_applies(d) || staged16_applies(d);
-      const int reg_form = s64_16 ? 1 : ((d.G == 4 && plan.ch <= 16) ? 2 : 0);
-      e = launch_attend_retained(d, a, plan.n_rslices, cus, reg_form, sd.stream);
+      e = launch_attend_retained(d, a, plan.n_rslices, cus, true, sd.stream);
       const hipError_t ej = hipEventRecord(sd.join, sd.stream);
       if (e == hipSuccess && ej == hipSuccess) e = launch_attend_vague_staged(d, a, plan, st);
       hipError_t ew = (ej == hipSuccess) ? hipStreamWaitEvent(st, sd.join, 0) : ej;
@@ -581,7 +581,7 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
       }
     }
   } else if (plan.mfma_retained) {
-    e = launch_attend_retained(d, a, plan.n_rslices, 0, 0, st);
+    e = launch_attend_retained(d, a, plan.n_rslices, 0, false, st);
   } else {
     a.tok_limit = plan.staged ? a.ret_cap : a.ret_cap + a.vague_cap;
     dim3 grid(plan.n_rslices, units);

@@ -291,7 +291,7 @@ __device__ __forceinline__ void attend_retained_body(const DevDesc& d, const Att
 }
 
 // Two kernels around the same body.  Alone, the kernel may use what three waves per SIMD leave (one head: four).  Next to
-// the staged kernel it is capped at 124 + 4 accumulation registers (the attribute counts in units of two on
+// a staged kernel it is capped at 124 + 4 accumulation registers (the attribute counts in units of two on
 // this target): 2 x 192 (two waves of the staged kernel, which then needs no spills) + 128 fill a SIMD's 512
 // registers exactly; the few spills of this kernel, which waits for HBM most of the time, cost nothing.
 template <int G>
@@ -304,27 +304,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(62))) void atte
   attend_retained_body<G, false>(d, a, n_rslices);
 }
 
-// Third form, 76 + 4 registers: what two waves of the general staged kernel with 16- or 8-channel chunks and
-// four query heads (about 212 registers each) leave of a SIMD.  It spills a lot and is slow, but it has six
-// times the general staged kernel's duration to finish in.
-template <int G>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(38))) void attend_retained_tight_kernel(
-    DevDesc d, AttendArgs a, int n_rslices) {
-  attend_retained_body<G, false>(d, a, n_rslices);
-}
-
 hipError_t launch_attend_retained(const DevDesc& d, const AttendArgs& a, int n_rslices, int max_wgs,
-                                  int reg_form, hipStream_t st) {
+                                  bool next_to_staged, hipStream_t st) {
   int n_wgs = d.B * d.Hkv * n_rslices;
   if (max_wgs > 0 && n_wgs > max_wgs) n_wgs = max_wgs;
   if (n_wgs < 1) return hipSuccess;
   const dim3 grid(n_wgs), block(256);
-  const size_t lds = retained_lds(d.G, a.slice_tokens, reg_form != 0);
-  if (reg_form == 2 && d.G == 4) {      // next to the general staged kernel in its widest form
-    hipLaunchKernelGGL(attend_retained_tight_kernel<4>, grid, block, lds, st, d, a, n_rslices);
-    return hipGetLastError();
-  }
-  if (reg_form == 1) {                  // next to the 64-channel staged kernel
+  const size_t lds = retained_lds(d.G, a.slice_tokens, next_to_staged);
+  if (next_to_staged) {
     switch (d.G) {
       case 1: hipLaunchKernelGGL(attend_retained_shared_kernel<1>, grid, block, lds, st, d, a, n_rslices); break;
       case 2: hipLaunchKernelGGL(attend_retained_shared_kernel<2>, grid, block, lds, st, d, a, n_rslices); break;

@@ -559,6 +559,23 @@ def test_attend_side_by_side(kvr, G):
     run_attend_case(kvr, rng, torch.float32, 1, 4, 1, 3, 6, 100, [150], 150, side=side)
 
 
+@pytest.mark.parametrize("G,r,w,cap", [(4, 3, 700, 27000), (1, 3, 1365, 27000), (4, 3, 1400, 20000), (2, 4, 1030, 20000)])
+def test_attend_side_by_side_wide_sketch(kvr, G, r, w, cap):
+    """The retained kernel's capped form next to the three-row 16-channel kernel and next to the general kernel: 128 units
+    with parts enough for two turns of the chip (units x parts >= 512).  Some units against the oracle, all of them bit
+    for bit against the call without the second stream."""
+    B, Hkv, got = 16, 8, []
+    nv = [cap - 7 * (i % 5) for i in range(B * Hkv)]
+    nv[9], nv[17] = 1, 0
+    side = kvr.SideStream()
+    for sd in (side, None):
+        say("attend side by side, wide sketch" if sd else "attend back to back, wide sketch", G, r, w)
+        rng = np.random.default_rng(59 + w)
+        run_attend_case(kvr, rng, torch.bfloat16, B, Hkv * G, Hkv, r, w, 150, nv, cap, side=sd, keep=got,
+                        check_units={(0, 0), (1, 1), (2, 1), (15, 7)})
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 def test_attend_eight_heads_per_kv_head(kvr):
     """bf16, r = 3, G = 8: the Vague list goes through the streaming LDS-staged kernel (the one of
     kvr_attend_multi, one query, 8 columns): several workgroups per unit, ragged tiles, empty and clamped

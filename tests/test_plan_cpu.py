@@ -50,6 +50,15 @@ def test_retained_kernel_fits_next_to_a_staged_one(plan, units):
     assert all(p[0] for p in plan(*[case(1, w) for w in (300, 341, 342, 1365)]))
 
 
+def test_registers_next_to_a_staged_kernel(plan):
+    """Four rows: 238 registers a wave in the 16-channel kernel, 194 and more in the general one with four heads; two
+    waves of those leave no 128.  Everything else does, LDS permitting."""
+    ok = [p[0] for p in plan((128, 4, 4, 819, 9000, 30000), (128, 1, 4, 300, 9000, 30000), (128, 4, 4, 1100, 9000, 30000),
+                             (128, 2, 4, 1100, 9000, 30000), (128, 1, 4, 1030, 9000, 30000), (128, 4, 3, 1400, 9000, 30000),
+                             (128, 8, 3, 60, 9000, 30000))]
+    assert ok == [0, 0, 0, 1, 1, 1, 0]
+
+
 @pytest.mark.parametrize("units", [1, 3, 8, 40, 128, 129, 200, 256, 300])
 def test_streamed_list_takes_one_turn_of_the_chip(plan, units):
     """Eight heads: as many parts as fit 256 workgroups, none below 256 tokens, none missing."""
