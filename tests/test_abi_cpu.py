@@ -116,6 +116,7 @@ def test_bad_descriptors_are_rejected_without_a_gpu():
         # a compute entry point with otherwise plausible (fake, never dereferenced) pointers
         p = 0x10000
         assert L.kvr_reconstruct(C.byref(d), p, p, p, p, 4, p, p, None) == code, (k, v)
+        assert L.kvr_compact(C.byref(d), p, p, p, 8, p, p, 4, p, p, p, 6, 6, None) == code, (k, v)
     assert L.kvr_workspace_size(None, kvr.KVR_OP_ATTEND, 100, 0, C.byref(sz)) == kvr.KVR_ERR_INVALID_ARG
 
 
@@ -142,6 +143,17 @@ def test_bad_arguments_are_rejected_without_a_gpu():
     # append
     assert L.kvr_append(dp, p, p, p, p, p, None, 10, None, None) == E
     assert L.kvr_append(dp, p, p, p, p, p, p, 0, None, None) == E
+    # compact: every pointer, alignment of the rows, every size
+    ok_args = [dp, p, p, p, 8, p, p, 4, p, p, p, 6, 6, None]
+    for i in (1, 2, 3, 5, 6, 8, 9, 10):
+        bad = list(ok_args); bad[i] = None
+        assert L.kvr_compact(*bad) == E, i
+    for i in (1, 2, 8, 9):
+        bad = list(ok_args); bad[i] = odd
+        assert L.kvr_compact(*bad) == E, i
+    for i, v in ((4, 0), (4, (1 << 30) + 1), (7, 0), (7, (1 << 30) + 1), (11, 0), (11, (1 << 30) + 1), (12, -1)):
+        bad = list(ok_args); bad[i] = v
+        assert L.kvr_compact(*bad) == E, (i, v)
     # step_update
     ok_args = [dp, p, p, p, p, p, p, 100, p, 1000, 10, 20, p, p, p, 8, p, p, 500, p, p, None]
     bad = list(ok_args); bad[1] = None

@@ -447,17 +447,17 @@ def test_attend_edges(kvr, dtype):
 
 
 def test_attend_staged_channel_chunks(kvr):
-    """bf16, r in {3, 4}, G <= 4 takes the LDS-staged kernel; the width of a
-    sketch row decides how many channels fit per phase (64 / 32 / 16 / 8).  Several
+    """bf16, r in {3, 4}, G <= 4 takes one of the LDS-staged kernels; rows and width of the
+    sketch decide which, and how many channels it takes per phase (64 / 16 / 8).  Several
     workgroups per unit, ragged last round, more than one 64-token round per wave."""
     rng = np.random.default_rng(55)
     dtype = torch.bfloat16
-    for (G, r, w, nv, cap, mode) in [(4, 3, 273, [5000, 4097], 5200, 0),      # 64 channels per phase
-                                     (4, 3, 400, [700, 1], 800, 0),           # 32
-                                     (2, 4, 500, [600, 333], 640, 0),         # 16, midmean
-                                     (2, 4, 500, [600, 333], 640, 1),         # 16, lower
-                                     (1, 3, 2000, [300, 64], 320, 0),         # 8
-                                     (4, 4, 30, [900, 65], 1000, 0)]:         # 64, r = 4
+    for (G, r, w, nv, cap, mode) in [(4, 3, 273, [5000, 4097], 5200, 0),      # 64-channel kernel
+                                     (4, 3, 400, [700, 1], 800, 0),           # 16-channel kernel, three rows
+                                     (2, 4, 500, [600, 333], 640, 0),         # 16-channel kernel, four rows, midmean
+                                     (2, 4, 500, [600, 333], 640, 1),         # the same, lower
+                                     (1, 3, 2000, [300, 64], 320, 0),         # general kernel, 8 channels
+                                     (4, 4, 30, [900, 65], 1000, 0)]:         # 16-channel kernel, narrow sketch
         say("attend staged", G, r, w, nv, mode)
         run_attend_case(kvr, rng, dtype, 1, 2 * G, 2, r, w, 130, nv, cap, mode=mode)
     say("attend staged, many units (XCD mapping), 3 rounds per wave")
