@@ -130,19 +130,22 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
   return p;
 }
 
-bool attend_side_fits(const DevDesc& d, const AttendPlan& p) {
-  if (!p.staged || !p.mfma_retained) return false;
+int attend_side_lds(const DevDesc& d, const AttendPlan& p) {
+  if (!p.staged || !p.mfma_retained) return 0;
   // Registers: two waves of the staged kernel and one of the retained kernel's capped form (128) share a SIMD's 512.  The
   // 64-channel kernel takes 192, the 16-channel kernel 192 with three rows and 238 with four, the general kernel up to 192
   // but for four rows and four heads.  Where they do not fit, the retained kernel only finds room where a workgroup has just
   // ended: 131072 tokens, four rows 571 us side by side, 511 back to back; 4400 rows in four, four heads 1105 and 1087.
   // Where they do: three rows of 1092 slots, 64 units 792 against 910 us, 1500 slots (general kernel), 32 units 907 / 947.
-  if (d.r != 3 && (staged16_applies(d) || d.G == 4)) return false;
-  // LDS: 16 x 8 units, four heads, 312 slots per row 352 us a call against 417 back to back, 313 slots 483 against 420
-  // (forked all the same, the retained kernel has the chip to itself with a workgroup per CU).
+  if (d.r != 3 && (staged16_applies(d) || d.G == 4)) return 0;
+  // LDS: room for a slice's logits, or for 512 tokens' and the sums.  16 x 8 units, four heads, 312 slots per row 352 us a
+  // call against 417 back to back, 313 slots 483 against 420 (forked all the same, the retained kernel has the chip to
+  // itself with a workgroup per CU); 300 slots, slices of 832 tokens: 346 us in pieces of 512, 437 where both do not fit.
   constexpr int UNIT = 1280;                   // LDS is handed out in these
-  const int ret = retained_lds(d.G, p.rslice_tokens, true) + 2 * 4 * d.G * (int)sizeof(float);   // + statistics
-  return (p.lds_bytes + UNIT - 1) / UNIT + (ret + UNIT - 1) / UNIT <= STAGED_LDS_LIMIT / UNIT;
+  const int room = (STAGED_LDS_LIMIT / UNIT - (p.lds_bytes + UNIT - 1) / UNIT) * UNIT -
+                   2 * 4 * d.G * (int)sizeof(float);                               // statistics of the four waves
+  const int whole = retained_lds(d.G, p.rslice_tokens), least = retained_lds(d.G, 0);
+  return whole <= room ? whole : least <= room ? least : 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -564,14 +567,15 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
   const int cus = cu_count();
   const bool big = (long long)units * plan.n_vslices >= 2ll * cus;
   // And only where a CU holds a workgroup of each.
-  const bool side = sd.stream != nullptr && big && attend_side_fits(d, plan);
+  const int side_lds = attend_side_lds(d, plan);
+  const bool side = sd.stream != nullptr && big && side_lds > 0;
   if (side) {
     e = hipEventRecord(sd.fork, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(sd.stream, sd.fork, 0);
     if (e == hipSuccess) {
       // From here on the side stream may hold work that writes the caller's workspace: whatever
       // fails below, `st` is made to wait for it before this call returns.
-      e = launch_attend_retained(d, a, plan.n_rslices, cus, true, sd.stream);
+      e = launch_attend_retained(d, a, plan.n_rslices, cus, side_lds, sd.stream);
       const hipError_t ej = hipEventRecord(sd.join, sd.stream);
       if (e == hipSuccess && ej == hipSuccess) e = launch_attend_vague_staged(d, a, plan, st);
       hipError_t ew = (ej == hipSuccess) ? hipStreamWaitEvent(st, sd.join, 0) : ej;
@@ -581,7 +585,7 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
       }
     }
   } else if (plan.mfma_retained) {
-    e = launch_attend_retained(d, a, plan.n_rslices, 0, false, st);
+    e = launch_attend_retained(d, a, plan.n_rslices, 0, 0, st);
   } else {
     a.tok_limit = plan.staged ? a.ret_cap : a.ret_cap + a.vague_cap;
     dim3 grid(plan.n_rslices, units);

@@ -17,7 +17,9 @@
 // Bound by HBM.  Alone, a wave requests the next tile's rows while it computes (168 registers keep three waves
 // per SIMD); the logits wait in LDS and leave together, 16 bytes a lane.  32 units x 29492 slots, 4 heads: 107 ->
 // 102 us = 4.7 TB/s (a large copy reaches 5.1); 40 units x 4104 slots, 8 heads: 32.4 -> 30.0 us.  Next to a staged kernel
-// there are no registers for it, nor LDS for the logits, which leave from the registers.
+// there are no registers for it; the logits wait in what LDS the staged kernel leaves, of a whole slice or of 512 tokens
+// at a time (16 x 8 units of 32768 tokens, three layers, on a second stream that overlaps badly: 926 us a step with whole
+// slices of 768 tokens, 934 with 512 tokens at a time, 942 with every tile's logits stored from the registers).
 //
 // A workgroup walks over (unit, slice) items with a grid stride, so the launch
 // can be as wide as the item count (stand-alone: many workgroups per CU hide the
@@ -97,13 +99,12 @@ __device__ __forceinline__ void load_pos_v(RetTile& t, const bf16_t* __restrict_
 // One 16-token tile.  NEXT: the tile at t_next follows, and its K rows are requested as soon as this tile's are
 // consumed, its positions and V rows behind this tile's p.v, all into the same registers.  No global store may sit
 // between these loads (reads and writes complete in no common order, so a wait for a read with a write outstanding
-// is a wait for everything): IN_LDS, the logits go to the workgroup's LDS else
-// straight to memory (null: not wanted).  log: where the tile's first token's go.
-template <int G, bool NEXT, bool IN_LDS>
+// is a wait for everything): the logits go to s_log.
+template <int G, bool NEXT>
 __device__ __forceinline__ void compute_tile(RetTile& t, const uint4 (&qb)[4], const bf16_t* __restrict__ kret,
                                              const bf16_t* __restrict__ vret, const int32_t* __restrict__ rp,
                                              float scale, int t0, int t_next, int t_end, int ret_cap, int r16, int col,
-                                             float* __restrict__ log, float& m_run, float& l_run,
+                                             float* __restrict__ s_log, float& m_run, float& l_run,
                                              float (&acc)[G][8]) {
   const float NEG_INF = -__builtin_inff();
   f32x4_t S = {0.f, 0.f, 0.f, 0.f};
@@ -124,15 +125,9 @@ __device__ __forceinline__ void compute_tile(RetTile& t, const uint4 (&qb)[4], c
     s[i] = ok ? S[i] * scale : NEG_INF;
     invalid = invalid || t.pos[i] < 0;
   }
-  if constexpr (IN_LDS) {
-    if (col < G) {
+  if (col < G) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) log[(4 * r16 + i) * G + col] = s[i];
-    }
-  } else if (log != nullptr && col < G) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (t0 + 4 * r16 + i < t_end) log[(4 * r16 + i) * G + col] = s[i];
+    for (int i = 0; i < 4; ++i) s_log[(4 * r16 + i) * G + col] = s[i];
   }
   float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
   mx = fmaxf(mx, __shfl_xor(mx, 16));
@@ -171,14 +166,16 @@ __device__ __forceinline__ void compute_tile(RetTile& t, const uint4 (&qb)[4], c
 }
 
 template <int G, bool AHEAD>
-__device__ __forceinline__ void attend_retained_body(const DevDesc& d, const AttendArgs& a, int n_rslices) {
+__device__ __forceinline__ void attend_retained_body(const DevDesc& d, const AttendArgs& a, int n_rslices,
+                                                     int seg_tiles) {
   constexpr int NW = 4;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane >> 4, col = lane & 15;
   const int tot_cap = a.ret_cap + a.vague_cap;
   const int n_items = d.B * d.Hkv * n_rslices;
   const float NEG_INF = -__builtin_inff();
-  // the waves' sums [NW][G][D]; AHEAD: the logits of the slice while it is walked, then the sums
+  // logits while the slice is walked (AHEAD: of the whole slice, else of seg_tiles tiles at a time), then the waves' sums
+  // [NW][G][D]
   extern __shared__ __align__(16) float s_dyn[];
   __shared__ float s_m[NW][G], s_l[NW][G];
 
@@ -218,20 +215,39 @@ __device__ __forceinline__ void attend_retained_body(const DevDesc& d, const Att
 #pragma unroll
       for (int c = 0; c < 8; ++c) acc[g][c] = 0.f;
 
+    // logits of n_tok tokens from the slice's token `first` on leave LDS together, 16 bytes a lane
+    auto store_logits = [&](int first, int n_tok) {
+      if (logits_unit == nullptr) return;
+      const int n = n_tok * G;                     // floats
+      float* dst = logits_unit + (size_t)(t_begin + first) * G;
+      if constexpr (G % 4 == 0) {
+        for (int i = threadIdx.x * 4; i < n; i += 1024)
+          *reinterpret_cast<float4*>(dst + i) = *reinterpret_cast<const float4*>(s_dyn + i);
+      } else {
+        for (int i = threadIdx.x; i < n; i += 256) dst[i] = s_dyn[i];
+      }
+    };
     if constexpr (AHEAD) {
       for (; ti + NW < n_tiles; ti += NW)
-        compute_tile<G, true, true>(tile, qb, kret, vret, rp, d.scale, t_begin + ti * 16, t_begin + (ti + NW) * 16,
-                                    t_end, a.ret_cap, r16, col, s_dyn + ti * 16 * G, m_run, l_run, acc);
+        compute_tile<G, true>(tile, qb, kret, vret, rp, d.scale, t_begin + ti * 16, t_begin + (ti + NW) * 16, t_end,
+                              a.ret_cap, r16, col, s_dyn + ti * 16 * G, m_run, l_run, acc);
       if (ti < n_tiles)
-        compute_tile<G, false, true>(tile, qb, kret, vret, rp, d.scale, t_begin + ti * 16, 0, t_end, a.ret_cap, r16,
-                                     col, s_dyn + ti * 16 * G, m_run, l_run, acc);
+        compute_tile<G, false>(tile, qb, kret, vret, rp, d.scale, t_begin + ti * 16, 0, t_end, a.ret_cap, r16, col,
+                               s_dyn + ti * 16 * G, m_run, l_run, acc);
+      __syncthreads();             // the slice's logits are complete
+      store_logits(0, t_end - t_begin);
+      __syncthreads();             // everyone has read them: the sums may take their place
     } else {
-      for (; ti < n_tiles; ti += NW) {
-        load_k(tile, kret, t_begin + ti * 16, a.ret_cap, r16, col);
-        load_pos_v(tile, vret, rp, t_begin + ti * 16, t_end, a.ret_cap, r16, col);
-        float* log = logits_unit ? logits_unit + (size_t)(t_begin + ti * 16) * G : nullptr;
-        compute_tile<G, false, false>(tile, qb, kret, vret, rp, d.scale, t_begin + ti * 16, 0, t_end, a.ret_cap, r16,
-                                      col, log, m_run, l_run, acc);
+      for (int s0 = 0; s0 < n_tiles; s0 += seg_tiles) {
+        for (; ti < min(s0 + seg_tiles, n_tiles); ti += NW) {
+          load_k(tile, kret, t_begin + ti * 16, a.ret_cap, r16, col);
+          load_pos_v(tile, vret, rp, t_begin + ti * 16, t_end, a.ret_cap, r16, col);
+          compute_tile<G, false>(tile, qb, kret, vret, rp, d.scale, t_begin + ti * 16, 0, t_end, a.ret_cap, r16, col,
+                                 s_dyn + (ti - s0) * 16 * G, m_run, l_run, acc);
+        }
+        __syncthreads();
+        store_logits(s0 * 16, min(t_end - t_begin - s0 * 16, seg_tiles * 16));
+        __syncthreads();
       }
     }
 
@@ -246,20 +262,6 @@ __device__ __forceinline__ void attend_retained_body(const DevDesc& d, const Att
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);
 
-    __syncthreads();             // the slice's logits are complete; the previous item's sums are read
-    if constexpr (AHEAD) {
-      if (logits_unit != nullptr) {
-        const int n = (t_end - t_begin) * G;       // floats
-        float* dst = logits_unit + (size_t)t_begin * G;
-        if constexpr (G % 4 == 0) {
-          for (int i = threadIdx.x * 4; i < n; i += 1024)
-            *reinterpret_cast<float4*>(dst + i) = *reinterpret_cast<const float4*>(s_dyn + i);
-        } else {
-          for (int i = threadIdx.x; i < n; i += 256) dst[i] = s_dyn[i];
-        }
-      }
-      __syncthreads();           // everyone has read them: the sums may take their place
-    }
     float (*s_acc)[G][D] = reinterpret_cast<float (*)[G][D]>(s_dyn);
     if (r16 == 0) {
 #pragma unroll
@@ -286,7 +288,7 @@ __device__ __forceinline__ void attend_retained_body(const DevDesc& d, const Att
       po[idx] = O;
       if (c == 0) { pml[g * 2] = M; pml[g * 2 + 1] = L; }
     }
-    if constexpr (AHEAD) __syncthreads();      // the next item writes its logits over the sums
+    __syncthreads();             // the next item writes its logits over the sums
   }
 }
 
@@ -296,26 +298,28 @@ __device__ __forceinline__ void attend_retained_body(const DevDesc& d, const Att
 // registers exactly; the few spills of this kernel, which waits for HBM most of the time, cost nothing.
 template <int G>
 __global__ __launch_bounds__(256, (G <= 1 ? 4 : G <= 4 ? 3 : 2)) void attend_retained_kernel(DevDesc d, AttendArgs a, int n_rslices) {
-  attend_retained_body<G, true>(d, a, n_rslices);
+  attend_retained_body<G, true>(d, a, n_rslices, 0);
 }
 template <int G>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(62))) void attend_retained_shared_kernel(
-    DevDesc d, AttendArgs a, int n_rslices) {
-  attend_retained_body<G, false>(d, a, n_rslices);
+    DevDesc d, AttendArgs a, int n_rslices, int seg_tiles) {
+  attend_retained_body<G, false>(d, a, n_rslices, seg_tiles);
 }
 
 hipError_t launch_attend_retained(const DevDesc& d, const AttendArgs& a, int n_rslices, int max_wgs,
-                                  bool next_to_staged, hipStream_t st) {
+                                  int side_lds, hipStream_t st) {
   int n_wgs = d.B * d.Hkv * n_rslices;
   if (max_wgs > 0 && n_wgs > max_wgs) n_wgs = max_wgs;
   if (n_wgs < 1) return hipSuccess;
   const dim3 grid(n_wgs), block(256);
-  const size_t lds = retained_lds(d.G, a.slice_tokens, next_to_staged);
-  if (next_to_staged) {
+  const int lds = side_lds ? side_lds : retained_lds(d.G, a.slice_tokens);
+  if (side_lds) {
+    if (side_lds < retained_lds(d.G, 0)) return hipErrorInvalidValue;
+    const int seg = side_lds / (d.G * 4 * 16) / 4 * 4;         // tiles, the same number for each of the four waves
     switch (d.G) {
-      case 1: hipLaunchKernelGGL(attend_retained_shared_kernel<1>, grid, block, lds, st, d, a, n_rslices); break;
-      case 2: hipLaunchKernelGGL(attend_retained_shared_kernel<2>, grid, block, lds, st, d, a, n_rslices); break;
-      case 4: hipLaunchKernelGGL(attend_retained_shared_kernel<4>, grid, block, lds, st, d, a, n_rslices); break;
+      case 1: hipLaunchKernelGGL(attend_retained_shared_kernel<1>, grid, block, lds, st, d, a, n_rslices, seg); break;
+      case 2: hipLaunchKernelGGL(attend_retained_shared_kernel<2>, grid, block, lds, st, d, a, n_rslices, seg); break;
+      case 4: hipLaunchKernelGGL(attend_retained_shared_kernel<4>, grid, block, lds, st, d, a, n_rslices, seg); break;
       default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

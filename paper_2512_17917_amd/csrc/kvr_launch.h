@@ -27,8 +27,8 @@ struct AttendPlan {
   size_t off_part_o, off_part_ml, off_logits, off_rec, off_partial, total_bytes;
 };
 AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long vague_cap);
-// a workgroup of the staged kernel and one of the retained kernel's capped form find room on one CU
-bool attend_side_fits(const DevDesc& d, const AttendPlan& p);
+// Dynamic LDS of the retained kernel's capped form next to the plan's staged kernel; 0 = a CU has no room for both.
+int attend_side_lds(const DevDesc& d, const AttendPlan& p);
 
 struct AttendArgs {
   const void* q;
@@ -64,16 +64,15 @@ struct AttendArgs {
 
 // Retained slots by the MFMA kernel (bf16): slices 0 .. n_rslices-1 of a.slice_tokens slots.
 // max_wgs > 0 caps the launch width (the workgroups then walk the items with a grid stride).
-// next_to_staged: the form capped at 128 registers, for the launch that shares the SIMDs with a staged kernel (G <= 4).
-// Dynamic LDS of a workgroup: the sums of its four waves, and alone, in the same place, the logits of its slice.  Next to
-// a staged kernel the sums alone: LDS of a CU holds both kernels' workgroups up to the widest sketch it can (128 units, 300
-// slots per row, slices of 832 tokens: a call takes 346 us, with 16 bytes of LDS per token of the slice 437).
-constexpr int retained_lds(int G, int slice_tokens, bool next_to_staged) {
-  const int sums = 4 * D, logits = (slice_tokens + 15) / 16 * 16;
-  return G * 4 * (next_to_staged || sums > logits ? sums : logits);          // <= 32 KB (1024 tokens, G = 8)
+// side_lds > 0: the form capped at 128 registers, for the launch that shares the CUs with a staged kernel (G <= 4), with
+// that much dynamic LDS (attend_side_lds).
+// Dynamic LDS of a workgroup: the sums of its four waves and, in the same place, the logits of as many tokens.
+constexpr int retained_lds(int G, int tokens) {
+  const int sums = 4 * D, logits = (tokens + 15) / 16 * 16;
+  return G * 4 * (sums > logits ? sums : logits);          // <= 32 KB (1024 tokens, G = 8)
 }
 hipError_t launch_attend_retained(const DevDesc& d, const AttendArgs& a, int n_rslices, int max_wgs,
-                                  bool next_to_staged, hipStream_t st);
+                                  int side_lds, hipStream_t st);
 
 // kept rows of a prompt's cache into the small slot array
 hipError_t launch_compact(const DevDesc& d, int dtype, const void* k_src, const void* v_src, const int32_t* src_pos,

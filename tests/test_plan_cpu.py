@@ -9,7 +9,8 @@ from paper_2512_17917_amd import build as B
 PROBE = r"""
 #include <cstdio>
 #include "kvr_launch.h"
-// per input line: units heads rows slots retained vague -> side-by-side fits, LDS of the staged and the retained kernel,
+// per input line: units heads rows slots retained vague -> LDS of the retained kernel next to the staged one (0: not side
+// by side), of the staged kernel, of the retained kernel alone,
 // parts of the Vague list, channels per phase of the staged kernel (0: the list is not staged)
 int main() {
   int units, G, r, w, ret, vague;
@@ -17,8 +18,8 @@ int main() {
     kvr::DevDesc d = {};
     d.B = 1; d.Hkv = units; d.Hq = units * G; d.G = G; d.r = r; d.w = w; d.sign_mask = 2;
     const kvr::AttendPlan p = kvr::attend_plan(d, KVR_BF16, ret, vague);
-    std::printf("%d %d %d %d %d\n", (int)kvr::attend_side_fits(d, p), p.lds_bytes,
-                kvr::retained_lds(G, p.rslice_tokens, true), p.n_vslices, p.staged ? p.ch : 0);
+    std::printf("%d %d %d %d %d\n", kvr::attend_side_lds(d, p), p.lds_bytes,
+                kvr::retained_lds(G, p.rslice_tokens), p.n_vslices, p.staged ? p.ch : 0);
   }
 }
 """
@@ -42,18 +43,21 @@ def plan(tmp_path_factory):
 @pytest.mark.parametrize("units", [64, 128, 192, 512])
 def test_retained_kernel_fits_next_to_a_staged_one(plan, units):
     """Whatever the slices of the retained slots: beside the 64-channel kernel up to 312 slots per row with four heads
-    (120 KB of chunk + 34 KB + 8.1 KB), and beside the three-row 16-channel kernel at every width it takes."""
+    (120 KB of chunk + 34 KB + 8.1 KB), and beside the three-row 16-channel kernel at every width it takes; with the logits
+    of a whole slice where there is room, else with those of the 512 tokens that fit its sums' place."""
     case = lambda G, w: (units, G, 3, w, 27 * w, 93 * w)
     for w, fits in [(6, 1), (273, 1), (291, 1), (300, 1), (312, 1), (313, 0), (333, 0), (334, 1), (700, 1), (1365, 1)]:
-        ok, staged, ret = plan(case(4, w))[0][:3]
-        assert ok == fits and (staged + ret + 128 <= 160 * 1024) == bool(fits), (w, staged, ret)
+        side, staged, alone = plan(case(4, w))[0][:3]
+        assert (side > 0) == bool(fits) and (staged + 8192 + 128 <= 160 * 1024) == bool(fits), (w, staged, side)
+        assert side in ((alone, 8192) if fits else (0,)) and staged + side + 128 <= 160 * 1024
+        assert side == alone or staged + alone + 128 > 160 * 1024 - 2 * 1280
     assert all(p[0] for p in plan(*[case(1, w) for w in (300, 341, 342, 1365)]))
 
 
 def test_registers_next_to_a_staged_kernel(plan):
     """Four rows: 238 registers a wave in the 16-channel kernel, 194 and more in the general one with four heads; two
     waves of those leave no 128.  Everything else does, LDS permitting."""
-    ok = [p[0] for p in plan((128, 4, 4, 819, 9000, 30000), (128, 1, 4, 300, 9000, 30000), (128, 4, 4, 1100, 9000, 30000),
+    ok = [int(p[0] > 0) for p in plan((128, 4, 4, 819, 9000, 30000), (128, 1, 4, 300, 9000, 30000), (128, 4, 4, 1100, 9000, 30000),
                              (128, 2, 4, 1100, 9000, 30000), (128, 1, 4, 1030, 9000, 30000), (128, 4, 3, 1400, 9000, 30000),
                              (128, 8, 3, 60, 9000, 30000))]
     assert ok == [0, 0, 0, 1, 1, 1, 0]
