@@ -39,11 +39,11 @@ OFFLINE_COUNTERS = {
     "c4": {
         # bytes per kvr_attend_decode call at the memory side of the L2: read requests priced by their size
         # (32 / 64 / 128 B request counters) + WRITE_SIZE, summed over the call's three kernels
-        "traffic": 781.5e6,
-        "traffic_note": "off-line counter reading (profiles/attend_call_c4_hbm_traffic.txt): 680.6 MB read "
+        "traffic": 782.7e6,
+        "traffic_note": "off-line counter reading (profiles/attend_call_c4_hbm_traffic.txt): 681.0 MB read "
                         "(TCC_EA0_RDREQ by request size; FETCH_SIZE prices this chip's 128-byte requests at 64 "
-                        "bytes and reads half of that) + 100.9 MB written (WRITE_SIZE), retained + staged + merge "
-                        "kernel of one call; the 198 MB above the algorithmic bytes are the logits handed from the "
+                        "bytes and reads half of that) + 101.6 MB written (WRITE_SIZE), retained + staged + merge "
+                        "kernel of one call; the 199 MB above the algorithmic bytes are the logits handed from the "
                         "attention kernels to the score pass, the slice partials and whole lines pulled by "
                         "4-byte score accesses",
         "alu": {"file": "profiles/attend_kernels_c4_sq_counters.txt", "kernel": "attend_vague_staged64_kernel<4>",

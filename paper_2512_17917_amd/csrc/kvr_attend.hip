@@ -300,6 +300,8 @@ __global__ __launch_bounds__(256) void attend_main_kernel(DevDesc d, AttendArgs 
 // merge kernel
 // ---------------------------------------------------------------------------
 
+// Waves per SIMD: the most whose registers hold the kernel without a spill (64 registers: 1 spilled with four heads, 62
+// with eight; 80: 9 with eight; 96: 6 with sixteen columns).
 template <int G>
 __global__ __launch_bounds__(256, (G <= 2 ? 8 : G <= 4 ? 7 : G == 8 ? 5 : 4)) void attend_combine_kernel(DevDesc d, AttendArgs a) {
   const int unit = blockIdx.y;

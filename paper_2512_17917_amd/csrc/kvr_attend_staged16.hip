@@ -10,10 +10,12 @@
 // Inside a chunk the unit of work is a *half piece*: 4 channels = 8 bytes, which
 // is exactly the contraction length of v_mfma_f32_4x4x4.
 //
-// Three rows, one layer's decode step against the general kernel with float32
-// p.v: 131072 tokens, 16 units 452 -> 235 us, 8 units 263 -> 175 us; 70000 tokens, 24 units 235 -> 189 us;
-// 42000 tokens, 48 units 259 -> 207 us, 8 units 92 -> 92 us.  With three rows a wave holds 192 registers (four:
-// 240), which leaves room for the retained-slot kernel next to it.
+// Vector ALUs 71 % busy with four rows; with three 58 % at 1092 slots per row and 68 % at 350, where the sixteen chunk
+// phases (copy, barriers, reduction) are worth 66 of a turn's 140 us and 30 of its 111.  Three rows against the general
+// kernel: 131072 tokens, 16 units 353 -> 136 us; one layer's whole decode step, with what else changed in it: 454 -> 231 us,
+// 8 units 263 -> 172; 70000 tokens, 24 units 235 -> 184; 42000 tokens, 48 units 260 -> 199, 8 units 92 -> 86.  (A sketch with
+// about as many slots as tokens loses: 256 units, 1500 tokens, 3 x 400 slots 182 -> 200 us a call.)  With three rows a
+// wave holds 192 registers (four: 240), which leaves room for the retained-slot kernel next to it.
 // Error of a call's output against float64, relative in the 2-norm, three rows: 1.6e-7 (200 tokens) .. 3.0e-7 (101580), as
 // with the general kernel's float32 multiply-adds (1.7e-7 .. 3.2e-7); weights as two bf16 parts: 8e-6 .. 1.1e-5, three
 // parts cost 1 % of the time.  Four rows: two parts, 7e-6 .. 1.1e-5.
