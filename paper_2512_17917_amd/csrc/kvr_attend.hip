@@ -50,14 +50,15 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
     const bool s64 = staged64_applies(d), s16 = staged16_applies(d);
     p.lds_bytes = s64 ? staged64_lds(d.w, d.G) : s16 ? staged16_lds(d) : 0;
     p.ch = s64 ? 64 : s16 ? 16 : 0;
-    // The general kernel: 16 channels where they fit (four heads: 5056 rows), else 8, up to 8000 rows: a chunk then passes
-    // through LDS 32 times for fewer and fewer tokens per row, and the gather of the generic kernel is no slower.
+    // The general kernel: 16 channels where they fit (four heads: 5056 rows), else 8, up to 8000 rows with four heads, 8288
+    // with two, 8432 with one (the gather takes more workspace, so the line stays where callers' workspaces know it): a chunk then
+    // passes through LDS 32 times for fewer and fewer tokens per row, and the gather of the generic kernel is no slower.
     // 16 units, 31 tokens per row, us with 8 channels / by the gather: four rows, four heads 7000 rows 924 / 995, 8000
     // 1030 / 1076, 9000 1165 / 1150; one head 6000 560 / 665, 7000 865 / 714; three rows, four heads 5100 483 / 502,
     // 6000 558 / 534, 7000 867 / 723 (three rows, and one head, lose from a narrower sketch on than the line says).
     // 16 against 8 channels: 32 units of 139000 tokens, 4500 rows, 1360 -> 946 us a call.
     for (int c = 16; c >= 8 && p.ch == 0; c >>= 1)
-      if (staged_lds(d.r * d.w, d.G, c) <= STAGED_LDS_LIMIT && (c == 16 || d.r * d.w <= 8000)) {
+      if (staged_lds(d.r * d.w, d.G, c) <= STAGED_LDS_LIMIT && (c == 16 || d.r * d.w <= 8576 - 144 * d.G)) {
         p.ch = c;
         p.lds_bytes = staged_lds(d.r * d.w, d.G, c);
       }

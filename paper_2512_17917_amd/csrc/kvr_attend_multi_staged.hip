@@ -426,7 +426,7 @@ int multi_staged_pad_tokens() { return MS_PAD_TOKENS; }
 // 82 us, 6 parts 49 us.  A turn of 256 workgroups, 8 columns, 273 slots per row: 34.7 us at 1024 tokens each, 87.5 at 4096.
 int multi_staged_part_tokens(long long vague_cap, long long units) {
   const long long turn = units < 256 ? 256 / units : 1;
-  const long long n = std::max(1ll, std::min(turn, (vague_cap + 255) / 256));
+  const long long n = std::max(1ll, std::min(turn, (vague_cap - 1) / 255));       // ceil(vague_cap / n) >= 256
   const long long t = std::max(256ll, (vague_cap + n - 1) / n);
   return (int)((t + 15) / 16 * 16);
 }
