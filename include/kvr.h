@@ -124,8 +124,9 @@ typedef struct kvr_desc {
  *       (not `stream` itself) and two hipEvent_t (timing may be disabled), created
  *       and owned by the caller; all three or none.  With them, and when the call is
  *       large enough for it to pay (bf16, the Vague list long enough to fill the
- *       chip twice over) and a compute unit has room for both, the kernel that streams the retained tokens runs on
- *       side_stream next to the kernel that rebuilds the Vague tokens on `stream`:
+ *       chip twice over) and a compute unit has room for both kernels, the one that
+ *       streams the retained tokens runs on side_stream next to the one that
+ *       rebuilds the Vague tokens on `stream`:
  *       fork_event is recorded on `stream` and awaited by side_stream, join_event is
  *       recorded on side_stream and awaited by `stream` before the merge kernel, on
  *       every path including errors, so the call stays ordered on `stream` and the

@@ -576,6 +576,44 @@ def test_attend_side_by_side_wide_sketch(kvr, G, r, w, cap):
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
 
 
+@pytest.mark.parametrize("w,ret,cap", [(312, 6001, 9400), (273, 7374, 9400), (1365, 9500, 27000)])
+def test_attend_side_by_side_long_slices(kvr, w, ret, cap):
+    """Slices of more than 512 retained tokens: next to a staged kernel their logits leave LDS 512 tokens at a time (w = 312
+    beside the 64-channel kernel, w = 1365 beside the 16-channel kernel) or all at once (w = 273).  Bit for bit against the
+    call without the second stream, with and without scores; a ragged last slice, empty slots, an empty unit."""
+    B, Hkv, G, D, dev = 16, 8, 4, 128, "cuda"
+    say("attend side by side, long slices", w, ret, cap)
+    g = torch.Generator(device=dev).manual_seed(w)
+    rn = lambda *shape: torch.randn(*shape, generator=g, device=dev, dtype=torch.bfloat16)
+    d = kvr.make_desc(B, Hkv * G, Hkv, 3, w, torch.bfloat16, seed=5)
+    q, K, V = rn(B, Hkv * G, D), rn(B, Hkv, ret, D), rn(B, Hkv, ret, D)
+    SK, SV = rn(B, Hkv, 3, w, D), rn(B, Hkv, 3, w, D)
+    perm = torch.randperm(ret + cap, generator=g, device=dev).to(torch.int32)
+    rp = perm[:ret].expand(B, Hkv, ret).contiguous()
+    rp[torch.rand(rp.shape, generator=g, device=dev) < 0.1] = -1
+    rp[2, 3] = -1
+    vp = perm[ret:].expand(B, Hkv, cap).contiguous()
+    nv = torch.randint(cap - 300, cap + 1, (B, Hkv), generator=g, device=dev).to(torch.int32)
+    nv[2, 3] = 0
+    ws = kvr.alloc_workspace(d, kvr.KVR_OP_ATTEND, ret, cap)
+    side, got = kvr.SideStream(), []
+    for sd in (side, None):
+        for with_scores in (True, False):
+            out = torch.full((B, Hkv * G, D), 9.0, device=dev)
+            sc = torch.ones(B, Hkv, ret + cap, device=dev)
+            ws.fill_(255)                                   # what a call leaves unwritten is NaN
+            kvr.kvr_attend_decode(d, q, K, V, rp, ret, SK, SV, vp, nv, cap, out, sc if with_scores else None, ret + cap, ws,
+                                  sd.opts() if sd else None)
+            torch.cuda.synchronize()
+            assert torch.isfinite(out).all() and torch.isfinite(sc).all()
+            assert not out[2, 3 * G:4 * G].any()
+            got.append((out, sc))
+    for a, b in zip(got[:2], got[2:]):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    assert torch.equal(got[0][0], got[1][0])
+    assert torch.allclose((got[0][1] - 1).sum(dim=2)[0], torch.full((Hkv,), float(G), device=dev), atol=1e-3)
+
+
 def test_attend_eight_heads_per_kv_head(kvr):
     """bf16, r = 3, G = 8: the Vague list goes through the streaming LDS-staged kernel (the one of
     kvr_attend_multi, one query, 8 columns): several workgroups per unit, ragged tiles, empty and clamped
