@@ -445,15 +445,12 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
   // Weights are formed against the wave's own maximum, which needs no barrier; the
   // workgroup's maximum is put together after the barrier that publishes the first
   // V chunk, and each wave's sums are rescaled by exp(own maximum - workgroup
-  // maximum) when they are merged.  s_stat: [8 waves][G] maxima, [NROW][G] row sums.
-  const int prow = wave * 4 + (lane >> 4);
+  // maximum) when they are merged.  s_stat: [G][8 waves] maxima, [G][8 waves] sums.
   float lsum[G];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    float x = row_max(mx[g]);
-    x = fmaxf(x, __shfl_xor(x, 16));
-    x = fmaxf(x, __shfl_xor(x, 32));
-    if (lane == 0) s_stat[wave * G + g] = x;
+    const float x = rows_max(row_max(mx[g]));
+    if (lane == 0) s_stat[g * ST_WAVES + wave] = x;
     lsum[g] = 0.f;
 #pragma unroll
     for (int k = 0; k < KMAX; ++k) {
@@ -465,8 +462,8 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
   }
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    lsum[g] = row_sum<1>(lsum[g]);
-    if ((lane & 15) == 0) s_stat[ST_WAVES * G + prow * G + g] = lsum[g];
+    lsum[g] = rows_sum(row_sum<1>(lsum[g]));
+    if (lane == 0) s_stat[(G + g) * ST_WAVES + wave] = lsum[g];
   }
   const size_t part = (size_t)unit_l * a.n_slices + a.n_rslices + opaque_s(__builtin_amdgcn_readfirstlane(vs));
 
@@ -516,41 +513,11 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
   // that 8 neighbouring lanes always cover 8 different 16-byte bank groups
   const int pa = sub + ((tl & 1) ? 4 : 0);
   const int pb = sub + ((tl & 1) ? 0 : 4);
-  float* s_fw = s_stat + (ST_WAVES + NROW) * G;     // [8 waves][G]: exp(wave maximum - workgroup maximum)
   float pend_v = 0.f;                      // chunk 0's output element of this thread, stored one barrier later
   for (int cc = 0; cc < NPH; ++cc) {
     stage_wait();
     lds_barrier();
-    if (cc == 0) {
-      // every wave's maximum and row sums are visible now (this wave's own maximum is
-      // read back too: it would not survive in registers without being spilled)
-      float mo[G], mw[G], mr[G], sr[G];
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        mo[g] = s_stat[(lane & 7) * G + g];                          // maximum of wave (lane mod 8)
-        mw[g] = s_stat[wave * G + g];
-        // lane l < 32 takes row l, which belongs to wave l / 4
-        mr[g] = s_stat[((lane & (NROW - 1)) >> 2) * G + g];
-        sr[g] = s_stat[ST_WAVES * G + (lane & (NROW - 1)) * G + g];
-      }
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        float M = dpp_max<0x121>(mo[g]);
-        M = dpp_max<0x122>(M);
-        M = dpp_max<0x124>(M);                               // over 8 neighbouring lanes = all 8 waves
-        // kept in LDS rather than in registers through the V phases; only this wave reads it back
-        if (lane == 0) s_fw[wave * G + g] = (mw[g] == -__builtin_inff()) ? 0.f : __expf(mw[g] - M);
-        if (wave == 0) {
-          const float fr = (mr[g] == -__builtin_inff()) ? 0.f : __expf(mr[g] - M);
-          float x = row_sum<1>(sr[g] * fr);
-          x += __shfl_xor(x, 16);
-          if (lane == 0) {
-            a.part_ml[(part * G + g) * 2] = M;
-            a.part_ml[(part * G + g) * 2 + 1] = x;
-          }
-        }
-      }
-    } else if (tid < G * CH) {
+    if (cc > 0 && tid < G * CH) {
       // chunk cc - 1's element; its latency now hides under this chunk's arithmetic
       a.part_o[part * G * D + (tid / CH) * D + (cc - 1) * CH + (tid % CH)] = pend_v;
     }
@@ -574,30 +541,59 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
     // Reduction over the workgroup's tokens.  Lane (quad, sub) holds, per head,
     // the 8 channels of piece pb summed over the tokens of its quad and of the
     // neighbouring quad; lanes l and l + 8 of a 16-lane row hold the same piece
-    // (one DPP rotation adds them), and the NROW rows meet in LDS.
-    if constexpr (true) {
+    // (one DPP rotation adds them).  The wave adds its four rows through its own share of s_part (no barrier: nobody else
+    // touches it), which leaves one row of G x CH sums per wave, at the start of that share.
+    // 8 instead of 32 rows are left behind the barrier, and the statistics are formed here, by the threads that use them,
+    // instead of by one wave ahead of the V phases: 16 x 8 units of 32768 tokens 261 -> 255 us a call, 8 x 8 of 2048 29.2 -> 28.7.
+    {
+      float* own = s_part + wave * 4 * G * CH;
       float o[G][8];
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const float f = s_fw[wave * G + g];
+      for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int c = 0; c < 8; ++c) o[g][c] = dpp_add<0x128>(acc[c][g]) * f;
-      }
+        for (int c = 0; c < 8; ++c) o[g][c] = dpp_add<0x128>(acc[c][g]);
       if ((lane & 15) < 8) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-          float* dst = s_part + (prow * G + g) * CH + pb * 8;
+          float* dst = own + ((lane >> 4) * G + g) * CH + pb * 8;
           *reinterpret_cast<float4*>(dst) = make_float4(o[g][0], o[g][1], o[g][2], o[g][3]);
           *reinterpret_cast<float4*>(dst + 4) = make_float4(o[g][4], o[g][5], o[g][6], o[g][7]);
         }
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (lane < G * CH / 4) {
+        float4 x[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = *reinterpret_cast<const float4*>(own + r * G * CH + lane * 4);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        *reinterpret_cast<float4*>(own + lane * 4) =
+            make_float4((x[0].x + x[1].x) + (x[2].x + x[3].x), (x[0].y + x[1].y) + (x[2].y + x[3].y),
+                        (x[0].z + x[1].z) + (x[2].z + x[3].z), (x[0].w + x[1].w) + (x[2].w + x[3].w));
       }
     }
     lds_barrier();
     static_assert(G * CH <= ST_THREADS, "one output element per thread and chunk");
     if (tid < G * CH) {
+      // each wave's sums were formed against its own maximum: f[x] = exp(maximum of wave x - workgroup's maximum)
+      const int g = tid / CH;
+      float m[ST_WAVES], f[ST_WAVES];
+#pragma unroll
+      for (int x = 0; x < ST_WAVES; ++x) m[x] = s_stat[g * ST_WAVES + x];
+      float M = m[0];
+#pragma unroll
+      for (int x = 1; x < ST_WAVES; ++x) M = fmaxf(M, m[x]);
+#pragma unroll
+      for (int x = 0; x < ST_WAVES; ++x) f[x] = (m[x] == -__builtin_inff()) ? 0.f : __expf(m[x] - M);
       float v = 0.f;
 #pragma unroll
-      for (int pr = 0; pr < NROW; ++pr) v += s_part[pr * G * CH + tid];
+      for (int x = 0; x < ST_WAVES; ++x) v += s_part[x * 4 * G * CH + tid] * f[x];
+      if (cc + 1 == NPH && tid % CH == 0) {
+        float L = 0.f;
+#pragma unroll
+        for (int x = 0; x < ST_WAVES; ++x) L += s_stat[(G + g) * ST_WAVES + x] * f[x];
+        a.part_ml[(part * G + g) * 2] = M;
+        a.part_ml[(part * G + g) * 2 + 1] = L;
+      }
       // The wait before the next barrier would also wait for this store: all but the
       // last chunk's element are held back until that barrier has passed.
       if (cc + 1 < NPH) pend_v = v;

@@ -165,6 +165,22 @@ __device__ __forceinline__ float row_max(float x) {
   return dpp_max<0x128>(x);
 }
 
+// Over the four 16-lane rows of a wave (lanes with equal number modulo 16), in every lane: two row exchanges on the vector
+// ALUs (v_permlane16_swap / v_permlane32_swap) where a shuffle would go through LDS.
+template <typename F>
+__device__ __forceinline__ float rows_fold(float x, F&& f) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = f(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float rows_max(float x) {
+  return rows_fold(x, [](float a, float b) { return fmaxf(a, b); });
+}
+__device__ __forceinline__ float rows_sum(float x) {
+  return rows_fold(x, [](float a, float b) { return a + b; });
+}
+
 // token info: 4 x 16 bits; bits 0..14 = LDS row index (i * w + h_i(J)), bit 15 = 1 iff g_i(J) = -1
 template <int I>
 __device__ __forceinline__ uint32_t info_row(uint2 inf) {
