@@ -241,7 +241,7 @@ __global__ __launch_bounds__(MS_THREADS) void attend_multi_staged_kernel(DevDesc
         const uint4 x0 = *reinterpret_cast<const uint4*>(s_sk + swz_piece(rb[0], p));
         const uint4 x1 = *reinterpret_cast<const uint4*>(s_sk + swz_piece(rb[1], p));
         const uint4 x2 = *reinterpret_cast<const uint4*>(s_sk + swz_piece(rb[2], p));
-        ka[kx] = med3_piece(x0, x1, x2);
+        ka[kx] = med3_fast_piece(x0, x1, x2);
       }
       f32x4_t S = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(MS_THREADS) void attend_multi_staged_kernel(DevDesc
         const uint32_t fm = (uint32_t)((int)rj[j].y >> 31) & 0x80008000u;
         x2.x ^= fm;
         x2.y ^= fm;
-        vt[j] = med3_half_piece(x0, x1, x2);
+        vt[j] = med3_fast_half_piece(x0, x1, x2);
       }
       short4_t bop[4];
       bop[0] = pack_k4(pair_lo(vt[0].x, vt[1].x), pair_lo(vt[2].x, vt[3].x));

@@ -67,7 +67,7 @@ __device__ __forceinline__ void load_rows(Rows<R>& o, const unsigned char* s_sk,
 template <int R, int MODE>
 __device__ __forceinline__ uint2 median_rows_of(const Rows<R>& v) {
   if constexpr (R == 3) {
-    return med3_half_piece(v.r[0], v.r[1], v.r[2]);
+    return med3_fast_half_piece(v.r[0], v.r[1], v.r[2]);
   } else {
     const uint32_t x[4] = {v.r[0].x, v.r[1].x, v.r[2].x, v.r[3].x};
     const uint32_t y[4] = {v.r[0].y, v.r[1].y, v.r[2].y, v.r[3].y};

@@ -32,7 +32,7 @@ __device__ __forceinline__ void load_rows3(Rows3& o, const unsigned char* s_sk, 
 }
 
 __device__ __forceinline__ uint4 median3(const Rows3& x) {
-  return med3_piece(x.r0, x.r1, x.r2);
+  return med3_fast_piece(x.r0, x.r1, x.r2);
 }
 
 // value of lane J of this lane's quad
