@@ -99,12 +99,11 @@ __device__ __forceinline__ void v_fetch(VItem& o, const VOwn& own, const unsigne
   load_rows3(o.rows, s_sk, rb, 0);
 }
 
+// (the result goes through v_perm_b32 before it reaches a matrix instruction)
 __device__ __forceinline__ uint4 v_median(const VItem& it) {
-  Rows3 x;
-  x.r0 = it.rows.r0;
-  x.r1 = it.rows.r1;
-  x.r2 = xor4(it.rows.r2, it.fm2);
-  return median3(x);
+  const uint4 a = it.rows.r0, b = it.rows.r1, c = xor4(it.rows.r2, it.fm2);
+  return make_uint4(med3_fast_alu(a.x, b.x, c.x), med3_fast_alu(a.y, b.y, c.y), med3_fast_alu(a.z, b.z, c.z),
+                    med3_fast_alu(a.w, b.w, c.w));
 }
 
 // acc[c] (4 head sums of channel c of the piece) += weights (4 heads x 4 tokens,
