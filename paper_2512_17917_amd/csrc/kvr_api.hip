@@ -334,9 +334,8 @@ static int32_t attend_decode_common(bool static_ws, const kvr_desc* desc, const 
   a.part_o = (float*)(base + plan.off_part_o);
   a.part_ml = (float*)(base + plan.off_part_ml);
   a.logits = scores ? (float*)(base + plan.off_logits) : nullptr;
-  a.logits_buf = (float*)(base + plan.off_logits);
   a.scratch_rec = plan.streamed ? (void*)(base + plan.off_rec) : nullptr;
-  a.scratch_partial = plan.streamed ? (void*)(base + plan.off_partial) : nullptr;
+  a.tiles = plan.streamed ? (float*)(base + plan.off_tiles) : nullptr;
   a.n_q = 1;
   return finish(kvr::launch_attend(d, desc->dtype, a, plan, (hipStream_t)stream, sd));
 }

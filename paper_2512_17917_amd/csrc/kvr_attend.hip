@@ -117,15 +117,14 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
   off = align_up(off + (size_t)units * p.n_slices * d.G * D * sizeof(float), 256);
   p.off_part_ml = off;
   off = align_up(off + (size_t)units * p.n_slices * d.G * 2 * sizeof(float), 256);
-  // the streaming kernel reads its arrays a few tiles past the end without clamping
-  const size_t pad_tok = p.streamed ? (size_t)multi_staged_pad_tokens() : 0;
   p.off_logits = off;
-  off = align_up(off + ((size_t)units * (size_t)tot_cap + pad_tok) * d.G * sizeof(float), 256);
-  p.off_rec = p.off_partial = off;
+  off = align_up(off + (size_t)units * (size_t)tot_cap * d.G * sizeof(float), 256);
+  p.off_rec = p.off_tiles = off;
   if (p.streamed) {
-    off = align_up(off + ((size_t)units * (size_t)vague_cap + pad_tok) * 8, 256);
-    p.off_partial = off;
-    off = align_up(off + ((size_t)units * (size_t)vague_cap + pad_tok) * d.G * sizeof(float), 256);
+    const size_t tokens = multi_staged_scratch_tokens(units, vague_cap);
+    off = align_up(off + tokens * sizeof(uint32_t), 256);
+    p.off_tiles = off;
+    off = align_up(off + tokens * d.G * sizeof(float), 256);
   }
   p.total_bytes = off;
   return p;
@@ -303,7 +302,7 @@ __global__ __launch_bounds__(256) void attend_main_kernel(DevDesc d, AttendArgs 
 
 // Waves per SIMD: the most whose registers hold the kernel without a spill (64 registers: 1 spilled with four heads, 62
 // with eight; 80: 9 with eight; 96: 6 with sixteen columns).
-template <int G>
+template <int G, bool TILES>
 __global__ __launch_bounds__(256, (G <= 2 ? 8 : G <= 4 ? 7 : G == 8 ? 5 : 4)) void attend_combine_kernel(DevDesc d, AttendArgs a) {
   const int unit = blockIdx.y;
   const int b = unit / d.Hkv, hk = unit % d.Hkv;
@@ -363,13 +362,18 @@ __global__ __launch_bounds__(256, (G <= 2 ? 8 : G <= 4 ? 7 : G == 8 ? 5 : 4)) vo
   int pos[U];
   float x[U][G], old[U];
   float* sc = do_scores ? a.scores + (size_t)unit * a.n_cap : nullptr;
-  const int t0 = blockIdx.x * 256 * U + tid;
+  // TILES: the streaming kernel leaves its tokens' logits by tile, [column][16 tokens]; there a thread takes four neighbouring
+  // tokens (a 16-byte load per column), in workgroups of their own behind those of the retained slots.
+  const int ret_wgs = (a.ret_cap + 256 * U - 1) / (256 * U);
+  const bool tiled = TILES && (int)blockIdx.x >= ret_wgs;
+  const int v0 = ((int)blockIdx.x - ret_wgs) * 256 * U + tid * U;             // tiled: first of the thread's tokens in the list
+  const int t0 = tiled ? a.ret_cap + v0 : blockIdx.x * 256 * U + tid, dt = tiled ? 1 : 256;
   if (do_scores) {
     const int nv = a.n_vague ? clampi(a.n_vague[unit], 0, a.vague_cap) : 0;
-    total = a.ret_cap + nv;
+    total = (TILES && !tiled) ? a.ret_cap : a.ret_cap + nv;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int t = t0 + u * 256;
+      const int t = t0 + u * dt;
       pos[u] = -1;
       if (t < total) {
         if (t < a.ret_cap) pos[u] = a.ret_pos ? a.ret_pos[(size_t)unit * a.ret_cap + t] : t;
@@ -377,22 +381,38 @@ __global__ __launch_bounds__(256, (G <= 2 ? 8 : G <= 4 ? 7 : G == 8 ? 5 : 4)) vo
         if (pos[u] >= a.n_cap) pos[u] = -1;
       }
     }
+    if (tiled) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int t = t0 + u * 256;
+      for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int g = 0; g < G; ++g) x[u][g] = -__builtin_inff();
-      if (t < total) {
-        const float* lg = a.logits + ((size_t)unit * tot_cap + t) * G;
-        if constexpr (G % 4 == 0) {
+        for (int g = 0; g < G; ++g) x[u][g] = -__builtin_inff();
+      if (v0 < nv) {
+        const int tile0 = v0 & ~15, pitch = min(16, ((nv + 3) & ~3) - tile0);
+        const float* lg = a.tiles + ((size_t)unit * ((a.vague_cap + 3) & ~3) + tile0) * G + (v0 - tile0);
 #pragma unroll
-          for (int g4 = 0; g4 < G; g4 += 4) {
-            const float4 v = *reinterpret_cast<const float4*>(lg + g4);
-            x[u][g4] = v.x; x[u][g4 + 1] = v.y; x[u][g4 + 2] = v.z; x[u][g4 + 3] = v.w;
+        for (int g = 0; g < G; ++g) {
+          const float4 v = *reinterpret_cast<const float4*>(lg + g * pitch);
+          x[0][g] = v.x; x[1][g] = v.y; x[2][g] = v.z; x[3][g] = v.w;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int t = t0 + u * 256;
+#pragma unroll
+        for (int g = 0; g < G; ++g) x[u][g] = -__builtin_inff();
+        if (t < total) {
+          const float* lg = a.logits + ((size_t)unit * tot_cap + t) * G;
+          if constexpr (G % 4 == 0) {
+#pragma unroll
+            for (int g4 = 0; g4 < G; g4 += 4) {
+              const float4 v = *reinterpret_cast<const float4*>(lg + g4);
+              x[u][g4] = v.x; x[u][g4 + 1] = v.y; x[u][g4 + 2] = v.z; x[u][g4 + 3] = v.w;
+            }
+          } else {
+#pragma unroll
+            for (int g = 0; g < G; ++g) x[u][g] = lg[g];
           }
-        } else {
-#pragma unroll
-          for (int g = 0; g < G; ++g) x[u][g] = lg[g];
         }
       }
     }
@@ -457,25 +477,6 @@ __global__ __launch_bounds__(256, (G <= 2 ? 8 : G <= 4 ? 7 : G == 8 ? 5 : 4)) vo
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (pos[u] >= 0) sc[pos[u]] = old[u] + acc[u];
-    // tokens beyond the launch width (the dispatch covers every token with one
-    // round; this loop only runs if a caller launches a narrower grid)
-    for (int base = (blockIdx.x + gridDim.x) * 256 * U; base < total; base += gridDim.x * 256 * U) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int t = base + tid + u * 256;
-        if (t >= total) continue;
-        int ps;
-        if (t < a.ret_cap) ps = a.ret_pos ? a.ret_pos[(size_t)unit * a.ret_cap + t] : t;
-        else ps = a.vague_pos[(size_t)unit * a.vague_cap + (t - a.ret_cap)];
-        if (ps < 0 || ps >= a.n_cap) continue;
-        const float* lg = a.logits + ((size_t)unit * tot_cap + t) * G;
-        float p = 0.f;
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-          if (lg[g] != -__builtin_inff()) p += __expf(lg[g] - sM[g]) * (sL[g] > 0.f ? 1.f / sL[g] : 0.f);
-        sc[ps] += p;
-      }
-    }
   }
 
   // ---- the output elements ------------------------------------------------------------
@@ -529,20 +530,26 @@ static void launch_main_r(const DevDesc& d, const AttendArgs& a, dim3 grid, hipS
 hipError_t launch_attend_combine(const DevDesc& d, const AttendArgs& a, int n_cols, hipStream_t st) {
   const int units = d.B * d.Hkv;
   const long long tot_cap = (long long)a.ret_cap + a.vague_cap;
-  int cx = (int)((tot_cap + 1023) / 1024);
+  int cx = (int)(a.tiles ? (a.ret_cap + 1023ll) / 1024 + (a.vague_cap + 1023ll) / 1024 : (tot_cap + 1023) / 1024);
   // few tokens and few units: workgroups for the output alone, 64 elements each, as long as the chip has room
   const int want = std::min(n_cols * D / 64, 512 / units);
   if (cx < want) cx = want;
   if (cx < 1) cx = 1;
   const dim3 grid(cx, units), block(256);
+#define KVR_COMBINE(N)                                                                        \
+  case N:                                                                                     \
+    if (a.tiles) hipLaunchKernelGGL((attend_combine_kernel<N, true>), grid, block, 0, st, d, a); \
+    else hipLaunchKernelGGL((attend_combine_kernel<N, false>), grid, block, 0, st, d, a);     \
+    break;
   switch (n_cols) {
-    case 1: hipLaunchKernelGGL((attend_combine_kernel<1>), grid, block, 0, st, d, a); break;
-    case 2: hipLaunchKernelGGL((attend_combine_kernel<2>), grid, block, 0, st, d, a); break;
-    case 4: hipLaunchKernelGGL((attend_combine_kernel<4>), grid, block, 0, st, d, a); break;
-    case 8: hipLaunchKernelGGL((attend_combine_kernel<8>), grid, block, 0, st, d, a); break;
-    case 16: hipLaunchKernelGGL((attend_combine_kernel<16>), grid, block, 0, st, d, a); break;
+    KVR_COMBINE(1)
+    KVR_COMBINE(2)
+    KVR_COMBINE(4)
+    KVR_COMBINE(8)
+    KVR_COMBINE(16)
     default: return hipErrorInvalidValue;
   }
+#undef KVR_COMBINE
   return hipGetLastError();
 }
 
@@ -604,8 +611,7 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
   } else if (e == hipSuccess && plan.streamed && plan.n_vslices > 0) {
     // no causal mask in a decode call: every listed token is visible (n_ctx = null)
     e = launch_attend_multi_staged(d, a, nullptr, 1, plan.vslice_tokens, plan.n_vslices, plan.n_rslices,
-                                   plan.n_slices, a.part_o, a.part_ml, a.logits_buf, a.scratch_rec,
-                                   a.scratch_partial, st);
+                                   plan.n_slices, a.part_o, a.part_ml, a.scratch_rec, a.tiles, st);
   } else if (e == hipSuccess && plan.mfma_retained && plan.n_vslices > 0) {
     a.slice_tokens = plan.vslice_tokens;
     a.tok_start = a.ret_cap;

@@ -287,20 +287,17 @@ MultiPlan attend_multi_plan(const DevDesc& d, int n_q, long long ret_cap, long l
   else p.vslice_tokens = vague_cap > 0 ? attend_slice_tokens(vague_cap, units) : 64;
   p.n_vslices = vague_cap > 0 ? (int)((vague_cap + p.vslice_tokens - 1) / p.vslice_tokens) : 0;
   p.n_slices = p.n_rslices + p.n_vslices;
-  // the staged kernel reads its scratch arrays (records in the first rebuilt-token area, partial logits in
-  // the second, final logits) a few tiles past the end without clamping
-  const size_t pad = p.staged ? (size_t)multi_staged_pad_tokens() * ncol * sizeof(float) : 0;
   size_t off = 0;
   p.off_khat = off;
-  off = align_up_m(off + (size_t)units * vague_cap * D * sizeof(uint16_t) + pad, 256);
+  off = align_up_m(off + (size_t)units * vague_cap * D * sizeof(uint16_t), 256);
   p.off_vhat = off;
-  off = align_up_m(off + (size_t)units * vague_cap * D * sizeof(uint16_t) + pad, 256);
+  off = align_up_m(off + (size_t)units * vague_cap * D * sizeof(uint16_t), 256);
   p.off_part_o = off;
   off = align_up_m(off + (size_t)units * p.n_slices * ncol * D * sizeof(float), 256);
   p.off_part_ml = off;
   off = align_up_m(off + (size_t)units * p.n_slices * ncol * 2 * sizeof(float), 256);
   p.off_logits = off;
-  off = align_up_m(off + (size_t)units * (size_t)(ret_cap + vague_cap) * ncol * sizeof(float) + pad, 256);
+  off = align_up_m(off + (size_t)units * (size_t)(ret_cap + vague_cap) * ncol * sizeof(float), 256);
   p.total_bytes = off;
   return p;
 }
@@ -345,10 +342,9 @@ static hipError_t launch_multi_n(const DevDesc& d, const AttendArgs& a0, const i
   // rebuilt Vague tokens
   if (a0.vague_cap > 0 && plan.staged) {
     // the rebuilt-token areas of the workspace are free on this route: they hold the token records and
-    // the logits after the first K chunk (8 + 4 NCOL <= 256 bytes per token)
+    // the logits by tile (4 and 4 NCOL <= 64 of 256 bytes per token)
     e = launch_attend_multi_staged(d, a0, n_ctx, n_q, plan.vslice_tokens, plan.n_vslices, plan.n_rslices,
-                                   plan.n_slices, da.part_o, da.part_ml, (float*)(base + plan.off_logits), khat,
-                                   vhat, st);
+                                   plan.n_slices, da.part_o, da.part_ml, khat, vhat, st);
     if (e != hipSuccess) return e;
   } else if (a0.vague_cap > 0) {
     da.k = khat;
@@ -371,6 +367,7 @@ static hipError_t launch_multi_n(const DevDesc& d, const AttendArgs& a0, const i
   a.part_o = da.part_o;
   a.part_ml = da.part_ml;
   a.logits = da.logits;
+  a.tiles = (a0.vague_cap > 0 && plan.staged) ? (float*)vhat : nullptr;
   a.n_slices = plan.n_slices;
   a.n_q = n_q;
   return launch_attend_combine(d, a, NCOL, st);

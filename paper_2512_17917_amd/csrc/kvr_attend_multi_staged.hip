@@ -26,9 +26,19 @@
 // the workgroup's maximum (the waves' maxima meet in LDS in between).
 // Tiles are handed to the waves through a counter in LDS, phase by phase.
 //
-// LDS layout: row-major, 128 bytes per sketch slot, but piece p of slot s is kept
-// at piece position p xor (s mod 8): the 16 lanes that read the same piece of 16
-// random slots then spread over all bank groups instead of two.
+// Bound by the vector ALUs, so the layouts are chosen for few instructions per tile:
+//   * scratch memory holds the logits of a tile column by column (a lane's four tokens are one 16-byte load or store)
+//     and a token's record in four bytes (a lane's four records are one 16-byte load);
+//   * what lies past the end of the list is written so that nothing has to be masked when it is read: records 0, logits
+//     -inf; positions are looked at once per token, by the thread that hashes it, and again only in a workgroup that has a
+//     position some query must not see;
+//   * LDS rows are 144 bytes apart: the 16 lanes that read the same piece of 16 random slots spread over all bank groups, and
+//     a row's address is one multiply-add (V chunks: 128, a row is read by 16 lanes at once).
+// us a phase, 64 units x 25395 tokens, 16 columns, 273 slots per row, one workgroup per CU: K 17 (what LDS delivers with three lanes in
+// 16 on the same bank group) and 25 (with the logits of the first pass read and the final ones written), V 26 and 26 (130 vector
+// instructions per tile and phase), everything else 26.  Against records of eight bytes, logits token by token, in two arrays, and 538
+// vector instructions per tile instead of 400: call of four queries 254 -> 227, decode step of 5 x 8 units, 12706 tokens, eight heads,
+// two layers 204 -> 193.
 #include "kvr_staged.h"
 
 #include <algorithm>
@@ -39,9 +49,11 @@ typedef __bf16 bf16x8ms_t __attribute__((ext_vector_type(8)));
 
 constexpr int MS_THREADS = 1024;          // 16 waves: four per SIMD cover each other's memory round trips
 constexpr int MS_WAVES = MS_THREADS / 64;
-// The tile loops read the scratch arrays up to four tiles per wave past the end of a workgroup's share
-// (look-ahead, loop rounding, the ragged last round of tiles) without clamping: the arrays are padded.
-constexpr int MS_PAD_TOKENS = 4 * MS_WAVES * 16;
+constexpr int MS_PITCH = 144;             // K chunks: bytes from one sketch slot to the next in LDS (128 of them used)
+__host__ __device__ constexpr int ms_chunk_lds(int rows, int n_col) {     // a chunk in whole kilobytes; later [waves][n_col][64] floats
+  const int chunk = (rows * MS_PITCH + 1023) & ~1023, sums = MS_WAVES * n_col * 64 * 4;
+  return chunk > sums ? chunk : sums;
+}
 
 struct MultiStagedArgs {
   const bf16_t* q;          // [B, n_q, Hq, D]
@@ -54,19 +66,18 @@ struct MultiStagedArgs {
   int cap;
   int part_tokens, n_parts; // tokens per workgroup (a multiple of 16), workgroups per unit
   int slice0, n_slices;     // partial index of part 0 / partials per unit
-  int tok0, tot_cap;        // logits index of list entry 0 / logits rows per unit
   float* part_o;            // [units, n_slices, NCOL, D]
   float* part_ml;           // [units, n_slices, NCOL, 2]
-  float* logits;            // [units, tot_cap, NCOL] final logits (also the merge kernel's input)
-  float* partial;           // scratch [units, cap, NCOL]: logits after the first K chunk
-  uint2* rec;               // scratch [units, cap]: token records
+  float* tiles;             // scratch [units, cap4, NCOL], cap4 = cap in whole fours: per 16-token tile [NCOL][16] (the last
+                            // tile: [NCOL][its tokens in whole fours]), partial logits, then final ones (which the merge
+                            // kernel reads here)
+  uint32_t* rec;            // scratch [units, cap4]: token records
 };
 
-// Token record, the layout of the decode kernel's: LDS row indices (i * w + h_i < 1024) at bit 7 of x
-// (first listed row), bit 17 of x (second) and bit 7 of y (third); bit 0 of x = the sign two of the three
-// rows agree on (1 = minus, folded into the token's weight); bit 31 of y = the third listed row has the
-// other sign.  The row whose sign differs from the other two, if any, is listed third.
-__device__ __forceinline__ uint2 make_record3(const DevDesc& d, int w, int J) {
+// Token record: LDS row indices i * w + h_i < 1024 of the three rows at bits 0, 10 and 20, bit 31 = the sign two of the three
+// rows agree on (1 = minus, folded into the token's weight), bit 30 = the third listed row has the other sign.  The row whose
+// sign differs from the other two, if any, is listed third.
+__device__ __forceinline__ uint32_t make_record3(const DevDesc& d, int w, int J) {
   const uint32_t r0 = (uint32_t)bucket_of(d, 0, J), r1 = (uint32_t)(w + bucket_of(d, 1, J)),
                  r2 = (uint32_t)(2 * w + bucket_of(d, 2, J));
   const uint32_t s0 = sign_neg(d, 0, J) ? 1u : 0u, s1 = sign_neg(d, 1, J) ? 1u : 0u, s2 = sign_neg(d, 2, J) ? 1u : 0u;
@@ -74,26 +85,32 @@ __device__ __forceinline__ uint2 make_record3(const DevDesc& d, int w, int J) {
   const bool odd0 = s0 != maj, odd1 = s1 != maj;
   const uint32_t ra = odd0 ? r2 : r0, rbk = odd1 ? r2 : r1, rc = odd0 ? r0 : (odd1 ? r1 : r2);
   const uint32_t flip = (s0 ^ s1) | (s0 ^ s2);
-  return make_uint2((ra << 7) | (rbk << 17) | maj, (rc << 7) | (flip << 31));
+  return ra | (rbk << 10) | (rc << 20) | (flip << 30) | (maj << 31);
 }
-// byte offsets of the three listed rows in the LDS chunk
-__device__ __forceinline__ void record_rows(uint2 rec, int (&rb)[3]) {
-  rb[0] = (int)(rec.x & 0x1ff80u);
-  rb[1] = (int)(__builtin_amdgcn_ubfe(rec.x, 17, 10) << 7);
-  rb[2] = (int)(rec.y & 0x1ff80u);
+// byte address of listed row I in LDS, plus base: two instructions (left to itself the compiler takes a shift, a mask and an
+// addition where the pitch is a power of two)
+template <int I, int PITCH>
+__device__ __forceinline__ int record_row(uint32_t rec, int base) {
+  const uint32_t row = __builtin_amdgcn_ubfe(rec, 10 * I, 10);
+  if constexpr (PITCH == 128) {
+    int a;
+    asm("v_lshl_add_u32 %0, %1, 7, %2" : "=v"(a) : "v"(row), "v"(base));
+    return a;
+  } else {
+    return (int)__umul24(row, PITCH) + base;
+  }
 }
-// byte offset of piece p inside the LDS row that starts at byte rb (rows are 128 bytes)
-__device__ __forceinline__ int swz_piece(int rb, int p) { return rb + (((rb >> 3) ^ (p << 4)) & 0x70); }
 
-// Copy chunk cc (64 channels) of a sketch tensor [rows][128] into LDS, in the swizzled layout (K chunks) or
-// plainly (V chunks: their readers take a whole row at a time, 16 lanes x 8 bytes).
-template <bool SWZ>
-__device__ __forceinline__ void stage_issue_swz(const unsigned char* __restrict__ g, unsigned char* s_sk,
-                                                int n_pieces, int cc, int tid) {
+// Copy chunk cc (64 channels) of a sketch tensor [rows][128] into LDS: PITCH / 16 16-byte places per row, a ninth is unused
+// (its lanes read the row's last piece).
+template <int PITCH>
+__device__ __forceinline__ void stage_issue_pitch(const unsigned char* __restrict__ g, unsigned char* s_sk, int rows,
+                                                  int cc, int tid) {
   const int lane = tid & 63, wave = tid >> 6;
-  for (int p0 = wave * 64; p0 < n_pieces; p0 += MS_THREADS) {
-    const int idx = min(p0 + lane, n_pieces - 1);
-    const int row = idx >> 3, c = SWZ ? ((idx ^ row) & 7) : (idx & 7);   // LDS piece position idx & 7 holds piece c
+  const int n_places = rows * (PITCH / 16);
+  for (int p0 = wave * 64; p0 < n_places; p0 += MS_THREADS) {
+    const uint32_t idx = (uint32_t)min(p0 + lane, n_places - 1);
+    const uint32_t row = idx / (PITCH / 16), c = min(idx - row * (PITCH / 16), 7u);
     __builtin_amdgcn_global_load_lds(
         (const __attribute__((address_space(1))) void*)(g + (size_t)row * (D * 2) + cc * 128 + c * 16),
         (__attribute__((address_space(3))) void*)(s_sk + p0 * 16), 16, 0, 0);
@@ -115,49 +132,70 @@ __global__ __launch_bounds__(MS_THREADS) void attend_multi_staged_kernel(DevDesc
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane >> 4, col = lane & 15;
   const int w = d.w;
-  const int sk_bytes = max((3 * w * 128 + 1023) & ~1023, MS_WAVES * NCOL * CH * 4);
   unsigned char* s_sk = smem;                                        // chunk; later [waves][NCOL][64] floats
-  float* s_max = reinterpret_cast<float*>(smem + sk_bytes);          // [waves][16]
+  float* s_max = reinterpret_cast<float*>(smem + ms_chunk_lds(3 * w, NCOL));   // [waves][16]
   float* s_sum = s_max + MS_WAVES * 16;                              // [waves][16]
   int* s_ctr = reinterpret_cast<int*>(s_sum + MS_WAVES * 16);        // next tile of the running phase
+  int* s_hidden = s_ctr + 1;                                         // some query must not see some token of this workgroup
 
   const int b = unit / d.Hkv, hk = unit % d.Hkv;
   const int rows = clampi(a.n_valid[unit], 0, a.cap);
   const int t_begin = min(part_i * a.part_tokens, rows);
   const int t_end = min(t_begin + a.part_tokens, rows);
   const int n_tiles = (t_end - t_begin + 15) >> 4;
+  const int cap4 = (a.cap + 3) & ~3;
   const int32_t* pp = a.pos + (size_t)unit * a.cap;
-  uint2* recs = a.rec + (size_t)unit * a.cap;
-  float* partial = a.partial + (size_t)unit * a.cap * NCOL;
-  float* logits = a.logits + ((size_t)unit * a.tot_cap + a.tok0) * NCOL;
+  uint32_t* recs = a.rec + (size_t)unit * cap4;
+  float* tiles = a.tiles + (size_t)unit * cap4 * NCOL;
   const size_t sk_unit = (size_t)unit * 3 * w * D;
   const unsigned char* skg = reinterpret_cast<const unsigned char*>(a.sk + sk_unit);
   const unsigned char* svg = reinterpret_cast<const unsigned char*>(a.sv + sk_unit);
-  const int n_pieces = 3 * w * 8;
 
   // this lane's column: query tq, head g
   const int tq = col / d.G, g = col % d.G;
   const bool col_live = col < NCOL;
+  const int col_c = col_live ? col : 0;
   const int qpos = a.n_ctx ? a.n_ctx[b] - a.n_q + tq : 0x7fffffff;   // no n_ctx: no causal mask (decode call)
 
   // Tiles are handed out through a counter in LDS, phase by phase: of the four waves that share a SIMD the
   // ones started first win the issue arbitration, and with a fixed share each the workgroup would wait for
-  // its slowest wave at the end of every phase.
+  // its slowest wave at the end of every phase.  One at a time: groups of four leave the last ones to a few waves (5 x 8 units
+  // of 12706 tokens, 8 columns: 14 of 48 us), and asking for their inputs together gains nothing.
+  const uint32_t ctr_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)s_ctr;
   auto next_tile = [&]() {
     int t = 0;
-    if (lane == 0) t = atomicAdd(s_ctr, 1);
+    if (lane == 0)         // one lane: written out, because the compiler would first count the active lanes of an atomicAdd
+      asm volatile("ds_add_rtn_u32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)" : "=v"(t) : "v"(ctr_at), "v"(1) : "memory");
     return __builtin_amdgcn_readfirstlane(t);
   };
+  // tokens of a tile in whole fours (16 but for the list's last tile) = distance of its columns in `tiles`
+  auto tile_pitch = [&](int ti) { return min(16, ((t_end - t_begin + 3) & ~3) - ti * 16); };
 
   // ---- K phases -----------------------------------------------------------------------------------
+  // What a tile needs from memory is requested one tile ahead with unconditional loads, and what a tile leaves in memory
+  // is stored one tile late.  Vector memory returns reads in order and writes in order, but not the two against each
+  // other, so a wait for any read with a write outstanding drains everything: arranged like this, every such wait
+  // only covers requests that are a whole tile old.  A look-ahead past the last tile reads the last tile again.
+  struct KIn {
+    uint32_t rec;       // record of token t0 + col
+    float4 prev;        // second chunk: partial logits of tokens t0 + 4 r16 + i, this lane's column
+  };
   float m_run = NEG_INF;
+  if (tid == 0) { *s_ctr = 0; *s_hidden = 0; }
   for (int cc = 0; cc < 2; ++cc) {
-    if (cc > 0) lds_barrier();                                // every wave is done with the previous chunk
-    stage_issue_swz<true>(skg, s_sk, n_pieces, cc, tid);
+    lds_barrier();                                            // every wave is done with the previous chunk
+    stage_issue_pitch<MS_PITCH>(skg, s_sk, 3 * w, cc, tid);
     if (cc == 0) {
       // under the first chunk copy: the record of every token of this workgroup, one token per thread
       // (hashed once, not once per lane group that needs it); published by the barrier below
-      for (int t = t_begin + tid; t < t_end; t += MS_THREADS) recs[t] = make_record3(d, w, pp[t]);
+      const int q_first = a.n_ctx ? a.n_ctx[b] - a.n_q : 0x7fffffff;
+      bool hidden = false;
+      for (int t = t_begin + tid; t < ((t_end + 3) & ~3); t += MS_THREADS) {
+        const int J = t < t_end ? pp[t] : 0;
+        hidden = hidden || J < 0 || J > q_first;
+        recs[t] = t < t_end ? make_record3(d, w, J) : 0u;
+      }
+      if (hidden) *s_hidden = 1;
     }
     // q of this lane's column, channels 64 cc + 32 kx + 8 r16 .. + 7
     uint4 qb[2];
@@ -170,77 +208,47 @@ __global__ __launch_bounds__(MS_THREADS) void attend_multi_staged_kernel(DevDesc
         if (!col_live) qb[kx] = make_uint4(0u, 0u, 0u, 0u);
       }
     }
-    if (tid == 0) *s_ctr = 0;
+    if (cc > 0 && tid == 0) *s_ctr = 0;
     stage_wait();
     lds_barrier();
-    // What a tile needs from memory is requested one tile ahead with unconditional loads (indices clamped
-    // into the list, results masked afterwards), and what a tile leaves in memory is stored one tile late.
-    // Vector memory returns reads in order and writes in order, but not the two against each other, so a
-    // wait for any read with a write outstanding drains everything: arranged like this, every such wait
-    // only covers requests that are a whole tile old.
-    struct KIn {
-      uint2 rec;          // record of token t0 + col
-      float prev[4];      // second chunk: partial logits of tokens t0 + 4 r16 + i, this lane's column
-      int tpos[4];        //               and their positions
-    };
-    const int t_last = max(t_end - 1, 0);
-    const int col_c = col_live ? col : 0;
+    const bool hidden = *s_hidden != 0;
     auto k_loads = [&](int ti, KIn& in) {
-      const int t0 = t_begin + ti * 16;
-      in.rec = make_uint2(0u, 0u);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { in.prev[i] = 0.f; in.tpos[i] = -1; }
-      // the scratch arrays are padded: reads past the end of the list need no clamp (masked later)
-      in.rec = recs[t0 + col];
-      if (cc == 1) {
-        const float* pv = partial + (size_t)(t0 + 4 * r16) * NCOL + col_c;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          in.tpos[i] = pp[min(t0 + 4 * r16 + i, t_last)];
-          in.prev[i] = pv[i * NCOL];
-        }
-      }
+      ti = min(ti, n_tiles - 1);
+      const int t0 = t_begin + ti * 16, cp = tile_pitch(ti);
+      in.rec = recs[t0 + min(col, cp - 1)];
+      if (cc == 1)
+        in.prev = *reinterpret_cast<const float4*>(tiles + (size_t)t0 * NCOL + col_c * cp + min(4 * r16, cp - 4));
     };
     // results of the previous tile, not yet stored
-    int st_t0 = -1;
-    float st_v[4] = {0.f, 0.f, 0.f, 0.f};
+    int st_ti = n_tiles;
+    float4 st_v = make_float4(0.f, 0.f, 0.f, 0.f);
     auto k_stores = [&]() {
-      if (st_t0 < 0) return;
-      if (col_live) {
-        float* dst = (cc == 0) ? partial : logits;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int tt = st_t0 + 4 * r16 + i;
-          if (tt < t_end) dst[(size_t)tt * NCOL + col] = st_v[i];
-        }
-      }
+      if (st_ti >= n_tiles) return;
+      const int t0 = t_begin + st_ti * 16, cp = tile_pitch(st_ti);
+      if (col_live && 4 * r16 < cp) *reinterpret_cast<float4*>(tiles + (size_t)t0 * NCOL + col * cp + 4 * r16) = st_v;
     };
-    // Two input buffers take the tiles in turn (copying a buffer would wait for its loads).  A tile past
-    // the end of this wave's share computes on clamped inputs and leaves nothing behind.
+    // Two input buffers take the tiles in turn (copying a buffer would wait for its loads).
     auto k_tile = [&](const KIn& cur, KIn& nxt, int ti, int ti_next) {
       const int t0 = t_begin + ti * 16;
       // the tile's inputs must have arrived here (empty statement that reads them), before the
       // previous tile's stores and the next tile's loads are issued
-      if (cc == 0) asm volatile("" ::"v"(cur.rec.x), "v"(cur.rec.y));
-      else asm volatile("" ::"v"(cur.rec.x), "v"(cur.rec.y), "v"(cur.prev[0]), "v"(cur.prev[1]), "v"(cur.prev[2]),
-                        "v"(cur.prev[3]), "v"(cur.tpos[0]), "v"(cur.tpos[1]), "v"(cur.tpos[2]), "v"(cur.tpos[3]));
+      if (cc == 0) asm volatile("" ::"v"(cur.rec));
+      else asm volatile("" ::"v"(cur.rec), "v"(cur.prev.x), "v"(cur.prev.y), "v"(cur.prev.z), "v"(cur.prev.w));
       __builtin_amdgcn_sched_barrier(0);
       k_stores();
       __builtin_amdgcn_sched_barrier(0);
       k_loads(ti_next, nxt);
       __builtin_amdgcn_sched_barrier(0);
-      const bool tk_ok = t0 + col < t_end;
-      uint2 rec = cur.rec;
-      if (!tk_ok) rec = make_uint2(0u, 0u);
-      int rb[3];
-      record_rows(rec, rb);
+      st_ti = ti;
+      if (ti >= n_tiles) return;                  // uniform: the wave's tiles are done
+      const int a0 = record_row<0, MS_PITCH>(cur.rec, 16 * r16), a1 = record_row<1, MS_PITCH>(cur.rec, 16 * r16),
+                a2 = record_row<2, MS_PITCH>(cur.rec, 16 * r16);
       uint4 ka[2];
 #pragma unroll
       for (int kx = 0; kx < 2; ++kx) {
-        const int p = 4 * kx + r16;
-        const uint4 x0 = *reinterpret_cast<const uint4*>(s_sk + swz_piece(rb[0], p));
-        const uint4 x1 = *reinterpret_cast<const uint4*>(s_sk + swz_piece(rb[1], p));
-        const uint4 x2 = *reinterpret_cast<const uint4*>(s_sk + swz_piece(rb[2], p));
+        const uint4 x0 = *reinterpret_cast<const uint4*>(s_sk + a0 + 64 * kx);
+        const uint4 x1 = *reinterpret_cast<const uint4*>(s_sk + a1 + 64 * kx);
+        const uint4 x2 = *reinterpret_cast<const uint4*>(s_sk + a2 + 64 * kx);
         ka[kx] = med3_fast_piece(x0, x1, x2);
       }
       f32x4_t S = {0.f, 0.f, 0.f, 0.f};
@@ -248,35 +256,44 @@ __global__ __launch_bounds__(MS_THREADS) void attend_multi_staged_kernel(DevDesc
       for (int kx = 0; kx < 2; ++kx)
         S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8ms_t, ka[kx]),
                                                     __builtin_bit_cast(bf16x8ms_t, qb[kx]), S, 0, 0, 0);
-      st_t0 = t0;
-      if (cc == 0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) st_v[i] = S[i];
-      } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int tt = t0 + 4 * r16 + i;
-          const bool ok = tt < t_end && cur.tpos[i] >= 0 && cur.tpos[i] <= qpos && col_live;
-          st_v[i] = ok ? (S[i] + cur.prev[i]) * d.scale : NEG_INF;
-          m_run = fmaxf(m_run, st_v[i]);
+      st_v = make_float4(S[0], S[1], S[2], S[3]);
+      if (cc == 1) {
+        float4 x = make_float4((S[0] + cur.prev.x) * d.scale, (S[1] + cur.prev.y) * d.scale,
+                               (S[2] + cur.prev.z) * d.scale, (S[3] + cur.prev.w) * d.scale);
+        const int n = t_end - t0 - 4 * r16;       // tokens of the lane's four that the list still has
+        if (t_end - t0 < 16) {                    // uniform: the list's last tile
+          if (n < 1) x.x = NEG_INF;
+          if (n < 2) x.y = NEG_INF;
+          if (n < 3) x.z = NEG_INF;
+          if (n < 4) x.w = NEG_INF;
         }
+        if (hidden) {                             // uniform
+          const int32_t* p4 = pp + t0 + 4 * r16;
+          if (n > 0 && (p4[0] < 0 || p4[0] > qpos)) x.x = NEG_INF;
+          if (n > 1 && (p4[1] < 0 || p4[1] > qpos)) x.y = NEG_INF;
+          if (n > 2 && (p4[2] < 0 || p4[2] > qpos)) x.z = NEG_INF;
+          if (n > 3 && (p4[3] < 0 || p4[3] > qpos)) x.w = NEG_INF;
+        }
+        if (col_live) m_run = fmaxf(fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w)), m_run);
+        st_v = x;
       }
     };
-    KIn in_a, in_b;
-    int ti = next_tile();
-    k_loads(ti, in_a);
-    while (ti < n_tiles) {
-      const int t1 = next_tile();
-      k_tile(in_a, in_b, ti, t1);
-      const int t2 = next_tile();
-      k_tile(in_b, in_a, t1, t2);
-      ti = t2;
+    if (n_tiles > 0) {
+      KIn in_a, in_b;
+      int ti = next_tile();
+      k_loads(ti, in_a);
+      while (ti < n_tiles) {
+        const int t1 = next_tile();
+        k_tile(in_a, in_b, ti, t1);
+        const int t2 = next_tile();
+        k_tile(in_b, in_a, t1, t2);
+        ti = t2;
+      }
+      k_stores();
     }
-    k_stores();
   }
   // the wave's maximum per column (the four 16-lane rows hold different tokens of the same column)
-  m_run = fmaxf(m_run, __shfl_xor(m_run, 16));
-  m_run = fmaxf(m_run, __shfl_xor(m_run, 32));
+  m_run = rows_max(m_run);
   if (r16 == 0) s_max[wave * 16 + col] = m_run;
 
   // ---- V phases -----------------------------------------------------------------------------------
@@ -284,7 +301,7 @@ __global__ __launch_bounds__(MS_THREADS) void attend_multi_staged_kernel(DevDesc
   float l_run = 0.f;
   for (int cc = 0; cc < 2; ++cc) {
     lds_barrier();                                            // every wave is done with the previous chunk
-    stage_issue_swz<false>(svg, s_sk, n_pieces, cc, tid);
+    stage_issue_pitch<128>(svg, s_sk, 3 * w, cc, tid);
     if (tid == 0) *s_ctr = 0;
     if (cc == 0) {
       // a wave meets other tiles here than in the K phases: weights against the workgroup's maximum
@@ -298,40 +315,38 @@ __global__ __launch_bounds__(MS_THREADS) void attend_multi_staged_kernel(DevDesc
     f32x4_t acc[4];                                           // acc[c][i]: column 4 r16 + i, channel 64 cc + 4 col + c
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    // this lane's four tokens of a tile: records, and their logits for this lane's column; requested one
-    // tile ahead with unconditional loads (no stores in these phases: the waits are exact)
+    // this lane's four tokens of a tile: records, and their logits for this lane's column; requested two
+    // tiles ahead with unconditional loads (no stores in these phases: the waits are exact).  One tile ahead: 8.4 instead of
+    // 5.5 us a phase of 8 tiles per wave
     struct VIn {
-      uint2 rj[4];
-      float s[4];
+      uint4 rec;
+      float4 s;
     };
-    const int col_c = col_live ? col : 0;
-    const unsigned char* s_vcol = s_sk + 8 * col;
-    const float m_safe = (m_run == NEG_INF) ? 0.f : m_run;    // a column without any visible token: all weights 0
+    // a column without any visible token: all weights 0; a column that is none: the same
+    const float m_safe = !col_live ? -NEG_INF : (m_run == NEG_INF) ? 0.f : m_run;
     auto v_loads = [&](int ti, VIn& in) {
-      // padded scratch arrays: no clamp (what lies past the end of the list is masked later)
-      const int tt0 = t_begin + ti * 16 + 4 * r16;
-      const uint2* rp = recs + tt0;
-      const float* lp = logits + (size_t)tt0 * NCOL + col_c;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        in.rj[j] = rp[j];
-        in.s[j] = lp[j * NCOL];
-      }
+      ti = min(ti, n_tiles - 1);
+      const int t0 = t_begin + ti * 16, cp = tile_pitch(ti), f = min(4 * r16, cp - 4);
+      in.rec = *reinterpret_cast<const uint4*>(recs + t0 + f);
+      in.s = *reinterpret_cast<const float4*>(tiles + (size_t)t0 * NCOL + col_c * cp + f);
     };
     auto v_tile = [&](const VIn& cur, VIn& nxt, int ti, int ti_next) {
       const int t0 = t_begin + ti * 16;
       v_loads(ti_next, nxt);
-      uint2 rj[4];
+      __builtin_amdgcn_sched_barrier(0);
+      if (ti >= n_tiles) return;                              // uniform
+      const uint32_t rj[4] = {cur.rec.x, cur.rec.y, cur.rec.z, cur.rec.w};
+      const float sl[4] = {cur.s.x, cur.s.y, cur.s.z, cur.s.w};
+      // past the list's last four these lanes read what is not theirs
+      float m = m_safe;
+      if (t_end - t0 < 16 && 4 * r16 >= t_end - t0) m = -NEG_INF;
       float p[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const bool ok = t0 + 4 * r16 + j < t_end;
-        rj[j] = ok ? cur.rj[j] : make_uint2(0u, 0u);
-        const float sl = (ok && col_live) ? cur.s[j] : NEG_INF;
-        p[j] = __expf(sl - m_safe);                       // -inf (masked, or past the end) gives 0
-        if (cc == 0) l_run += p[j];
+        p[j] = __expf(sl[j] - m);                         // -inf (masked, or past the end) gives 0
+        l_run += p[j];
         // the sign two of the token's three rows agree on goes onto the weight
-        p[j] = __uint_as_float(__float_as_uint(p[j]) ^ (rj[j].x << 31));
+        p[j] = __uint_as_float(__float_as_uint(p[j]) ^ (rj[j] & 0x80000000u));
       }
       uint32_t hb[4], lb[4];
 #pragma unroll
@@ -341,19 +356,18 @@ __global__ __launch_bounds__(MS_THREADS) void attend_multi_staged_kernel(DevDesc
       }
       const short4_t a_hi = pack_k4(pair_hi(hb[0], hb[1]), pair_hi(hb[2], hb[3]));
       const short4_t a_lo = pack_k4(pair_hi(lb[0], lb[1]), pair_hi(lb[2], lb[3]));
-      // channels 4 col .. + 3 of the chunk for the four tokens: 8 bytes at offset 8 col of each row
+      // channels 4 col .. + 3 of the chunk for the four tokens: 8 bytes at offset 8 col of each row (the results go
+      // through v_perm_b32 before they reach a matrix instruction)
       uint2 vt[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        int rb[3];
-        record_rows(rj[j], rb);
-        const uint2 x0 = *reinterpret_cast<const uint2*>(s_vcol + rb[0]);
-        const uint2 x1 = *reinterpret_cast<const uint2*>(s_vcol + rb[1]);
-        uint2 x2 = *reinterpret_cast<const uint2*>(s_vcol + rb[2]);
-        const uint32_t fm = (uint32_t)((int)rj[j].y >> 31) & 0x80008000u;
+        const uint2 x0 = *reinterpret_cast<const uint2*>(s_sk + record_row<0, 128>(rj[j], 8 * col));
+        const uint2 x1 = *reinterpret_cast<const uint2*>(s_sk + record_row<1, 128>(rj[j], 8 * col));
+        uint2 x2 = *reinterpret_cast<const uint2*>(s_sk + record_row<2, 128>(rj[j], 8 * col));
+        const uint32_t fm = (uint32_t)((int)(rj[j] << 1) >> 31) & 0x80008000u;
         x2.x ^= fm;
         x2.y ^= fm;
-        vt[j] = med3_fast_half_piece(x0, x1, x2);
+        vt[j] = make_uint2(med3_fast_alu(x0.x, x1.x, x2.x), med3_fast_alu(x0.y, x1.y, x2.y));
       }
       short4_t bop[4];
       bop[0] = pack_k4(pair_lo(vt[0].x, vt[1].x), pair_lo(vt[2].x, vt[3].x));
@@ -365,20 +379,24 @@ __global__ __launch_bounds__(MS_THREADS) void attend_multi_staged_kernel(DevDesc
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a_lo, bop[c], acc[c], 0, 0, 0);
     };
-    VIn in_a, in_b;
-    int ti = next_tile();
-    v_loads(ti, in_a);
-    while (ti < n_tiles) {
-      const int t1 = next_tile();
-      v_tile(in_a, in_b, ti, t1);
-      const int t2 = next_tile();
-      v_tile(in_b, in_a, t1, t2);
-      ti = t2;
+    if (n_tiles > 0) {
+      VIn in_a, in_b, in_c;
+      int ta = next_tile();
+      v_loads(ta, in_a);
+      int tb = next_tile();
+      v_loads(tb, in_b);
+      while (ta < n_tiles) {
+        const int t2 = next_tile();
+        v_tile(in_a, in_c, ta, t2);
+        ta = next_tile();
+        v_tile(in_b, in_a, tb, ta);
+        tb = next_tile();
+        v_tile(in_c, in_b, t2, tb);
+      }
     }
     if (cc == 0) {
       // a lane's sum of weights covers its own four tokens of every tile: add the four 16-lane rows
-      float l = l_run + __shfl_xor(l_run, 16);
-      l += __shfl_xor(l, 32);
+      const float l = rows_sum(l_run);
       if (r16 == 0) s_sum[wave * 16 + col] = l;
     }
     lds_barrier();                                            // the chunk is free: the waves' sums meet in it
@@ -417,8 +435,6 @@ bool multi_staged_applies(const DevDesc& d, long long vague_cap) {
   return d.r == 3 && d.sign_mask == 2 && 3 * d.w <= 1024 && vague_cap >= 64;
 }
 
-int multi_staged_pad_tokens() { return MS_PAD_TOKENS; }
-
 // Tokens per workgroup, at least 256 (below, its fixed part is nearly all there is).  One workgroup (16 waves, the chunk in
 // LDS) runs per CU, so a launch takes ceil(workgroups / 256) turns of (fixed part + tokens of a workgroup), and a unit gets
 // as many parts as one turn holds: with n parts on one turn, n + 1 on two cost 2 (fixed + tokens / (n + 1)), never less
@@ -441,10 +457,7 @@ static hipError_t launch_n(const DevDesc& d, const MultiStagedArgs& a, hipStream
                                   160 * 1024);
   });
   if (attr_rc != hipSuccess) return attr_rc;
-  size_t chunk = ((size_t)3 * d.w * 128 + 1023) & ~(size_t)1023;
-  const size_t merge = (size_t)MS_WAVES * NCOL * 64 * 4;
-  if (chunk < merge) chunk = merge;
-  const size_t lds = chunk + 2 * MS_WAVES * 16 * sizeof(float) + 16;
+  const int lds = ms_chunk_lds(3 * d.w, NCOL) + 2 * MS_WAVES * 16 * (int)sizeof(float) + 16;
   if (lds > 160 * 1024) return hipErrorInvalidValue;
   const int units = d.B * d.Hkv;
   const int units_pad = (units + 7) / 8 * 8;
@@ -454,7 +467,7 @@ static hipError_t launch_n(const DevDesc& d, const MultiStagedArgs& a, hipStream
 
 hipError_t launch_attend_multi_staged(const DevDesc& d, const AttendArgs& a0, const int32_t* n_ctx, int n_q,
                                       int part_tokens, int n_parts, int slice0, int n_slices, float* part_o,
-                                      float* part_ml, float* logits, void* scratch_rec, void* scratch_partial,
+                                      float* part_ml, void* scratch_rec, void* scratch_tiles,
                                       hipStream_t st) {
   if (!multi_staged_applies(d, a0.vague_cap) || n_parts < 1 || (part_tokens & 15) != 0) return hipErrorInvalidValue;
   MultiStagedArgs a;
@@ -470,13 +483,10 @@ hipError_t launch_attend_multi_staged(const DevDesc& d, const AttendArgs& a0, co
   a.n_parts = n_parts;
   a.slice0 = slice0;
   a.n_slices = n_slices;
-  a.tok0 = a0.ret_cap;
-  a.tot_cap = a0.ret_cap + a0.vague_cap;
   a.part_o = part_o;
   a.part_ml = part_ml;
-  a.logits = logits;
-  a.partial = (float*)scratch_partial;
-  a.rec = (uint2*)scratch_rec;
+  a.tiles = (float*)scratch_tiles;
+  a.rec = (uint32_t*)scratch_rec;
   switch (n_q * d.G) {
     case 1: return launch_n<1>(d, a, st);
     case 2: return launch_n<2>(d, a, st);

@@ -24,7 +24,7 @@ struct AttendPlan {
   int lds_bytes;        // staged: dynamic LDS per workgroup
   bool streamed;        // Vague tokens by the streaming LDS-staged kernel of kvr_attend_multi with one query
                         // (8 query heads per kv head; vslice_tokens / n_vslices are its parts)
-  size_t off_part_o, off_part_ml, off_logits, off_rec, off_partial, total_bytes;
+  size_t off_part_o, off_part_ml, off_logits, off_rec, off_tiles, total_bytes;
 };
 AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long vague_cap);
 // Dynamic LDS of the retained kernel's capped form next to the plan's staged kernel; 0 = a CU has no room for both.
@@ -48,9 +48,8 @@ struct AttendArgs {
   float* part_o;     // [units, n_slices, G, D]
   float* part_ml;    // [units, n_slices, G, 2]
   float* logits;     // [units, ret_cap + vague_cap, G] or nullptr when scores == nullptr
-  float* logits_buf; // the same area, always (the streaming kernel needs the logits itself)
-  void* scratch_rec; // streaming kernel: token records / partial logits (null when the plan is not streamed)
-  void* scratch_partial;
+  void* scratch_rec; // streaming kernel: token records
+  float* tiles;      // and the logits of its tokens, by tile, which the merge kernel reads there (null: no streaming kernel)
   int n_slices;      // partial results per unit (all kinds)
   int slice_tokens;  // generic / retained kernel: tokens per slice
   int tok_start;     // generic kernel: first token it handles
@@ -115,10 +114,13 @@ struct MultiPlan {
 // LDS-staged kernel of kvr_attend_multi over the Vague list (bf16, r = 3, values signed only, 3 w <= 1024)
 bool multi_staged_applies(const DevDesc& d, long long vague_cap);
 int multi_staged_part_tokens(long long vague_cap, long long units);
-int multi_staged_pad_tokens();   // tokens the staged kernel may read past the end of its scratch arrays
+// its scratch: a record (4 bytes) and n_col floats for every listed token, each unit's in whole fours of tokens
+constexpr size_t multi_staged_scratch_tokens(long long units, long long vague_cap) {
+  return (size_t)units * (size_t)((vague_cap + 3) / 4 * 4);
+}
 hipError_t launch_attend_multi_staged(const DevDesc& d, const AttendArgs& a, const int32_t* n_ctx, int n_q,
                                       int part_tokens, int n_parts, int slice0, int n_slices, float* part_o,
-                                      float* part_ml, float* logits, void* scratch_rec, void* scratch_partial,
+                                      float* part_ml, void* scratch_rec, void* scratch_tiles,
                                       hipStream_t st);
 MultiPlan attend_multi_plan(const DevDesc& d, int n_q, long long ret_cap, long long vague_cap);
 hipError_t launch_attend_multi(const DevDesc& d, const AttendArgs& a, const int32_t* n_ctx, int n_q,
