@@ -40,6 +40,12 @@ struct EvictHandOver {
   int pos[ENC_SMALL_CAP];
 };
 
+// Barrier for what a workgroup exchanges through LDS: unlike __syncthreads it does not wait for the wave's global stores
+// (lists, freed slots, the new row), a memory round trip each time.
+__device__ __forceinline__ void wg_lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // ---------------------------------------------------------------------------
 // append
 // ---------------------------------------------------------------------------
@@ -87,44 +93,20 @@ __device__ __forceinline__ int append_body(const DevDesc& d, int unit, const T* 
   return s;
 }
 
-// The same with the slot positions already in registers (pre[j] = ret_pos of slot
-// j * NT + tid, or 0 for slots past ret_cap): no scan of ret_pos.
-template <typename T, int NT, int KPT>
-__device__ __forceinline__ int append_body_pre(const DevDesc& d, int unit, const T* __restrict__ k_new,
-                                               const T* __restrict__ v_new, const int32_t* __restrict__ n_ctx,
-                                               T* __restrict__ k_ret, T* __restrict__ v_ret,
-                                               int32_t* __restrict__ ret_pos, int ret_cap, const int (&pre)[KPT],
-                                               const uint4* row_in = nullptr) {
-  // row_in (may be null): this thread's 16 bytes of the new K row (tid < LPT) or V row (tid < 2 LPT),
-  // loaded by the caller ahead of time
+// The stores of the append into slot s (>= ret_cap: there is no empty slot).  row_in: this thread's 16 bytes of the new K row
+// (tid < LPT) or V row (tid < 2 LPT), loaded by the caller ahead of time.
+template <typename T>
+__device__ __forceinline__ void append_store(const DevDesc& d, int unit, const int32_t* __restrict__ n_ctx,
+                                             T* __restrict__ k_ret, T* __restrict__ v_ret,
+                                             int32_t* __restrict__ ret_pos, int ret_cap, int s, uint4 row_in) {
   constexpr int VEC = Store<T>::VEC;
   constexpr int LPT = D / VEC;
   const int tid = threadIdx.x;
-  int32_t* rp = ret_pos + (size_t)unit * ret_cap;
-  __shared__ int s_free;
-  if (tid == 0) s_free = 0x7fffffff;
-  __syncthreads();
-  int mine = 0x7fffffff;
-#pragma unroll
-  for (int j = KPT - 1; j >= 0; --j) {
-    const int s = j * NT + tid;
-    if (s < ret_cap && pre[j] < 0) mine = s;
-  }
-  if (mine != 0x7fffffff) atomicMin(&s_free, mine);
-  __syncthreads();
-  const int s = s_free;
-  if (s >= ret_cap) return -1;
+  if (s >= ret_cap) return;
   const size_t dst = ((size_t)unit * ret_cap + s) * D;
-  if (tid < LPT) {
-    const uint4 v = row_in ? *row_in : *reinterpret_cast<const uint4*>(k_new + (size_t)unit * D + tid * VEC);
-    *reinterpret_cast<uint4*>(k_ret + dst + tid * VEC) = v;
-  } else if (tid < 2 * LPT) {
-    const int l2 = tid - LPT;
-    const uint4 v = row_in ? *row_in : *reinterpret_cast<const uint4*>(v_new + (size_t)unit * D + l2 * VEC);
-    *reinterpret_cast<uint4*>(v_ret + dst + l2 * VEC) = v;
-  }
-  if (tid == 0) rp[s] = n_ctx[unit / d.Hkv] - 1;
-  return s;
+  if (tid < LPT) *reinterpret_cast<uint4*>(k_ret + dst + tid * VEC) = row_in;
+  else if (tid < 2 * LPT) *reinterpret_cast<uint4*>(v_ret + dst + (tid - LPT) * VEC) = row_in;
+  if (tid == 0) ret_pos[(size_t)unit * ret_cap + s] = n_ctx[unit / d.Hkv] - 1;
 }
 
 // ---------------------------------------------------------------------------
@@ -149,17 +131,51 @@ __device__ __forceinline__ unsigned long long shfl_xor_u64(unsigned long long v,
   return ((unsigned long long)hi << 32) | lo;
 }
 
+// Minimum over a wave, in every lane: row rotations (DPP) and row exchanges on the vector ALUs.
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_min_u64(unsigned long long v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, 0xf, 0xf, true);
+  const unsigned long long o = ((unsigned long long)hi << 32) | lo;
+  return o < v ? o : v;
+}
+__device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v) {
+  v = dpp_min_u64<0x121>(v);
+  v = dpp_min_u64<0x122>(v);
+  v = dpp_min_u64<0x124>(v);
+  v = dpp_min_u64<0x128>(v);
+  {
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(v >> 32), (uint32_t)(v >> 32), false, false);
+    const unsigned long long a = ((unsigned long long)hi[0] << 32) | lo[0], b = ((unsigned long long)hi[1] << 32) | lo[1];
+    v = a < b ? a : b;
+  }
+  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(v >> 32), (uint32_t)(v >> 32), false, false);
+  const unsigned long long a = ((unsigned long long)hi[0] << 32) | lo[0], b = ((unsigned long long)hi[1] << 32) | lo[1];
+  return a < b ? a : b;
+}
+
+// Sum over a wave, in every lane.
+template <int CTRL>
+__device__ __forceinline__ int dpp_add_i(int v) {
+  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+__device__ __forceinline__ int wave_sum(int v) {
+  v = dpp_add_i<0x128>(dpp_add_i<0x124>(dpp_add_i<0x122>(dpp_add_i<0x121>(v))));
+  const auto a = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+  v = (int)(a[0] + a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+  return (int)(b[0] + b[1]);
+}
+
 // Block-wide minimum of one value per thread (KEY_NONE = nothing).
 __device__ __forceinline__ unsigned long long block_min(unsigned long long v, SelShared& sh) {
-#pragma unroll
-  for (int m = 1; m < WAVE; m <<= 1) {
-    const unsigned long long o = shfl_xor_u64(v, m);
-    v = o < v ? o : v;
-  }
+  v = wave_min_u64(v);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  __syncthreads();                       // wmin may still be read from the previous round
+  wg_lds_barrier();                      // wmin may still be read from the previous round
   if (lane == 0) sh.wmin[wave] = v;
-  __syncthreads();
+  wg_lds_barrier();
   unsigned long long r = sh.wmin[0];
 #pragma unroll
   for (int w_ = 1; w_ < SEL_WAVES; ++w_) r = sh.wmin[w_] < r ? sh.wmin[w_] : r;
@@ -177,7 +193,7 @@ __device__ __forceinline__ int block_scan(int v, SelShared& sh, int* total = nul
     if (lane >= off) incl += y;
   }
   if (lane == WAVE - 1) sh.wsum[wave] = incl;
-  __syncthreads();
+  wg_lds_barrier();
   int before = 0, tot = 0;
 #pragma unroll
   for (int w_ = 0; w_ < SEL_WAVES; ++w_) {
@@ -206,7 +222,7 @@ __device__ __forceinline__ void pick_digit(SelShared& sh, int shift) {
     sh.whole = left == (first ? a : b);
     sh.prefix |= (unsigned long long)(first ? hi_bin : hi_bin - 1) << shift;
   }
-  __syncthreads();
+  wg_lds_barrier();
 }
 
 // Workgroup of SEL_THREADS threads.  REG: ret_cap <= SEL_THREADS * KPT, keys live
@@ -224,7 +240,9 @@ __device__ __forceinline__ void select_body(
     int32_t* __restrict__ ret_pos, int ret_cap, const int32_t* __restrict__ n_ctx, int n_recent, int k_cand,
     int32_t* __restrict__ evict_slot, int32_t* __restrict__ evict_pos, int32_t* __restrict__ n_evict,
     int evict_cap, int32_t* __restrict__ vague_pos, int32_t* __restrict__ n_vague, int vague_cap,
-    const int* pre = nullptr, const float* pre_sc = nullptr, EvictHandOver* ho = nullptr) {
+    const int* pre = nullptr, const float* pre_sc = nullptr, EvictHandOver* ho = nullptr,
+    int eligible = -1, int nv_ahead = 0) {
+  // eligible >= 0: the caller has counted the unit's eligible slots, and nv_ahead is what it read from n_vague
   const int b = unit / d.Hkv;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -265,10 +283,12 @@ __device__ __forceinline__ void select_body(
     }
   };
 
+  // read ahead of its use, which is many barriers away
+  const int nv_read = eligible >= 0 ? nv_ahead : (vague_pos && n_vague) ? n_vague[unit] : 0;
   if (tid == 0) { sh.cnt = 0; sh.prefix = 0ull; sh.krem = k_cand; sh.nlist = 0; }
-  __syncthreads();
+  wg_lds_barrier();
+  int c = 0;
   {
-    int c = 0;
     if constexpr (REG) {
 #pragma unroll
       for (int j = 0; j < KPT; ++j) {
@@ -280,10 +300,13 @@ __device__ __forceinline__ void select_body(
     } else {
       for_keys(0, n_chunks, [&](int, bool ok, unsigned long long) { c += ok ? 1 : 0; });
     }
-    if (c) atomicAdd(&sh.cnt, c);
   }
-  __syncthreads();
-  const int n_e = sh.cnt - k_cand;
+  if (eligible < 0) {
+    if (c) atomicAdd(&sh.cnt, c);
+    wg_lds_barrier();
+    eligible = sh.cnt;
+  }
+  const int n_e = eligible - k_cand;
   if (n_e <= 0) {
     if (tid == 0) {
       n_evict[unit] = 0;
@@ -291,7 +314,7 @@ __device__ __forceinline__ void select_body(
     }
     return;
   }
-  const int nv_old = (vague_pos && n_vague) ? clampi(n_vague[unit], 0, vague_cap) : 0;
+  const int nv_old = (vague_pos && n_vague) ? clampi(nv_read, 0, vague_cap) : 0;
   if (n_e > evict_cap || (vague_pos && n_vague && nv_old + n_e > vague_cap)) {
     if (tid == 0) {
       n_evict[unit] = -n_e;
@@ -324,13 +347,13 @@ __device__ __forceinline__ void select_body(
     for (int shift = 64 - SEL_DIGIT, known = 64; ;
          known = shift, shift = shift > SEL_DIGIT ? shift - SEL_DIGIT : 0) {     // bits from `known` up are decided
       for (int i = tid; i < SEL_BINS; i += SEL_THREADS) sh.hist[i] = 0u;
-      __syncthreads();
+      wg_lds_barrier();
       const unsigned long long prefix = sh.prefix;
       for_keys(0, n_chunks, [&](int, bool ok, unsigned long long key) {
         const bool match = known >= 64 || (key >> known) == (prefix >> known);
         if (ok && match) atomicAdd(&sh.hist[(unsigned)(key >> shift) & (SEL_BINS - 1)], 1u);
       });
-      __syncthreads();
+      wg_lds_barrier();
       pick_digit(sh, shift);
       if (sh.whole || shift == 0) break;             // uniform: read behind pick_digit's barrier
     }
@@ -344,7 +367,7 @@ __device__ __forceinline__ void select_body(
 #pragma unroll
       for (int j = 0; j < KPT; ++j)
         if (rkey[j] != KEY_NONE && rkey[j] <= cut) sh.list[atomicAdd(&sh.nlist, 1)] = j * SEL_THREADS + tid;
-      __syncthreads();
+      wg_lds_barrier();
 #pragma unroll
       for (int j = 0; j < KPT; ++j) {
         if (rkey[j] != KEY_NONE && rkey[j] <= cut) {
@@ -374,18 +397,18 @@ __device__ __forceinline__ void select_body(
   for (int c0 = 0; c0 < n_chunks; c0 += SEL_PLACE_CHUNKS) {
     const int c1 = min(c0 + SEL_PLACE_CHUNKS, n_chunks);
     const int n_cnt = (REG ? KPT : c1 - c0) * SEL_WAVES;
-    __syncthreads();                                 // nobody reads hist / the previous places any more
+    wg_lds_barrier();                                 // nobody reads hist / the previous places any more
     for_keys(c0, c1, [&](int j, bool ok, unsigned long long key) {
       const unsigned long long bal = __ballot(ok && key <= cut);
       if (lane == 0) sh.place[(j - c0) * SEL_WAVES + wave] = __popcll(bal);
     });
-    __syncthreads();
+    wg_lds_barrier();
     const int a = (2 * tid < n_cnt) ? sh.place[2 * tid] : 0, b_ = (2 * tid + 1 < n_cnt) ? sh.place[2 * tid + 1] : 0;
     int total;
     const int excl = base + block_scan(a + b_, sh, &total) - a - b_;
     if (2 * tid < n_cnt) sh.place[2 * tid] = excl;
     if (2 * tid + 1 < n_cnt) sh.place[2 * tid + 1] = excl + a;
-    __syncthreads();
+    wg_lds_barrier();
     for_keys(c0, c1, [&](int j, bool ok, unsigned long long key) {
       const bool flag = ok && key <= cut;
       const unsigned long long bal = __ballot(flag);
@@ -441,7 +464,7 @@ __device__ __forceinline__ void encode_small_body(
     s_sign[tid] = sg;
     if (out_sign) out_sign[(size_t)unit * cap + tid] = (uint8_t)sg;
   }
-  __syncthreads();
+  wg_lds_barrier();
   // thread = (row group, channel): rows i0, i0 + groups, ... (groups = blockDim / D)
   const int c = tid % D;
   const int groups = blockDim.x / D;
