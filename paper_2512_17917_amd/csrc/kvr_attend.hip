@@ -151,12 +151,14 @@ int attend_side_lds(const DevDesc& d, const AttendPlan& p) {
 // ---------------------------------------------------------------------------
 // generic slice kernel
 // ---------------------------------------------------------------------------
-template <typename T, int G, int R>
-__global__ __launch_bounds__(256) void attend_main_kernel(DevDesc d, AttendArgs a) {
+// NW waves per workgroup walk a slice, WAVE / LPT tokens a wave at a time, each a chain of its own (position -> sketch rows ->
+// lane sums -> exponential).  Launches that leave CUs without a workgroup take 16 waves instead of four, so that a slice is
+// walked in a quarter of the steps; elsewhere four waves and several workgroups per CU do the same with smaller merges.
+template <typename T, int G, int R, int NW>
+__global__ __launch_bounds__(64 * NW) void attend_main_kernel(DevDesc d, AttendArgs a) {
   constexpr int VEC = Store<T>::VEC;
   constexpr int LPT = D / VEC;       // lanes that share one token
   constexpr int TPW = WAVE / LPT;    // tokens per wave per iteration
-  constexpr int NW = 4;
   const int unit = blockIdx.y, slice = blockIdx.x;
   const int b = unit / d.Hkv, hk = unit % d.Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -279,7 +281,7 @@ __global__ __launch_bounds__(256) void attend_main_kernel(DevDesc d, AttendArgs 
   __syncthreads();
   float* po = a.part_o + ((size_t)unit * a.n_slices + a.slice0 + slice) * G * D;
   float* pml = a.part_ml + ((size_t)unit * a.n_slices + a.slice0 + slice) * G * 2;
-  for (int idx = threadIdx.x; idx < G * D; idx += 256) {
+  for (int idx = threadIdx.x; idx < G * D; idx += 64 * NW) {
     const int g = idx / D, c = idx % D;
     float M = s_m[0][g];
 #pragma unroll
@@ -518,13 +520,23 @@ static int cu_count() {
   return cus;
 }
 
+template <typename T, int G, int NW>
+static void launch_main_nw(const DevDesc& d, const AttendArgs& a, dim3 grid, hipStream_t st) {
+  switch (d.r) {
+    case 3: hipLaunchKernelGGL((attend_main_kernel<T, G, 3, NW>), grid, dim3(64 * NW), 0, st, d, a); break;
+    case 4: hipLaunchKernelGGL((attend_main_kernel<T, G, 4, NW>), grid, dim3(64 * NW), 0, st, d, a); break;
+    default: hipLaunchKernelGGL((attend_main_kernel<T, G, 0, NW>), grid, dim3(64 * NW), 0, st, d, a); break;
+  }
+}
 template <typename T, int G>
 static void launch_main_r(const DevDesc& d, const AttendArgs& a, dim3 grid, hipStream_t st) {
-  switch (d.r) {
-    case 3: hipLaunchKernelGGL((attend_main_kernel<T, G, 3>), grid, dim3(256), 0, st, d, a); break;
-    case 4: hipLaunchKernelGGL((attend_main_kernel<T, G, 4>), grid, dim3(256), 0, st, d, a); break;
-    default: hipLaunchKernelGGL((attend_main_kernel<T, G, 0>), grid, dim3(256), 0, st, d, a); break;
+  // 16 waves hold 128 registers each (bf16 with four heads needs 156).  us a call, four and 16 waves: float32, 1 unit of 2049 tokens, one
+  // head 21.3 and 14.8, four heads 29.1 and 18.6; 2 units of 6700 tokens, four heads 32.2 and 20.1; bf16, 1 unit of 6700 tokens, two heads,
+  // five rows 51.8 and 40.5
+  if constexpr (G <= (sizeof(T) == 4 ? 4 : 2)) {
+    if ((long long)grid.x * grid.y <= cu_count()) return launch_main_nw<T, G, 16>(d, a, grid, st);
   }
+  launch_main_nw<T, G, 4>(d, a, grid, st);
 }
 
 hipError_t launch_attend_combine(const DevDesc& d, const AttendArgs& a, int n_cols, hipStream_t st) {
