@@ -31,7 +31,13 @@
 // then insert), and stores the estimate into the Candidate's slot.  A channel is
 // only ever touched by its own thread, so no barrier is needed between the query
 // and the update.  Thread 0 exchanges the two positions in ret_pos / vague_pos.
+//
+// Bound by memory round trips.  All swaps of a scan are decided before the first is carried out, so the values of four
+// swaps are requested together; a value that an earlier one of the four has just written (the same slot of a sketch row, the
+// same retained slot: equal for all channels) is taken from registers instead.  One swap at a time, each waiting for its loads behind
+// the stores of the one before, and wave extremes by 64-bit shuffles: 32 units, 4 swaps 41 -> 22 us.
 #include "kvr_launch.h"
+#include "kvr_update.h"
 
 namespace kvr {
 
@@ -40,6 +46,7 @@ constexpr int SWP_WAVES = SWP_THREADS / WAVE;
 constexpr int SWP_KV = 26;                             // REG: Vague keys per thread
 constexpr int SWP_KC = 8;                              // REG: slot keys per thread
 constexpr int SWP_LIST = 16;                           // list length per scan
+constexpr int SWP_ROOM = SWP_KV * SWP_LIST;            // keys of SWP_LIST threads
 constexpr unsigned long long SWP_NONE_MAX = 0ull;      // below every key (the low word ~position of a key is never 0)
 constexpr unsigned long long SWP_NONE_MIN = ~0ull;     // above every key of a finite score
 
@@ -49,6 +56,11 @@ struct SwapShared {
   int vidx[SWP_LIST + 1], cslot[SWP_LIST + 1];                 // Vague list index / retained slot of each entry
   int nvl, ncl;                                                // entries in use
   int go;                                                      // swaps decided for this scan
+  // REG, [0] Vague keys, [1] Candidate keys inverted, so that both parts look for their largest (0 = none)
+  unsigned long long top[2][SWP_WAVES * SWP_LIST];             // each wave's largest thread maxima
+  unsigned long long floor[2];                                 // the m-th largest thread maximum of the workgroup
+  unsigned long long lkey[2][SWP_ROOM];                        // keys from the floor up, in any order
+  int lidx[2][SWP_ROOM], ln[2];
   int dec[SWP_LIST][4];                                        // per swap: Vague position, Candidate position, list index, slot
 };
 
@@ -66,11 +78,6 @@ __device__ __forceinline__ float key_score(unsigned long long key) {
   return __uint_as_float(mono ^ ((mono >> 31) ? 0x80000000u : 0xffffffffu));
 }
 
-__device__ __forceinline__ unsigned long long shfl_xor_u64s(unsigned long long v, int m) {
-  const uint32_t lo = __shfl_xor((int)(uint32_t)v, m), hi = __shfl_xor((int)(uint32_t)(v >> 32), m);
-  return ((unsigned long long)hi << 32) | lo;
-}
-
 __device__ __forceinline__ unsigned long long vague_key_at(const int32_t* vp, const float* sc, int i, int nv,
                                                            long long n_cap) {
   if (i >= nv) return SWP_NONE_MAX;
@@ -86,40 +93,138 @@ __device__ __forceinline__ unsigned long long cand_key_at(const int32_t* rp, con
 
 // Scan both parts of a unit and leave the m largest Vague keys and the m
 // smallest Candidate keys, in order, in sh (with the Vague list index / the
-// retained slot of each).  Not inlined: the keys it holds in registers (REG) are
+// retained slot of each).  Not inlined: the keys it holds in registers are
 // dead when it returns and must not count against the caller's registers.
-template <bool REG>
+//
+// Every one of the m largest keys is at least as large as the m-th largest of the threads' maxima (m threads have a key from
+// there up).  So: a maximum per thread, the m largest per wave, the m-th largest of all (one wave per part), the keys from
+// there up into a list (at most those of m threads), and the list's m largest in order (one wave per part): three barriers whatever m
+// is, and every key is looked at twice, where m rounds of a workgroup-wide extreme took two barriers and another look each.
 __device__ __noinline__ void swap_build_lists(SwapShared& sh, const int32_t* vp, const int32_t* rp,
                                               const float* sc, int nv, int ret_cap, int recent_from,
                                               long long n_cap, int m) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  unsigned long long vk[REG ? SWP_KV : 1], ck[REG ? SWP_KC : 1];
-  if constexpr (REG) {
-    // all positions first, then all scores (clamped addresses, no branches): two
-    // rounds of independent loads instead of one dependent pair per token
-    int pv[SWP_KV], pc[SWP_KC];
+  // all positions first, then all scores (clamped addresses, no branches): two
+  // rounds of independent loads instead of one dependent pair per token
+  int pv[SWP_KV], pc[SWP_KC];
+#pragma unroll
+  for (int j = 0; j < SWP_KV; ++j) {
+    const int i = j * SWP_THREADS + tid;
+    pv[j] = vp[min(i, max(nv - 1, 0))];
+    if (i >= nv || pv[j] >= n_cap) pv[j] = -1;
+  }
+#pragma unroll
+  for (int j = 0; j < SWP_KC; ++j) {
+    const int s_ = j * SWP_THREADS + tid;
+    pc[j] = rp[min(s_, ret_cap - 1)];
+    if (s_ >= ret_cap || pc[j] >= recent_from || pc[j] >= n_cap) pc[j] = -1;
+  }
+  float fv[SWP_KV], fc[SWP_KC];
+#pragma unroll
+  for (int j = 0; j < SWP_KV; ++j) fv[j] = sc[max(pv[j], 0)];
+#pragma unroll
+  for (int j = 0; j < SWP_KC; ++j) fc[j] = sc[max(pc[j], 0)];
+  if (tid < 2) sh.ln[tid] = 0;
+  // the halves of a key: the score's image, and ~position (Vague) or, of the inverted key, the position (Candidate)
+  uint32_t hv[SWP_KV], hc[SWP_KC];
+  uint32_t bv = 0u, bc = 0u;
+#pragma unroll
+  for (int j = 0; j < SWP_KV; ++j) {
+    hv[j] = pv[j] >= 0 ? (uint32_t)(swap_key(fv[j], 0) >> 32) : 0u;
+    bv = max(bv, hv[j]);
+  }
+#pragma unroll
+  for (int j = 0; j < SWP_KC; ++j) {
+    hc[j] = pc[j] >= 0 ? ~(uint32_t)(swap_key(fc[j], 0) >> 32) : 0u;
+    bc = max(bc, hc[j]);
+  }
+  uint32_t lv = 0u, lc = 0u;
+#pragma unroll
+  for (int j = 0; j < SWP_KV; ++j) lv = max(lv, hv[j] == bv ? ~(uint32_t)pv[j] : 0u);
+#pragma unroll
+  for (int j = 0; j < SWP_KC; ++j) lc = max(lc, hc[j] == bc ? (uint32_t)pc[j] : 0u);
+  const unsigned long long tv = bv ? ((unsigned long long)bv << 32) | lv : 0ull;
+  const unsigned long long tc = bc ? ((unsigned long long)bc << 32) | lc : 0ull;
+  {
+    unsigned long long xv = tv, xc = tc;
+    for (int k = 0; k < m; ++k) {
+      const unsigned long long gv = wave_max_u64(xv), gc = wave_max_u64(xc);
+      if (lane == 0) { sh.top[0][wave * m + k] = gv; sh.top[1][wave * m + k] = gc; }
+      if (xv == gv) xv = 0ull;
+      if (xc == gc) xc = 0ull;
+    }
+  }
+  wg_lds_barrier();
+  if (wave < 2) {
+    unsigned long long x[SWP_LIST / 4];              // SWP_WAVES * m entries over 64 lanes
+#pragma unroll
+    for (int e = 0; e < SWP_LIST / 4; ++e) x[e] = (e * 64 + lane < SWP_WAVES * m) ? sh.top[wave][e * 64 + lane] : 0ull;
+    unsigned long long g = 0ull;
+    for (int k = 0; k < m; ++k) {
+      unsigned long long y = x[0];
+#pragma unroll
+      for (int e = 1; e < SWP_LIST / 4; ++e) y = x[e] > y ? x[e] : y;
+      g = wave_max_u64(y);
+#pragma unroll
+      for (int e = 0; e < SWP_LIST / 4; ++e)
+        if (x[e] == g) x[e] = 0ull;
+    }
+    if (lane == 0) sh.floor[wave] = g;               // 0: fewer than m threads have a key
+  }
+  wg_lds_barrier();
+  const unsigned long long floor_v = sh.floor[0], floor_c = sh.floor[1];
+  if (tv >= floor_v && tv != 0ull) {
 #pragma unroll
     for (int j = 0; j < SWP_KV; ++j) {
-      const int i = j * SWP_THREADS + tid;
-      pv[j] = vp[min(i, max(nv - 1, 0))];
-      if (i >= nv || pv[j] >= n_cap) pv[j] = -1;
+      const unsigned long long key = ((unsigned long long)hv[j] << 32) | ~(uint32_t)pv[j];
+      if (hv[j] != 0u && key >= floor_v) {
+        const int at = atomicAdd(&sh.ln[0], 1);
+        if (at < SWP_ROOM) { sh.lkey[0][at] = key; sh.lidx[0][at] = j * SWP_THREADS + tid; }
+      }
     }
+  }
+  if (tc >= floor_c && tc != 0ull) {
 #pragma unroll
     for (int j = 0; j < SWP_KC; ++j) {
-      const int s_ = j * SWP_THREADS + tid;
-      pc[j] = rp[min(s_, ret_cap - 1)];
-      if (s_ >= ret_cap || pc[j] >= recent_from || pc[j] >= n_cap) pc[j] = -1;
+      const unsigned long long key = ((unsigned long long)hc[j] << 32) | (uint32_t)pc[j];
+      if (hc[j] != 0u && key >= floor_c) {
+        const int at = atomicAdd(&sh.ln[1], 1);
+        if (at < SWP_ROOM) { sh.lkey[1][at] = key; sh.lidx[1][at] = j * SWP_THREADS + tid; }
+      }
     }
-    float sv_[SWP_KV], sc_[SWP_KC];
-#pragma unroll
-    for (int j = 0; j < SWP_KV; ++j) sv_[j] = sc[max(pv[j], 0)];
-#pragma unroll
-    for (int j = 0; j < SWP_KC; ++j) sc_[j] = sc[max(pc[j], 0)];
-#pragma unroll
-    for (int j = 0; j < SWP_KV; ++j) vk[j] = pv[j] >= 0 ? swap_key(sv_[j], pv[j]) : SWP_NONE_MAX;
-#pragma unroll
-    for (int j = 0; j < SWP_KC; ++j) ck[j] = pc[j] >= 0 ? swap_key(sc_[j], pc[j]) : SWP_NONE_MIN;
   }
+  wg_lds_barrier();
+  if (wave < 2) {
+    const int n = min(sh.ln[wave], SWP_ROOM);      // more only if a position is listed twice
+    unsigned long long prev = ~0ull;
+    int found = 0;
+    for (int k = 0; k < m; ++k) {
+      unsigned long long best = 0ull;
+      int at = 0;
+      for (int e = lane; e < n; e += 64) {
+        const unsigned long long key = sh.lkey[wave][e];
+        if (key < prev && key > best) { best = key; at = e; }
+      }
+      const unsigned long long g = wave_max_u64(best);
+      if (g == 0ull) break;
+      if (best == g) {                               // keys are distinct: one owner
+        if (wave == 0) { sh.vkey[k] = g; sh.vidx[k] = sh.lidx[0][at]; }
+        else { sh.ckey[k] = ~g; sh.cslot[k] = sh.lidx[1][at]; }
+      }
+      prev = g;
+      ++found;
+    }
+    if (lane == 0) { if (wave == 0) sh.nvl = found; else sh.ncl = found; }
+  }
+  wg_lds_barrier();
+}
+
+// The same for parts that do not fit registers: m rounds of a workgroup-wide extreme, keys read again from memory by the
+// threads that need their next one.
+__device__ __noinline__ void swap_build_lists_long(SwapShared& sh, const int32_t* vp, const int32_t* rp,
+                                              const float* sc, int nv, int ret_cap, int recent_from,
+                                              long long n_cap, int m) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // A thread offers the best key it still has; only the thread whose key was taken
   // looks for its next one (the taken keys are exactly those beyond the last extreme).
   unsigned long long vprev = SWP_NONE_MIN, cprev = SWP_NONE_MAX;       // previous extremes (exclusive bounds)
@@ -131,40 +236,22 @@ __device__ __noinline__ void swap_build_lists(SwapShared& sh, const int32_t* vp,
     if (redo_v) {
       kmax = SWP_NONE_MAX;
       imax = -1;
-      if constexpr (REG) {
-#pragma unroll
-        for (int j = 0; j < SWP_KV; ++j)
-          if (vk[j] < vprev && vk[j] > kmax) { kmax = vk[j]; imax = j * SWP_THREADS + tid; }
-      } else {
-        for (int i = tid; i < nv; i += SWP_THREADS) {
-          const unsigned long long key = vague_key_at(vp, sc, i, nv, n_cap);
-          if (key < vprev && key > kmax) { kmax = key; imax = i; }
-        }
+      for (int i = tid; i < nv; i += SWP_THREADS) {
+        const unsigned long long key = vague_key_at(vp, sc, i, nv, n_cap);
+        if (key < vprev && key > kmax) { kmax = key; imax = i; }
       }
       redo_v = false;
     }
     if (redo_c) {
       kmin = SWP_NONE_MIN;
       smin = -1;
-      if constexpr (REG) {
-#pragma unroll
-        for (int j = 0; j < SWP_KC; ++j)
-          if (ck[j] > cprev && ck[j] < kmin) { kmin = ck[j]; smin = j * SWP_THREADS + tid; }
-      } else {
-        for (int s_ = tid; s_ < ret_cap; s_ += SWP_THREADS) {
-          const unsigned long long key = cand_key_at(rp, sc, s_, ret_cap, recent_from, n_cap);
-          if (key > cprev && key < kmin) { kmin = key; smin = s_; }
-        }
+      for (int s_ = tid; s_ < ret_cap; s_ += SWP_THREADS) {
+        const unsigned long long key = cand_key_at(rp, sc, s_, ret_cap, recent_from, n_cap);
+        if (key > cprev && key < kmin) { kmin = key; smin = s_; }
       }
       redo_c = false;
     }
-    unsigned long long wmx = kmax, wmn = kmin;
-#pragma unroll
-    for (int x = 1; x < WAVE; x <<= 1) {
-      const unsigned long long o1 = shfl_xor_u64s(wmx, x), o2 = shfl_xor_u64s(wmn, x);
-      wmx = o1 > wmx ? o1 : wmx;
-      wmn = o2 < wmn ? o2 : wmn;
-    }
+    const unsigned long long wmx = wave_max_u64(kmax), wmn = wave_min_u64(kmin);
     if (lane == 0) { sh.wmax[k & 1][wave] = wmx; sh.wmin[k & 1][wave] = wmn; }
     __syncthreads();
     unsigned long long gmax = sh.wmax[k & 1][0], gmin = sh.wmin[k & 1][0];
@@ -190,6 +277,81 @@ __device__ __noinline__ void swap_build_lists(SwapShared& sh, const int32_t* vp,
   __syncthreads();
 }
 
+// Carry out the swaps [k0, k0 + n) of sh.dec, n <= NB, on this thread's channel.  sx: the channel in the unit's sketch, xr: in the
+// unit's retained rows.  RR: rows there is room for, r <= RR.
+template <typename T, int NB, int RR>
+__device__ __forceinline__ void swap_apply(const DevDesc& d, const SwapShared& sh, int k0, int n, T* sx, T* xr, bool flip) {
+  int off_d[NB][RR], off_c[NB][RR], slot[NB];        // uniform
+  uint32_t neg_d[NB], neg_c[NB];
+  float val_d[NB][RR], val_c[NB][RR], cand[NB];
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+    // past n: the last swap's addresses again, nothing is stored
+    const int kk = k0 + min(k, n - 1);
+    const int J = __builtin_amdgcn_readfirstlane(sh.dec[kk][0]), pc = __builtin_amdgcn_readfirstlane(sh.dec[kk][1]);
+    slot[k] = __builtin_amdgcn_readfirstlane(sh.dec[kk][3]);
+    neg_d[k] = neg_c[k] = 0u;
+#pragma unroll
+    for (int i = 0; i < RR; ++i) {
+      off_d[k][i] = off_c[k][i] = 0;
+      val_d[k][i] = val_c[k][i] = 0.f;
+      if (i < d.r) {
+        off_d[k][i] = (i * d.w + bucket_of(d, i, J)) * D;
+        off_c[k][i] = (i * d.w + bucket_of(d, i, pc)) * D;
+        if (flip && sign_neg(d, i, J)) neg_d[k] |= 1u << i;
+        if (flip && sign_neg(d, i, pc)) neg_c[k] |= 1u << i;
+        val_d[k][i] = Store<T>::load1(sx + off_d[k][i]);
+        val_c[k][i] = Store<T>::load1(sx + off_c[k][i]);
+      }
+    }
+    cand[k] = Store<T>::load1(xr + (size_t)slot[k] * D);
+  }
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+    if (k >= n) break;
+    // what the earlier swaps of this call have written since
+#pragma unroll
+    for (int j = 0; j < k; ++j) {
+#pragma unroll
+      for (int i = 0; i < RR; ++i) {
+        if (i < d.r) {
+          if (off_d[k][i] == off_d[j][i]) val_d[k][i] = val_d[j][i];
+          if (off_d[k][i] == off_c[j][i]) val_d[k][i] = val_c[j][i];
+          if (off_c[k][i] == off_d[j][i]) val_c[k][i] = val_d[j][i];
+          if (off_c[k][i] == off_c[j][i]) val_c[k][i] = val_c[j][i];
+        }
+      }
+      if (slot[k] == slot[j]) cand[k] = cand[j];
+    }
+    float rows[KVR_MAX_ROWS];
+#pragma unroll
+    for (int i = 0; i < KVR_MAX_ROWS; ++i) rows[i] = (i < RR) ? (((neg_d[k] >> i) & 1u) ? -val_d[k][i < RR ? i : 0] : val_d[k][i < RR ? i : 0]) : 0.f;
+    const float est = median_rows<0, T>(rows, d.r, d.median_mode);
+#pragma unroll
+    for (int i = 0; i < RR; ++i) {
+      if (i < d.r) {
+        // delete first, then insert; float32 sums, one rounding per touched slot
+        const float gd = ((neg_d[k] >> i) & 1u) ? -1.f : 1.f;
+        const float gc = ((neg_c[k] >> i) & 1u) ? -1.f : 1.f;
+        float acc = val_d[k][i] + (-gd) * est;
+        if (off_c[k][i] == off_d[k][i]) {
+          acc = acc + gc * cand[k];
+          Store<T>::store1(sx + off_d[k][i], acc);
+          val_d[k][i] = val_c[k][i] = Store<T>::round(acc);
+        } else {
+          const float ins = val_c[k][i] + gc * cand[k];
+          Store<T>::store1(sx + off_d[k][i], acc);
+          Store<T>::store1(sx + off_c[k][i], ins);
+          val_d[k][i] = Store<T>::round(acc);
+          val_c[k][i] = Store<T>::round(ins);
+        }
+      }
+    }
+    Store<T>::store1(xr + (size_t)slot[k] * D, est);
+    cand[k] = Store<T>::round(est);                  // from here on: what the slot holds
+  }
+}
+
 template <typename T, bool REG>
 __global__ __launch_bounds__(SWP_THREADS) void swap_back_kernel(
     DevDesc d, const float* __restrict__ scores, long long n_cap, T* k_ret, T* v_ret, int32_t* ret_pos,
@@ -209,7 +371,8 @@ __global__ __launch_bounds__(SWP_THREADS) void swap_back_kernel(
 
   while (done < max_swaps) {
     const int m = min(max_swaps - done, SWP_LIST);
-    swap_build_lists<REG>(sh, vp, rp, sc, nv, ret_cap, recent_from, n_cap, m);
+    if constexpr (REG) swap_build_lists(sh, vp, rp, sc, nv, ret_cap, recent_from, n_cap, m);
+    else swap_build_lists_long(sh, vp, rp, sc, nv, ret_cap, recent_from, n_cap, m);
 
     // ---- up to m swaps on the lists.  Which tokens change places depends on scores and
     //      positions only, not on sketch contents: thread 0 decides all swaps of this scan
@@ -217,88 +380,63 @@ __global__ __launch_bounds__(SWP_THREADS) void swap_back_kernel(
     //      after the other without a barrier in between (a later swap that touches a slot
     //      or a retained row of an earlier one is ordered by the thread's own program
     //      order: a channel is only ever touched by its own thread). -------------------------
-    if (tid == 0) {
-      int n_dec = 0;
-      for (int k = 0; k < m; ++k) {
-        if (sh.nvl <= 0 || sh.ncl <= 0) break;
-        const unsigned long long kv = sh.vkey[0], kc = sh.ckey[0];
+    if (tid < WAVE) {
+      // lane i holds entry i of both lists
+      int nvl = sh.nvl, ncl = sh.ncl, n_dec = 0;
+      unsigned long long vk = tid < nvl ? sh.vkey[tid] : SWP_NONE_MAX, ck = tid < ncl ? sh.ckey[tid] : SWP_NONE_MIN;
+      int vi = tid < nvl ? sh.vidx[tid] : 0, cs = tid < ncl ? sh.cslot[tid] : 0;
+      auto next = [](unsigned long long v) {                              // of the lane above
+        const uint32_t lo = __shfl_down((int)(uint32_t)v, 1), hi = __shfl_down((int)(uint32_t)(v >> 32), 1);
+        return ((unsigned long long)hi << 32) | lo;
+      };
+      auto first = [](unsigned long long v) {
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+        return ((unsigned long long)hi << 32) | lo;
+      };
+      while (n_dec < m && nvl > 0 && ncl > 0) {
+        const unsigned long long kv = first(vk), kc = first(ck);
         const float lhs = key_score(kc) * replace_rate;                   // float32 product, float32 compare
         if (!(lhs < key_score(kv))) break;
-        const int v_idx = sh.vidx[0], c_slot = sh.cslot[0];
-        sh.dec[n_dec][0] = (int)(~(uint32_t)kv);
-        sh.dec[n_dec][1] = (int)(~(uint32_t)kc);
-        sh.dec[n_dec][2] = v_idx;
-        sh.dec[n_dec][3] = c_slot;
+        const int v_idx = __builtin_amdgcn_readfirstlane(vi), c_slot = __builtin_amdgcn_readfirstlane(cs);
+        if (tid == 0) {
+          sh.dec[n_dec][0] = (int)(~(uint32_t)kv);
+          sh.dec[n_dec][1] = (int)(~(uint32_t)kc);
+          sh.dec[n_dec][2] = v_idx;
+          sh.dec[n_dec][3] = c_slot;
+        }
         ++n_dec;
         // pop both heads; the Candidate's key enters the Vague list (at the Vague token's list
-        // index), the Vague token's key enters the Candidate list (in the Candidate's slot)
-        int n = sh.nvl - 1, at = 0;
-        for (int i = 0; i < n; ++i) { sh.vkey[i] = sh.vkey[i + 1]; sh.vidx[i] = sh.vidx[i + 1]; }
-        while (at < n && sh.vkey[at] > kc) ++at;
-        for (int i = n; i > at; --i) { sh.vkey[i] = sh.vkey[i - 1]; sh.vidx[i] = sh.vidx[i - 1]; }
-        sh.vkey[at] = kc;
-        sh.vidx[at] = v_idx;
-        n = sh.ncl - 1;
-        at = 0;
-        for (int i = 0; i < n; ++i) { sh.ckey[i] = sh.ckey[i + 1]; sh.cslot[i] = sh.cslot[i + 1]; }
-        while (at < n && sh.ckey[at] < kv) ++at;
-        for (int i = n; i > at; --i) { sh.ckey[i] = sh.ckey[i - 1]; sh.cslot[i] = sh.cslot[i - 1]; }
-        sh.ckey[at] = kv;
-        sh.cslot[at] = c_slot;
+        // index), the Vague token's key enters the Candidate list (in the Candidate's slot).  What stays in front of the
+        // new entry moves up by one, what comes behind it stays where it was.
+        const unsigned long long vn = next(vk), cn = next(ck);
+        const int vin = __shfl_down(vi, 1), csn = __shfl_down(cs, 1);
+        const int va = __popcll(__ballot(tid < nvl - 1 && vn > kc)), ca = __popcll(__ballot(tid < ncl - 1 && cn < kv));
+        if (tid < va) { vk = vn; vi = vin; }
+        else if (tid == va) { vk = kc; vi = v_idx; }
+        if (tid < ca) { ck = cn; cs = csn; }
+        else if (tid == ca) { ck = kv; cs = c_slot; }
       }
-      sh.go = n_dec;
+      if (tid == 0) sh.go = n_dec;
     }
     __syncthreads();
     const int swaps_here = sh.go;
     const bool stop = swaps_here < m;                                       // the loop condition failed (uniform)
-    for (int k = 0; k < swaps_here; ++k) {
-      const int J = sh.dec[k][0], pc = sh.dec[k][1], v_idx = sh.dec[k][2], c_slot = sh.dec[k][3];
-      if (tid < 2 * D) {
-        const bool is_v = tid >= D;
-        const int c = is_v ? tid - D : tid;
-        T* sx = (is_v ? sv : sk) + (size_t)unit * d.r * d.w * D + c;
-        T* xr = (is_v ? v_ret : k_ret) + ((size_t)unit * ret_cap + c_slot) * D + c;
-        const bool flip = is_v ? (d.sign_mask & 2) != 0 : (d.sign_mask & 1) != 0;
-        // every value the update needs is requested before any is used: one round trip
-        int off_d[KVR_MAX_ROWS], off_c[KVR_MAX_ROWS];
-        float old_d[KVR_MAX_ROWS], old_c[KVR_MAX_ROWS], rows[KVR_MAX_ROWS];
-#pragma unroll
-        for (int i = 0; i < KVR_MAX_ROWS; ++i) {
-          off_d[i] = off_c[i] = 0;
-          old_d[i] = old_c[i] = 0.f;
-          if (i < d.r) {
-            off_d[i] = (i * d.w + bucket_of(d, i, J)) * D;
-            off_c[i] = (i * d.w + bucket_of(d, i, pc)) * D;
-            old_d[i] = Store<T>::load1(sx + off_d[i]);
-            old_c[i] = Store<T>::load1(sx + off_c[i]);
-          }
-        }
-        const float cand = Store<T>::load1(xr);
-#pragma unroll
-        for (int i = 0; i < KVR_MAX_ROWS; ++i)
-          rows[i] = (i < d.r && flip && sign_neg(d, i, J)) ? -old_d[i] : old_d[i];
-        const float est = median_rows<0, T>(rows, d.r, d.median_mode);
-#pragma unroll
-        for (int i = 0; i < KVR_MAX_ROWS; ++i) {
-          if (i < d.r) {
-            // delete first, then insert; float32 sums, one rounding per touched slot
-            const float gd = (flip && sign_neg(d, i, J)) ? -1.f : 1.f;
-            const float gc = (flip && sign_neg(d, i, pc)) ? -1.f : 1.f;
-            float acc = old_d[i] + (-gd) * est;
-            if (off_c[i] == off_d[i]) {
-              acc = acc + gc * cand;
-              Store<T>::store1(sx + off_d[i], acc);
-            } else {
-              Store<T>::store1(sx + off_d[i], acc);
-              Store<T>::store1(sx + off_c[i], old_c[i] + gc * cand);
-            }
-          }
-        }
-        Store<T>::store1(xr, est);
+    if (tid < 2 * D) {
+      const bool is_v = tid >= D;
+      const int c = is_v ? tid - D : tid;
+      T* sx = (is_v ? sv : sk) + (size_t)unit * d.r * d.w * D + c;
+      T* xr = (is_v ? v_ret : k_ret) + (size_t)unit * ret_cap * D + c;
+      const bool flip = is_v ? (d.sign_mask & 2) != 0 : (d.sign_mask & 1) != 0;
+      if (d.r <= 4) {
+        for (int k = 0; k < swaps_here; k += 4) swap_apply<T, 4, 4>(d, sh, k, min(4, swaps_here - k), sx, xr, flip);
+      } else {
+        for (int k = 0; k < swaps_here; k += 2) swap_apply<T, 2, KVR_MAX_ROWS>(d, sh, k, min(2, swaps_here - k), sx, xr, flip);
       }
-      if (tid == 0) {
-        rp[c_slot] = J;
-        vp[v_idx] = pc;
+    } else if (tid == 2 * D) {
+      for (int k = 0; k < swaps_here; ++k) {
+        const int J = sh.dec[k][0], pc = sh.dec[k][1];
+        rp[sh.dec[k][3]] = J;
+        vp[sh.dec[k][2]] = pc;
         if (swap_log) {
           swap_log[((size_t)unit * max_swaps + done + k) * 2] = J;
           swap_log[((size_t)unit * max_swaps + done + k) * 2 + 1] = pc;

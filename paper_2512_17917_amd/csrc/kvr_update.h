@@ -156,6 +156,8 @@ __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v)
   return a < b ? a : b;
 }
 
+__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) { return ~wave_min_u64(~v); }
+
 // Sum over a wave, in every lane.
 template <int CTRL>
 __device__ __forceinline__ int dpp_add_i(int v) {
