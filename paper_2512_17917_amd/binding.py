@@ -9,6 +9,7 @@ There is no fallback: if the library is missing, loading raises.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 
 import torch
@@ -28,6 +29,7 @@ _ERR_NAMES = {-1: "KVR_ERR_INVALID_ARG", -2: "KVR_ERR_UNSUPPORTED",
               -3: "KVR_ERR_WORKSPACE_TOO_SMALL", -4: "KVR_ERR_HIP"}
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libkvr.so")
+FAST_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_kvr_fast.so")
 
 EXPORTS = ["kvr_version", "kvr_last_hip_error", "kvr_recent_size", "kvr_hash_params_from_seed", "kvr_hash_host",
            "kvr_workspace_size", "kvr_append", "kvr_select", "kvr_encode", "kvr_compact", "kvr_step_update",
@@ -55,6 +57,7 @@ class kvr_attend_opts(C.Structure):
                 ("prof_start", C.c_void_p), ("prof_stop", C.c_void_p)]
 
 
+_fast = None
 _lib = None
 _hip = None
 
@@ -159,8 +162,23 @@ def lib() -> C.CDLL:
         L.kvr_attend_multi.restype = i32
         L.kvr_attend_multi.argtypes = [dp, vp, i32, vp, vp, vp, vp, i32, vp, vp, vp, vp, i32, vp, vp, i64,
                                        vp, sz, vp]
+        _load_fast(L)
         _lib = L
     return _lib
+
+
+def _load_fast(L):
+    """The two calls of a decode step make some thirty tensor checks, 0.75 us each in Python; _kvr_fast.so makes the same
+    checks in C and hands back None where one fails, so that the Python code below says what is wrong."""
+    global _fast
+    if os.path.exists(FAST_PATH):
+        spec = importlib.util.spec_from_file_location("_kvr_fast", FAST_PATH)
+        m = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(m)
+        address = lambda f: C.cast(f, C.c_void_p).value
+        m.setup(address(L.kvr_step_update), address(L.kvr_attend_decode), torch.float32, torch.bfloat16, torch.int32,
+                torch.uint8)
+        _fast = m
 
 
 def _check(fn, rc):
@@ -322,6 +340,13 @@ def kvr_compact(desc, k_src, v_src, src_pos, src_cap, evict_slot, n_evict, evict
 def kvr_step_update(desc, k_new, v_new, n_ctx, k_ret, v_ret, ret_pos, ret_cap, scores, n_cap, n_recent,
                     k_candidate, evict_slot, evict_pos, n_evict, evict_cap, vague_pos, n_vague, vague_cap,
                     sketch_k, sketch_v):
+    lib()
+    if _fast is not None and isinstance(k_new, torch.Tensor) and k_new.is_cuda:
+        rc = _fast.step_update(C.addressof(desc), _stream(), k_new, v_new, n_ctx, k_ret, v_ret, ret_pos, ret_cap, scores, n_cap,
+                               n_recent, k_candidate, evict_slot, evict_pos, n_evict, evict_cap, vague_pos, n_vague, vague_cap,
+                               sketch_k, sketch_v)
+        if rc is not None:
+            return _check("kvr_step_update", rc)
     U, D, dt = desc.batch * desc.n_kv_heads, desc.head_dim, _torch_dtype(desc)
     S = desc.r * desc.w * D
     rc = lib().kvr_step_update(
@@ -367,6 +392,12 @@ def kvr_reconstruct(desc, sketch_k, sketch_v, tok_pos, count, cap, k_out, v_out)
 
 def kvr_attend_decode(desc, q, k_ret, v_ret, ret_pos, ret_cap, sketch_k, sketch_v, vague_pos, n_vague,
                       vague_cap, out, scores, n_cap, ws, opts=None):
+    lib()
+    if _fast is not None and isinstance(q, torch.Tensor) and q.is_cuda:
+        rc = _fast.attend_decode(C.addressof(desc), _stream(), C.addressof(opts) if opts is not None else 0, q, k_ret, v_ret,
+                                 ret_pos, ret_cap, sketch_k, sketch_v, vague_pos, n_vague, vague_cap, out, scores, n_cap, ws)
+        if rc is not None:
+            return _check("kvr_attend_decode", rc)
     U, D, dt = desc.batch * desc.n_kv_heads, desc.head_dim, _torch_dtype(desc)
     S = desc.r * desc.w * D
     wp, wb = _ws(ws)

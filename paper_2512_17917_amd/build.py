@@ -8,12 +8,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libkvr.so")
 OBJ_DIR = os.path.join(HERE, "_build")
+FAST = os.path.join(HERE, "_kvr_fast.so")          # host code: the two calls of a decode step, checked and made in C
 
 SOURCES = ["kvr_api.hip", "kvr_reconstruct.hip", "kvr_attend.hip", "kvr_attend_staged.hip", "kvr_attend_staged64.hip", "kvr_attend_staged16.hip", "kvr_attend_retained.hip", "kvr_select.hip", "kvr_compact.hip",
            "kvr_encode.hip", "kvr_swap.hip", "kvr_attend_multi.hip", "kvr_attend_multi_staged.hip"]
@@ -52,6 +54,7 @@ def build(verbose: bool = False) -> str:
             if verbose and r.stderr:
                 sys.stderr.write(r.stderr)
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", OUT, *[j[0] for j in jobs]])
+    _run(["gcc", "-O2", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], "-o", FAST, os.path.join(CSRC, "kvr_fast.c")])
     return OUT
 
 

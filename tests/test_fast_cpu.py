@@ -1,0 +1,93 @@
+"""The C route of a decode step's two calls refuses exactly what the Python checks refuse.  On the CPU: objects that answer
+like device tensors, and a library whose entry points only record their arguments."""
+import ctypes as C
+
+import pytest
+import torch
+
+from paper_2512_17917_amd import binding as kvr
+
+P, I, L = C.c_void_p, C.c_int32, C.c_int64
+
+
+class Fake:
+    def __init__(self, dtype, n, at, cuda=True, contiguous=True):
+        self.dtype, self.is_cuda, self._n, self._at, self._c = dtype, cuda, n, at, contiguous
+
+    def is_contiguous(self):
+        return self._c
+
+    def numel(self):
+        return self._n
+
+    def data_ptr(self):
+        return self._at
+
+
+@pytest.fixture()
+def fast():
+    kvr.lib()
+    m, got = kvr._fast, []
+    assert m is not None
+    step = C.CFUNCTYPE(I, P, P, P, P, P, P, P, I, P, L, I, I, P, P, P, I, P, P, I, P, P, P)(lambda *a: got.append(a) or 7)
+    att = C.CFUNCTYPE(I, P, P, P, P, P, I, P, P, P, P, I, P, P, L, P, C.c_size_t, P, P)(lambda *a: got.append(a) or 9)
+    types = (torch.float32, torch.bfloat16, torch.int32, torch.uint8)
+    m.setup(C.cast(step, P).value, C.cast(att, P).value, *types)
+    yield m, got
+    real = kvr.lib()
+    m.setup(C.cast(real.kvr_step_update, P).value, C.cast(real.kvr_attend_decode, P).value, *types)
+
+
+def call(dt):
+    """(desc, arguments of step_update, of attend_decode): B 2, 8 heads on 4, three rows of 5 slots."""
+    d = kvr.make_desc(2, 8, 4, 3, 5, dt, seed=1)
+    U, R, V, N, E = 8, 6, 11, 20, 4
+    i32, f32 = torch.int32, torch.float32
+    t = lambda k, ty, n: Fake(ty, n, 1000 + 16 * k)
+    step = [t(0, dt, U * 128), t(1, dt, U * 128), t(2, i32, 2), t(3, dt, U * R * 128), t(4, dt, U * R * 128), t(5, i32, U * R), R,
+            t(6, f32, U * N), N, 3, 2, t(7, i32, U * E), t(8, i32, U * E), t(9, i32, U), E, t(10, i32, U * V), t(11, i32, U), V,
+            t(12, dt, U * 15 * 128), t(13, dt, U * 15 * 128)]
+    att = [t(0, dt, 16 * 128), t(1, dt, U * R * 128), t(2, dt, U * R * 128), t(3, i32, U * R), R, t(4, dt, U * 15 * 128),
+           t(5, dt, U * 15 * 128), t(6, i32, U * V), t(7, i32, U), V, t(8, f32, 16 * 128), t(9, f32, U * N), N, t(10, torch.uint8, 4096)]
+    return d, step, att
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_arguments_arrive(fast, dt):
+    m, got = fast
+    d, step, att = call(dt)
+    at = [x.data_ptr() if isinstance(x, Fake) else x for x in step]
+    assert m.step_update(C.addressof(d), 77, *step) == 7
+    assert list(got[-1]) == [C.addressof(d), *at, 77]
+    at = [x.data_ptr() if isinstance(x, Fake) else x for x in att]
+    assert m.attend_decode(C.addressof(d), 77, 55, *att) == 9
+    assert list(got[-1]) == [C.addressof(d), *at, 4096, 55, 77]
+    for k in (3, 5, 6, 7, 8, 11):                     # the tensors that may be absent
+        less = list(att)
+        less[k] = None
+        assert m.attend_decode(C.addressof(d), 77, 0, *less) == 9 and got[-1][k + 1] is None
+
+
+@pytest.mark.parametrize("which", [0, 1])
+def test_every_check_refuses(fast, which):
+    m, got = fast
+    dt = torch.bfloat16
+    d, *both = call(dt)
+    run = [lambda a: m.step_update(C.addressof(d), 0, *a), lambda a: m.attend_decode(C.addressof(d), 0, 0, *a)][which]
+    good = both[which]
+    assert run(good) is not None
+    n = len(got)
+    none_ok = [(15, 16), (3, 5, 6, 7, 8, 11)][which]
+    for k, x in enumerate(good):
+        if isinstance(x, Fake):
+            other = torch.float16
+            bad = [Fake(other, x._n, x._at), Fake(x.dtype, x._n, x._at, cuda=False), Fake(x.dtype, x._n, x._at, contiguous=False), 3, "x"]
+            if x.dtype != torch.uint8:
+                bad.append(Fake(x.dtype, x._n - 1, x._at))
+            if k not in none_ok:
+                bad.append(None)
+        else:
+            bad = [None, 1.5, "x", 1 << 70]
+        for b in bad:
+            assert run(good[:k] + [b] + good[k + 1:]) is None, (k, b)
+    assert run(good[:-1]) is None and len(got) == n
