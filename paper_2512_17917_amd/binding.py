@@ -5,6 +5,10 @@ of its C entry point, takes torch tensors where the C call takes device
 pointers, checks dtype / device / contiguity / minimum size, and passes
 `data_ptr()` plus the current torch HIP stream.  Nothing is computed here.
 There is no fallback: if the library is missing, loading raises.
+
+The two calls of a decode step (`kvr_step_update`, `kvr_attend_decode`) are
+checked and made by `_kvr_fast.so` (csrc/kvr_fast.c) where every argument is as
+it should be; anything else comes back to the checks here, which raise.
 """
 from __future__ import annotations
 

@@ -17,6 +17,8 @@
 //  * Copies overlap: the first K chunk is fetched while the hashes are
 //    computed, the first V chunk during the softmax, the second V chunk during
 //    the reduction of the first (which has LDS scratch of its own).
+//  * A few retained slots ride along (RET): every wave takes a 16-token tile per
+//    K phase (kvr_ret_stream.h), and the retained kernel is not launched.
 #include "kvr_ret_stream.h"
 
 namespace kvr {

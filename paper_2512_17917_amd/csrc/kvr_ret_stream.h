@@ -63,8 +63,6 @@ struct RetStream {
     for (int j = 0; j < 4; ++j)
       vv[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(vb + min(4 * r16 + j, last) * D + 8 * col));
   }
-  // tiles that are left, the one in flight among them
-  __device__ __forceinline__ int left() const { return t0 < ret_cap ? (ret_cap - t0 + step - 1) / step : 0; }
 
   // take in the tile that is in flight and move on to the next one (not yet requested).  s_q: q in LDS,
   // [G][16 pieces]; logits_unit: where the unit's retained logits go, may be null

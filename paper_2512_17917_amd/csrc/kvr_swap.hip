@@ -35,7 +35,7 @@
 // Bound by memory round trips.  All swaps of a scan are decided before the first is carried out, so the values of four
 // swaps are requested together; a value that an earlier one of the four has just written (the same slot of a sketch row, the
 // same retained slot: equal for all channels) is taken from registers instead.  One swap at a time, each waiting for its loads behind
-// the stores of the one before, and wave extremes by 64-bit shuffles: 32 units, 4 swaps 41 -> 22 us.
+// the stores of the one before, and wave extremes by 64-bit shuffles: 32 units, 4 swaps 41 -> 32.5 us.
 #include "kvr_launch.h"
 #include "kvr_update.h"
 

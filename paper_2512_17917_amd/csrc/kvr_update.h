@@ -126,11 +126,6 @@ __device__ __forceinline__ bool pos_key(int pos, float scv, int slot, int ret_ca
 
 __device__ __forceinline__ int key_pos(unsigned long long key) { return (int)(~(uint32_t)key); }
 
-__device__ __forceinline__ unsigned long long shfl_xor_u64(unsigned long long v, int m) {
-  const uint32_t lo = __shfl_xor((int)(uint32_t)v, m), hi = __shfl_xor((int)(uint32_t)(v >> 32), m);
-  return ((unsigned long long)hi << 32) | lo;
-}
-
 // Minimum over a wave, in every lane: row rotations (DPP) and row exchanges on the vector ALUs.
 template <int CTRL>
 __device__ __forceinline__ unsigned long long dpp_min_u64(unsigned long long v) {
