@@ -39,7 +39,7 @@ OFFLINE_COUNTERS = {
     "c4": {
         # bytes per kvr_attend_decode call at the memory side of the L2: read requests priced by their size
         # (32 / 64 / 128 B request counters) + WRITE_SIZE, summed over the call's three kernels
-        "traffic": 782.7e6,
+        "traffic": 782.6e6,
         "traffic_note": "off-line counter reading (profiles/attend_call_c4_hbm_traffic.txt): 681.0 MB read "
                         "(TCC_EA0_RDREQ by request size; FETCH_SIZE prices this chip's 128-byte requests at 64 "
                         "bytes and reads half of that) + 101.6 MB written (WRITE_SIZE), retained + staged + merge "
@@ -47,8 +47,8 @@ OFFLINE_COUNTERS = {
                         "attention kernels to the score pass, the slice partials and whole lines pulled by "
                         "4-byte score accesses",
         "alu": {"file": "profiles/attend_kernels_c4_sq_counters.txt", "kernel": "attend_vague_staged64_kernel<4>",
-                "valu_insts_per_launch": 60048000.0, "waves_per_launch": 10240,
-                "valu_busy": 0.71, "lds_busy": 0.41, "lds_bank_conflict_share": 0.46},
+                "valu_insts_per_launch": 59849088.0, "waves_per_launch": 10240,
+                "valu_busy": 0.71, "lds_busy": 0.45, "lds_bank_conflict_share": 0.47},
     },
 }
 # plain vector ALU peak: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz lane-operations per second (the 157.3 TFLOP/s
