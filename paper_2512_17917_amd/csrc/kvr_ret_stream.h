@@ -115,8 +115,7 @@ struct RetStream {
       const uint32_t hi = __float_as_uint(p) & 0xffff0000u;
       const float r1 = p - __uint_as_float(hi);
       const uint32_t mid = __float_as_uint(r1) & 0xffff0000u;
-      // eight bits left, so the low half is zero, but where p < 2^-118 and the rest is denormal
-      const uint32_t lo = __float_as_uint(r1 - __uint_as_float(mid)) & 0xffff0000u;
+      const uint32_t lo = __float_as_uint(r1 - __uint_as_float(mid));     // eight bits left: the low half is zero
       a1[i] = ((col & 1) ? mid : hi) >> down;
       a2[i] = ((col & 1) ? 0u : lo) >> down;
     }
