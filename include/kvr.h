@@ -131,8 +131,7 @@ typedef struct kvr_desc {
  *       recorded on side_stream and awaited by `stream` before the merge kernel, on
  *       every path including errors, so the call stays ordered on `stream` and the
  *       workspace is free when work enqueued after the call runs.  Without them the
- *       two kernels run back to back on `stream`; results are the same.  (A few
- *       retained slots need no kernel of their own and no second stream.)  The three
+ *       two kernels run back to back on `stream`; results are the same.  The three
  *       handles must not be used by another call that can run at the same time.
  *   prof_start, prof_stop: two hipEvent_t with timing enabled, both or none;
  *       recorded on `stream` right before the call's first and right after its last

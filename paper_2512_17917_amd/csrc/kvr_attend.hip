@@ -40,7 +40,7 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
   AttendPlan p;
   const long long units = (long long)d.B * d.Hkv;
   const long long tot_cap = ret_cap + vague_cap;
-  p.staged = p.fused = false;
+  p.staged = false;
   p.n_vslices = 0;
   p.ch = 0;
   p.lds_bytes = 0;
@@ -86,13 +86,6 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
       }
       p.staged = true;
       p.n_vslices = best_n;
-      // Few retained slots: the staged kernel's waves take them along, two 16-token tiles each at most, one per K phase.  us a call,
-      // with a launch of their own and without: 8 x 8 units, 1862 + 187 tokens 28.5 and 25.7; 1 x 8, 12728 + 3688 31.9 and 28.9; 2 x 8,
-      // 3100 + 900 27.9 and 25.3.  With three tiles and more a wave waits for them: 24 units of two heads, 5300 + 2700 tokens 34.5
-      // and 39, 96 units of one head, 3876 + 1132 45.5 and 50.  Not where the launch is long enough for the retained kernel to run
-      // next to it on a second stream: 512 units of one head, 3700 + 400 tokens 116 on a second stream, 125 taken along.
-      p.fused = s64 && (ret_cap + 15) / 16 <= 2 * 8 * best_n && units * best_n < 2 * 256 &&
-                staged64_ret_lds(d.w, d.G) <= STAGED_LDS_LIMIT;
     }
   }
   p.mfma_retained = (dtype == KVR_BF16);
@@ -111,7 +104,6 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
       p.vslice_tokens = slice_tokens_for(vague_cap, units);
       p.n_vslices = (int)((vague_cap + p.vslice_tokens - 1) / p.vslice_tokens);
     }
-    if (p.fused) p.n_rslices = 0;
     p.n_slices = p.n_rslices + p.n_vslices;
   } else {
     // one generic launch over all tokens
@@ -598,7 +590,7 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
   const bool big = (long long)units * plan.n_vslices >= 2ll * cus;
   // And only where a CU holds a workgroup of each.
   const int side_lds = attend_side_lds(d, plan);
-  const bool side = sd.stream != nullptr && big && side_lds > 0 && !plan.fused;
+  const bool side = sd.stream != nullptr && big && side_lds > 0;
   if (side) {
     e = hipEventRecord(sd.fork, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(sd.stream, sd.fork, 0);
@@ -614,8 +606,6 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
         if (e == hipSuccess) e = ew;
       }
     }
-  } else if (plan.fused) {
-    // the staged kernel takes them along
   } else if (plan.mfma_retained) {
     e = launch_attend_retained(d, a, plan.n_rslices, 0, 0, st);
   } else {

@@ -17,9 +17,7 @@
 //  * Copies overlap: the first K chunk is fetched while the hashes are
 //    computed, the first V chunk during the softmax, the second V chunk during
 //    the reduction of the first (which has LDS scratch of its own).
-//  * A few retained slots ride along (RET): every wave takes a 16-token tile per
-//    K phase (kvr_ret_stream.h), and the retained kernel is not launched.
-#include "kvr_ret_stream.h"
+#include "kvr_staged.h"
 
 namespace kvr {
 
@@ -273,9 +271,13 @@ __device__ __forceinline__ void v_pass(const unsigned char* s_sk, const uint2 (&
   }
 static_assert(ST_KMAX == 6, "KVR_DISPATCH_NK covers 1..6 rounds");
 
-// RET: the retained slots too, at most two tiles a wave (kvr_ret_stream.h); one partial per workgroup for both.
-template <int G, bool RET>
-__device__ __forceinline__ void staged64_body(const DevDesc& d, const AttendArgs& a) {
+template <int G>
+// Register cap: 192 per lane (the attribute counts in units of two on this target).  Two
+// waves of this kernel and one wave of the retained-slot kernel in its 128-register form
+// then fill a SIMD's 512 registers exactly, which is what lets the two kernels run side by
+// side on a CU.
+__global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) void attend_vague_staged64_kernel(
+    DevDesc d, AttendArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int R = 3, CH = 64, NC = 8, ROWB = 128, ROWB_LOG2 = 7, NPH = D / CH, KMAX = ST_KMAX;
   constexpr int NROW = ST_WAVES * 4;         // 16-lane rows per workgroup
@@ -306,12 +308,6 @@ __device__ __forceinline__ void staged64_body(const DevDesc& d, const AttendArgs
   if (n_k > KMAX) n_k = KMAX;             // cannot happen when the plan was made for vague_cap
   n_k = __builtin_amdgcn_readfirstlane(n_k);      // equal in all lanes of a wave; now the compiler knows
   const int turn = __builtin_amdgcn_readfirstlane(wave >> 2);   // waves i and i + 4 share a SIMD
-  RetStream<G> ret;
-  const int ret_first = __builtin_amdgcn_readfirstlane(gw);
-  if constexpr (RET) ret.init(a, unit, ret_first, NWT);
-  float* ret_logits = (RET && a.logits) ? a.logits + (size_t)unit * (a.ret_cap + a.vague_cap) * G : nullptr;
-  float* s_ret = reinterpret_cast<float*>(s_q + G * 16);                  // RET: [8 waves][G][128], then maxima and sums [G][8]
-  float* s_rstat = s_ret + ST_WAVES * G * D;
 
   const size_t sk_unit = (size_t)unit * R * w * D;      // elements
   const unsigned char* skg = reinterpret_cast<const unsigned char*>((const bf16_t*)a.sk + sk_unit);
@@ -384,7 +380,6 @@ __device__ __forceinline__ void staged64_body(const DevDesc& d, const AttendArgs
   asm volatile("" ::"v"(touched));       // the touch load has no other use: keep it
   if (tid < G * 16) s_q[tid] = qv;
   stage_wait();
-  if constexpr (RET) ret.issue(lane);
   lds_barrier();
 
   // ---- K phases: logits -----------------------------------------------------
@@ -397,11 +392,8 @@ __device__ __forceinline__ void staged64_body(const DevDesc& d, const AttendArgs
   for (int cc = 0; cc < NPH; ++cc) {
     if (cc > 0) {
       lds_barrier();
-      if constexpr (RET) __builtin_amdgcn_s_waitcnt(0x0F70);     // the tile is here: nothing below waits for the copy
       stage_issue<NC, ROWB>(skg, s_sk, n_pieces, cc, tid);
-      if constexpr (RET) ret.consume(lane, s_q, d.scale, ret_logits);
       stage_wait();
-      if constexpr (RET) ret.issue(lane);
       lds_barrier();
     }
     {
@@ -420,23 +412,7 @@ __device__ __forceinline__ void staged64_body(const DevDesc& d, const AttendArgs
 
   // ---- the first V chunk is on its way during the softmax ----------------------
   lds_barrier();                           // every wave is done with the K chunk
-  if constexpr (RET) __builtin_amdgcn_s_waitcnt(0x0F70);
   stage_issue<NC, ROWB>(svg, s_sk, n_pieces, 0, tid);
-  if constexpr (RET) {
-    ret.consume(lane, s_q, d.scale, ret_logits);
-    float o[8];
-    ret.result(lane, ret_first * 16, s_q, d.scale, o);
-    const float l = ret.sum();
-    if ((lane >> 4) < G) {
-      float* dst = s_ret + (wave * G + (lane >> 4)) * D + 8 * (lane & 15);
-      *reinterpret_cast<float4*>(dst) = make_float4(o[0], o[1], o[2], o[3]);
-      *reinterpret_cast<float4*>(dst + 4) = make_float4(o[4], o[5], o[6], o[7]);
-    }
-    if (lane < 4 * G && (lane & 3) == 0) {
-      s_rstat[(lane >> 2) * ST_WAVES + wave] = ret.m_run;
-      s_rstat[(G + (lane >> 2)) * ST_WAVES + wave] = l;
-    }
-  }
 
   // ---- softmax weights against the workgroup's own maximum -------------------
   const int tot_cap = a.ret_cap + a.vague_cap;
@@ -605,25 +581,13 @@ __device__ __forceinline__ void staged64_body(const DevDesc& d, const AttendArgs
       float M = m[0];
 #pragma unroll
       for (int x = 1; x < ST_WAVES; ++x) M = fmaxf(M, m[x]);
-      if constexpr (RET) {
-#pragma unroll
-        for (int x = 0; x < ST_WAVES; ++x) M = fmaxf(M, s_rstat[g * ST_WAVES + x]);
-      }
 #pragma unroll
       for (int x = 0; x < ST_WAVES; ++x) f[x] = (m[x] == -__builtin_inff()) ? 0.f : __expf(m[x] - M);
       float v = 0.f;
 #pragma unroll
       for (int x = 0; x < ST_WAVES; ++x) v += s_part[x * 4 * G * CH + tid] * f[x];
-      float L = 0.f;
-      if constexpr (RET) {
-#pragma unroll
-        for (int x = 0; x < ST_WAVES; ++x) {
-          const float mr = s_rstat[g * ST_WAVES + x], fr = (mr == -__builtin_inff()) ? 0.f : __expf(mr - M);
-          v += s_ret[(x * G + g) * D + cc * CH + tid % CH] * fr;
-          L += s_rstat[(G + g) * ST_WAVES + x] * fr;
-        }
-      }
       if (cc + 1 == NPH && tid % CH == 0) {
+        float L = 0.f;
 #pragma unroll
         for (int x = 0; x < ST_WAVES; ++x) L += s_stat[(G + g) * ST_WAVES + x] * f[x];
         a.part_ml[(part * G + g) * 2] = M;
@@ -639,24 +603,11 @@ __device__ __forceinline__ void staged64_body(const DevDesc& d, const AttendArgs
   }
 }
 
-// The Vague list alone.  Register cap: 192 per lane (the attribute counts in units of two on this target).  Two
-// waves of this kernel and one wave of the retained-slot kernel in its 128-register form
-// then fill a SIMD's 512 registers exactly, which is what lets the two kernels run side by
-// side on a CU.
 template <int G>
-__global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) void attend_vague_staged64_kernel(
-    DevDesc d, AttendArgs a) {
-  staged64_body<G, false>(d, a);
-}
-// With the retained slots: all 256 registers that two waves leave each other.
-template <int G>
-__global__ __launch_bounds__(ST_THREADS) void attend_staged64_kernel(DevDesc d, AttendArgs a) {
-  staged64_body<G, true>(d, a);
-}
-
-template <typename K>
-static hipError_t launch64(K kern, std::once_flag& once, hipError_t& attr_rc, const DevDesc& d, const AttendArgs& a,
-                           int lds, hipStream_t st) {
+static hipError_t launch64(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan, hipStream_t st) {
+  auto kern = attend_vague_staged64_kernel<G>;
+  static std::once_flag once;
+  static hipError_t attr_rc = hipSuccess;
   std::call_once(once, [&]() {
     attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                   160 * 1024);
@@ -664,25 +615,17 @@ static hipError_t launch64(K kern, std::once_flag& once, hipError_t& attr_rc, co
   if (attr_rc != hipSuccess) return attr_rc;
   const int units = d.B * d.Hkv;
   const int units_pad = (units + 7) / 8 * 8;
-  hipLaunchKernelGGL(kern, dim3(units_pad * a.n_vslices), dim3(ST_THREADS), lds, st, d, a);
+  hipLaunchKernelGGL(kern, dim3(units_pad * plan.n_vslices), dim3(ST_THREADS), plan.lds_bytes, st, d, a);
   return hipGetLastError();
-}
-
-template <int G>
-static hipError_t launch64_g(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan, hipStream_t st) {
-  static std::once_flag once[2];
-  static hipError_t rc[2] = {hipSuccess, hipSuccess};
-  return plan.fused ? launch64(attend_staged64_kernel<G>, once[0], rc[0], d, a, staged64_ret_lds(d.w, G), st)
-                    : launch64(attend_vague_staged64_kernel<G>, once[1], rc[1], d, a, plan.lds_bytes, st);
 }
 
 hipError_t launch_attend_vague_staged64(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
                                         hipStream_t st) {
   if (!staged64_applies(d) || plan.lds_bytes < staged64_lds(d.w, d.G)) return hipErrorInvalidValue;
   switch (d.G) {
-    case 1: return launch64_g<1>(d, a, plan, st);
-    case 2: return launch64_g<2>(d, a, plan, st);
-    case 4: return launch64_g<4>(d, a, plan, st);
+    case 1: return launch64<1>(d, a, plan, st);
+    case 2: return launch64<2>(d, a, plan, st);
+    case 4: return launch64<4>(d, a, plan, st);
     default: return hipErrorInvalidValue;
   }
 }

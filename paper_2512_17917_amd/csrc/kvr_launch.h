@@ -22,7 +22,6 @@ struct AttendPlan {
   int vslice_tokens;    // generic kernel over the Vague list: tokens per slice
   int ch;               // staged: channels per LDS phase
   int lds_bytes;        // staged: dynamic LDS per workgroup
-  bool fused;           // retained slots by the waves of the 64-channel staged kernel (n_rslices = 0: one partial for both)
   bool streamed;        // Vague tokens by the streaming LDS-staged kernel of kvr_attend_multi with one query
                         // (8 query heads per kv head; vslice_tokens / n_vslices are its parts)
   size_t off_part_o, off_part_ml, off_logits, off_rec, off_tiles, total_bytes;
@@ -156,8 +155,6 @@ hipError_t launch_attend_vague_staged16(const DevDesc& d, const AttendArgs& a, c
 constexpr int staged64_lds(int w, int G) {
   return ((3 * w * 128 + 1023) & ~1023) + 32 * G * 64 * 4 + staged_stat_lds(G) + G * 256;
 }
-// and with the retained slots' sums and statistics of the eight waves behind it
-constexpr int staged64_ret_lds(int w, int G) { return staged64_lds(w, G) + 8 * G * (D + 2) * 4; }
 // Range: with four heads what LDS holds (less the last kilobyte: w <= 333), with fewer what ten bits hold (w <= 341).
 inline bool staged64_applies(const DevDesc& d) {
   return d.r == 3 && d.G <= 4 && d.sign_mask == 2 && 3 * d.w <= (d.G == 4 ? 1000 : 1024);
