@@ -345,7 +345,7 @@ def kvr_step_update(desc, k_new, v_new, n_ctx, k_ret, v_ret, ret_pos, ret_cap, s
                     k_candidate, evict_slot, evict_pos, n_evict, evict_cap, vague_pos, n_vague, vague_cap,
                     sketch_k, sketch_v):
     lib()
-    if _fast is not None and isinstance(k_new, torch.Tensor) and k_new.is_cuda:
+    if _fast is not None and isinstance(desc, kvr_desc) and isinstance(k_new, torch.Tensor) and k_new.is_cuda:
         rc = _fast.step_update(C.addressof(desc), _stream(), k_new, v_new, n_ctx, k_ret, v_ret, ret_pos, ret_cap, scores, n_cap,
                                n_recent, k_candidate, evict_slot, evict_pos, n_evict, evict_cap, vague_pos, n_vague, vague_cap,
                                sketch_k, sketch_v)
@@ -397,7 +397,8 @@ def kvr_reconstruct(desc, sketch_k, sketch_v, tok_pos, count, cap, k_out, v_out)
 def kvr_attend_decode(desc, q, k_ret, v_ret, ret_pos, ret_cap, sketch_k, sketch_v, vague_pos, n_vague,
                       vague_cap, out, scores, n_cap, ws, opts=None):
     lib()
-    if _fast is not None and isinstance(q, torch.Tensor) and q.is_cuda:
+    if (_fast is not None and isinstance(desc, kvr_desc) and (opts is None or isinstance(opts, kvr_attend_opts))
+            and isinstance(q, torch.Tensor) and q.is_cuda):
         rc = _fast.attend_decode(C.addressof(desc), _stream(), C.addressof(opts) if opts is not None else 0, q, k_ret, v_ret,
                                  ret_pos, ret_cap, sketch_k, sketch_v, vague_pos, n_vague, vague_cap, out, scores, n_cap, ws)
         if rc is not None:

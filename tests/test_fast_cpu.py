@@ -1,6 +1,8 @@
-"""The C route of a decode step's two calls refuses exactly what the Python checks refuse.  On the CPU: objects that answer
-like device tensors, and a library whose entry points only record their arguments."""
+"""The C route of a decode step's two calls takes what the Python checks take and hands back the rest; through the binding
+both routes raise the same errors.  On the CPU: objects that answer like device tensors, and a library whose entry points
+only record their arguments."""
 import ctypes as C
+import types
 
 import pytest
 import torch
@@ -10,9 +12,19 @@ from paper_2512_17917_amd import binding as kvr
 P, I, L = C.c_void_p, C.c_int32, C.c_int64
 
 
-class Fake:
-    def __init__(self, dtype, n, at, cuda=True, contiguous=True):
-        self.dtype, self.is_cuda, self._n, self._at, self._c = dtype, cuda, n, at, contiguous
+class Fake(torch.Tensor):
+    """Answers like a device tensor; a type by itself stands for any other type."""
+
+    def __new__(cls, dtype, n, at, cuda=True, contiguous=True):
+        t = torch.Tensor._make_subclass(cls, torch.empty(0))
+        t._dtype, t._cuda, t._n, t._at, t._c = dtype, cuda, n, at, contiguous
+        return t
+
+    dtype = property(lambda self: self._dtype)
+    is_cuda = property(lambda self: self._cuda)
+
+    def element_size(self):
+        return 1
 
     def is_contiguous(self):
         return self._c
@@ -91,3 +103,68 @@ def test_every_check_refuses(fast, which):
         for b in bad:
             assert run(good[:k] + [b] + good[k + 1:]) is None, (k, b)
     assert run(good[:-1]) is None and len(got) == n
+
+
+# --- through the binding ------------------------------------------------------------------------------------------------
+class Other(C.Structure):
+    """Not the options, not the descriptor."""
+    _fields_ = [("x", C.c_int32)]
+
+
+class Alike(C.Structure):
+    """The descriptor's fields under another name."""
+    _fields_ = kvr.kvr_desc._fields_
+
+
+class Sub(kvr.kvr_desc):
+    pass
+
+
+@pytest.fixture()
+def routes(fast, monkeypatch):
+    """run(name, desc, *args) -> [(what came out of the call, recorded arguments) of the C route, of the Python route]"""
+    m, got = fast
+    real = kvr.lib()
+    take = lambda a: got.append([C.addressof(x.contents) if isinstance(x, C._Pointer) and x else
+                                 None if isinstance(x, C._Pointer) else x for x in a]) or 0
+    entry = lambda f: C.CFUNCTYPE(f.restype, *f.argtypes)(lambda *a: take(a))      # checks its arguments as the library's does
+    e = {n: entry(getattr(real, n)) for n in ("kvr_step_update", "kvr_attend_decode")}
+    m.setup(*(C.cast(e[n], P).value for n in e), torch.float32, torch.bfloat16, torch.int32, torch.uint8)
+    stand_in = types.SimpleNamespace(**e)
+
+    def run(name, *args, **more):
+        came = []
+        for route in (m, None):
+            del got[:]
+            with monkeypatch.context() as p:
+                p.setattr(kvr, "_lib", stand_in)
+                p.setattr(kvr, "_stream", lambda: 77)
+                p.setattr(kvr, "_fast", route)
+                try:
+                    came.append((getattr(kvr, name)(*args, **more), list(got)))
+                except Exception as x:
+                    assert not got
+                    came.append((type(x), str(x)))
+        return came
+    return run
+
+
+def test_types_of_the_structures(routes):
+    """A structure of another type, a pointer or a number in place of the descriptor or the options is refused by both."""
+    d, step, att = call(torch.bfloat16)
+    o = kvr.kvr_attend_opts()
+    for opts in (None, o):
+        c, py = routes("kvr_attend_decode", d, *att, opts=opts)
+        assert c == py and len(c[1]) == 1
+    c, py = routes("kvr_step_update", d, *step)
+    assert c == py and len(c[1]) == 1
+    sub = Sub.from_buffer_copy(bytes(d))
+    c, py = routes("kvr_step_update", sub, *step)
+    assert c == py and len(c[1]) == 1
+    for bad in (d, C.c_int(5), Other(), C.pointer(o), C.byref(o), 5, "x"):
+        c, py = routes("kvr_attend_decode", d, *att, opts=bad)
+        assert c == py and issubclass(c[0], (C.ArgumentError, TypeError)), (bad, c, py)
+    for bad in (o, C.c_int(5), Other(), Alike.from_buffer_copy(bytes(d)), C.pointer(d), 5, None):
+        for name, args in (("kvr_step_update", step), ("kvr_attend_decode", att)):
+            c, py = routes(name, bad, *args)
+            assert c == py and issubclass(c[0], (C.ArgumentError, TypeError, AttributeError)), (bad, c, py)
