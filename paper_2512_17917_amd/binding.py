@@ -181,7 +181,7 @@ def _load_fast(L):
         spec.loader.exec_module(m)
         address = lambda f: C.cast(f, C.c_void_p).value
         m.setup(address(L.kvr_step_update), address(L.kvr_attend_decode), torch.float32, torch.bfloat16, torch.int32,
-                torch.uint8)
+                torch.uint8, torch.Tensor)
         _fast = m
 
 

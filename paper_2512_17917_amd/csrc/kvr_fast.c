@@ -1,5 +1,5 @@
 /* The two calls of a decode step without the interpreter between the checks: the same checks of every tensor that
- * binding._ptr makes (type, place, contiguity, size), made through the tensor's own attributes, and the call itself.  A
+ * binding._ptr makes (that it is one, type, place, contiguity, size), made through the tensor's own attributes, and the call itself.  A
  * check that fails, or an argument of an unexpected kind, returns None: the caller then takes the Python path, which
  * says what is wrong.  Nothing is kept between calls but the names, the types and the two entry points. */
 #define PY_SSIZE_T_CLEAN
@@ -16,7 +16,7 @@ typedef int32_t (*attend_fn)(const kvr_desc*, const void*, const void*, const vo
                              void*, size_t, const kvr_attend_opts*, void*);
 
 static PyObject *n_dtype, *n_is_cuda, *n_is_contiguous, *n_numel, *n_data_ptr;
-static PyObject *t_f32, *t_bf16, *t_i32, *t_u8;
+static PyObject *t_f32, *t_bf16, *t_i32, *t_u8, *t_tensor;
 static step_fn f_step;
 static attend_fn f_attend;
 
@@ -44,6 +44,7 @@ static int tensor(PyObject* t, PyObject* dtype, int64_t need, int none_ok, void*
   int64_t n, a;
   *p = NULL;
   if (t == Py_None) return none_ok;
+  if (PyObject_IsInstance(t, t_tensor) != 1) return 0;
   PyObject* dt = PyObject_GetAttr(t, n_dtype);
   const int same = dt == dtype;
   Py_XDECREF(dt);
@@ -61,11 +62,11 @@ static PyObject* refuse(void) {
 
 static PyObject* setup(PyObject* self, PyObject* const* a, Py_ssize_t n) {
   int64_t s, t;
-  if (n != 6 || !integer(a[0], &s) || !integer(a[1], &t)) return PyErr_Format(PyExc_TypeError, "setup");
+  if (n != 7 || !integer(a[0], &s) || !integer(a[1], &t)) return PyErr_Format(PyExc_TypeError, "setup");
   f_step = (step_fn)(uintptr_t)s;
   f_attend = (attend_fn)(uintptr_t)t;
-  Py_INCREF(a[2]); Py_INCREF(a[3]); Py_INCREF(a[4]); Py_INCREF(a[5]);
-  t_f32 = a[2]; t_bf16 = a[3]; t_i32 = a[4]; t_u8 = a[5];
+  for (int i = 2; i < 7; ++i) Py_INCREF(a[i]);
+  t_f32 = a[2]; t_bf16 = a[3]; t_i32 = a[4]; t_u8 = a[5]; t_tensor = a[6];
   Py_RETURN_NONE;
 }
 

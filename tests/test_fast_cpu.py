@@ -43,7 +43,7 @@ def fast():
     assert m is not None
     step = C.CFUNCTYPE(I, P, P, P, P, P, P, P, I, P, L, I, I, P, P, P, I, P, P, I, P, P, P)(lambda *a: got.append(a) or 7)
     att = C.CFUNCTYPE(I, P, P, P, P, P, I, P, P, P, P, I, P, P, L, P, C.c_size_t, P, P)(lambda *a: got.append(a) or 9)
-    types = (torch.float32, torch.bfloat16, torch.int32, torch.uint8)
+    types = (torch.float32, torch.bfloat16, torch.int32, torch.uint8, torch.Tensor)
     m.setup(C.cast(step, P).value, C.cast(att, P).value, *types)
     yield m, got
     real = kvr.lib()
@@ -129,7 +129,7 @@ def routes(fast, monkeypatch):
                                  None if isinstance(x, C._Pointer) else x for x in a]) or 0
     entry = lambda f: C.CFUNCTYPE(f.restype, *f.argtypes)(lambda *a: take(a))      # checks its arguments as the library's does
     e = {n: entry(getattr(real, n)) for n in ("kvr_step_update", "kvr_attend_decode")}
-    m.setup(*(C.cast(e[n], P).value for n in e), torch.float32, torch.bfloat16, torch.int32, torch.uint8)
+    m.setup(*(C.cast(e[n], P).value for n in e), torch.float32, torch.bfloat16, torch.int32, torch.uint8, torch.Tensor)
     stand_in = types.SimpleNamespace(**e)
 
     def run(name, *args, **more):
@@ -168,3 +168,27 @@ def test_types_of_the_structures(routes):
         for name, args in (("kvr_step_update", step), ("kvr_attend_decode", att)):
             c, py = routes(name, bad, *args)
             assert c == py and issubclass(c[0], (C.ArgumentError, TypeError, AttributeError)), (bad, c, py)
+
+
+class NoTensor:
+    """Answers like a tensor and is none."""
+
+    def __init__(self, t):
+        self.dtype, self.is_cuda = t.dtype, t.is_cuda
+        self.is_contiguous, self.numel, self.data_ptr, self.element_size = t.is_contiguous, t.numel, t.data_ptr, t.element_size
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_every_argument_by_both_routes(routes, dt):
+    """Each argument of each call replaced by what it must not be: the same error by both routes."""
+    d, step, att = call(dt)
+    for name, args in (("kvr_step_update", step), ("kvr_attend_decode", att)):
+        for k, x in enumerate(args):
+            if isinstance(x, Fake):
+                bad = [Fake(torch.float16, x._n, x._at), Fake(x.dtype, x._n, x._at, cuda=False),
+                       Fake(x.dtype, x._n, x._at, contiguous=False), Fake(x.dtype, x._n - 1, x._at), NoTensor(x), None, 3, "x"]
+            else:
+                bad = [None, 1.5, "x", -1, True]
+            for b in bad:
+                c, py = routes(name, d, *args[:k], b, *args[k + 1:])
+                assert c == py, (name, k, b if not isinstance(b, Fake) else (b._dtype, b._n))
