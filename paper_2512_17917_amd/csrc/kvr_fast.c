@@ -55,6 +55,16 @@ static int tensor(PyObject* t, PyObject* dtype, int64_t need, int none_ok, void*
   return 1;
 }
 
+/* The products of sizes that the checks form stay within 64 bits: the descriptor's are what the library takes at most, every
+ * count fits 32 bits.  Others go to the Python checks, whose integers have no end. */
+static int sizes_fit(const kvr_desc* d, const int64_t* count, int n) {
+  const int64_t U = (int64_t)d->batch * d->n_kv_heads, H = (int64_t)d->batch * d->n_q_heads;
+  if (U > 65535 || H > 8 * 65535 || d->head_dim != KVR_HEAD_DIM || d->r > KVR_MAX_ROWS || d->w > 65536) return 0;
+  for (int i = 0; i < n; ++i)
+    if (count[i] != (int32_t)count[i]) return 0;
+  return 1;
+}
+
 static PyObject* refuse(void) {
   PyErr_Clear();
   Py_RETURN_NONE;
@@ -78,6 +88,7 @@ static PyObject* step_update(PyObject* self, PyObject* const* a, Py_ssize_t n) {
       !integer(a[11], &n_recent) || !integer(a[12], &k_cand) || !integer(a[16], &evict_cap) || !integer(a[19], &vague_cap))
     return refuse();
   const kvr_desc* d = (const kvr_desc*)(uintptr_t)da;
+  if (!sizes_fit(d, (int64_t[]){ret_cap, n_cap, n_recent, k_cand, evict_cap, vague_cap}, 6)) return refuse();
   PyObject* dt = d->dtype == KVR_F32 ? t_f32 : t_bf16;
   const int64_t U = (int64_t)d->batch * d->n_kv_heads, D = d->head_dim, S = (int64_t)d->r * d->w * D;
   if (!tensor(a[2], dt, U * D, 0, &kn, 0) || !tensor(a[3], dt, U * D, 0, &vn, 0) || !tensor(a[4], t_i32, d->batch, 0, &nc, 0) ||
@@ -86,9 +97,6 @@ static PyObject* step_update(PyObject* self, PyObject* const* a, Py_ssize_t n) {
       !tensor(a[13], t_i32, U * evict_cap, 0, &es, 0) || !tensor(a[14], t_i32, U * evict_cap, 0, &ep, 0) ||
       !tensor(a[15], t_i32, U, 0, &ne, 0) || !tensor(a[17], t_i32, U * vague_cap, 1, &vp, 0) || !tensor(a[18], t_i32, U, 1, &nv, 0) ||
       !tensor(a[20], dt, U * S, 0, &sk, 0) || !tensor(a[21], dt, U * S, 0, &sv, 0))
-    return refuse();
-  if (ret_cap != (int32_t)ret_cap || n_recent != (int32_t)n_recent || k_cand != (int32_t)k_cand ||
-      evict_cap != (int32_t)evict_cap || vague_cap != (int32_t)vague_cap)
     return refuse();
   int32_t rc;
   Py_BEGIN_ALLOW_THREADS
@@ -106,6 +114,7 @@ static PyObject* attend_decode(PyObject* self, PyObject* const* a, Py_ssize_t n)
       !integer(a[12], &vague_cap) || !integer(a[15], &n_cap))
     return refuse();
   const kvr_desc* d = (const kvr_desc*)(uintptr_t)da;
+  if (!sizes_fit(d, (int64_t[]){ret_cap, vague_cap, n_cap}, 3)) return refuse();
   PyObject* dt = d->dtype == KVR_F32 ? t_f32 : t_bf16;
   const int64_t U = (int64_t)d->batch * d->n_kv_heads, D = d->head_dim, S = (int64_t)d->r * d->w * D, H = (int64_t)d->batch * d->n_q_heads;
   if (!tensor(a[3], dt, H * D, 0, &q, 0) || !tensor(a[4], dt, U * ret_cap * D, 0, &kr, 0) ||
@@ -114,7 +123,6 @@ static PyObject* attend_decode(PyObject* self, PyObject* const* a, Py_ssize_t n)
       !tensor(a[11], t_i32, U, 1, &nv, 0) || !tensor(a[13], t_f32, H * D, 0, &out, 0) || !tensor(a[14], t_f32, U * n_cap, 1, &sc, 0) ||
       !tensor(a[16], t_u8, 0, 0, &ws, &wb))
     return refuse();
-  if (ret_cap != (int32_t)ret_cap || vague_cap != (int32_t)vague_cap) return refuse();
   int32_t rc;
   Py_BEGIN_ALLOW_THREADS
   rc = f_attend(d, q, kr, vr, rp, (int32_t)ret_cap, sk, sv, vp, nv, (int32_t)vague_cap, out, sc, n_cap, ws, (size_t)wb,

@@ -192,3 +192,20 @@ def test_every_argument_by_both_routes(routes, dt):
             for b in bad:
                 c, py = routes(name, d, *args[:k], b, *args[k + 1:])
                 assert c == py, (name, k, b if not isinstance(b, Fake) else (b._dtype, b._n))
+
+
+def test_sizes_whose_products_wrap(routes):
+    """Counts and descriptors whose products leave 64 bits (some come back as 0): refused as by the Python checks."""
+    d, step, att = call(torch.bfloat16)
+    for name, args, counts in (("kvr_step_update", step, (6, 8, 14, 17)), ("kvr_attend_decode", att, (4, 9, 12))):
+        for k in counts:
+            for n in (1 << 31, 1 << 54, 1 << 57, 1 << 61, 1 << 62, (1 << 63) - 1, 1 << 64):
+                c, py = routes(name, d, *args[:k], n, *args[k + 1:])
+                assert c == py and c[0] is ValueError, (name, k, n, c, py)
+        for fields in (dict(batch=1 << 30, n_kv_heads=1 << 30), dict(w=1 << 30, head_dim=1 << 30), dict(r=1 << 28, w=1 << 28),
+                       dict(batch=1 << 30, n_q_heads=1 << 30), dict(head_dim=1 << 30)):
+            x = kvr.kvr_desc.from_buffer_copy(bytes(d))
+            for f, v in fields.items():
+                setattr(x, f, v)
+            c, py = routes(name, x, *args)
+            assert c == py and c[0] is ValueError, (name, fields, c, py)
