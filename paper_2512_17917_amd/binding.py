@@ -7,12 +7,14 @@ pointers, checks dtype / device / contiguity / minimum size, and passes
 There is no fallback: if the library is missing, loading raises.
 
 The two calls of a decode step (`kvr_step_update`, `kvr_attend_decode`) are
-checked and made by `_kvr_fast.so` (csrc/kvr_fast.c) where every argument is as
-it should be; anything else comes back to the checks here, which raise.
+checked and made by the extension `_kvr_fast` (csrc/kvr_fast.c), where it was built
+and every argument is as it should be; anything else comes back to the checks here,
+which raise.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
 import importlib.util
 import os
 
@@ -33,7 +35,8 @@ _ERR_NAMES = {-1: "KVR_ERR_INVALID_ARG", -2: "KVR_ERR_UNSUPPORTED",
               -3: "KVR_ERR_WORKSPACE_TOO_SMALL", -4: "KVR_ERR_HIP"}
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libkvr.so")
-FAST_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_kvr_fast.so")
+# named for the interpreter it was built for; another one's is not looked at
+FAST_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_kvr_fast" + importlib.machinery.EXTENSION_SUFFIXES[0])
 
 EXPORTS = ["kvr_version", "kvr_last_hip_error", "kvr_recent_size", "kvr_hash_params_from_seed", "kvr_hash_host",
            "kvr_workspace_size", "kvr_append", "kvr_select", "kvr_encode", "kvr_compact", "kvr_step_update",
@@ -172,7 +175,7 @@ def lib() -> C.CDLL:
 
 
 def _load_fast(L):
-    """The two calls of a decode step make some thirty tensor checks, 0.75 us each in Python; _kvr_fast.so makes the same
+    """The two calls of a decode step make some thirty tensor checks, 0.75 us each in Python; _kvr_fast makes the same
     checks in C and hands back None where one fails, so that the Python code below says what is wrong."""
     global _fast
     if os.path.exists(FAST_PATH):

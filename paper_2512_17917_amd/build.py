@@ -1,10 +1,13 @@
 """Compile the HIP sources in csrc/ into paper_2512_17917_amd/libkvr.so for gfx950.
 
 hipcc cross-compiles without a GPU.  Objects go to paper_2512_17917_amd/_build/.
+The host extension of the binding (csrc/kvr_fast.c) is built beside it where there is
+a C compiler and Python.h; without it the binding makes the same calls through ctypes.
 Usage: python -m paper_2512_17917_amd.build
 """
 from __future__ import annotations
 
+import importlib.machinery
 import os
 import subprocess
 import sys
@@ -15,7 +18,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libkvr.so")
 OBJ_DIR = os.path.join(HERE, "_build")
-FAST = os.path.join(HERE, "_kvr_fast.so")          # host code: the two calls of a decode step, checked and made in C
+# host code: the two calls of a decode step, checked and made in C; the suffix names the interpreter it is built for
+FAST = os.path.join(HERE, "_kvr_fast" + importlib.machinery.EXTENSION_SUFFIXES[0])
+CC = "gcc"
 
 SOURCES = ["kvr_api.hip", "kvr_reconstruct.hip", "kvr_attend.hip", "kvr_attend_staged.hip", "kvr_attend_staged64.hip", "kvr_attend_staged16.hip", "kvr_attend_retained.hip", "kvr_select.hip", "kvr_compact.hip",
            "kvr_encode.hip", "kvr_swap.hip", "kvr_attend_multi.hip", "kvr_attend_multi_staged.hip"]
@@ -38,7 +43,7 @@ def _run(cmd):
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         sys.stderr.write(" ".join(cmd) + "\n" + r.stdout + r.stderr)
-        raise RuntimeError("hipcc failed: " + cmd[-1])
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed: " + cmd[-1])
     return r
 
 
@@ -54,8 +59,20 @@ def build(verbose: bool = False) -> str:
             if verbose and r.stderr:
                 sys.stderr.write(r.stderr)
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", OUT, *[j[0] for j in jobs]])
-    _run(["gcc", "-O2", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], "-o", FAST, os.path.join(CSRC, "kvr_fast.c")])
+    build_fast()
     return OUT
+
+
+def build_fast() -> bool:
+    """The binding's host extension, or a message and none (nor one from before, made from other sources)."""
+    if os.path.exists(FAST):
+        os.remove(FAST)
+    try:
+        _run([CC, "-O2", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], "-o", FAST, os.path.join(CSRC, "kvr_fast.c")])
+    except (OSError, RuntimeError) as e:
+        sys.stderr.write(f"{os.path.basename(FAST)} left out ({e}): the binding checks and calls through ctypes\n")
+        return False
+    return True
 
 
 if __name__ == "__main__":

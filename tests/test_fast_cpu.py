@@ -2,12 +2,15 @@
 both routes raise the same errors.  On the CPU: objects that answer like device tensors, and a library whose entry points
 only record their arguments."""
 import ctypes as C
+import os
+import shutil
 import types
 
 import pytest
 import torch
 
 from paper_2512_17917_amd import binding as kvr
+from paper_2512_17917_amd import build as B
 
 P, I, L = C.c_void_p, C.c_int32, C.c_int64
 
@@ -38,6 +41,8 @@ class Fake(torch.Tensor):
 
 @pytest.fixture()
 def fast():
+    if not os.path.exists(B.FAST):
+        pytest.skip("the extension was left out of the build")
     kvr.lib()
     m, got = kvr._fast, []
     assert m is not None
@@ -209,3 +214,28 @@ def test_sizes_whose_products_wrap(routes):
                 setattr(x, f, v)
             c, py = routes(name, x, *args)
             assert c == py and c[0] is ValueError, (name, fields, c, py)
+
+
+# --- the build ----------------------------------------------------------------------------------------------------------
+def test_build_leaves_the_extension_out(tmp_path, monkeypatch, capsys):
+    """Without a compiler or Python.h: a message, no extension (nor a stale one), and a binding that calls through ctypes."""
+    name = os.path.basename(B.FAST)
+    assert B.FAST == kvr.FAST_PATH and name.startswith("_kvr_fast.") and name.count(".") == 2        # _kvr_fast.<interpreter>.so
+    monkeypatch.setattr(B, "FAST", str(tmp_path / name))
+    none = tmp_path / "empty"
+    none.mkdir()
+    for cc, include in ((str(tmp_path / "no-such-compiler"), None), ("gcc", str(none))):
+        open(B.FAST, "w").write("from before")
+        with monkeypatch.context() as p:
+            p.setattr(B, "CC", cc)
+            if include:
+                p.setattr(B.sysconfig, "get_paths", lambda: {"include": include})
+            assert B.build_fast() is False
+        assert not os.path.exists(B.FAST) and "left out" in capsys.readouterr().err
+    (tmp_path / "_kvr_fast.so").write_text("another interpreter's")
+    monkeypatch.setattr(kvr, "FAST_PATH", B.FAST)
+    monkeypatch.setattr(kvr, "_fast", None)
+    kvr._load_fast(kvr.lib())
+    assert kvr._fast is None
+    if shutil.which(B.CC) and os.path.exists(os.path.join(B.sysconfig.get_paths()["include"], "Python.h")):
+        assert B.build_fast() is True and os.path.exists(B.FAST)
