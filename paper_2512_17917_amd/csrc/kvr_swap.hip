@@ -13,11 +13,11 @@
 // distinct.  V.Max is the largest key of the Vague index list, C.Min the smallest
 // key of the retained slots outside the Recent window.
 //
-// One scan serves many rounds.  The keys are loaded once (REG: into registers, up
-// to 26 Vague tokens and 8 slots per thread; otherwise they are re-read from
-// memory), and the m = min(max_swaps, 16) largest Vague keys and m smallest
-// Candidate keys are extracted by m workgroup-wide reductions into two sorted
-// lists in LDS.  A swap pops both heads and inserts each token's key into the
+// One scan serves many rounds.  It leaves the m = min(max_swaps, 16) largest Vague
+// keys and m smallest Candidate keys in two sorted lists in LDS.  REG: up to 26
+// Vague tokens and 8 slots per thread, keys loaded once into registers, and both
+// lists by one floor each in three barriers; longer parts: m workgroup-wide
+// reductions, keys read again from memory.  A swap pops both heads and inserts each token's key into the
 // other list; since a round removes only the head, the head of a list stays the
 // true extreme of its part for m rounds (the j-th extreme of the scanned part is
 // in the list for j <= m, and every key that entered the part since is in it
@@ -30,7 +30,7 @@
 // (one sum, one rounding, if both fall into the same slot of a row: delete first,
 // then insert), and stores the estimate into the Candidate's slot.  A channel is
 // only ever touched by its own thread, so no barrier is needed between the query
-// and the update.  Thread 0 exchanges the two positions in ret_pos / vague_pos.
+// and the update.  Thread 2 D exchanges the two positions in ret_pos / vague_pos.
 //
 // Bound by memory round trips.  All swaps of a scan are decided before the first is carried out, so the values of four
 // swaps are requested together; a value that an earlier one of the four has just written (the same slot of a sketch row, the
@@ -375,8 +375,8 @@ __global__ __launch_bounds__(SWP_THREADS) void swap_back_kernel(
     else swap_build_lists_long(sh, vp, rp, sc, nv, ret_cap, recent_from, n_cap, m);
 
     // ---- up to m swaps on the lists.  Which tokens change places depends on scores and
-    //      positions only, not on sketch contents: thread 0 decides all swaps of this scan
-    //      first and leaves the pairs in LDS, then the channel threads carry them out one
+    //      positions only, not on sketch contents: the first wave decides all swaps of this
+    //      scan first and leaves the pairs in LDS, then the channel threads carry them out one
     //      after the other without a barrier in between (a later swap that touches a slot
     //      or a retained row of an earlier one is ordered by the thread's own program
     //      order: a channel is only ever touched by its own thread). -------------------------
