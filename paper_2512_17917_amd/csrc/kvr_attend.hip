@@ -118,7 +118,7 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
   p.off_part_ml = off;
   off = align_up(off + (size_t)units * p.n_slices * d.G * 2 * sizeof(float), 256);
   p.off_logits = off;
-  off = align_up(off + (size_t)units * (size_t)tot_cap * d.G * sizeof(float), 256);
+  off = align_up(off + (size_t)units * (size_t)(p.streamed ? ret_cap : tot_cap) * d.G * sizeof(float), 256);
   p.off_rec = p.off_tiles = off;
   if (p.streamed) {
     const size_t tokens = multi_staged_scratch_tokens(units, vague_cap);
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(256, (G <= 2 ? 8 : G <= 4 ? 7 : G == 8 ? 5 : 4)) vo
   //      side by side instead of one after the other.  Four tokens per thread. ----
   constexpr int U = 4;
   const bool do_scores = a.scores != nullptr;
-  const int tot_cap = a.ret_cap + a.vague_cap;
+  const int logit_rows = TILES ? a.ret_cap : a.ret_cap + a.vague_cap;      // of a unit
   int total = 0;
   int pos[U];
   float x[U][G], old[U];
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(256, (G <= 2 ? 8 : G <= 4 ? 7 : G == 8 ? 5 : 4)) vo
 #pragma unroll
         for (int g = 0; g < G; ++g) x[u][g] = -__builtin_inff();
         if (t < total) {
-          const float* lg = a.logits + ((size_t)unit * tot_cap + t) * G;
+          const float* lg = a.logits + ((size_t)unit * logit_rows + t) * G;
           if constexpr (G % 4 == 0) {
 #pragma unroll
             for (int g4 = 0; g4 < G; g4 += 4) {
@@ -607,7 +607,9 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
       }
     }
   } else if (plan.mfma_retained) {
-    e = launch_attend_retained(d, a, plan.n_rslices, 0, 0, st);
+    AttendArgs ar = a;
+    if (plan.streamed) ar.vague_cap = 0;       // the list's logits lie by tile: the others have rows for the retained slots only
+    e = launch_attend_retained(d, ar, plan.n_rslices, 0, 0, st);
   } else {
     a.tok_limit = plan.staged ? a.ret_cap : a.ret_cap + a.vague_cap;
     dim3 grid(plan.n_rslices, units);

@@ -297,7 +297,7 @@ MultiPlan attend_multi_plan(const DevDesc& d, int n_q, long long ret_cap, long l
   p.off_part_ml = off;
   off = align_up_m(off + (size_t)units * p.n_slices * ncol * 2 * sizeof(float), 256);
   p.off_logits = off;
-  off = align_up_m(off + (size_t)units * (size_t)(ret_cap + vague_cap) * ncol * sizeof(float), 256);
+  off = align_up_m(off + (size_t)units * (size_t)(p.staged ? ret_cap : ret_cap + vague_cap) * ncol * sizeof(float), 256);
   p.total_bytes = off;
   return p;
 }
@@ -322,7 +322,7 @@ static hipError_t launch_multi_n(const DevDesc& d, const AttendArgs& a0, const i
   da.n_ctx = n_ctx;
   da.n_q = n_q;
   da.n_slices = plan.n_slices;
-  da.tot_cap = a0.ret_cap + a0.vague_cap;
+  da.tot_cap = plan.staged ? a0.ret_cap : a0.ret_cap + a0.vague_cap;      // staged: the list's logits lie by tile
   da.part_o = (float*)(base + plan.off_part_o);
   da.part_ml = (float*)(base + plan.off_part_ml);
   da.logits = a0.scores ? (float*)(base + plan.off_logits) : nullptr;

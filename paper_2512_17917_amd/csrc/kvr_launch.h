@@ -47,7 +47,7 @@ struct AttendArgs {
   // workspace carve-up
   float* part_o;     // [units, n_slices, G, D]
   float* part_ml;    // [units, n_slices, G, 2]
-  float* logits;     // [units, ret_cap + vague_cap, G] or nullptr when scores == nullptr
+  float* logits;     // [units, ret_cap + vague_cap, G] (tiles: [units, ret_cap, G]) or nullptr when scores == nullptr
   void* scratch_rec; // streaming kernel: token records
   float* tiles;      // and the logits of its tokens, by tile, which the merge kernel reads there (null: no streaming kernel)
   int n_slices;      // partial results per unit (all kinds)

@@ -86,3 +86,28 @@ def test_channels_per_phase(plan, G, r, edges):
         assert p[4] == ch and p[1] <= 160 * 1024, (w, p)
         if ch and r * w > 4096:
             assert p[1] == -(-r * w * ch * 2 // 1024) * 1024 + 2 * 32 * G * 4 + G * 256
+
+
+@pytest.mark.parametrize("batch,ret_cap,vague_cap", [(1, 187, 64), (5, 4104, 12307), (8, 7374, 25395)])
+def test_workspace_of_a_streamed_list(batch, ret_cap, vague_cap):
+    """The streaming kernel's logits lie by tile and nowhere else: a listed token takes a record and one float per column (in
+    kvr_attend_multi within its two rebuilt rows), a retained slot one float per column, and the rest are partial results."""
+    import ctypes as C
+
+    from paper_2512_17917_amd import binding as kvr
+    units, areas = batch * 8, 6 * 256
+    partials = lambda col, total: total % (units * col * 130 * 4) if total > 0 else -1           # [slices, col, 128 + 2] floats a unit
+    list4 = (vague_cap + 3) // 4 * 4
+    for heads, n_q in ((8, 0), (4, 4), (2, 2)):
+        d = kvr.make_desc(batch, 8 * heads, 8, 3, 60, kvr.KVR_BF16, seed=1)
+        col = heads * max(n_q, 1)
+        if n_q:
+            size = kvr.kvr_attend_multi_workspace_size(d, n_q, ret_cap, vague_cap)
+            fixed = units * (2 * vague_cap * 256 + ret_cap * col * 4)
+        else:
+            size = kvr.kvr_workspace_size(d, kvr.KVR_OP_ATTEND, ret_cap, vague_cap)
+            fixed = units * (list4 * (4 + col * 4) + ret_cap * col * 4)
+        left = size - fixed                                    # whole partials and what the areas are rounded up by
+        assert 0 < left and partials(col, left) <= areas, (heads, n_q, size, fixed)
+        slices = left // (units * col * 130 * 4)
+        assert slices <= -(-1536 // units) + 256 // units + 1 + (ret_cap + 127) // 128, slices
