@@ -47,8 +47,8 @@ OFFLINE_COUNTERS = {
                         "attention kernels to the score pass, the slice partials and whole lines pulled by "
                         "4-byte score accesses",
         "alu": {"file": "profiles/attend_kernels_c4_sq_counters.txt", "kernel": "attend_vague_staged64_kernel<4>",
-                "valu_insts_per_launch": 59849088.0, "waves_per_launch": 10240,
-                "valu_busy": 0.71, "lds_busy": 0.45, "lds_bank_conflict_share": 0.47},
+                "valu_insts_per_launch": 59644800.0, "waves_per_launch": 10240,
+                "valu_busy": 0.70, "lds_busy": 0.45, "lds_bank_conflict_share": 0.47},
     },
 }
 # plain vector ALU peak: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz lane-operations per second (the 157.3 TFLOP/s
