@@ -36,6 +36,55 @@ static int slice_tokens_for(long long tokens, long long units) {
 
 int attend_slice_tokens(long long tokens, long long units) { return slice_tokens_for(tokens, units); }
 
+// The 64-channel kernel's launch: n_vslices workgroups per unit over the Vague list and n_ret_wgs workgroups over the
+// retained slots, at most `most` slices of both kinds per unit (what callers' workspaces hold).  A workgroup of either kind
+// has a CU to itself (its registers fill the SIMDs) and a unit's workgroups share an XCD of 32 CUs, so the launch takes
+// turns * (time of a list workgroup) on the CUs that the retained slots leave.  In us: a list workgroup takes 11.5 at 273
+// slots per row, 7 at six, and 5 per round of 64 tokens a wave (one head 3.5), at 25 rounds as at two; a CU streams
+// 35 .. 40 KB of retained rows per us whatever its waves have in flight, and a slice ends with 2 us of merging.
+// Before, retained slots and list were launches of their own, one behind the other or on two streams, with at most 6 rounds
+// a wave; both, us from the first start to the last end of a call: 8 units of 25395 + 7374 tokens 42.1 -> 32.6 (25 list
+// workgroups per unit, 56 for the slots; 16 and 128: 38), 32 units 104.5 -> 70 (6 and 64; 5 and 96: 73, 8 and none: 80 with
+// every list workgroup taking a slice along), 128 units 311 (on two streams 258 .. 284) -> 230 .. 255 (3 and 64), 64 units of
+// 1862 + 187 33.4 -> 27.4, 96 units of 3753 + 1128, one head 45.2 -> 36.0.
+static void plan_pair64(AttendPlan& p, const DevDesc& d, int units, int ret_cap, int vague_cap, int most) {
+  constexpr double RATE = 38e3, SLICE = 2.0, CHIP = 5.0e6;
+  const double fixed = 6.5 + 0.018 * d.w, round = 3.0 + 0.5 * d.G;
+  const int wr = (vague_cap + 63) / 64, units8 = (units + 7) / 8, tiles = (ret_cap + 15) / 16;
+  const double bytes = 512.0 * units * ret_cap;
+  // largest slice, in tiles (LDS holds its logits)
+  const int most_tiles = (STAGED_LDS_LIMIT - ret_stream_lds(d.G, 0)) / (64 * d.G) / 8 * 8;
+  const int least = (tiles + most_tiles - 1) / most_tiles;
+  double best = 1e30;
+  int best_n = 1, best_r = 0, last = 0;
+  for (int rho = 1; rho <= STAGED64_KMAX; ++rho) {
+    const int n = (wr + 8 * rho - 1) / (8 * rho);
+    if (n == last) continue;
+    last = n;
+    if (n + least > most && rho < STAGED64_KMAX) continue;
+    const double wg = fixed + round * ((wr + 8 * n - 1) / (8 * n));
+    const int per_xcd = units8 * n, turns = (per_xcd + 31) / 32;
+    for (int k = turns; k <= turns + 2; ++k) {
+      const int r = ret_cap > 0 ? 8 * (32 - (per_xcd + k - 1) / k) : 0;
+      if (ret_cap > 0 && r <= 0) continue;
+      const double t = std::max(k * wg, ret_cap > 0 ? SLICE + std::max(bytes / (RATE * r), bytes / CHIP) : 0.0);
+      if (t < best - 1e-9) { best = t; best_n = n; best_r = r; }
+    }
+  }
+  p.n_vslices = best_n;
+  // slices of the retained slots: a number that spreads evenly over the workgroups
+  int slices = 1;
+  double best_c = 1e30;
+  for (int s = std::max(least, 1), end = std::max(std::min({tiles, s + 31, most - best_n}), s); s <= end && best_r > 0; ++s) {
+    const double c = (double)((units * s + best_r - 1) / best_r) * ((double)((tiles + s - 1) / s) * 8192.0 / RATE + SLICE);
+    if (c < best_c - 1e-9) { best_c = c; slices = s; }
+  }
+  p.rslice_tokens = tiles > 0 ? (tiles + slices - 1) / slices * 16 : 16;
+  p.n_rslices = (ret_cap + p.rslice_tokens - 1) / p.rslice_tokens;
+  p.n_ret_wgs = std::min(best_r, (units * p.n_rslices + 7) / 8 * 8);
+  p.pair_lds = std::max(p.lds_bytes, ret_cap > 0 ? ret_stream_lds(d.G, p.rslice_tokens) : 0);
+}
+
 AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long vague_cap) {
   AttendPlan p;
   const long long units = (long long)d.B * d.Hkv;
@@ -44,6 +93,7 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
   p.n_vslices = 0;
   p.ch = 0;
   p.lds_bytes = 0;
+  p.n_ret_wgs = p.pair_lds = 0;
   // staged kernel: bf16, the paper's sign setting, G <= 4, r = 3 or 4, bucket fits 15 bits
   if (dtype == KVR_BF16 && d.sign_mask == 2 && d.G <= 4 && (d.r == 3 || d.r == 4) && d.w <= 32768 &&
       vague_cap >= 64) {
@@ -100,6 +150,8 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
     if (p.streamed) {
       p.vslice_tokens = multi_staged_part_tokens(vague_cap, units);
       p.n_vslices = (int)((vague_cap + p.vslice_tokens - 1) / p.vslice_tokens);
+    } else if (p.staged && p.ch == 64) {
+      plan_pair64(p, d, (int)units, (int)ret_cap, (int)vague_cap, p.n_rslices + p.n_vslices);
     } else if (!p.staged && vague_cap > 0) {
       p.vslice_tokens = slice_tokens_for(vague_cap, units);
       p.n_vslices = (int)((vague_cap + p.vslice_tokens - 1) / p.vslice_tokens);
@@ -590,8 +642,11 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
   const bool big = (long long)units * plan.n_vslices >= 2ll * cus;
   // And only where a CU holds a workgroup of each.
   const int side_lds = attend_side_lds(d, plan);
-  const bool side = sd.stream != nullptr && big && side_lds > 0;
-  if (side) {
+  const bool pair = plan.staged && plan.ch == 64;
+  const bool side = !pair && sd.stream != nullptr && big && side_lds > 0;
+  if (pair) {
+    e = launch_attend_pair64(d, a, plan, st);
+  } else if (side) {
     e = hipEventRecord(sd.fork, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(sd.stream, sd.fork, 0);
     if (e == hipSuccess) {
@@ -618,7 +673,7 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
     e = hipGetLastError();
   }
   // 2. the Vague list
-  if (side) {
+  if (side || pair) {
     // already launched above
   } else if (e == hipSuccess && plan.staged) {
     e = launch_attend_vague_staged(d, a, plan, st);

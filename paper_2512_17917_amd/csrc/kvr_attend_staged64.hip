@@ -17,9 +17,32 @@
 //  * Copies overlap: the first K chunk is fetched while the hashes are
 //    computed, the first V chunk during the softmax, the second V chunk during
 //    the reduction of the first (which has LDS scratch of its own).
-#include "kvr_staged.h"
+//  * A wave takes up to 25 rounds of 64 tokens, five registers each (a one-dword record, four logits that become the packed
+//    weights), in straight-line code that it leaves by one jump behind its last round.  What a workgroup costs besides its
+//    rounds (chunk copies, statistics, reductions: two to three rounds' worth) is paid less often: 128 units of 25395 tokens,
+//    the list alone, 10 workgroups per unit of 5 rounds 176 us, 4 of 13 rounds 153, 2 of 25 rounds 143; 32 units 60 -> 49.5.
+//  * The same launch holds workgroups that stream the retained slots (kvr_ret_stream.h) on CUs of their own.  Bound by
+//    vector issue on the list's CUs (995 vector and 128 matrix instructions a round) and by the latency of memory on the others.
+#include "kvr_ret_stream.h"
+
+#include <type_traits>
 
 namespace kvr {
+
+constexpr int S64_KMAX = STAGED64_KMAX;   // wave-rounds (64 tokens) per wave
+
+// f(0), f(1), .. of the n rounds a wave has, as straight-line code with constant round numbers (what a round keeps lives
+// in registers).  n is uniform over the wave; the rounds it does not have are one jump: skipping them one by one
+// walks through as many instruction-cache misses.
+template <int N, int K = 0, typename F>
+__device__ __forceinline__ void for_rounds(int n, F&& f) {
+  if constexpr (K < N) {
+    if (K < n) {
+      f(std::integral_constant<int, K>{});
+      for_rounds<N, K + 1>(n, f);
+    }
+  }
+}
 
 struct Rows3 {
   uint4 r0, r1, r2;
@@ -61,12 +84,15 @@ __device__ __forceinline__ float xchg4(float x) {
 // agree; that majority sign is folded into the token's softmax weight, and the
 // row with the other sign (if there is one) is listed last, so that only one row
 // ever has to be flipped.
-__device__ __forceinline__ void rec_offsets(uint2 rec, int base, int (&rb)[3]) {
-  rb[0] = (int)(rec.x & 0x1ff80u) + base;
-  rb[1] = (int)(__builtin_amdgcn_ubfe(rec.x, 17, 10) << 7) + base;
-  rb[2] = (int)(rec.y & 0x1ff80u) + base;
+__device__ __forceinline__ void rec_offsets(uint32_t rec, int (&rb)[3]) {
+  rb[0] = (int)(rec & 0x1ff80u);
+  rb[1] = (int)((rec >> 10) & 0x1ff80u);
+  rb[2] = (int)(__builtin_amdgcn_alignbit(rec, rec, 20) & 0x1ff80u);
 }
-__device__ __forceinline__ uint32_t rec_flip2(uint2 rec) { return (uint32_t)((int)rec.y >> 31) & 0x80008000u; }
+__device__ __forceinline__ uint32_t rec_flip2(uint32_t rec) {
+  return (uint32_t)__builtin_amdgcn_sbfe(rec, 6, 1) & 0x80008000u;
+}
+__device__ __forceinline__ uint32_t rec_sign(uint32_t rec) { return (rec << 26) & 0x80000000u; }
 
 // V phases: the rows of one piece of token J of the quad, plus the mask that
 // flips the last row relative to the other two
@@ -83,9 +109,9 @@ struct VOwn {
   int o0, o1, o2;
   uint32_t fm;
 };
-__device__ __forceinline__ VOwn v_own(uint2 rec) {
+__device__ __forceinline__ VOwn v_own(uint32_t rec) {
   int rb[3];
-  rec_offsets(rec, 0, rb);
+  rec_offsets(rec, rb);
   return VOwn{rb[0], rb[1], rb[2], rec_flip2(rec)};
 }
 
@@ -134,8 +160,8 @@ __device__ __forceinline__ void pv_piece(const uint4 (&med)[4], short4_t a_hi, s
 // The same value, but the compiler can no longer tell: whatever is derived from
 // it is computed where it is used instead of once per kernel and kept in
 // registers through all phases (the row offsets of every round would be).
-__device__ __forceinline__ uint2 opaque(uint2 v) {
-  asm volatile("" : "+v"(v.x), "+v"(v.y));
+__device__ __forceinline__ uint32_t opaque(uint32_t v) {
+  asm volatile("" : "+v"(v));
   return v;
 }
 // same for a wave-uniform integer: addresses built from it are formed where they
@@ -178,34 +204,35 @@ __device__ __forceinline__ void take_turn(int t) {
 //
 // qx[j]: q of head (lane mod 4) for the piece that the block's first pair reads
 // at step j; the second pair reads the piece one further, i.e. qx[(j + 1) mod 8].
-template <int NK, int G>
-__device__ __forceinline__ void k_pass(const unsigned char* s_sk, const uint2 (&info)[ST_KMAX],
+template <int G>
+__device__ __forceinline__ void k_pass(const unsigned char* s_sk, const uint32_t (&info)[S64_KMAX], int n_k,
                                        const uint4 (&qx)[8], const int (&co)[8], bool second_pair,
-                                       int turn, float (&s)[ST_KMAX][G]) {
+                                       int turn, float (&s)[S64_KMAX][G]) {
   // Three-stage pipeline over the steps t = 8 k + j of all rounds: at step t the
   // rows of step t + 3 are requested, the medians of step t + 1 are formed, and
   // the matrix instructions of step t run on medians formed one step earlier.
+  // (Behind the last round it reads rows that a zero record names, and drops them.)
   Rows3 buf[3];                          // rows of step t live in buf[t % 3]
   int rb[3];
-  rec_offsets(opaque(info[0]), 0, rb);
+  rec_offsets(opaque(info[0]), rb);
   load_rows3(buf[0], s_sk, rb, co[0]);
   load_rows3(buf[1], s_sk, rb, co[1]);
   load_rows3(buf[2], s_sk, rb, co[2]);
   uint4 m[2];                            // medians of step t in m[t % 2]
   m[0] = median3(buf[0]);
-#pragma unroll
-  for (int k = 0; k < NK; ++k) {
-    int rn[3] = {0, 0, 0};
-    if (k + 1 < NK) rec_offsets(opaque(info[k + 1]), 0, rn);
+  for_rounds<S64_KMAX>(n_k, [&](auto kc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc)::value;
+    int rn[3];
+    rec_offsets(opaque(info[k + 1 < S64_KMAX ? k + 1 : k]), rn);
     f32x4_t ax = {0.f, 0.f, 0.f, 0.f}, ay = {0.f, 0.f, 0.f, 0.f};
     take_turn(k + turn);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int t = 8 * k + j;
       if (j < 5) load_rows3(buf[(t + 3) % 3], s_sk, rb, co[j + 3]);
-      else if (k + 1 < NK) load_rows3(buf[(t + 3) % 3], s_sk, rn, co[j - 5]);
+      else load_rows3(buf[(t + 3) % 3], s_sk, rn, co[j - 5]);
       KVR_PIN();
-      if (j < 7 || k + 1 < NK) m[(t + 1) & 1] = median3(buf[(t + 1) % 3]);
+      m[(t + 1) & 1] = median3(buf[(t + 1) % 3]);
       KVR_PIN();
       const uint4 mc = m[t & 1];
       const short4_t b_lo = pack_k4(mc.x, mc.y), b_hi = pack_k4(mc.z, mc.w);
@@ -217,23 +244,25 @@ __device__ __forceinline__ void k_pass(const unsigned char* s_sk, const uint2 (&
       KVR_PIN();
     }
 #pragma unroll
-    for (int g = 0; g < G; ++g) s[k][g] += second_pair ? ay[g] : ax[g];
+    for (int g = 0; g < G; ++g) {
+      s[k][g] += second_pair ? ay[g] : ax[g];
+      asm volatile("" : "+v"(s[k][g]));        // formed here, not where it is used next (which would keep both sums)
+    }
     rb[0] = rn[0]; rb[1] = rn[1]; rb[2] = rn[2];
-  }
+  });
   __builtin_amdgcn_s_setprio(1);
 }
 
-// One V pass over NK rounds for the piece at byte offset co of each row: the
+// One V pass over the rounds for the piece at byte offset co of each row: the
 // quad's 4 tokens per round, same pipeline, then the matrix instructions.
-template <int NK>
-__device__ __forceinline__ void v_pass(const unsigned char* s_sk, const uint2 (&info)[ST_KMAX],
-                                       const uint32_t (&W)[ST_KMAX][4], int co, int turn, f32x4_t (&acc)[8]) {
+__device__ __forceinline__ void v_pass(const unsigned char* s_sk, const uint32_t (&info)[S64_KMAX], int n_k,
+                                       const uint32_t (&W)[S64_KMAX][4], int co, int turn, f32x4_t (&acc)[8]) {
   VItem buf[4];
-  VOwn own = v_own(info[0]);
+  VOwn own = v_own(opaque(info[0]));
   v_fetch<0>(buf[0], own, s_sk, co);
   v_fetch<1>(buf[1], own, s_sk, co);
-#pragma unroll
-  for (int k = 0; k < NK; ++k) {
+  for_rounds<S64_KMAX>(n_k, [&](auto kc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc)::value;
     uint4 med[4];
     take_turn(k + turn);
     v_fetch<2>(buf[2], own, s_sk, co);
@@ -241,55 +270,29 @@ __device__ __forceinline__ void v_pass(const unsigned char* s_sk, const uint2 (&
     med[0] = v_median(buf[0]);
     KVR_PIN();
     v_fetch<3>(buf[3], own, s_sk, co);
-    if (k + 1 < NK) own = v_own(info[k + 1]);
+    own = v_own(opaque(info[k + 1 < S64_KMAX ? k + 1 : k]));
     KVR_PIN();
     med[1] = v_median(buf[1]);
     KVR_PIN();
-    if (k + 1 < NK) v_fetch<0>(buf[0], own, s_sk, co);
+    v_fetch<0>(buf[0], own, s_sk, co);
     KVR_PIN();
     med[2] = v_median(buf[2]);
     KVR_PIN();
-    if (k + 1 < NK) v_fetch<1>(buf[1], own, s_sk, co);
+    v_fetch<1>(buf[1], own, s_sk, co);
     KVR_PIN();
     med[3] = v_median(buf[3]);
     pv_piece(med, pack_k4(W[k][0], W[k][1]), pack_k4(W[k][2], W[k][3]), acc);
     KVR_PIN();
-  }
+  });
   __builtin_amdgcn_s_setprio(1);
 }
 
-// the round count is uniform over a wave: one scalar branch into straight-line code
-#define KVR_DISPATCH_NK(n, CALL) \
-  switch (n) {                   \
-    case 1: { constexpr int NK = 1; CALL; } break; \
-    case 2: { constexpr int NK = 2; CALL; } break; \
-    case 3: { constexpr int NK = 3; CALL; } break; \
-    case 4: { constexpr int NK = 4; CALL; } break; \
-    case 5: { constexpr int NK = 5; CALL; } break; \
-    case 6: { constexpr int NK = 6; CALL; } break; \
-    default: break;              \
-  }
-static_assert(ST_KMAX == 6, "KVR_DISPATCH_NK covers 1..6 rounds");
-
+// One workgroup's share (part vs of a.n_vslices) of a unit's Vague list.
 template <int G>
-// Register cap: 192 per lane (the attribute counts in units of two on this target).  Two
-// waves of this kernel and one wave of the retained-slot kernel in its 128-register form
-// then fill a SIMD's 512 registers exactly, which is what lets the two kernels run side by
-// side on a CU.
-__global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) void attend_vague_staged64_kernel(
-    DevDesc d, AttendArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int R = 3, CH = 64, NC = 8, ROWB = 128, ROWB_LOG2 = 7, NPH = D / CH, KMAX = ST_KMAX;
+__device__ __forceinline__ void vague64_part(const DevDesc& d, const AttendArgs& a, int unit, int vs,
+                                             unsigned char* smem) {
+  constexpr int R = 3, CH = 64, NC = 8, ROWB = 128, NPH = D / CH, KMAX = S64_KMAX;
   constexpr int NROW = ST_WAVES * 4;         // 16-lane rows per workgroup
-
-  // XCD-aware mapping: workgroup ids are dealt round-robin to the 8 XCDs, so all
-  // workgroups of a unit get ids that are equal modulo 8 (they share one L2).
-  const int lin = blockIdx.x;
-  const int xcd = lin & 7, jj = lin >> 3;
-  const int unit = (jj / a.n_vslices) * 8 + xcd;
-  const int vs = jj % a.n_vslices;
-  const int units = d.B * d.Hkv;
-  if (unit >= units) return;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int b = unit / d.Hkv, hk = unit % d.Hkv;
@@ -320,11 +323,11 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
   //      chunks' lines are in L2 when their turn comes) ----------------------------
   int Jv[KMAX];
   const int32_t* vpos = a.vague_pos + (size_t)unit * a.vague_cap;
-#pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
+  for_rounds<S64_KMAX>(n_k, [&](auto kc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc)::value;
     const int tok = (gw + k * NWT) * 64 + lane;
-    Jv[k] = (k < n_k && tok < nv) ? vpos[tok] : -1;
-  }
+    Jv[k] = vpos[min(tok, nv - 1)];        // (a choice made here would wait for the load, round by round)
+  });
   uint4 qv = make_uint4(0u, 0u, 0u, 0u);
   if (tid < G * 16)
     qv = reinterpret_cast<const uint4*>((const bf16_t*)a.q + ((size_t)b * d.Hq + (size_t)hk * G) * D)[tid];
@@ -348,19 +351,19 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
   stage_issue<NC, ROWB>(skg, s_sk, n_pieces, 0, tid);
 
   // ---- hash every token once (kept in registers); q to LDS -------------------
-  uint2 info[KMAX];
+  uint32_t info[KMAX];
   uint32_t vmask = 0;
 #pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
+  for (int k = 0; k < KMAX; ++k) info[k] = 0u;
+  for_rounds<S64_KMAX>(n_k, [&](auto kc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc)::value;
     const int J = Jv[k];
-    uint2 pk = make_uint2(0u, 0u);
-    if (J >= 0) {
-      // token record (2 dwords), laid out so that every field is one or two
-      // instructions away from its use: LDS row indices (< 1024 here) sit at
-      // bit 7 (first listed row: x[7..16], third: y[7..16]) or at bit 17 (second:
-      // x[17..26]); bit 0 of x is the majority sign of g_0, g_1, g_2 (1 = minus),
-      // bit 31 of y says whether the third listed row has the other sign.  The
-      // row whose sign differs from the other two, if any, is listed third.
+    uint32_t pk = 0u;
+    if (J >= 0 && (gw + k * NWT) * 64 + lane < nv) {
+      // Token record: the LDS row indices (< 1024 here) of the first listed row at bits 7..16, of the second at 17..26,
+      // of the third at 27..31 and 0..4 (seven below its place after a rotation by 20), each one or two instructions
+      // from a byte offset; bit 5 is the majority sign of g_0, g_1, g_2 (1 = minus), bit 6 says whether the third
+      // listed row has the other sign.  The row whose sign differs from the other two, if any, is listed third.
       const uint32_t r0 = (uint32_t)bucket_of(d, 0, J), r1 = (uint32_t)(w + bucket_of(d, 1, J)),
                      r2 = (uint32_t)(2 * w + bucket_of(d, 2, J));
       const uint32_t s0 = sign_neg(d, 0, J) ? 1u : 0u, s1 = sign_neg(d, 1, J) ? 1u : 0u,
@@ -372,11 +375,11 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
       const uint32_t rbk = odd1 ? r2 : r1;                   // second listed
       const uint32_t rc = odd0 ? r0 : (odd1 ? r1 : r2);      // third listed
       const uint32_t flip = (s0 ^ s1) | (s0 ^ s2);           // 1 iff the signs are not all equal
-      pk = make_uint2((ra << 7) | (rbk << 17) | maj, (rc << 7) | (flip << 31));
+      pk = (ra << 7) | (rbk << 17) | (rc << 27) | (rc >> 5) | (maj << 5) | (flip << 6);
       vmask |= 1u << k;
     }
     info[k] = pk;
-  }
+  });
   asm volatile("" ::"v"(touched));       // the touch load has no other use: keep it
   if (tid < G * 16) s_q[tid] = qv;
   stage_wait();
@@ -406,7 +409,7 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
         qx[j] = (head < G) ? s_q[head * 16 + cc * NC + ((blk2 + j) & 7)] : make_uint4(0u, 0u, 0u, 0u);
       }
       const bool second_pair = (lane & 2) != 0;
-      KVR_DISPATCH_NK(n_k, (k_pass<NK, G>(s_sk, info, qx, co, second_pair, turn, s)))
+      k_pass<G>(s_sk, info, n_k, qx, co, second_pair, turn, s);
     }
   }
 
@@ -421,9 +424,8 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
   float mx[G];
 #pragma unroll
   for (int g = 0; g < G; ++g) mx[g] = -__builtin_inff();
-#pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
-    if (k >= n_k) break;                   // uniform over the wave: rounds it does not have cost nothing
+  for_rounds<S64_KMAX>(n_k, [&](auto kc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc)::value;
     const bool valid = (vmask >> k) & 1u;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -440,7 +442,7 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
         for (int g = 0; g < G; ++g) lg[g] = s[k][g];
       }
     }
-  }
+  });
   // Weights are formed against the wave's own maximum, which needs no barrier; the
   // workgroup's maximum is put together after the barrier that publishes the first
   // V chunk, and each wave's sums are rescaled by exp(own maximum - workgroup
@@ -451,13 +453,12 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
     const float x = rows_max(row_max(mx[g]));
     if (lane == 0) s_stat[g * ST_WAVES + wave] = x;
     lsum[g] = 0.f;
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-      if (k >= n_k) break;
+    for_rounds<S64_KMAX>(n_k, [&](auto kc) __attribute__((always_inline)) {
+      constexpr int k = decltype(kc)::value;
       const float p = (s[k][g] == -__builtin_inff()) ? 0.f : __expf(s[k][g] - x);
       s[k][g] = p;                 // from here on s holds the weights
       lsum[g] += p;
-    }
+    });
   }
 #pragma unroll
   for (int g = 0; g < G; ++g) {
@@ -472,12 +473,10 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
   // in: a 4x4 transpose inside the quad.  Split into bf16 hi + lo (16 mantissa
   // bits together) and packed as the two A operands of a round.
   const int sub = lane & 3, tl = lane >> 2;
-  uint32_t W[KMAX][4];
-#pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
-    W[k][0] = W[k][1] = W[k][2] = W[k][3] = 0u;
-    if (k >= n_k) continue;
-    const uint32_t sgn = info[k].x << 31;
+  uint32_t W[KMAX][4];                     // (of the rounds there are)
+  for_rounds<S64_KMAX>(n_k, [&](auto kc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc)::value;
+    const uint32_t sgn = rec_sign(info[k]);
     float pf[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) pf[g] = __uint_as_float(__float_as_uint(s[k][g]) ^ sgn);
@@ -505,7 +504,7 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
     W[k][1] = pair_hi(hb[2], hb[3]);
     W[k][2] = pair_hi(lb[0], lb[1]);
     W[k][3] = pair_hi(lb[2], lb[3]);
-  }
+  });
 
   // ---- V phases: weighted values ------------------------------------------------
   // the two pieces of this lane: odd quads take them in the opposite order, so
@@ -528,12 +527,16 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
     f32x4_t acc[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    KVR_DISPATCH_NK(n_k, (v_pass<NK>(s_sk, info, W, pa * 16, turn, acc)))
+#pragma unroll 1
+    for (int pass = 0; pass < 2; ++pass) {   // one copy of the code: the rounds of both passes are what the instruction cache holds
+      if (pass > 0) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c)
+        for (int c = 0; c < 8; ++c)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) acc[c][g] = xchg4(acc[c][g]);
-    KVR_DISPATCH_NK(n_k, (v_pass<NK>(s_sk, info, W, pb * 16, turn + 1, acc)))
+          for (int g = 0; g < 4; ++g) acc[c][g] = xchg4(acc[c][g]);
+      }
+      v_pass(s_sk, info, n_k, W, (pass > 0 ? pb : pa) * 16, turn + pass, acc);
+    }
     lds_barrier();                         // every wave is done with this V chunk
     if (cc + 1 < NPH) stage_issue<NC, ROWB>(svg, s_sk, n_pieces, cc + 1, tid);
 
@@ -603,9 +606,27 @@ __global__ __launch_bounds__(ST_THREADS) __attribute__((amdgpu_num_vgpr(96))) vo
   }
 }
 
+// The first n_ret_wgs workgroups walk slices of the retained slots, the others take parts of the Vague lists.
+template <int G>
+__global__ __launch_bounds__(ST_THREADS, 2) void attend_pair64_kernel(DevDesc d, AttendArgs a, int n_ret_wgs) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  if ((int)blockIdx.x < n_ret_wgs) {
+    for (int item = blockIdx.x; item < d.B * d.Hkv * a.n_rslices; item += n_ret_wgs)
+      ret_stream_slice<G>(d, a, item / a.n_rslices, item % a.n_rslices, smem);
+    return;
+  }
+  // XCD-aware mapping: workgroup ids are dealt round-robin to the 8 XCDs, so all
+  // workgroups of a unit get ids that are equal modulo 8 (they share one L2).
+  const int lin = blockIdx.x - n_ret_wgs;
+  const int xcd = lin & 7, jj = lin >> 3;
+  const int unit = (jj / a.n_vslices) * 8 + xcd;
+  if (unit >= d.B * d.Hkv) return;
+  vague64_part<G>(d, a, unit, jj % a.n_vslices, smem);
+}
+
 template <int G>
 static hipError_t launch64(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan, hipStream_t st) {
-  auto kern = attend_vague_staged64_kernel<G>;
+  auto kern = attend_pair64_kernel<G>;
   static std::once_flag once;
   static hipError_t attr_rc = hipSuccess;
   std::call_once(once, [&]() {
@@ -615,13 +636,13 @@ static hipError_t launch64(const DevDesc& d, const AttendArgs& a, const AttendPl
   if (attr_rc != hipSuccess) return attr_rc;
   const int units = d.B * d.Hkv;
   const int units_pad = (units + 7) / 8 * 8;
-  hipLaunchKernelGGL(kern, dim3(units_pad * plan.n_vslices), dim3(ST_THREADS), plan.lds_bytes, st, d, a);
+  hipLaunchKernelGGL(kern, dim3(plan.n_ret_wgs + units_pad * plan.n_vslices), dim3(ST_THREADS), plan.pair_lds, st, d, a,
+                     plan.n_ret_wgs);
   return hipGetLastError();
 }
 
-hipError_t launch_attend_vague_staged64(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
-                                        hipStream_t st) {
-  if (!staged64_applies(d) || plan.lds_bytes < staged64_lds(d.w, d.G)) return hipErrorInvalidValue;
+hipError_t launch_attend_pair64(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan, hipStream_t st) {
+  if (!staged64_applies(d) || plan.pair_lds < staged64_lds(d.w, d.G)) return hipErrorInvalidValue;
   switch (d.G) {
     case 1: return launch64<1>(d, a, plan, st);
     case 2: return launch64<2>(d, a, plan, st);

@@ -24,6 +24,8 @@ struct AttendPlan {
   int lds_bytes;        // staged: dynamic LDS per workgroup
   bool streamed;        // Vague tokens by the streaming LDS-staged kernel of kvr_attend_multi with one query
                         // (8 query heads per kv head; vslice_tokens / n_vslices are its parts)
+  int n_ret_wgs;        // 64-channel staged kernel: workgroups of its launch that take the retained slots
+  int pair_lds;         // and its dynamic LDS (a workgroup of either kind)
   size_t off_part_o, off_part_ml, off_logits, off_rec, off_tiles, total_bytes;
 };
 AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long vague_cap);
@@ -150,7 +152,7 @@ bool staged16_applies(const DevDesc& d);
 int staged16_lds(const DevDesc& d);               // bytes of a workgroup
 hipError_t launch_attend_vague_staged16(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
                                          hipStream_t st);
-// Its specialisation for r = 3 and 64-channel chunks (launch_attend_vague_staged forwards to it); 10-bit row indices.
+// Its specialisation for r = 3 and 64-channel chunks, whose launch also takes the retained slots; 10-bit row indices.
 // Its chunk stays whole through the V phases, so the reduction scratch is a place of its own.
 constexpr int staged64_lds(int w, int G) {
   return ((3 * w * 128 + 1023) & ~1023) + 32 * G * 64 * 4 + staged_stat_lds(G) + G * 256;
@@ -160,9 +162,11 @@ inline bool staged64_applies(const DevDesc& d) {
   return d.r == 3 && d.G <= 4 && d.sign_mask == 2 && 3 * d.w <= (d.G == 4 ? 1000 : 1024);
 }
 static_assert(staged64_lds(1000 / 3, 4) <= STAGED_LDS_LIMIT && staged64_lds(1024 / 3, 2) <= STAGED_LDS_LIMIT, "LDS");
-hipError_t launch_attend_vague_staged64(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
-                                        hipStream_t st);
-
+constexpr int STAGED64_KMAX = 25;                 // wave-rounds (64 tokens) per wave: what 256 registers hold
+// LDS of a workgroup of its launch that takes retained slots: the waves' sums, their statistics, the logits of a slice (a
+// tile of 16 tokens for every wave at a time)
+constexpr int ret_stream_lds(int G, int tokens) { return 8 * G * D * 4 + 2 * 8 * 4 * 4 + (tokens + 127) / 128 * 128 * G * 4; }
+hipError_t launch_attend_pair64(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan, hipStream_t st);
 
 hipError_t launch_select(const DevDesc& d, const float* scores, long long n_cap, int32_t* ret_pos,
                          int ret_cap, const int32_t* n_ctx, int n_recent, int k_candidate,

@@ -1,0 +1,68 @@
+"""The launch that holds the 64-channel list workgroups and those of the retained slots: one to 25 rounds of 64 tokens a wave,
+lists that end inside a round, a wave and a workgroup, slices that end inside a tile, empty slots, any number of units.
+Against attention in float64 over the rows that kvr_reconstruct gives (bit-exact against the oracle in its own tests).
+
+Tolerance: a list token's weight has 16 bits in bf16 parts, so an output is off by at most 2^-16 of sum(p |v|), and float32
+sums of n terms add less than 2^-20 of it for the n here; checked against 2^-15 of the largest |v| of the unit.  A
+probability is off by its logit's error, 2^-20 of |q||k| / sqrt(128) (< 2^-17 for the rows below), relative."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+D = 128
+
+
+@pytest.fixture(scope="module")
+def kvr():
+    from paper_2512_17917_amd import binding
+    return binding
+
+
+@pytest.mark.parametrize("units,G,w,ret_cap,cap", [
+    (200, 4, 20, 100, 12800),        # one workgroup per unit, 25 rounds
+    (224, 2, 333, 17, 12300),        # 25 rounds, the last two not in every wave; one slice of two tiles
+    (120, 1, 341, 1000, 12800),      # two turns or more; slices of several items per workgroup
+    (8, 4, 333, 3000, 6000),         # few rounds, many workgroups; slices that end inside a tile
+    (9, 4, 6, 1, 64),                # the smallest list that is staged
+    (3, 1, 6, 9300, 700),            # more slots than LDS holds logits of with four heads
+    (1, 4, 40, 9300, 3000),
+])
+def test_rounds_and_slices(kvr, units, G, w, ret_cap, cap):
+    print("pair64", units, G, w, ret_cap, cap, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(units * 7 + w)
+    dt = torch.bfloat16
+    d = kvr.make_desc(1, units * G, units, 3, w, dt, seed=5)
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda").to(dt)
+    k_ret, v_ret, sk, sv = (rn(1, units, n, D) for n in (ret_cap, ret_cap, 3 * w, 3 * w))
+    q = rn(1, units * G, D)
+    n = ret_cap + cap
+    perm = torch.argsort(torch.rand(units, n, generator=g, device="cuda"), dim=1).to(torch.int32)
+    ret_pos, vague_pos = perm[:, :ret_cap].contiguous(), perm[:, ret_cap:].contiguous()
+    empty = torch.rand(units, ret_cap, generator=g, device="cuda") < 0.1
+    ret_pos[empty] = -1
+    k_ret[0][empty] = float("nan")
+    v_ret[0][empty] = float("nan")
+    ends = [cap, 0, 1, 63, 64, 65, 511, 512, 513, cap - 1, cap - 64, cap // 2 + 1]
+    n_vague = torch.tensor([min(max(ends[u % 12] if u % 24 < 12 else cap, 0), cap) for u in range(units)], dtype=torch.int32, device="cuda")
+    scores, out = torch.zeros(units, n, device="cuda"), torch.zeros(units * G, D, device="cuda")
+    ws = kvr.alloc_workspace(d, kvr.KVR_OP_ATTEND, ret_cap, cap).fill_(255)
+    kvr.kvr_attend_decode(d, q, k_ret, v_ret, ret_pos, ret_cap, sk, sv, vague_pos, n_vague, cap, out, scores, n, ws)
+    kh, vh = (torch.zeros(units, cap, D, dtype=dt, device="cuda") for _ in range(2))
+    kvr.kvr_reconstruct(d, sk, sv, vague_pos, n_vague, cap, kh, vh)
+    assert torch.isfinite(out).all() and torch.isfinite(scores).all()
+    for u in range(units):
+        m = int(n_vague[u])
+        K = torch.cat([torch.where(empty[u][:, None], 0, k_ret[0, u]), kh[u, :m]]).double()
+        V = torch.cat([torch.where(empty[u][:, None], 0, v_ret[0, u]), vh[u, :m]]).double()
+        pos = torch.cat([ret_pos[u], vague_pos[u, :m]]).long()
+        x = (q[0, u * G:(u + 1) * G].double() @ K.T) * d.softmax_scale
+        x[:, pos < 0] = float("-inf")
+        if bool((pos < 0).all()):
+            assert bool((out[u * G:(u + 1) * G] == 0).all())
+            continue
+        p = torch.softmax(x, dim=1)
+        err = (out[u * G:(u + 1) * G].double() - p @ V).abs().max().item()
+        assert err <= 2.0 ** -15 * V.abs().max().item(), (u, m, err)
+        want = torch.zeros(n, dtype=torch.float64, device="cuda")
+        want[pos[pos >= 0]] = p.sum(dim=0)[pos >= 0]
+        assert bool(((scores[u].double() - want).abs() <= 2.0 ** -16 * want + 1e-12).all()), (u, m)
