@@ -36,20 +36,27 @@ static int slice_tokens_for(long long tokens, long long units) {
 
 int attend_slice_tokens(long long tokens, long long units) { return slice_tokens_for(tokens, units); }
 
-// The 64-channel kernel's launch: n_vslices workgroups per unit over the Vague list and n_ret_wgs workgroups over the
-// retained slots, at most `most` slices of both kinds per unit (what callers' workspaces hold).  A workgroup of either kind
-// has a CU to itself (its registers fill the SIMDs) and a unit's workgroups share an XCD of 32 CUs, so the launch takes
-// turns * (time of a list workgroup) on the CUs that the retained slots leave.  In us: a list workgroup takes 11.5 at 273
-// slots per row, 7 at six, and 5 per round of 64 tokens a wave (one head 3.5), at 25 rounds as at two; a CU streams
-// 35 .. 40 KB of retained rows per us whatever its waves have in flight, and a slice ends with 2 us of merging.
-// Before, retained slots and list were launches of their own, one behind the other or on two streams, with at most 6 rounds
-// a wave; both, us from the first start to the last end of a call: 8 units of 25395 + 7374 tokens 42.1 -> 32.6 (25 list
-// workgroups per unit, 56 for the slots; 16 and 128: 38), 32 units 104.5 -> 70 (6 and 64; 5 and 96: 73, 8 and none: 80 with
-// every list workgroup taking a slice along), 128 units 311 (on two streams 258 .. 284) -> 230 .. 255 (3 and 64), 64 units of
-// 1862 + 187 33.4 -> 27.4, 96 units of 3753 + 1128, one head 45.2 -> 36.0.
-static void plan_pair64(AttendPlan& p, const DevDesc& d, int units, int ret_cap, int vague_cap, int most) {
+// One launch for the retained slots and the Vague list (64- and 16-channel kernels): n_vslices workgroups per unit over the
+// list and n_ret_wgs workgroups over the slots, at most `most` slices of both kinds per unit (what callers' workspaces hold).
+// A workgroup of either kind has a CU to itself (its registers fill the SIMDs) and a unit's workgroups share an XCD of 32
+// CUs, so the launch takes turns * (time of a list workgroup) on the CUs that the slots leave; where it leaves none, the slots
+// go first, on all of them.  In us, measured: a list workgroup of the 64-channel kernel takes 11.5 at 273 slots per row, 7 at six,
+// and 5 per round of 64 tokens a wave (one head 3.5), at 25 rounds as at two; of the 16-channel kernel 27 at 1050 sketch rows,
+// 68 at 3276, and 5.5 a round (four rows 10.5).  A CU streams 35 .. 40 KB of retained rows per us whatever its waves have in
+// flight, and a slice ends with 2 us of merging.
+// Before, slots and list were launches of their own, one behind the other or on two streams, with at most 6 rounds (16
+// channels: 13) a wave.  Both, us from the first start to the last end of a call: 64 channels: 8 units of 25395 + 7374 tokens
+// 42.1 -> 32.6 (25 list workgroups per unit, 56 for the slots; 16 and 128: 38), 32 units 104.5 -> 70 (6 and 64; 5 and 96: 73, 8
+// and none: 80 with every list workgroup taking a slice along), 128 units 311 (on two streams 258 .. 284) -> 230 .. 255 (3 and
+// 64), 64 units of 1862 + 187 33.4 -> 27.4, 96 units of 3753 + 1128, one head 45.2 -> 36.0.  16 channels: 16 units of 101580 +
+// 29492 206 -> 174 (13 and 48; 12 and 64: 191, 14 and 32: 198), 24 units of 70000 tokens in all 164 -> 132, 8 of 42000 65 -> 50; four
+// rows: 32 units of 101580 + 29492 520 -> 476 .. 506 (14 and 32; 21 and 32: 499), 16 of 60000 in all 151 -> 125, 128 of 9000, one head
+// 130 -> 122 (slots first; 3 and 64: 142).
+static void plan_pair(AttendPlan& p, const DevDesc& d, int units, int ret_cap, int vague_cap, int most) {
   constexpr double RATE = 38e3, SLICE = 2.0, CHIP = 5.0e6;
-  const double fixed = 6.5 + 0.018 * d.w, round = 3.0 + 0.5 * d.G;
+  const bool s64 = p.ch == 64;
+  const int kmax = s64 ? STAGED64_KMAX : staged16_kmax(d.r);
+  const double fixed = s64 ? 6.5 + 0.018 * d.w : 8.5 + 0.018 * d.r * d.w, round = s64 ? 3.0 + 0.5 * d.G : d.r == 3 ? 5.5 : 10.5;
   const int wr = (vague_cap + 63) / 64, units8 = (units + 7) / 8, tiles = (ret_cap + 15) / 16;
   const double bytes = 512.0 * units * ret_cap;
   // largest slice, in tiles (LDS holds its logits)
@@ -57,17 +64,22 @@ static void plan_pair64(AttendPlan& p, const DevDesc& d, int units, int ret_cap,
   const int least = (tiles + most_tiles - 1) / most_tiles;
   double best = 1e30;
   int best_n = 1, best_r = 0, last = 0;
-  for (int rho = 1; rho <= STAGED64_KMAX; ++rho) {
+  for (int rho = 1; rho <= kmax; ++rho) {
     const int n = (wr + 8 * rho - 1) / (8 * rho);
     if (n == last) continue;
     last = n;
-    if (n + least > most && rho < STAGED64_KMAX) continue;
+    if (n + least > most && rho < kmax) continue;
     const double wg = fixed + round * ((wr + 8 * n - 1) / (8 * n));
     const int per_xcd = units8 * n, turns = (per_xcd + 31) / 32;
     for (int k = turns; k <= turns + 2; ++k) {
-      const int r = ret_cap > 0 ? 8 * (32 - (per_xcd + k - 1) / k) : 0;
-      if (ret_cap > 0 && r <= 0) continue;
-      const double t = std::max(k * wg, ret_cap > 0 ? SLICE + std::max(bytes / (RATE * r), bytes / CHIP) : 0.0);
+      int r = ret_cap > 0 ? 8 * (32 - (per_xcd + k - 1) / k) : 0;
+      double t = k * wg;
+      if (r > 0) {
+        t = std::max(t, SLICE + std::max(bytes / (RATE * r), bytes / CHIP));
+      } else if (ret_cap > 0) {              // no CU is left: the slots first, on all of them
+        r = 256;
+        t += 2.0 + SLICE + bytes / CHIP;
+      }
       if (t < best - 1e-9) { best = t; best_n = n; best_r = r; }
     }
   }
@@ -89,7 +101,7 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
   AttendPlan p;
   const long long units = (long long)d.B * d.Hkv;
   const long long tot_cap = ret_cap + vague_cap;
-  p.staged = false;
+  p.staged = p.pair = false;
   p.n_vslices = 0;
   p.ch = 0;
   p.lds_bytes = 0;
@@ -114,16 +126,12 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
       }
     if (p.ch) {
       const long long wr = (vague_cap + 63) / 64;          // wave-rounds to cover the list
-      // Cost model: a workgroup that gives every wave rho rounds of 64 tokens takes
-      // about (fixed + rho) round times (fixed part: staging the sketch chunks,
-      // hashes, softmax, reductions: 2.8 rounds' worth for four 64-channel chunks,
-      // 7.5 for the sixteen 16-channel chunks of that kernel, whose waves may
-      // also take more rounds), and the launch runs ceil(workgroups / 256)
-      // such workgroups one after another on each CU.  Measured on one turn of the 16-channel kernel: four rows 4.6 (w =
-      // 600) .. 5.9 (819) rounds of 11 us; three rows 4.8 (w = 350), 7.7 (700), 11.5 (1092) rounds of 6 us.  With three rows
-      // the counts chosen with 7.5 cost at most 4 % more than those chosen with each width's own figure (99 of 100
-      // sizes: the same counts).
-      const int kmax = s16 ? STAGED16_KMAX : STAGED_KMAX;
+      // Cost model: a workgroup that gives every wave rho
+      // rounds of 64 tokens takes about (fixed + rho) round times (fixed part: staging the sketch chunks,
+      // hashes, softmax, reductions), and the launch runs ceil(workgroups / 256)
+      // such workgroups one after another on each CU.  It decides for the general kernel; for the other two it only bounds
+      // the number of slices (plan_pair).
+      const int kmax = s16 ? 13 : STAGED_KMAX;
       const double fixed_rounds = s16 ? 7.5 : 2.8;
       double best = 1e30;
       int best_n = 1;
@@ -135,6 +143,7 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
         if (cost < best - 1e-9) { best = cost; best_n = (int)n; }
       }
       p.staged = true;
+      p.pair = s64 || s16;
       p.n_vslices = best_n;
     }
   }
@@ -150,8 +159,8 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
     if (p.streamed) {
       p.vslice_tokens = multi_staged_part_tokens(vague_cap, units);
       p.n_vslices = (int)((vague_cap + p.vslice_tokens - 1) / p.vslice_tokens);
-    } else if (p.staged && p.ch == 64) {
-      plan_pair64(p, d, (int)units, (int)ret_cap, (int)vague_cap, p.n_rslices + p.n_vslices);
+    } else if (p.pair) {
+      plan_pair(p, d, (int)units, (int)ret_cap, (int)vague_cap, p.n_rslices + p.n_vslices);
     } else if (!p.staged && vague_cap > 0) {
       p.vslice_tokens = slice_tokens_for(vague_cap, units);
       p.n_vslices = (int)((vague_cap + p.vslice_tokens - 1) / p.vslice_tokens);
@@ -642,10 +651,9 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
   const bool big = (long long)units * plan.n_vslices >= 2ll * cus;
   // And only where a CU holds a workgroup of each.
   const int side_lds = attend_side_lds(d, plan);
-  const bool pair = plan.staged && plan.ch == 64;
-  const bool side = !pair && sd.stream != nullptr && big && side_lds > 0;
-  if (pair) {
-    e = launch_attend_pair64(d, a, plan, st);
+  const bool side = !plan.pair && sd.stream != nullptr && big && side_lds > 0;
+  if (plan.pair) {
+    e = plan.ch == 64 ? launch_attend_pair64(d, a, plan, st) : launch_attend_pair16(d, a, plan, st);
   } else if (side) {
     e = hipEventRecord(sd.fork, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(sd.stream, sd.fork, 0);
@@ -673,7 +681,7 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
     e = hipGetLastError();
   }
   // 2. the Vague list
-  if (side || pair) {
+  if (side || plan.pair) {
     // already launched above
   } else if (e == hipSuccess && plan.staged) {
     e = launch_attend_vague_staged(d, a, plan, st);

@@ -363,7 +363,6 @@ static hipError_t launch_r(const DevDesc& d, const AttendArgs& a, const AttendPl
 
 hipError_t launch_attend_vague_staged(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
                                       hipStream_t st) {
-  if (staged16_applies(d)) return launch_attend_vague_staged16(d, a, plan, st);
   switch (d.G) {
     case 1: return launch_r<1>(d, a, plan, st);
     case 2: return launch_r<2>(d, a, plan, st);

@@ -14,8 +14,10 @@
 // phases (copy, barriers, reduction) are worth 66 of a turn's 140 us and 30 of its 111.  Three rows against the general
 // kernel: 131072 tokens, 16 units 353 -> 136 us; one layer's whole decode step, with what else changed in it: 454 -> 231 us,
 // 8 units 263 -> 172; 70000 tokens, 24 units 235 -> 184; 42000 tokens, 48 units 260 -> 199, 8 units 92 -> 86.  (A sketch with
-// about as many slots as tokens loses: 256 units, 1500 tokens, 3 x 400 slots 182 -> 200 us a call.)  With three rows a
-// wave holds 192 registers (four: 240), which leaves room for the retained-slot kernel next to it.
+// about as many slots as tokens loses: 256 units, 1500 tokens, 3 x 400 slots 182 -> 200 us a call.)
+// The launch also holds workgroups that stream the retained slots (kvr_ret_stream.h) on CUs of their own, and a wave takes up
+// to 17 rounds of 64 tokens (four rows: 24) in 256 registers, where it took 13: 16 units of 101580 + 29492 tokens, us a call
+// 206 -> 174, four rows, 32 units 520 -> 476 .. 506.
 // Error of a call's output against float64, relative in the 2-norm, three rows: 1.6e-7 (200 tokens) .. 3.0e-7 (101580), as
 // with the general kernel's float32 multiply-adds (1.7e-7 .. 3.2e-7); weights as two bf16 parts: 8e-6 .. 1.1e-5, three
 // parts cost 1 % of the time.  Four rows: two parts, 7e-6 .. 1.1e-5.
@@ -41,7 +43,7 @@
 //  * The copy of the next chunk is started as soon as every wave is done with the
 //    current one and overlaps the reduction of the V partial sums, which have LDS
 //    of their own (two sets that take turns, so that a chunk needs two barriers).
-#include "kvr_staged.h"
+#include "kvr_ret_stream.h"
 
 namespace kvr {
 namespace {
@@ -51,7 +53,6 @@ constexpr int S16_ROWB = 32;               // bytes per LDS row
 constexpr int S16_NHP = 4;                 // 8-byte half pieces per LDS row
 constexpr int S16_NCHUNK = D / S16_CH;      // chunks per tensor
 constexpr int S16_NROW = ST_WAVES * 4;     // 16-lane rows per workgroup
-constexpr int S16_KMAX = STAGED16_KMAX;   // wave-rounds (64 tokens) per wave
 
 template <int R>
 struct Rows {
@@ -216,15 +217,16 @@ __device__ __forceinline__ void take_turn(int t) {
   else __builtin_amdgcn_s_setprio(1);
 }
 
-// K pass over NK rounds of one chunk.  qx[j]: the 4 channels of q for head (lane
+// K pass over the rounds of one chunk.  qx[j]: the 4 channels of q for head (lane
 // mod 4) that belong to the half piece this lane's block reads at step j (byte
 // offset co[j] of the row).  s[k][i]: logit of token i of this lane's quad in round
 // k, for head (lane mod 4).  Pipeline over the steps t = 4 k + j: rows of step t + 2
-// requested, median of step t + 1 formed, matrix instruction of step t issued.
-template <int NK, int R, int MODE>
-__device__ __forceinline__ void k_pass(const unsigned char* s_sk, const uint2 (&info)[S16_KMAX],
+// requested, median of step t + 1 formed, matrix instruction of step t issued.  (Behind the last round it reads rows that a
+// zero record names, and drops them.)
+template <int KMAX, int R, int MODE>
+__device__ __forceinline__ void k_pass(const unsigned char* s_sk, const uint2 (&info)[KMAX], int n_k,
                                        const uint2 (&qx)[S16_NHP], const int (&co)[S16_NHP], int turn,
-                                       float (&s)[S16_KMAX][4]) {
+                                       float (&s)[KMAX][4]) {
   Rows<R> buf[3];                        // rows of step t live in buf[t % 3]
   int rb[R];
   rec_offsets<R>(opaque(info[0]), rb);
@@ -232,44 +234,47 @@ __device__ __forceinline__ void k_pass(const unsigned char* s_sk, const uint2 (&
   load_rows<R>(buf[1], s_sk, rb, co[1]);
   uint2 m[2];                            // median of step t in m[t % 2]
   m[0] = median_rows_of<R, MODE>(buf[0]);
-#pragma unroll
-  for (int k = 0; k < NK; ++k) {
-    int rn[R] = {};
-    if (k + 1 < NK) rec_offsets<R>(opaque(info[k + 1]), rn);
+  for_rounds<KMAX>(n_k, [&](auto kc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc)::value;
+    int rn[R];
+    rec_offsets<R>(opaque(info[k + 1 < KMAX ? k + 1 : k]), rn);
     f32x4_t ax = {0.f, 0.f, 0.f, 0.f};
     take_turn(k + turn);
 #pragma unroll
     for (int j = 0; j < S16_NHP; ++j) {
       const int t = S16_NHP * k + j;
       if (j + 2 < S16_NHP) load_rows<R>(buf[(t + 2) % 3], s_sk, rb, co[j + 2]);
-      else if (k + 1 < NK) load_rows<R>(buf[(t + 2) % 3], s_sk, rn, co[j + 2 - S16_NHP]);
+      else load_rows<R>(buf[(t + 2) % 3], s_sk, rn, co[j + 2 - S16_NHP]);
       KVR_PIN();
-      if (j + 1 < S16_NHP || k + 1 < NK) m[(t + 1) & 1] = median_rows_of<R, MODE>(buf[(t + 1) % 3]);
+      m[(t + 1) & 1] = median_rows_of<R, MODE>(buf[(t + 1) % 3]);
       KVR_PIN();
       const uint2 mc = m[t & 1];
       ax = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(pack_k4(mc.x, mc.y), pack_k4(qx[j].x, qx[j].y), ax, 0, 0, 0);
       KVR_PIN();
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s[k][i] += ax[i];
+    for (int i = 0; i < 4; ++i) {
+      s[k][i] += ax[i];
+      asm volatile("" : "+v"(s[k][i]));        // formed here, not where it is used next
+    }
 #pragma unroll
     for (int i = 0; i < R; ++i) rb[i] = rn[i];
-  }
+  });
   __builtin_amdgcn_s_setprio(1);
 }
 
-// V pass over NK rounds of one chunk for the half piece at byte offset co of each
+// V pass over the rounds of one chunk for the half piece at byte offset co of each
 // row: the quad's 4 tokens per round, same kind of pipeline.
-template <int NK, int R, int MODE>
-__device__ __forceinline__ void v_pass(const unsigned char* s_sk, const uint2 (&info)[S16_KMAX],
-                                       const uint32_t (&W)[S16_KMAX][2 * weight_parts<R>()], int co, int turn,
+template <int KMAX, int R, int MODE>
+__device__ __forceinline__ void v_pass(const unsigned char* s_sk, const uint2 (&info)[KMAX], int n_k,
+                                       const uint32_t (&W)[KMAX][2 * weight_parts<R>()], int co, int turn,
                                        f32x4_t (&acc)[4]) {
   VItem<R> buf[4];
-  VOwn<R> own = v_own<R>(info[0]);
+  VOwn<R> own = v_own<R>(opaque(info[0]));
   v_fetch<0, R, MODE>(buf[0], own, s_sk, co);
   v_fetch<1, R, MODE>(buf[1], own, s_sk, co);
-#pragma unroll
-  for (int k = 0; k < NK; ++k) {
+  for_rounds<KMAX>(n_k, [&](auto kc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc)::value;
     uint2 med[4];
     take_turn(k + turn);
     v_fetch<2, R, MODE>(buf[2], own, s_sk, co);
@@ -277,42 +282,22 @@ __device__ __forceinline__ void v_pass(const unsigned char* s_sk, const uint2 (&
     med[0] = v_median<R, MODE>(buf[0]);
     KVR_PIN();
     v_fetch<3, R, MODE>(buf[3], own, s_sk, co);
-    if (k + 1 < NK) own = v_own<R>(info[k + 1]);
+    own = v_own<R>(opaque(info[k + 1 < KMAX ? k + 1 : k]));
     KVR_PIN();
     med[1] = v_median<R, MODE>(buf[1]);
     KVR_PIN();
-    if (k + 1 < NK) v_fetch<0, R, MODE>(buf[0], own, s_sk, co);
+    v_fetch<0, R, MODE>(buf[0], own, s_sk, co);
     KVR_PIN();
     med[2] = v_median<R, MODE>(buf[2]);
     KVR_PIN();
-    if (k + 1 < NK) v_fetch<1, R, MODE>(buf[1], own, s_sk, co);
+    v_fetch<1, R, MODE>(buf[1], own, s_sk, co);
     KVR_PIN();
     med[3] = v_median<R, MODE>(buf[3]);
     pv_half_piece<weight_parts<R>()>(med, W[k], acc);
     KVR_PIN();
-  }
+  });
   __builtin_amdgcn_s_setprio(1);
 }
-
-// the round count is uniform over a wave: one scalar branch into straight-line code
-#define KVR_DISPATCH_NK(n, CALL) \
-  switch (n) {                   \
-    case 1: { constexpr int NK = 1; CALL; } break; \
-    case 2: { constexpr int NK = 2; CALL; } break; \
-    case 3: { constexpr int NK = 3; CALL; } break; \
-    case 4: { constexpr int NK = 4; CALL; } break; \
-    case 5: { constexpr int NK = 5; CALL; } break; \
-    case 6: { constexpr int NK = 6; CALL; } break; \
-    case 7: { constexpr int NK = 7; CALL; } break; \
-    case 8: { constexpr int NK = 8; CALL; } break; \
-    case 9: { constexpr int NK = 9; CALL; } break; \
-    case 10: { constexpr int NK = 10; CALL; } break; \
-    case 11: { constexpr int NK = 11; CALL; } break; \
-    case 12: { constexpr int NK = 12; CALL; } break; \
-    case 13: { constexpr int NK = 13; CALL; } break; \
-    default: break;              \
-  }
-static_assert(STAGED16_KMAX <= 13, "KVR_DISPATCH_NK covers 1..13 rounds");
 
 // LDS of a workgroup: one chunk, two sets of V partial sums [NROW][G][CH], wave statistics, q
 __host__ __device__ constexpr int chunk_bytes(int r, int w) { return (r * w * S16_ROWB + 1023) & ~1023; }
@@ -320,19 +305,10 @@ __host__ __device__ constexpr int stat_floats(int G) { return 3 * ST_WAVES * G; 
 
 }  // namespace
 
+// One workgroup's share (part vs of a.n_vslices) of a unit's Vague list.
 template <int G, int R, int MODE>
-__global__ __launch_bounds__(ST_THREADS) void attend_vague_staged16_kernel(DevDesc d, AttendArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int KMAX = S16_KMAX, CH = S16_CH;
-
-  // XCD-aware mapping: workgroup ids are dealt round-robin to the 8 XCDs, so all
-  // workgroups of a unit get ids that are equal modulo 8 (they share one L2).
-  const int lin = blockIdx.x;
-  const int xcd = lin & 7, jj = lin >> 3;
-  const int unit = (jj / a.n_vslices) * 8 + xcd;
-  const int vs = jj % a.n_vslices;
-  const int units = d.B * d.Hkv;
-  if (unit >= units) return;
+__device__ __forceinline__ void vague16_part(const DevDesc& d, const AttendArgs& a, int unit, int vs, unsigned char* smem) {
+  constexpr int KMAX = staged16_kmax(R), CH = S16_CH;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int b = unit / d.Hkv, hk = unit % d.Hkv;
@@ -361,11 +337,11 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged16_kernel(DevDe
   // ---- loads first: Vague positions of this wave's tokens and q ---------------
   int Jv[KMAX];
   const int32_t* vpos = a.vague_pos + (size_t)unit * a.vague_cap;
-#pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
+  for_rounds<KMAX>(n_k, [&](auto kc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc)::value;
     const int tok = (gw + k * NWT) * 64 + lane;
-    Jv[k] = (k < n_k && tok < nv) ? vpos[tok] : -1;
-  }
+    Jv[k] = vpos[min(tok, nv - 1)];        // (a choice made here would wait for the load, round by round)
+  });
   uint4 qv = make_uint4(0u, 0u, 0u, 0u);
   if (tid < G * 16)
     qv = reinterpret_cast<const uint4*>((const bf16_t*)a.q + ((size_t)b * d.Hq + (size_t)hk * G) * D)[tid];
@@ -378,10 +354,12 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged16_kernel(DevDe
 
   uint2 info[KMAX];
 #pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
+  for (int k = 0; k < KMAX; ++k) info[k] = make_uint2(0u, 0u);
+  for_rounds<KMAX>(n_k, [&](auto kc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc)::value;
     const int J = Jv[k];
-    info[k] = (J >= 0) ? make_record<R, MODE>(d, w, J) : make_uint2(0u, 0u);
-  }
+    if (J >= 0 && (gw + k * NWT) * 64 + lane < nv) info[k] = make_record<R, MODE>(d, w, J);
+  });
   if (tid < G * 16) reinterpret_cast<uint4*>(s_q)[tid] = qv;
 
   // ---- K phases: logits -----------------------------------------------------
@@ -405,7 +383,7 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged16_kernel(DevDe
         co[j] = hp * 8;
         qx[j] = (sub < G) ? s_q[sub * 32 + cc * S16_NHP + hp] : make_uint2(0u, 0u);
       }
-      KVR_DISPATCH_NK(n_k, (k_pass<NK, R, MODE>(s_sk, info, qx, co, turn, s)))
+      k_pass<KMAX, R, MODE>(s_sk, info, n_k, qx, co, turn, s);
     }
     lds_barrier();                         // every wave is done with chunk cc
     if (cc + 1 < S16_NCHUNK) stage_issue<S16_ROWB / 16, S16_ROWB>(skg, s_sk, n_pieces, cc + 1, tid);
@@ -420,9 +398,8 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged16_kernel(DevDe
   const int gw_l = opaque_s(__builtin_amdgcn_readfirstlane(gw));
   const bool head_ok = sub < G;
   float mx = -__builtin_inff();
-#pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
-    if (k >= n_k) continue;                // uniform over the wave: rounds it does not have cost nothing
+  for_rounds<KMAX>(n_k, [&](auto kc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc)::value;
     const int tok0 = (gw_l + k * NWT) * 64 + (lane & ~3);        // first token of the quad in this round
     const int n_ok = nv - tok0;                                   // tokens i < n_ok of the quad exist
     float* lg = a.logits + ((size_t)unit_l * tot_cap + a.ret_cap + tok0) * G + sub;
@@ -433,7 +410,7 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged16_kernel(DevDe
       mx = fmaxf(mx, s[k][i]);
       if (a.logits != nullptr && valid && head_ok) lg[i * G] = s[k][i];
     }
-  }
+  });
   // Weights are formed against the wave's own maximum, which needs no barrier; the
   // workgroup's maximum is put together after the barrier that publishes the first
   // V chunk, and each wave's sums are rescaled by exp(own maximum - workgroup
@@ -446,16 +423,15 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged16_kernel(DevDe
     x = fmaxf(x, __shfl_xor(x, 32));
     if (lane < G) s_stat[wave * G + lane] = x;
     float lsum = 0.f;
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-      if (k >= n_k) continue;
+    for_rounds<KMAX>(n_k, [&](auto kc) __attribute__((always_inline)) {
+      constexpr int k = decltype(kc)::value;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float p = (s[k][i] == -__builtin_inff()) ? 0.f : __expf(s[k][i] - x);
         s[k][i] = p;                 // from here on s holds the weights
         lsum += p;
       }
-    }
+    });
     lsum = row_sum<4>(lsum);
     lsum += __shfl_xor(lsum, 16);
     lsum += __shfl_xor(lsum, 32);
@@ -474,12 +450,9 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged16_kernel(DevDe
   // cancels.
   constexpr int NP = weight_parts<R>();
   const uint32_t neg_quad = (R == 3) ? (uint32_t)(lane & 4) << 29 : 0u;
-  uint32_t W[KMAX][2 * NP];
-#pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
-#pragma unroll
-    for (int p = 0; p < 2 * NP; ++p) W[k][p] = 0u;
-    if (k >= n_k) continue;
+  uint32_t W[KMAX][2 * NP];                // (of the rounds there are)
+  for_rounds<KMAX>(n_k, [&](auto kc) __attribute__((always_inline)) {
+    constexpr int k = decltype(kc)::value;
     const uint32_t rx = info[k].x;
     const uint32_t sg[4] = {quad_bcast<0>(rx) << 31, quad_bcast<1>(rx) << 31, quad_bcast<2>(rx) << 31,
                             quad_bcast<3>(rx) << 31};
@@ -498,7 +471,7 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged16_kernel(DevDe
       W[k][2 * p] = pair_hi(part[0], part[1]);
       W[k][2 * p + 1] = pair_hi(part[2], part[3]);
     }
-  }
+  });
 
   // ---- V phases: weighted values ------------------------------------------------
   float* s_fw = s_stat + 2 * ST_WAVES * G;          // [8 waves][G]: exp(wave maximum - workgroup maximum)
@@ -545,7 +518,7 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged16_kernel(DevDe
     f32x4_t acc[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    KVR_DISPATCH_NK(n_k, (v_pass<NK, R, MODE>(s_sk, info, W, sub * 8, turn, acc)))
+    v_pass<KMAX, R, MODE>(s_sk, info, n_k, W, sub * 8, turn, acc);
     lds_barrier();                         // every wave is done with this V chunk
     if (cc + 1 < S16_NCHUNK) stage_issue<S16_ROWB / 16, S16_ROWB>(svg, s_sk, n_pieces, cc + 1, tid);
 
@@ -584,9 +557,27 @@ __global__ __launch_bounds__(ST_THREADS) void attend_vague_staged16_kernel(DevDe
   }
 }
 
+// The first n_ret_wgs workgroups walk slices of the retained slots, the others take parts of the Vague lists.
+template <int G, int R, int MODE>
+__global__ __launch_bounds__(ST_THREADS, 2) void attend_pair16_kernel(DevDesc d, AttendArgs a, int n_ret_wgs) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  if ((int)blockIdx.x < n_ret_wgs) {
+    for (int item = blockIdx.x; item < d.B * d.Hkv * a.n_rslices; item += n_ret_wgs)
+      ret_stream_slice<G>(d, a, item / a.n_rslices, item % a.n_rslices, smem);
+    return;
+  }
+  // XCD-aware mapping: workgroup ids are dealt round-robin to the 8 XCDs, so all
+  // workgroups of a unit get ids that are equal modulo 8 (they share one L2).
+  const int lin = blockIdx.x - n_ret_wgs;
+  const int xcd = lin & 7, jj = lin >> 3;
+  const int unit = (jj / a.n_vslices) * 8 + xcd;
+  if (unit >= d.B * d.Hkv) return;
+  vague16_part<G, R, MODE>(d, a, unit, jj % a.n_vslices, smem);
+}
+
 template <int G, int R, int MODE>
 static hipError_t launch16(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan, hipStream_t st) {
-  auto kern = attend_vague_staged16_kernel<G, R, MODE>;
+  auto kern = attend_pair16_kernel<G, R, MODE>;
   static std::once_flag once;
   static hipError_t attr_rc = hipSuccess;
   std::call_once(once, [&]() {
@@ -596,7 +587,8 @@ static hipError_t launch16(const DevDesc& d, const AttendArgs& a, const AttendPl
   if (attr_rc != hipSuccess) return attr_rc;
   const int units = d.B * d.Hkv;
   const int units_pad = (units + 7) / 8 * 8;
-  hipLaunchKernelGGL(kern, dim3(units_pad * plan.n_vslices), dim3(ST_THREADS), staged16_lds(d), st, d, a);
+  hipLaunchKernelGGL(kern, dim3(plan.n_ret_wgs + units_pad * plan.n_vslices), dim3(ST_THREADS), plan.pair_lds, st, d, a,
+                     plan.n_ret_wgs);
   return hipGetLastError();
 }
 
@@ -617,9 +609,9 @@ bool staged16_applies(const DevDesc& d) {
          staged16_lds(d) <= STAGED_LDS_LIMIT;
 }
 
-hipError_t launch_attend_vague_staged16(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
+hipError_t launch_attend_pair16(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
                                         hipStream_t st) {
-  if (!staged16_applies(d) || plan.n_vslices < 1) return hipErrorInvalidValue;    // 12-bit LDS row indices, LDS size
+  if (!staged16_applies(d) || plan.n_vslices < 1 || plan.pair_lds < staged16_lds(d)) return hipErrorInvalidValue;    // 12-bit LDS row indices, LDS size
   switch (d.G) {
     case 1: return launch16_r<1>(d, a, plan, st);
     case 2: return launch16_r<2>(d, a, plan, st);

@@ -25,24 +25,9 @@
 //    vector issue on the list's CUs (995 vector and 128 matrix instructions a round) and by the latency of memory on the others.
 #include "kvr_ret_stream.h"
 
-#include <type_traits>
-
 namespace kvr {
 
 constexpr int S64_KMAX = STAGED64_KMAX;   // wave-rounds (64 tokens) per wave
-
-// f(0), f(1), .. of the n rounds a wave has, as straight-line code with constant round numbers (what a round keeps lives
-// in registers).  n is uniform over the wave; the rounds it does not have are one jump: skipping them one by one
-// walks through as many instruction-cache misses.
-template <int N, int K = 0, typename F>
-__device__ __forceinline__ void for_rounds(int n, F&& f) {
-  if constexpr (K < N) {
-    if (K < n) {
-      f(std::integral_constant<int, K>{});
-      for_rounds<N, K + 1>(n, f);
-    }
-  }
-}
 
 struct Rows3 {
   uint4 r0, r1, r2;

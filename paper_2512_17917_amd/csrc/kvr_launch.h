@@ -24,7 +24,8 @@ struct AttendPlan {
   int lds_bytes;        // staged: dynamic LDS per workgroup
   bool streamed;        // Vague tokens by the streaming LDS-staged kernel of kvr_attend_multi with one query
                         // (8 query heads per kv head; vslice_tokens / n_vslices are its parts)
-  int n_ret_wgs;        // 64-channel staged kernel: workgroups of its launch that take the retained slots
+  bool pair;            // staged, and its launch takes the retained slots along (64- and 16-channel kernels)
+  int n_ret_wgs;        // pair: workgroups for the retained slots
   int pair_lds;         // and its dynamic LDS (a workgroup of either kind)
   size_t off_part_o, off_part_ml, off_logits, off_rec, off_tiles, total_bytes;
 };
@@ -143,14 +144,14 @@ __host__ __device__ constexpr int staged_stat_lds(int G) { return 2 * 32 * G * 4
 constexpr int staged_lds(int rows, int G, int channels) {
   return staged_chunk_lds(rows, G, channels) + staged_stat_lds(G) + G * 256;
 }
-// Its specialisation for chunks of 16 channels (kvr_attend_staged16.hip; launch_attend_vague_staged forwards
-// to it): four rows, and three rows whose sketch is too wide for the 64-channel kernel.  A wave
-// of that kernel takes up to STAGED16_KMAX rounds of 64 tokens (every workgroup stages the unit's whole
-// sketch, sixteen chunks of it, so few large workgroups are better than many small ones).
-constexpr int STAGED16_KMAX = 13;
+// Its specialisation for chunks of 16 channels (kvr_attend_staged16.hip): four rows, and three rows whose sketch is too
+// wide for the 64-channel kernel.  Its launch takes the retained slots along, and a wave up to staged16_kmax rounds of 64 tokens,
+// what 256 registers hold (every workgroup stages the unit's whole sketch, sixteen chunks of it, so few large workgroups are
+// better than many small ones).
+__host__ __device__ constexpr int staged16_kmax(int r) { return r == 3 ? 17 : 24; }
 bool staged16_applies(const DevDesc& d);
 int staged16_lds(const DevDesc& d);               // bytes of a workgroup
-hipError_t launch_attend_vague_staged16(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
+hipError_t launch_attend_pair16(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan,
                                          hipStream_t st);
 // Its specialisation for r = 3 and 64-channel chunks, whose launch also takes the retained slots; 10-bit row indices.
 // Its chunk stays whole through the V phases, so the reduction scratch is a place of its own.

@@ -2,6 +2,8 @@
 #pragma once
 #include "kvr_launch.h"
 
+#include <type_traits>
+
 namespace kvr {
 
 constexpr int ST_THREADS = 512;
@@ -9,6 +11,19 @@ constexpr int ST_WAVES = 8;
 constexpr int ST_KMAX = 6;
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+
+// f(0), f(1), .. of the n rounds a wave has, as straight-line code with constant round numbers (what a round keeps lives
+// in registers).  n is uniform over the wave; the rounds it does not have are one jump: skipping them one by one
+// walks through as many instruction-cache misses.
+template <int N, int K = 0, typename F>
+__device__ __forceinline__ void for_rounds(int n, F&& f) {
+  if constexpr (K < N) {
+    if (K < n) {
+      f(std::integral_constant<int, K>{});
+      for_rounds<N, K + 1>(n, f);
+    }
+  }
+}
 
 // Per-channel median of three on packed bf16, taken on the raw bit patterns with
 // v_med3_f16 (bf16 and f16 are both sign-magnitude with the exponent above the

@@ -1,5 +1,5 @@
-"""The launch that holds the 64-channel list workgroups and those of the retained slots: one to 25 rounds of 64 tokens a wave,
-lists that end inside a round, a wave and a workgroup, slices that end inside a tile, empty slots, any number of units.
+"""The launches that hold list workgroups (64- and 16-channel kernels) and those of the retained slots: one to 25 rounds of 64
+tokens a wave, lists that end inside a round, a wave and a workgroup, slices that end inside a tile, empty slots, any number of units.
 Against attention in float64 over the rows that kvr_reconstruct gives (bit-exact against the oracle in its own tests).
 
 Tolerance: a list token's weight has 16 bits in bf16 parts, so an output is off by at most 2^-16 of sum(p |v|), and float32
@@ -18,22 +18,27 @@ def kvr():
     return binding
 
 
-@pytest.mark.parametrize("units,G,w,ret_cap,cap", [
-    (200, 4, 20, 100, 12800),        # one workgroup per unit, 25 rounds
-    (224, 2, 333, 17, 12300),        # 25 rounds, the last two not in every wave; one slice of two tiles
-    (120, 1, 341, 1000, 12800),      # two turns or more; slices of several items per workgroup
-    (8, 4, 333, 3000, 6000),         # few rounds, many workgroups; slices that end inside a tile
-    (9, 4, 6, 1, 64),                # the smallest list that is staged
-    (3, 1, 6, 9300, 700),            # more slots than LDS holds logits of with four heads
-    (1, 4, 40, 9300, 3000),
+@pytest.mark.parametrize("units,G,r,w,ret_cap,cap", [
+    (200, 4, 3, 20, 100, 12800),     # one workgroup per unit, 25 rounds
+    (224, 2, 3, 333, 17, 12300),     # 25 rounds, the last two not in every wave; one slice of two tiles
+    (120, 1, 3, 341, 1000, 12800),   # two turns or more; slices of several items per workgroup
+    (8, 4, 3, 333, 3000, 6000),      # few rounds, many workgroups; slices that end inside a tile
+    (9, 4, 3, 6, 1, 64),             # the smallest list that is staged
+    (3, 1, 3, 6, 9300, 700),         # more slots than LDS holds logits of with four heads
+    (1, 4, 3, 40, 9300, 3000),
+    (200, 4, 3, 400, 100, 8704),     # 16 channels, three rows: 17 rounds
+    (8, 2, 3, 1365, 2000, 3000),
+    (200, 1, 4, 50, 100, 12288),     # four rows: 24 rounds
+    (32, 4, 4, 300, 150, 700),       # no CU left by the list: the slots first
+    (9, 2, 4, 6, 1, 64),
 ])
-def test_rounds_and_slices(kvr, units, G, w, ret_cap, cap):
-    print("pair64", units, G, w, ret_cap, cap, flush=True)
+def test_rounds_and_slices(kvr, units, G, r, w, ret_cap, cap):
+    print("pair", units, G, r, w, ret_cap, cap, flush=True)
     g = torch.Generator(device="cuda").manual_seed(units * 7 + w)
     dt = torch.bfloat16
-    d = kvr.make_desc(1, units * G, units, 3, w, dt, seed=5)
+    d = kvr.make_desc(1, units * G, units, r, w, dt, seed=5)
     rn = lambda *s: torch.randn(s, generator=g, device="cuda").to(dt)
-    k_ret, v_ret, sk, sv = (rn(1, units, n, D) for n in (ret_cap, ret_cap, 3 * w, 3 * w))
+    k_ret, v_ret, sk, sv = (rn(1, units, n, D) for n in (ret_cap, ret_cap, r * w, r * w))
     q = rn(1, units * G, D)
     n = ret_cap + cap
     perm = torch.argsort(torch.rand(units, n, generator=g, device="cuda"), dim=1).to(torch.int32)
