@@ -36,6 +36,25 @@ static int slice_tokens_for(long long tokens, long long units) {
 
 int attend_slice_tokens(long long tokens, long long units) { return slice_tokens_for(tokens, units); }
 
+constexpr double RET_RATE = 38e3, RET_CHIP = 5.0e6, RET_SLICE = 6.0;   // bytes per us of a CU, of all; us a slice ends with
+// us for n_wgs workgroups, each on a CU of its own, to stream `bytes` of retained rows
+static double ret_time(double bytes, int n_wgs) {
+  return RET_SLICE + std::max(bytes / (RET_RATE * n_wgs), bytes / RET_CHIP);
+}
+// Slices of a unit's retained slots for n_wgs workgroups of `waves` waves: a number that spreads evenly over them, of slices as
+// large as LDS allows and at most `most`.  40 units of 4104 slots, eight heads, 56 workgroups: one slice a unit (16 workgroups
+// with none) 51 us, four 57.
+static int ret_slices(int units, int ret_cap, int n_wgs, int n_col, int waves, int most) {
+  const int tiles = (ret_cap + 15) / 16, biggest = ret_stream_most(n_col, waves), least = std::max(1, (tiles + biggest - 1) / biggest);
+  int slices = least;
+  double best = 1e30;
+  for (int s = least, end = std::min({tiles, least + 31, most}); s <= end; ++s) {
+    const double t = (double)((units * s + n_wgs - 1) / n_wgs) * ((double)((tiles + s - 1) / s) * 8192.0 / 45e3 + RET_SLICE);
+    if (t < best - 1e-9) { best = t; slices = s; }
+  }
+  return slices;
+}
+
 // One launch for the retained slots and the Vague list (64- and 16-channel kernels): n_vslices workgroups per unit over the
 // list and n_ret_wgs workgroups over the slots, at most `most` slices of both kinds per unit (what callers' workspaces hold).
 // A workgroup of either kind has a CU to itself (its registers fill the SIMDs) and a unit's workgroups share an XCD of 32
@@ -43,7 +62,7 @@ int attend_slice_tokens(long long tokens, long long units) { return slice_tokens
 // go first, on all of them.  In us, measured: a list workgroup of the 64-channel kernel takes 11.5 at 273 slots per row, 7 at six,
 // and 5 per round of 64 tokens a wave (one head 3.5), at 25 rounds as at two; of the 16-channel kernel 27 at 1050 sketch rows,
 // 68 at 3276, and 5.5 a round (four rows 10.5).  A CU streams 35 .. 40 KB of retained rows per us whatever its waves have in
-// flight, and a slice ends with 2 us of merging.
+// flight, and a slice ends with 6 us of merging and starting anew.
 // Before, slots and list were launches of their own, one behind the other or on two streams, with at most 6 rounds (16
 // channels: 13) a wave.  Both, us from the first start to the last end of a call: 64 channels: 8 units of 25395 + 7374 tokens
 // 42.1 -> 32.6 (25 list workgroups per unit, 56 for the slots; 16 and 128: 38), 32 units 104.5 -> 70 (6 and 64; 5 and 96: 73, 8
@@ -53,15 +72,12 @@ int attend_slice_tokens(long long tokens, long long units) { return slice_tokens
 // rows: 32 units of 101580 + 29492 520 -> 476 .. 506 (14 and 32; 21 and 32: 499), 16 of 60000 in all 151 -> 125, 128 of 9000, one head
 // 130 -> 122 (slots first; 3 and 64: 142).
 static void plan_pair(AttendPlan& p, const DevDesc& d, int units, int ret_cap, int vague_cap, int most) {
-  constexpr double RATE = 38e3, SLICE = 2.0, CHIP = 5.0e6;
   const bool s64 = p.ch == 64;
   const int kmax = s64 ? STAGED64_KMAX : staged16_kmax(d.r);
   const double fixed = s64 ? 6.5 + 0.018 * d.w : 8.5 + 0.018 * d.r * d.w, round = s64 ? 3.0 + 0.5 * d.G : d.r == 3 ? 5.5 : 10.5;
-  const int wr = (vague_cap + 63) / 64, units8 = (units + 7) / 8, tiles = (ret_cap + 15) / 16;
+  const int wr = (vague_cap + 63) / 64, units8 = (units + 7) / 8;
   const double bytes = 512.0 * units * ret_cap;
-  // largest slice, in tiles (LDS holds its logits)
-  const int most_tiles = (STAGED_LDS_LIMIT - ret_stream_lds(d.G, 0)) / (64 * d.G) / 8 * 8;
-  const int least = (tiles + most_tiles - 1) / most_tiles;
+  const int biggest = 16 * ret_stream_most(d.G, 8), least = (ret_cap + biggest - 1) / biggest;
   double best = 1e30;
   int best_n = 1, best_r = 0, last = 0;
   for (int rho = 1; rho <= kmax; ++rho) {
@@ -75,26 +91,57 @@ static void plan_pair(AttendPlan& p, const DevDesc& d, int units, int ret_cap, i
       int r = ret_cap > 0 ? 8 * (32 - (per_xcd + k - 1) / k) : 0;
       double t = k * wg;
       if (r > 0) {
-        t = std::max(t, SLICE + std::max(bytes / (RATE * r), bytes / CHIP));
+        t = std::max(t, ret_time(bytes, r));
       } else if (ret_cap > 0) {              // no CU is left: the slots first, on all of them
         r = 256;
-        t += 2.0 + SLICE + bytes / CHIP;
+        t += 2.0 + ret_time(bytes, r);
       }
       if (t < best - 1e-9) { best = t; best_n = n; best_r = r; }
     }
   }
   p.n_vslices = best_n;
-  // slices of the retained slots: a number that spreads evenly over the workgroups
-  int slices = 1;
-  double best_c = 1e30;
-  for (int s = std::max(least, 1), end = std::max(std::min({tiles, s + 31, most - best_n}), s); s <= end && best_r > 0; ++s) {
-    const double c = (double)((units * s + best_r - 1) / best_r) * ((double)((tiles + s - 1) / s) * 8192.0 / RATE + SLICE);
-    if (c < best_c - 1e-9) { best_c = c; slices = s; }
-  }
-  p.rslice_tokens = tiles > 0 ? (tiles + slices - 1) / slices * 16 : 16;
+  const int slices = best_r > 0 ? ret_slices(units, ret_cap, best_r, d.G, 8, most - best_n) : 1;
+  p.rslice_tokens = std::max(1, ((ret_cap + 15) / 16 + slices - 1) / slices) * 16;
   p.n_rslices = (ret_cap + p.rslice_tokens - 1) / p.rslice_tokens;
   p.n_ret_wgs = std::min(best_r, (units * p.n_rslices + 7) / 8 * 8);
-  p.pair_lds = std::max(p.lds_bytes, ret_cap > 0 ? ret_stream_lds(d.G, p.rslice_tokens) : 0);
+  p.pair_lds = std::max(p.lds_bytes, ret_cap > 0 ? ret_stream_lds(d.G, 8, p.rslice_tokens) : 0);
+}
+
+// The streaming kernel's launch, likewise: one of its workgroups per CU (16 waves, 17 us and 17 ns per token of its part).  It
+// takes as many parts as one turn holds; with enough slots to matter, fewer where the CUs that leaves them gain more.  us
+// from the first start to the last end of a call, slots and list before as two launches: eight heads, 40 units of 12307 + 4104
+// tokens 88 -> 65 (5 parts and 56 workgroups; 4 and 96: 69, 6 and 16: 150), 16 units of 32768 79 -> 55 (13 and 48; 12 and 64: 56,
+// 16 parts, the slots first: 65), 64 units 194 -> 167 (3 and 64; slots first 203), 8 of 900 34 -> 22.
+StreamPlan plan_stream(const DevDesc& d, int n_col, int units, int ret_cap, int vague_cap, int most) {
+  constexpr double FIXED = 17.0, TOKEN = 0.017;
+  StreamPlan p;
+  const int units8 = (units + 7) / 8;
+  const double bytes = 512.0 * units * ret_cap;
+  const int full = multi_staged_part_tokens(vague_cap, units), n_full = (vague_cap + full - 1) / full;
+  double best = 1e30;
+  int best_r = 0;
+  p.vslice_tokens = full;
+  for (int n = n_full; n >= 1 && n >= n_full / 2; --n) {
+    const int tokens = n == n_full ? full : (vague_cap + 16 * n - 1) / (16 * n) * 16;
+    const int per_xcd = units8 * ((vague_cap + tokens - 1) / tokens), turns = (per_xcd + 31) / 32;
+    int r = ret_cap > 0 ? 8 * (32 - (per_xcd + turns - 1) / turns) : 0;
+    double t = turns * (FIXED + TOKEN * tokens);
+    if (r > 0) {
+      t = std::max(t, ret_time(bytes, r));
+    } else if (ret_cap > 0) {
+      r = 256;
+      t += 2.0 + ret_time(bytes, r);
+    }
+    if (t < best - 1e-9) { best = t; best_r = r; p.vslice_tokens = tokens; }
+    if (ret_cap < 512) break;                // a few slots: first, on all CUs, they cost no more than a part less would
+  }
+  p.n_vslices = (vague_cap + p.vslice_tokens - 1) / p.vslice_tokens;
+  int slices = best_r > 0 ? ret_slices(units, ret_cap, best_r, n_col, 16, most - p.n_vslices) : 1;
+  p.rslice_tokens = std::max(1, ((ret_cap + 15) / 16 + slices - 1) / slices) * 16;
+  p.n_rslices = (ret_cap + p.rslice_tokens - 1) / p.rslice_tokens;
+  p.n_ret_wgs = std::min(best_r, (units * p.n_rslices + 7) / 8 * 8);
+  p.lds = std::max(multi_staged_lds(d, n_col), ret_cap > 0 ? ret_stream_lds(n_col, 16, p.rslice_tokens) : 0);
+  return p;
 }
 
 AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long vague_cap) {
@@ -157,8 +204,12 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
     p.rslice_tokens = slice_tokens_for(ret_cap, units);
     p.n_rslices = (int)((ret_cap + p.rslice_tokens - 1) / p.rslice_tokens);
     if (p.streamed) {
-      p.vslice_tokens = multi_staged_part_tokens(vague_cap, units);
-      p.n_vslices = (int)((vague_cap + p.vslice_tokens - 1) / p.vslice_tokens);
+      const int full = multi_staged_part_tokens(vague_cap, units);
+      p.stream = plan_stream(d, d.G, (int)units, (int)ret_cap, (int)vague_cap, p.n_rslices + (int)((vague_cap + full - 1) / full));
+      p.rslice_tokens = p.stream.rslice_tokens;
+      p.n_rslices = p.stream.n_rslices;
+      p.vslice_tokens = p.stream.vslice_tokens;
+      p.n_vslices = p.stream.n_vslices;
     } else if (p.pair) {
       plan_pair(p, d, (int)units, (int)ret_cap, (int)vague_cap, p.n_rslices + p.n_vslices);
     } else if (!p.staged && vague_cap > 0) {
@@ -669,10 +720,11 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
         if (e == hipSuccess) e = ew;
       }
     }
+  } else if (plan.streamed) {
+    // no causal mask in a decode call: every listed token is visible (n_ctx = null)
+    e = launch_attend_multi_staged(d, a, nullptr, 1, plan.stream, st);
   } else if (plan.mfma_retained) {
-    AttendArgs ar = a;
-    if (plan.streamed) ar.vague_cap = 0;       // the list's logits lie by tile: the others have rows for the retained slots only
-    e = launch_attend_retained(d, ar, plan.n_rslices, 0, 0, st);
+    e = launch_attend_retained(d, a, plan.n_rslices, 0, 0, st);
   } else {
     a.tok_limit = plan.staged ? a.ret_cap : a.ret_cap + a.vague_cap;
     dim3 grid(plan.n_rslices, units);
@@ -681,14 +733,10 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
     e = hipGetLastError();
   }
   // 2. the Vague list
-  if (side || plan.pair) {
+  if (side || plan.pair || plan.streamed) {
     // already launched above
   } else if (e == hipSuccess && plan.staged) {
     e = launch_attend_vague_staged(d, a, plan, st);
-  } else if (e == hipSuccess && plan.streamed && plan.n_vslices > 0) {
-    // no causal mask in a decode call: every listed token is visible (n_ctx = null)
-    e = launch_attend_multi_staged(d, a, nullptr, 1, plan.vslice_tokens, plan.n_vslices, plan.n_rslices,
-                                   plan.n_slices, a.part_o, a.part_ml, a.scratch_rec, a.tiles, st);
   } else if (e == hipSuccess && plan.mfma_retained && plan.n_vslices > 0) {
     a.slice_tokens = plan.vslice_tokens;
     a.tok_start = a.ret_cap;

@@ -283,8 +283,14 @@ MultiPlan attend_multi_plan(const DevDesc& d, int n_q, long long ret_cap, long l
   p.rslice_tokens = attend_slice_tokens(ret_cap, units);
   p.n_rslices = (int)((ret_cap + p.rslice_tokens - 1) / p.rslice_tokens);
   p.staged = vague_cap > 0 && multi_staged_applies(d, vague_cap);
-  if (p.staged) p.vslice_tokens = multi_staged_part_tokens(vague_cap, units);
-  else p.vslice_tokens = vague_cap > 0 ? attend_slice_tokens(vague_cap, units) : 64;
+  if (p.staged) {
+    p.vslice_tokens = multi_staged_part_tokens(vague_cap, units);
+    p.stream = plan_stream(d, ncol, (int)units, (int)ret_cap, (int)vague_cap,
+                           p.n_rslices + (int)((vague_cap + p.vslice_tokens - 1) / p.vslice_tokens));
+    p.rslice_tokens = p.stream.rslice_tokens;
+    p.n_rslices = p.stream.n_rslices;
+    p.vslice_tokens = p.stream.vslice_tokens;
+  } else p.vslice_tokens = vague_cap > 0 ? attend_slice_tokens(vague_cap, units) : 64;
   p.n_vslices = vague_cap > 0 ? (int)((vague_cap + p.vslice_tokens - 1) / p.vslice_tokens) : 0;
   p.n_slices = p.n_rslices + p.n_vslices;
   size_t off = 0;
@@ -317,15 +323,30 @@ static hipError_t launch_multi_n(const DevDesc& d, const AttendArgs& a0, const i
     e = launch_reconstruct(d, KVR_BF16, a0.sk, a0.sv, a0.vague_pos, a0.n_vague, a0.vague_cap, khat, vhat, st);
     if (e != hipSuccess) return e;
   }
+  AttendArgs a = a0;
+  a.part_o = (float*)(base + plan.off_part_o);
+  a.part_ml = (float*)(base + plan.off_part_ml);
+  a.logits = a0.scores ? (float*)(base + plan.off_logits) : nullptr;
+  a.n_slices = plan.n_slices;
+  a.n_q = n_q;
+  if (plan.staged) {
+    // the rebuilt-token areas of the workspace are free on this route: they hold the token records and
+    // the logits by tile (4 and 4 NCOL <= 64 of 256 bytes per token)
+    a.scratch_rec = khat;
+    a.tiles = (float*)vhat;
+    e = launch_attend_multi_staged(d, a, n_ctx, n_q, plan.stream, st);
+    return e == hipSuccess ? launch_attend_combine(d, a, NCOL, st) : e;
+  }
+  a.tiles = nullptr;
   DenseArgs da;
   da.q = (const bf16_t*)a0.q;
   da.n_ctx = n_ctx;
   da.n_q = n_q;
   da.n_slices = plan.n_slices;
-  da.tot_cap = plan.staged ? a0.ret_cap : a0.ret_cap + a0.vague_cap;      // staged: the list's logits lie by tile
-  da.part_o = (float*)(base + plan.off_part_o);
-  da.part_ml = (float*)(base + plan.off_part_ml);
-  da.logits = a0.scores ? (float*)(base + plan.off_logits) : nullptr;
+  da.tot_cap = a0.ret_cap + a0.vague_cap;
+  da.part_o = a.part_o;
+  da.part_ml = a.part_ml;
+  da.logits = a.logits;
   // retained slots
   da.k = (const bf16_t*)a0.k_ret;
   da.v = (const bf16_t*)a0.v_ret;
@@ -340,13 +361,7 @@ static hipError_t launch_multi_n(const DevDesc& d, const AttendArgs& a0, const i
   e = launch_dense<NCOL>(d, da, st);
   if (e != hipSuccess) return e;
   // rebuilt Vague tokens
-  if (a0.vague_cap > 0 && plan.staged) {
-    // the rebuilt-token areas of the workspace are free on this route: they hold the token records and
-    // the logits by tile (4 and 4 NCOL <= 64 of 256 bytes per token)
-    e = launch_attend_multi_staged(d, a0, n_ctx, n_q, plan.vslice_tokens, plan.n_vslices, plan.n_rslices,
-                                   plan.n_slices, da.part_o, da.part_ml, khat, vhat, st);
-    if (e != hipSuccess) return e;
-  } else if (a0.vague_cap > 0) {
+  if (a0.vague_cap > 0) {
     da.k = khat;
     da.v = vhat;
     if (in_kernel) {
@@ -363,13 +378,6 @@ static hipError_t launch_multi_n(const DevDesc& d, const AttendArgs& a0, const i
     e = launch_dense<NCOL>(d, da, st);
     if (e != hipSuccess) return e;
   }
-  AttendArgs a = a0;
-  a.part_o = da.part_o;
-  a.part_ml = da.part_ml;
-  a.logits = da.logits;
-  a.tiles = (a0.vague_cap > 0 && plan.staged) ? (float*)vhat : nullptr;
-  a.n_slices = plan.n_slices;
-  a.n_q = n_q;
   return launch_attend_combine(d, a, NCOL, st);
 }
 

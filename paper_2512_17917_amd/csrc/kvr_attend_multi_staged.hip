@@ -39,7 +39,7 @@
 // instructions per tile and phase), everything else 26.  Against records of eight bytes, logits token by token, in two arrays, and 538
 // vector instructions per tile instead of 400: call of four queries 254 -> 227, decode step of 5 x 8 units, 12706 tokens, eight heads,
 // two layers 204 -> 193.
-#include "kvr_staged.h"
+#include "kvr_ret_stream.h"
 
 #include <algorithm>
 
@@ -72,6 +72,8 @@ struct MultiStagedArgs {
                             // tile: [NCOL][its tokens in whole fours]), partial logits, then final ones (which the merge
                             // kernel reads here)
   uint32_t* rec;            // scratch [units, cap4]: token records
+  RetStream ret;            // the retained slots: the first n_ret_wgs workgroups
+  int n_ret_wgs;            // a multiple of 8 (XCDs)
 };
 
 // Token record: LDS row indices i * w + h_i < 1024 of the three rows at bits 0, 10 and 20, bit 31 = the sign two of the three
@@ -124,7 +126,12 @@ __global__ __launch_bounds__(MS_THREADS) void attend_multi_staged_kernel(DevDesc
   const float NEG_INF = -__builtin_inff();
   const int units = d.B * d.Hkv;
   // workgroup ids go round-robin to the 8 XCDs: all parts of a unit get ids that are equal modulo 8
-  const int lin = blockIdx.x;
+  if ((int)blockIdx.x < a.n_ret_wgs) {
+    // weights in three parts (as many bits as float32) but for 16 columns: two products as well
+    ret_stream_role<NCOL, (NCOL <= 8 ? 3 : 2), MS_WAVES>(d, a.ret, blockIdx.x, a.n_ret_wgs, smem);
+    return;
+  }
+  const int lin = blockIdx.x - a.n_ret_wgs;
   const int unit = ((lin >> 3) / a.n_parts) * 8 + (lin & 7);
   const int part_i = (lin >> 3) % a.n_parts;
   if (unit >= units) return;
@@ -448,7 +455,7 @@ int multi_staged_part_tokens(long long vague_cap, long long units) {
 }
 
 template <int NCOL>
-static hipError_t launch_n(const DevDesc& d, const MultiStagedArgs& a, hipStream_t st) {
+static hipError_t launch_n(const DevDesc& d, const MultiStagedArgs& a, int lds, hipStream_t st) {
   auto kern = attend_multi_staged_kernel<NCOL>;
   static std::once_flag once;
   static hipError_t attr_rc = hipSuccess;
@@ -457,19 +464,20 @@ static hipError_t launch_n(const DevDesc& d, const MultiStagedArgs& a, hipStream
                                   160 * 1024);
   });
   if (attr_rc != hipSuccess) return attr_rc;
-  const int lds = ms_chunk_lds(3 * d.w, NCOL) + 2 * MS_WAVES * 16 * (int)sizeof(float) + 16;
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
+  if (lds < multi_staged_lds(d, NCOL) || lds > STAGED_LDS_LIMIT) return hipErrorInvalidValue;
   const int units = d.B * d.Hkv;
   const int units_pad = (units + 7) / 8 * 8;
-  hipLaunchKernelGGL(kern, dim3(units_pad * a.n_parts), dim3(MS_THREADS), lds, st, d, a);
+  hipLaunchKernelGGL(kern, dim3(a.n_ret_wgs + units_pad * a.n_parts), dim3(MS_THREADS), lds, st, d, a);
   return hipGetLastError();
 }
 
+int multi_staged_lds(const DevDesc& d, int n_col) {
+  return ms_chunk_lds(3 * d.w, n_col) + 2 * MS_WAVES * 16 * (int)sizeof(float) + 16;
+}
+
 hipError_t launch_attend_multi_staged(const DevDesc& d, const AttendArgs& a0, const int32_t* n_ctx, int n_q,
-                                      int part_tokens, int n_parts, int slice0, int n_slices, float* part_o,
-                                      float* part_ml, void* scratch_rec, void* scratch_tiles,
-                                      hipStream_t st) {
-  if (!multi_staged_applies(d, a0.vague_cap) || n_parts < 1 || (part_tokens & 15) != 0) return hipErrorInvalidValue;
+                                      const StreamPlan& plan, hipStream_t st) {
+  if (!multi_staged_applies(d, a0.vague_cap) || plan.n_vslices < 1 || (plan.vslice_tokens & 15) != 0) return hipErrorInvalidValue;
   MultiStagedArgs a;
   a.q = (const bf16_t*)a0.q;
   a.n_ctx = n_ctx;
@@ -479,20 +487,23 @@ hipError_t launch_attend_multi_staged(const DevDesc& d, const AttendArgs& a0, co
   a.pos = a0.vague_pos;
   a.n_valid = a0.n_vague;
   a.cap = a0.vague_cap;
-  a.part_tokens = part_tokens;
-  a.n_parts = n_parts;
-  a.slice0 = slice0;
-  a.n_slices = n_slices;
-  a.part_o = part_o;
-  a.part_ml = part_ml;
-  a.tiles = (float*)scratch_tiles;
-  a.rec = (uint32_t*)scratch_rec;
+  a.part_tokens = plan.vslice_tokens;
+  a.n_parts = plan.n_vslices;
+  a.slice0 = plan.n_rslices;
+  a.n_slices = plan.n_rslices + plan.n_vslices;
+  a.part_o = a0.part_o;
+  a.part_ml = a0.part_ml;
+  a.tiles = a0.tiles;
+  a.rec = (uint32_t*)a0.scratch_rec;
+  a.ret = RetStream{(const bf16_t*)a0.q, (const bf16_t*)a0.k_ret, (const bf16_t*)a0.v_ret, a0.ret_pos, n_ctx, n_q, a0.ret_cap,
+                    plan.rslice_tokens, plan.n_rslices, a.n_slices, a0.ret_cap, a0.part_o, a0.part_ml, a0.logits};
+  a.n_ret_wgs = plan.n_ret_wgs;
   switch (n_q * d.G) {
-    case 1: return launch_n<1>(d, a, st);
-    case 2: return launch_n<2>(d, a, st);
-    case 4: return launch_n<4>(d, a, st);
-    case 8: return launch_n<8>(d, a, st);
-    case 16: return launch_n<16>(d, a, st);
+    case 1: return launch_n<1>(d, a, plan.lds, st);
+    case 2: return launch_n<2>(d, a, plan.lds, st);
+    case 4: return launch_n<4>(d, a, plan.lds, st);
+    case 8: return launch_n<8>(d, a, plan.lds, st);
+    case 16: return launch_n<16>(d, a, plan.lds, st);
     default: return hipErrorInvalidValue;
   }
 }

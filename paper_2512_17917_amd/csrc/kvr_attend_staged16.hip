@@ -562,8 +562,7 @@ template <int G, int R, int MODE>
 __global__ __launch_bounds__(ST_THREADS, 2) void attend_pair16_kernel(DevDesc d, AttendArgs a, int n_ret_wgs) {
   extern __shared__ __align__(16) unsigned char smem[];
   if ((int)blockIdx.x < n_ret_wgs) {
-    for (int item = blockIdx.x; item < d.B * d.Hkv * a.n_rslices; item += n_ret_wgs)
-      ret_stream_slice<G>(d, a, item / a.n_rslices, item % a.n_rslices, smem);
+    ret_stream_role<G, 3, ST_WAVES>(d, ret_stream_of(a), blockIdx.x, n_ret_wgs, smem);
     return;
   }
   // XCD-aware mapping: workgroup ids are dealt round-robin to the 8 XCDs, so all

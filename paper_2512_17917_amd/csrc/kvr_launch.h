@@ -10,6 +10,12 @@
 
 namespace kvr {
 
+// Launch of the streaming kernel of kvr_attend_multi: parts of the Vague lists, slices of the retained slots and workgroups for them; at most `most` parts and
+// slices of a unit.
+struct StreamPlan {
+  int vslice_tokens, n_vslices, rslice_tokens, n_rslices, n_ret_wgs, lds;
+};
+
 // How one kvr_attend_decode call is cut into workgroups.  Slices 0 .. n_rslices-1
 // cover the retained slots, slices n_rslices .. n_slices-1 the Vague index list.
 struct AttendPlan {
@@ -27,6 +33,7 @@ struct AttendPlan {
   bool pair;            // staged, and its launch takes the retained slots along (64- and 16-channel kernels)
   int n_ret_wgs;        // pair: workgroups for the retained slots
   int pair_lds;         // and its dynamic LDS (a workgroup of either kind)
+  StreamPlan stream;    // streamed
   size_t off_part_o, off_part_ml, off_logits, off_rec, off_tiles, total_bytes;
 };
 AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long vague_cap);
@@ -108,23 +115,25 @@ int attend_slice_tokens(long long tokens, long long units);
 // merge kernel alone: n_cols = partial columns per unit (G for one query, n_q * G for several)
 hipError_t launch_attend_combine(const DevDesc& d, const AttendArgs& a, int n_cols, hipStream_t st);
 
-// kvr_attend_multi: workspace carve-up and launch (bf16, n_q * G in {1, 2, 4, 8, 16})
-struct MultiPlan {
-  int rslice_tokens, n_rslices, vslice_tokens, n_vslices, n_slices;
-  bool staged;           // Vague list through the LDS-staged kernel (vslice_tokens / n_vslices = its parts)
-  size_t off_khat, off_vhat, off_part_o, off_part_ml, off_logits, total_bytes;
-};
 // LDS-staged kernel of kvr_attend_multi over the Vague list (bf16, r = 3, values signed only, 3 w <= 1024)
 bool multi_staged_applies(const DevDesc& d, long long vague_cap);
 int multi_staged_part_tokens(long long vague_cap, long long units);
+int multi_staged_lds(const DevDesc& d, int n_col);
+StreamPlan plan_stream(const DevDesc& d, int n_col, int units, int ret_cap, int vague_cap, int most);
 // its scratch: a record (4 bytes) and n_col floats for every listed token, each unit's in whole fours of tokens
 constexpr size_t multi_staged_scratch_tokens(long long units, long long vague_cap) {
   return (size_t)units * (size_t)((vague_cap + 3) / 4 * 4);
 }
+// a: the call's arguments, with the workspace's areas, slice counts and a.tiles (logits by tile) / a.scratch_rec (records)
 hipError_t launch_attend_multi_staged(const DevDesc& d, const AttendArgs& a, const int32_t* n_ctx, int n_q,
-                                      int part_tokens, int n_parts, int slice0, int n_slices, float* part_o,
-                                      float* part_ml, void* scratch_rec, void* scratch_tiles,
-                                      hipStream_t st);
+                                      const StreamPlan& plan, hipStream_t st);
+// kvr_attend_multi: workspace carve-up and launch (bf16, n_q * G in {1, 2, 4, 8, 16})
+struct MultiPlan {
+  int rslice_tokens, n_rslices, vslice_tokens, n_vslices, n_slices;
+  bool staged;           // Vague list through the LDS-staged kernel (its launch: stream)
+  StreamPlan stream;
+  size_t off_khat, off_vhat, off_part_o, off_part_ml, off_logits, total_bytes;
+};
 MultiPlan attend_multi_plan(const DevDesc& d, int n_q, long long ret_cap, long long vague_cap);
 hipError_t launch_attend_multi(const DevDesc& d, const AttendArgs& a, const int32_t* n_ctx, int n_q,
                                const MultiPlan& plan, void* ws, hipStream_t st);
@@ -164,9 +173,16 @@ inline bool staged64_applies(const DevDesc& d) {
 }
 static_assert(staged64_lds(1000 / 3, 4) <= STAGED_LDS_LIMIT && staged64_lds(1024 / 3, 2) <= STAGED_LDS_LIMIT, "LDS");
 constexpr int STAGED64_KMAX = 25;                 // wave-rounds (64 tokens) per wave: what 256 registers hold
-// LDS of a workgroup of its launch that takes retained slots: the waves' sums, their statistics, the logits of a slice (a
-// tile of 16 tokens for every wave at a time)
-constexpr int ret_stream_lds(int G, int tokens) { return 8 * G * D * 4 + 2 * 8 * 4 * 4 + (tokens + 127) / 128 * 128 * G * 4; }
+// LDS of a workgroup (8 or 16 waves) of such a launch that takes retained slots: the waves' statistics, then the logits of a
+// slice (a tile of 16 tokens for every wave at a time) and in the same place their sums
+constexpr int ret_stream_lds(int n_col, int waves, int tokens) {
+  const int logits = (tokens + 16 * waves - 1) / (16 * waves) * (16 * waves), sums = waves * D;
+  return 2 * waves * 16 * 4 + n_col * 4 * (logits > sums ? logits : sums);
+}
+// and the largest slice that fits, in tiles of 16 tokens
+constexpr int ret_stream_most(int n_col, int waves) {
+  return (STAGED_LDS_LIMIT - 2 * waves * 16 * 4) / (n_col * 4 * 16 * waves) * waves;
+}
 hipError_t launch_attend_pair64(const DevDesc& d, const AttendArgs& a, const AttendPlan& plan, hipStream_t st);
 
 hipError_t launch_select(const DevDesc& d, const float* scores, long long n_cap, int32_t* ret_pos,
