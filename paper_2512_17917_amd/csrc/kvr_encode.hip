@@ -12,6 +12,8 @@
 //     token ordinals of each (unit, row) by slot (stable, so list order survives
 //     inside a slot), then one wave per (unit, row, slot) adds its segment
 //     sequentially, lanes across channels.
+#include <mutex>
+
 #include "kvr_launch.h"
 #include "kvr_update.h"
 
@@ -90,6 +92,12 @@ __global__ __launch_bounds__(256) void encode_hash_kernel(
 // the top bit (source rows are below 2^30).
 constexpr int SORT_MAX_SEGS = 16;
 constexpr int SORT_LDS_INTS = 15360;       // 60 KB of table: segs * w + w <= this
+// The records are put in place in LDS where they fit beside the table (16 segments, 273 slots: 36320 tokens), and leave in
+// order: a store of 64 scattered dwords is 64 requests.  64 units x 3 rows x 25395 tokens: 55 us with a drain of memory per
+// chunk (a volatile cursor), 51 without, 31.7 with the records in LDS; compressing 8 x 8 units of 32768 tokens 542 -> 517 us,
+// 128 units 1011 -> 944, 32 units of 45000, four rows 521 -> 491.  Longer lists go straight to memory (16 units of 131072
+// 899 -> 859 from the cursors alone).
+constexpr size_t SORT_GATHER_LDS = 160 * 1024;
 
 static int sort_segments(int w) {
   int segs = (SORT_LDS_INTS - w) / w;
@@ -98,14 +106,17 @@ static int sort_segments(int w) {
   return segs;
 }
 
+template <bool GATHER>
 __global__ __launch_bounds__(SORT_MAX_SEGS * WAVE) void encode_sort_kernel(
     DevDesc d, const int32_t* __restrict__ count, int cap, const int32_t* __restrict__ ws_bucket,
     const int32_t* __restrict__ src_slot, const int32_t* __restrict__ tok_pos,
     int32_t* __restrict__ ws_order, int32_t* __restrict__ ws_start) {
-  extern __shared__ int s_tab[];             // [segs][w] counts / cursors, then [w] totals / starts
+  extern __shared__ int s_tab[];             // [segs][w] counts / cursors, [w] totals / starts, [1]; GATHER: [cap] records
   const int w = d.w;
   const int segs = blockDim.x / WAVE;
   int* s_tot = s_tab + segs * w;
+  int* s_end = s_tot + w;                    // tokens that have a place (one with a bad source row has none)
+  int* s_out = s_end + 1;
   const int ur = blockIdx.x;                 // unit * r + row
   const int unit = ur / d.r, row = ur % d.r;
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
@@ -153,7 +164,7 @@ __global__ __launch_bounds__(SORT_MAX_SEGS * WAVE) void encode_sort_kernel(
       if (s < w) { s_tot[s] = carry + incl - c; start[s] = carry + incl - c; }
       carry += __shfl(incl, WAVE - 1);
     }
-    if (lane == 0) start[w] = carry;
+    if (lane == 0) { start[w] = carry; *s_end = carry; }
   }
   __syncthreads();
   for (int s = tid; s < w; s += blockDim.x) {
@@ -161,48 +172,67 @@ __global__ __launch_bounds__(SORT_MAX_SEGS * WAVE) void encode_sort_kernel(
     for (int g = 0; g < segs; ++g) s_tab[g * w + s] += st;
   }
   __syncthreads();
-  volatile int* cur = mine;
-  constexpr int NA = 4;                       // 64-token chunks whose loads are requested together
+  // bits that tell the slots and "no token" (-1, all ones) apart: w < 2^bits, 14 at most
+  const int bits = 32 - __builtin_clz((unsigned)w);
+  constexpr int NA = 4;                       // 64-token chunks whose loads are requested together, one group ahead
+  int s_n[NA], slot_n[NA], pos_n[NA];
+  auto request = [&](int e00) {               // unconditional: past the segment its last token again (cap > 0)
+#pragma unroll
+    for (int u = 0; u < NA; ++u) {
+      const int e = max(min(e00 + u * WAVE + lane, hi - 1), 0);
+      s_n[u] = bk[e];
+      slot_n[u] = src_slot[(size_t)unit * cap + e];
+      pos_n[u] = tok_pos[(size_t)unit * cap + e];
+    }
+  };
+  request(lo);
   for (int e00 = lo; e00 < hi; e00 += NA * WAVE) {
     int s4[NA], slot4[NA], pos4[NA];
 #pragma unroll
     for (int u = 0; u < NA; ++u) {
-      const int e = e00 + u * WAVE + lane;
-      const bool in = e < hi;
-      s4[u] = in ? bk[e] : -1;
-      slot4[u] = in ? src_slot[(size_t)unit * cap + e] : 0;
-      pos4[u] = in ? tok_pos[(size_t)unit * cap + e] : 0;
+      s4[u] = s_n[u];
+      slot4[u] = slot_n[u];
+      pos4[u] = pos_n[u];
+      // arrived here, ahead of the next group's requests: a wait for a load drains the stores too
+      asm volatile("" : "+v"(s4[u]), "+v"(slot4[u]), "+v"(pos4[u]));
     }
+    request(e00 + NA * WAVE);
 #pragma unroll
     for (int u = 0; u < NA; ++u) {
       if (e00 + u * WAVE >= hi) break;        // uniform over the wave
-      const int s = s4[u];
+      const int s = (e00 + u * WAVE + lane < hi) ? s4[u] : -1;
       // what the accumulation needs of this token, so that it does not have to chase
       // the ordinal: its source row and, in the top bit, whether g_row(J) = -1
-      int rec = 0;
-      if (s >= 0) {
-        rec = slot4[u];
-        if (sign_neg(d, row, pos4[u])) rec |= (int)0x80000000u;
-      }
-      // lanes with the same slot: one ballot per bit of the slot number (13 bits cover
-      // the largest w of this path; -1 = no token gets a bit pattern of its own)
-      unsigned long long same = ~0ull;
-      const unsigned su = (unsigned)s & 0x3fffu;
+      const int rec = slot4[u] | (sign_neg(d, row, pos4[u]) ? (int)0x80000000u : 0);
+      // lanes with the same slot: one ballot per bit of the slot number
+      uint32_t same_lo = ~0u, same_hi = ~0u;
 #pragma unroll
       for (int bit = 0; bit < 14; ++bit) {
-        const bool one = (su >> bit) & 1u;
-        const unsigned long long bal = __ballot(one);
-        same &= one ? bal : ~bal;
+        if (bit >= bits) break;               // uniform
+        const uint32_t one = (uint32_t)((int)((uint32_t)s << (31 - bit)) >> 31);      // all ones or 0
+        const unsigned long long bal = __ballot(one != 0u);
+        same_lo &= ~((uint32_t)bal ^ one);
+        same_hi &= ~((uint32_t)(bal >> 32) ^ one);
       }
+      const unsigned long long same = ((unsigned long long)same_hi << 32) | same_lo;
       const int lower = __popcll(same & ((1ull << lane) - 1ull));
       const bool higher = (lane < WAVE - 1) && ((same >> (lane + 1)) != 0ull);
+      // the cursors are read here and moved on below by one lane per slot: LDS accesses of one wave keep their order,
+      // and wavefront-scope atomics keep the compiler to it (volatile makes them flat accesses that drain memory)
       if (s >= 0) {
-        const int dst = cur[s] + lower;
-        order[dst] = rec;
-        if (!higher) cur[s] = dst + 1;     // read above, written here by one lane per slot: same wave, program order
+        const int dst = __hip_atomic_load(&mine[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) + lower;
+        if (GATHER) s_out[dst] = rec;
+        else order[dst] = rec;
+        if (!higher) __hip_atomic_store(&mine[s], dst + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
       }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
     }
+  }
+  if (GATHER) {
+    __syncthreads();
+    const int placed = *s_end;
+    for (int i = tid; i < placed; i += blockDim.x) order[i] = s_out[i];
   }
 }
 
@@ -306,9 +336,20 @@ static hipError_t launch_t(const DevDesc& d, const void* k_src, const void* v_sr
   if (e != hipSuccess) return e;
   {
     const int segs = sort_segments(d.w);
-    hipLaunchKernelGGL(encode_sort_kernel, dim3(units * d.r), dim3(segs * WAVE),
-                       (size_t)(segs + 1) * d.w * sizeof(int), st, d, count, cap, ws_bucket, src_slot, tok_pos,
-                       ws_order, ws_start);
+    const size_t tab = ((size_t)(segs + 1) * d.w + 1) * sizeof(int), gather = tab + (size_t)cap * sizeof(int);
+    static std::once_flag once;
+    static hipError_t attr_rc = hipSuccess;
+    std::call_once(once, [&]() {
+      attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(encode_sort_kernel<true>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    });
+    if (attr_rc != hipSuccess) return attr_rc;
+    if (gather <= SORT_GATHER_LDS)
+      hipLaunchKernelGGL(encode_sort_kernel<true>, dim3(units * d.r), dim3(segs * WAVE), gather, st, d, count, cap,
+                         ws_bucket, src_slot, tok_pos, ws_order, ws_start);
+    else
+      hipLaunchKernelGGL(encode_sort_kernel<false>, dim3(units * d.r), dim3(segs * WAVE), tab, st, d, count, cap,
+                         ws_bucket, src_slot, tok_pos, ws_order, ws_start);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
