@@ -122,11 +122,12 @@ typedef struct kvr_desc {
  * every field may be NULL, and a NULL kvr_attend_opts* means all NULL).
  *   side_stream, fork_event, join_event: a second hipStream_t of default priority
  *       (not `stream` itself) and two hipEvent_t (timing may be disabled), created
- *       and owned by the caller; all three or none.  With them, and when the call is
- *       large enough for it to pay (bf16, the Vague list long enough to fill the
- *       chip twice over) and a compute unit has room for both kernels, the one that
- *       streams the retained tokens runs on side_stream next to the one that
- *       rebuilds the Vague tokens on `stream`:
+ *       and owned by the caller; all three or none.  Most calls make
+ *       one launch for the retained and the Vague tokens and leave them alone.
+ *       Where the two are separate kernels (bf16, a sketch too wide for the kernels
+ *       that take both), the Vague list is long enough to fill the chip twice over
+ *       and a compute unit has room for both, the one that streams the retained
+ *       tokens runs on side_stream next to the one that rebuilds the Vague tokens:
  *       fork_event is recorded on `stream` and awaited by side_stream, join_event is
  *       recorded on side_stream and awaited by `stream` before the merge kernel, on
  *       every path including errors, so the call stays ordered on `stream` and the

@@ -244,15 +244,12 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
 
 int attend_side_lds(const DevDesc& d, const AttendPlan& p) {
   if (!p.staged || !p.mfma_retained) return 0;
-  // Registers: two waves of the staged kernel and one of the retained kernel's capped form (128) share a SIMD's 512.  The
-  // 64-channel kernel takes 192, the 16-channel kernel 192 with three rows and 238 with four, the general kernel up to 192
-  // but for four rows and four heads.  Where they do not fit, the retained kernel only finds room where a workgroup has just
-  // ended: 131072 tokens, four rows 571 us side by side, 511 back to back; 4400 rows in four, four heads 1105 and 1087.
-  // Where they do: three rows of 1092 slots, 64 units 792 against 910 us, 1500 slots (general kernel), 32 units 907 / 947.
+  // Registers: two waves of a staged kernel of up to 192 and one of the retained kernel's capped form (128) share a SIMD's
+  // 512.  Four rows and four heads take more in the general kernel, four rows always in the 16-channel kernel, and the retained
+  // kernel only finds room where a workgroup has just ended: 4400 rows in four, four heads 1105 us side by side, 1087 back to
+  // back.  Where they fit: three rows of 1500 slots (general kernel), 32 units 907 / 947.
   if (d.r != 3 && (staged16_applies(d) || d.G == 4)) return 0;
-  // LDS: room for a slice's logits, or for 512 tokens' and the sums.  16 x 8 units, four heads, 312 slots per row 352 us a
-  // call against 417 back to back, 313 slots 483 against 420 (forked all the same, the retained kernel has the chip to
-  // itself with a workgroup per CU); 300 slots, slices of 832 tokens: 346 us in pieces of 512, 437 where both do not fit.
+  // LDS: room for a slice's logits, or for 512 tokens' and the sums.
   constexpr int UNIT = 1280;                   // LDS is handed out in these
   const int room = (STAGED_LDS_LIMIT / UNIT - (p.lds_bytes + UNIT - 1) / UNIT) * UNIT -
                    2 * 4 * d.G * (int)sizeof(float);                               // statistics of the four waves
@@ -691,10 +688,9 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
   a.slice_tokens = plan.rslice_tokens;
   a.tok_start = 0;
   a.slice0 = 0;
-  // The retained kernel is bound by HBM, the staged kernel by the vector ALUs and
-  // LDS, and their registers and LDS fit on a CU together: when the caller lends a
-  // second stream they run side by side, the retained kernel on that stream, forked
-  // from and joined back into `st` with the caller's two events.
+  // Where the general staged kernel takes the list (the others hold the slots in their own launch): the retained kernel is
+  // bound by HBM, the staged kernel by the vector ALUs and LDS, so when the caller lends a second stream they run side by
+  // side, the retained kernel on that stream, forked from and joined back into `st` with the caller's two events.
   // Only when the staged kernel fills the chip several times over: a launch of a few workgroups is
   // short, the fork and join then cost more than the overlap saves, and the retained kernel is better
   // off with a launch as wide as its item count than with one workgroup per CU.

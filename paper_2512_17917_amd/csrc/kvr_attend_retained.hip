@@ -18,13 +18,12 @@
 // per SIMD); the logits wait in LDS and leave together, 16 bytes a lane.  32 units x 29492 slots, 4 heads: 107 ->
 // 102 us = 4.7 TB/s (a large copy reaches 5.1); 40 units x 4104 slots, 8 heads: 32.4 -> 30.0 us.  Next to a staged kernel
 // there are no registers for it; the logits wait in what LDS the staged kernel leaves, of a whole slice or of 512 tokens
-// at a time (16 x 8 units of 32768 tokens, three layers, on a second stream that overlaps badly: 926 us a step with whole
-// slices of 768 tokens, 934 with 512 tokens at a time, 942 with every tile's logits stored from the registers).
+// at a time.
 //
 // A workgroup walks over (unit, slice) items with a grid stride, so the launch
 // can be as wide as the item count (stand-alone: many workgroups per CU hide the
-// HBM latency) or as narrow as one workgroup per CU (next to the staged kernel,
-// whose registers and LDS leave room for exactly that).
+// HBM latency) or as narrow as one workgroup per CU (next to the general staged
+// kernel, whose registers and LDS leave room for exactly that).
 #include "kvr_launch.h"
 
 namespace kvr {

@@ -37,7 +37,8 @@ struct AttendPlan {
   size_t off_part_o, off_part_ml, off_logits, off_rec, off_tiles, total_bytes;
 };
 AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long vague_cap);
-// Dynamic LDS of the retained kernel's capped form next to the plan's staged kernel; 0 = a CU has no room for both.
+// Dynamic LDS of the retained kernel's capped form next to the plan's staged kernel; 0 = a CU has no room for both.  (Used
+// where the general kernel takes the list; the others have the slots in their own launch.)
 int attend_side_lds(const DevDesc& d, const AttendPlan& p);
 
 struct AttendArgs {
