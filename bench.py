@@ -38,17 +38,17 @@ HBM_PEAK_GBS = 8000.0           # MI355X published HBM3E bandwidth
 OFFLINE_COUNTERS = {
     "c4": {
         # bytes per kvr_attend_decode call at the memory side of the L2: read requests priced by their size
-        # (32 / 64 / 128 B request counters) + WRITE_SIZE, summed over the call's three kernels
-        "traffic": 782.6e6,
-        "traffic_note": "off-line counter reading (profiles/attend_call_c4_hbm_traffic.txt): 681.0 MB read "
+        # (32 / 64 / 128 B request counters) + WRITE_SIZE, summed over the call's two kernels
+        "traffic": 782.1e6,
+        "traffic_note": "off-line counter reading (profiles/attend_call_c4_hbm_traffic.txt): 688.0 MB read "
                         "(TCC_EA0_RDREQ by request size; FETCH_SIZE prices this chip's 128-byte requests at 64 "
-                        "bytes and reads half of that) + 101.6 MB written (WRITE_SIZE), retained + staged + merge "
-                        "kernel of one call; the 199 MB above the algorithmic bytes are the logits handed from the "
+                        "bytes and reads half of that) + 94.1 MB written (WRITE_SIZE), attention + merge "
+                        "kernel of one call; the 198 MB above the algorithmic bytes are the logits handed from the "
                         "attention kernels to the score pass, the slice partials and whole lines pulled by "
                         "4-byte score accesses",
-        "alu": {"file": "profiles/attend_kernels_c4_sq_counters.txt", "kernel": "attend_vague_staged64_kernel<4>",
-                "valu_insts_per_launch": 59644800.0, "waves_per_launch": 10240,
-                "valu_busy": 0.70, "lds_busy": 0.45, "lds_bank_conflict_share": 0.47},
+        "alu": {"file": "profiles/attend_kernels_c4_sq_counters.txt", "kernel": "attend_pair64_kernel<4>",
+                "valu_insts_per_launch": 62467769.3, "waves_per_launch": 3584,
+                "valu_busy": 0.66, "lds_busy": 0.37, "lds_bank_conflict_share": 0.45},
     },
 }
 # plain vector ALU peak: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz lane-operations per second (the 157.3 TFLOP/s
@@ -370,11 +370,11 @@ def run_workload(args):
         },
         "roofline": {
             "kernel": "one kvr_attend_decode call = attention over retained + reconstructed tokens of one layer, all "
-                      "units: attend_retained_shared_kernel (streams the retained rows; on the lent side stream) next "
-                      "to attend_vague_staged64_kernel (rebuilds the Vague tokens from the sketch in LDS), then "
+                      "units: attend_pair64_kernel (one launch: workgroups that rebuild the Vague tokens from the "
+                      "sketch in LDS, and workgroups that stream the retained rows), then "
                       "attend_combine_kernel (merge + score accumulation); HIP events on the caller's stream before "
-                      "the first and after the last of them" if wl.name in ("c4",) and side is not None else
-                      "one kvr_attend_decode call (retained-slot kernel, Vague-list kernel, merge kernel of one "
+                      "the first and after the last of them" if wl.name in ("c4",) else
+                      "one kvr_attend_decode call (retained slots, Vague list and merge of one "
                       "layer, all units); HIP events on the caller's stream before the first and after the last",
             "bound": "hbm",
             "achieved": achieved,
@@ -385,7 +385,7 @@ def run_workload(args):
             "traffic_note": off.get("traffic_note", "not measured for this workload"),
             "algorithmic_bytes_per_launch": bytes_launch,
             "algorithmic_bytes_note": "retained K,V + sketch K,V + Vague index list + scores read and written + q, out: "
-                                      "all of it moved by the three kernels inside the timed region",
+                                      "all of it moved by the two kernels inside the timed region",
             "avg_launch_ms": avg_kern_s * 1e3,
             "launches_timed": len(kern_ms),
             "launch_sampling": f"HIP events on every {ev_every}. call of the timed region",
