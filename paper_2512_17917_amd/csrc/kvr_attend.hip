@@ -44,7 +44,7 @@ static double ret_time(double bytes, int n_wgs) {
 // Slices of a unit's retained slots for n_wgs workgroups of `waves` waves: a number that spreads evenly over them, of slices as
 // large as LDS allows and at most `most`.  40 units of 4104 slots, eight heads, 56 workgroups: one slice a unit (16 workgroups
 // with none) 51 us, four 57.
-static int ret_slices(int units, int ret_cap, int n_wgs, int n_col, int waves, int most) {
+static int ret_slices(long long units, int ret_cap, int n_wgs, int n_col, int waves, int most) {
   const int tiles = (ret_cap + 15) / 16, biggest = ret_stream_most(n_col, waves), least = std::max(1, (tiles + biggest - 1) / biggest);
   int slices = least;
   double best = 1e30;
@@ -71,11 +71,12 @@ static int ret_slices(int units, int ret_cap, int n_wgs, int n_col, int waves, i
 // 29492 206 -> 174 (13 and 48; 12 and 64: 191, 14 and 32: 198), 24 units of 70000 tokens in all 164 -> 132, 8 of 42000 65 -> 50; four
 // rows: 32 units of 101580 + 29492 520 -> 476 .. 506 (14 and 32; 21 and 32: 499), 16 of 60000 in all 151 -> 125, 128 of 9000, one head
 // 130 -> 122 (slots first; 3 and 64: 142).
-static void plan_pair(AttendPlan& p, const DevDesc& d, int units, int ret_cap, int vague_cap, int most) {
+static void plan_pair(AttendPlan& p, const DevDesc& d, long long units, int ret_cap, int vague_cap, int most) {
   const bool s64 = p.ch == 64;
   const int kmax = s64 ? STAGED64_KMAX : staged16_kmax(d.r);
   const double fixed = s64 ? 6.5 + 0.018 * d.w : 8.5 + 0.018 * d.r * d.w, round = s64 ? 3.0 + 0.5 * d.G : d.r == 3 ? 5.5 : 10.5;
-  const int wr = (vague_cap + 63) / 64, units8 = (units + 7) / 8;
+  const int wr = (vague_cap + 63) / 64;
+  const long long units8 = (units + 7) / 8;
   const double bytes = 512.0 * units * ret_cap;
   const int biggest = 16 * ret_stream_most(d.G, 8), least = (ret_cap + biggest - 1) / biggest;
   double best = 1e30;
@@ -86,10 +87,10 @@ static void plan_pair(AttendPlan& p, const DevDesc& d, int units, int ret_cap, i
     last = n;
     if (n + least > most && rho < kmax) continue;
     const double wg = fixed + round * ((wr + 8 * n - 1) / (8 * n));
-    const int per_xcd = units8 * n, turns = (per_xcd + 31) / 32;
-    for (int k = turns; k <= turns + 2; ++k) {
-      int r = ret_cap > 0 ? 8 * (32 - (per_xcd + k - 1) / k) : 0;
-      double t = k * wg;
+    const long long per_xcd = units8 * n, turns = (per_xcd + 31) / 32;
+    for (long long k = turns; k <= turns + 2; ++k) {
+      int r = ret_cap > 0 ? 8 * (32 - (int)((per_xcd + k - 1) / k)) : 0;
+      double t = (double)k * wg;
       if (r > 0) {
         t = std::max(t, ret_time(bytes, r));
       } else if (ret_cap > 0) {              // no CU is left: the slots first, on all of them
@@ -103,7 +104,7 @@ static void plan_pair(AttendPlan& p, const DevDesc& d, int units, int ret_cap, i
   const int slices = best_r > 0 ? ret_slices(units, ret_cap, best_r, d.G, 8, most - best_n) : 1;
   p.rslice_tokens = std::max(1, ((ret_cap + 15) / 16 + slices - 1) / slices) * 16;
   p.n_rslices = (ret_cap + p.rslice_tokens - 1) / p.rslice_tokens;
-  p.n_ret_wgs = std::min(best_r, (units * p.n_rslices + 7) / 8 * 8);
+  p.n_ret_wgs = (int)std::min<long long>(best_r, (units * p.n_rslices + 7) / 8 * 8);
   p.pair_lds = std::max(p.lds_bytes, ret_cap > 0 ? ret_stream_lds(d.G, 8, p.rslice_tokens) : 0);
 }
 
@@ -112,10 +113,10 @@ static void plan_pair(AttendPlan& p, const DevDesc& d, int units, int ret_cap, i
 // from the first start to the last end of a call, slots and list before as two launches: eight heads, 40 units of 12307 + 4104
 // tokens 88 -> 65 (5 parts and 56 workgroups; 4 and 96: 69, 6 and 16: 150), 16 units of 32768 79 -> 55 (13 and 48; 12 and 64: 56,
 // 16 parts, the slots first: 65), 64 units 194 -> 167 (3 and 64; slots first 203), 8 of 900 34 -> 22.
-StreamPlan plan_stream(const DevDesc& d, int n_col, int units, int ret_cap, int vague_cap, int most) {
+StreamPlan plan_stream(const DevDesc& d, int n_col, long long units, int ret_cap, int vague_cap, int most) {
   constexpr double FIXED = 17.0, TOKEN = 0.017;
   StreamPlan p;
-  const int units8 = (units + 7) / 8;
+  const long long units8 = (units + 7) / 8;
   const double bytes = 512.0 * units * ret_cap;
   const int full = multi_staged_part_tokens(vague_cap, units), n_full = (vague_cap + full - 1) / full;
   double best = 1e30;
@@ -123,9 +124,9 @@ StreamPlan plan_stream(const DevDesc& d, int n_col, int units, int ret_cap, int 
   p.vslice_tokens = full;
   for (int n = n_full; n >= 1 && n >= n_full / 2; --n) {
     const int tokens = n == n_full ? full : (vague_cap + 16 * n - 1) / (16 * n) * 16;
-    const int per_xcd = units8 * ((vague_cap + tokens - 1) / tokens), turns = (per_xcd + 31) / 32;
-    int r = ret_cap > 0 ? 8 * (32 - (per_xcd + turns - 1) / turns) : 0;
-    double t = turns * (FIXED + TOKEN * tokens);
+    const long long per_xcd = units8 * ((vague_cap + tokens - 1) / tokens), turns = (per_xcd + 31) / 32;
+    int r = ret_cap > 0 ? 8 * (32 - (int)((per_xcd + turns - 1) / turns)) : 0;
+    double t = (double)turns * (FIXED + TOKEN * tokens);
     if (r > 0) {
       t = std::max(t, ret_time(bytes, r));
     } else if (ret_cap > 0) {
@@ -139,7 +140,7 @@ StreamPlan plan_stream(const DevDesc& d, int n_col, int units, int ret_cap, int 
   int slices = best_r > 0 ? ret_slices(units, ret_cap, best_r, n_col, 16, most - p.n_vslices) : 1;
   p.rslice_tokens = std::max(1, ((ret_cap + 15) / 16 + slices - 1) / slices) * 16;
   p.n_rslices = (ret_cap + p.rslice_tokens - 1) / p.rslice_tokens;
-  p.n_ret_wgs = std::min(best_r, (units * p.n_rslices + 7) / 8 * 8);
+  p.n_ret_wgs = (int)std::min<long long>(best_r, (units * p.n_rslices + 7) / 8 * 8);
   p.lds = std::max(multi_staged_lds(d, n_col), ret_cap > 0 ? ret_stream_lds(n_col, 16, p.rslice_tokens) : 0);
   return p;
 }
@@ -205,13 +206,13 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
     p.n_rslices = (int)((ret_cap + p.rslice_tokens - 1) / p.rslice_tokens);
     if (p.streamed) {
       const int full = multi_staged_part_tokens(vague_cap, units);
-      p.stream = plan_stream(d, d.G, (int)units, (int)ret_cap, (int)vague_cap, p.n_rslices + (int)((vague_cap + full - 1) / full));
+      p.stream = plan_stream(d, d.G, units, (int)ret_cap, (int)vague_cap, p.n_rslices + (int)((vague_cap + full - 1) / full));
       p.rslice_tokens = p.stream.rslice_tokens;
       p.n_rslices = p.stream.n_rslices;
       p.vslice_tokens = p.stream.vslice_tokens;
       p.n_vslices = p.stream.n_vslices;
     } else if (p.pair) {
-      plan_pair(p, d, (int)units, (int)ret_cap, (int)vague_cap, p.n_rslices + p.n_vslices);
+      plan_pair(p, d, units, (int)ret_cap, (int)vague_cap, p.n_rslices + p.n_vslices);
     } else if (!p.staged && vague_cap > 0) {
       p.vslice_tokens = slice_tokens_for(vague_cap, units);
       p.n_vslices = (int)((vague_cap + p.vslice_tokens - 1) / p.vslice_tokens);

@@ -285,7 +285,7 @@ MultiPlan attend_multi_plan(const DevDesc& d, int n_q, long long ret_cap, long l
   p.staged = vague_cap > 0 && multi_staged_applies(d, vague_cap);
   if (p.staged) {
     p.vslice_tokens = multi_staged_part_tokens(vague_cap, units);
-    p.stream = plan_stream(d, ncol, (int)units, (int)ret_cap, (int)vague_cap,
+    p.stream = plan_stream(d, ncol, units, (int)ret_cap, (int)vague_cap,
                            p.n_rslices + (int)((vague_cap + p.vslice_tokens - 1) / p.vslice_tokens));
     p.rslice_tokens = p.stream.rslice_tokens;
     p.n_rslices = p.stream.n_rslices;

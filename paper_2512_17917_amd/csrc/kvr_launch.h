@@ -120,7 +120,7 @@ hipError_t launch_attend_combine(const DevDesc& d, const AttendArgs& a, int n_co
 bool multi_staged_applies(const DevDesc& d, long long vague_cap);
 int multi_staged_part_tokens(long long vague_cap, long long units);
 int multi_staged_lds(const DevDesc& d, int n_col);
-StreamPlan plan_stream(const DevDesc& d, int n_col, int units, int ret_cap, int vague_cap, int most);
+StreamPlan plan_stream(const DevDesc& d, int n_col, long long units, int ret_cap, int vague_cap, int most);
 // its scratch: a record (4 bytes) and n_col floats for every listed token, each unit's in whole fours of tokens
 constexpr size_t multi_staged_scratch_tokens(long long units, long long vague_cap) {
   return (size_t)units * (size_t)((vague_cap + 3) / 4 * 4);

@@ -11,15 +11,20 @@ PROBE = r"""
 #include "kvr_launch.h"
 // per input line: units heads rows slots retained vague -> LDS of the retained kernel next to the staged one (0: not side
 // by side), of the staged kernel, of the retained kernel alone,
-// parts of the Vague list, channels per phase of the staged kernel (0: the list is not staged)
+// parts of the Vague list, channels per phase of the staged kernel (0: the list is not staged); then slices of the retained
+// slots and their tokens, workgroups for them in the list's launch, LDS of that launch (0: a launch of their own), tokens that
+// the parts hold at most, bytes of workspace
 int main() {
   int units, G, r, w, ret, vague;
   while (std::scanf("%d %d %d %d %d %d", &units, &G, &r, &w, &ret, &vague) == 6) {
     kvr::DevDesc d = {};
     d.B = 1; d.Hkv = units; d.Hq = units * G; d.G = G; d.r = r; d.w = w; d.sign_mask = 2;
     const kvr::AttendPlan p = kvr::attend_plan(d, KVR_BF16, ret, vague);
-    std::printf("%d %d %d %d %d\n", kvr::attend_side_lds(d, p), p.lds_bytes,
-                kvr::retained_lds(G, p.rslice_tokens), p.n_vslices, p.staged ? p.ch : 0);
+    const long long part = p.streamed ? p.vslice_tokens : p.ch == 64 ? 512 * kvr::STAGED64_KMAX : 512 * kvr::staged16_kmax(r);
+    std::printf("%d %d %d %d %d %d %d %d %d %lld %zu\n", kvr::attend_side_lds(d, p), p.lds_bytes,
+                kvr::retained_lds(G, p.rslice_tokens), p.n_vslices, p.staged ? p.ch : 0, p.n_rslices, p.rslice_tokens,
+                p.pair ? p.n_ret_wgs : p.streamed ? p.stream.n_ret_wgs : 0, p.pair ? p.pair_lds : p.streamed ? p.stream.lds : 0,
+                part * p.n_vslices, p.total_bytes);
   }
 }
 """
@@ -111,3 +116,17 @@ def test_workspace_of_a_streamed_list(batch, ret_cap, vague_cap):
         assert 0 < left and partials(col, left) <= areas, (heads, n_q, size, fixed)
         slices = left // (units * col * 130 * 4)
         assert slices <= -(-1536 // units) + 256 // units + 1 + (ret_cap + 127) // 128, slices
+
+
+@pytest.mark.parametrize("G,r,w", [(1, 3, 100), (4, 3, 333), (4, 3, 700), (1, 4, 400), (4, 4, 819), (8, 3, 60)])
+def test_one_launch_up_to_the_largest_sizes(plan, G, r, w):
+    """Kernels that take the slots along, up to the sizes that the calls take (65535 units, 2^30 tokens: the question for a
+    workspace reads no memory).  Slots and list are covered, the launch has workgroups for the slots in whole eights and fits
+    LDS, and the workspace holds its parts."""
+    cases = [(units, G, r, w, ret, vague) for units in (1, 9, 640, 4100, 65535) for ret in (1, 5000, 1 << 20, 1 << 30)
+             for vague in (64, 40000, 1 << 22, 1 << 28, 1 << 30)]
+    for (units, _, _, _, ret, vague), p in zip(cases, plan(*cases)):
+        parts, slices, tokens, wgs, lds, listed, size = p[3], *p[5:]
+        assert parts >= 1 and listed >= vague and slices * tokens >= ret > (slices - 1) * tokens, (units, ret, vague, p)
+        assert 8 <= wgs <= 256 and wgs % 8 == 0 and 0 < lds <= 160 * 1024, (units, ret, vague, p)
+        assert size >= units * G * ((slices + parts) * 130 * 4 + (ret if G == 8 else ret + vague) * 4), (units, ret, vague, p)
