@@ -111,11 +111,11 @@ __global__ __launch_bounds__(SORT_MAX_SEGS * WAVE) void encode_sort_kernel(
     DevDesc d, const int32_t* __restrict__ count, int cap, const int32_t* __restrict__ ws_bucket,
     const int32_t* __restrict__ src_slot, const int32_t* __restrict__ tok_pos,
     int32_t* __restrict__ ws_order, int32_t* __restrict__ ws_start) {
-  extern __shared__ int s_tab[];             // [segs][w] counts / cursors, [w] totals / starts, [1]; GATHER: [cap] records
+  extern __shared__ int s_tab[];             // [segs][w] counts / cursors, [w] totals / starts; GATHER: [1], [cap] records
   const int w = d.w;
   const int segs = blockDim.x / WAVE;
   int* s_tot = s_tab + segs * w;
-  int* s_end = s_tot + w;                    // tokens that have a place (one with a bad source row has none)
+  int* s_end = s_tot + w;                    // GATHER: tokens that have a place (one with a bad source row has none)
   int* s_out = s_end + 1;
   const int ur = blockIdx.x;                 // unit * r + row
   const int unit = ur / d.r, row = ur % d.r;
@@ -164,7 +164,10 @@ __global__ __launch_bounds__(SORT_MAX_SEGS * WAVE) void encode_sort_kernel(
       if (s < w) { s_tot[s] = carry + incl - c; start[s] = carry + incl - c; }
       carry += __shfl(incl, WAVE - 1);
     }
-    if (lane == 0) { start[w] = carry; *s_end = carry; }
+    if (lane == 0) {
+      start[w] = carry;
+      if (GATHER) *s_end = carry;
+    }
   }
   __syncthreads();
   for (int s = tid; s < w; s += blockDim.x) {
@@ -336,7 +339,8 @@ static hipError_t launch_t(const DevDesc& d, const void* k_src, const void* v_sr
   if (e != hipSuccess) return e;
   {
     const int segs = sort_segments(d.w);
-    const size_t tab = ((size_t)(segs + 1) * d.w + 1) * sizeof(int), gather = tab + (size_t)cap * sizeof(int);
+    // (the table is 64 KB at 8192 slots, what a launch may ask for as it is; the other form's limit is raised)
+    const size_t tab = (size_t)(segs + 1) * d.w * sizeof(int), gather = tab + ((size_t)cap + 1) * sizeof(int);
     static std::once_flag once;
     static hipError_t attr_rc = hipSuccess;
     std::call_once(once, [&]() {

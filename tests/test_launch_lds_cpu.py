@@ -1,0 +1,59 @@
+"""Dynamic LDS of the bulk insert's launches, on the CPU: a host program that puts its own launch calls and
+hipFuncSetAttribute before the runtime's, so that nothing is launched and every launch is listed.  A kernel may ask for more
+than 64 KB only where its limit was raised for it."""
+import os
+import subprocess
+
+from paper_2512_17917_amd import build as B
+
+PROBE = r"""
+#include <cstdio>
+#include <map>
+#include "kvr_launch.h"
+static size_t asked;
+static std::map<const void*, int> limit;
+extern "C" hipError_t hipFuncSetAttribute(const void* f, hipFuncAttribute a, int value) {
+  if (a == hipFuncAttributeMaxDynamicSharedMemorySize) limit[f] = value;
+  return hipSuccess;
+}
+extern "C" hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t lds, hipStream_t) {
+  std::printf(" %zu:%d", lds, limit.count(f) ? limit[f] : 65536);
+  return hipSuccess;
+}
+extern "C" hipError_t __hipPushCallConfiguration(dim3, dim3, size_t lds, hipStream_t) { asked = lds; return hipSuccess; }
+extern "C" hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t* st) {
+  *g = dim3(1); *b = dim3(1); *lds = asked; *st = nullptr;
+  return hipSuccess;
+}
+extern "C" hipError_t hipGetLastError() { return hipSuccess; }
+// per input line: units rows slots tokens -> the launches' LDS and limits
+int main() {
+  int units, r, w, cap;
+  while (std::scanf("%d %d %d %d", &units, &r, &w, &cap) == 4) {
+    kvr::DevDesc d = {};
+    d.B = 1; d.Hkv = d.Hq = units; d.G = 1; d.r = r; d.w = w;
+    int32_t x = 0;                           // no kernel runs: never read
+    const kvr::EncodePlan plan = kvr::encode_plan(d, cap);
+    const hipError_t e = kvr::launch_encode(d, KVR_BF16, &x, &x, 1, &x, &x, &x, cap, &x, &x, nullptr, nullptr, &x, plan, nullptr);
+    std::printf(" %d\n", (int)e);
+  }
+}
+"""
+
+
+def test_bulk_insert_stays_within_its_lds_limit(tmp_path):
+    src, exe = str(tmp_path / "probe.hip"), str(tmp_path / "probe")
+    open(src, "w").write(PROBE)
+    subprocess.run([B._hipcc(), "--offload-host-only", "-std=c++17", "-I", B.CSRC, src, "-L", os.path.dirname(B.OUT),
+                    "-l:" + os.path.basename(B.OUT), f"-Wl,-rpath,{os.path.dirname(B.OUT)}", "-o", exe], check=True, capture_output=True)
+    cases = [(2, 3, w, cap) for w in (1, 29, 273, 511, 4000, 5120, 7680, 8191, 8192) for cap in (65, 2000, 24575, 24576, 40000, 1 << 20)]
+    # lists first that take the plain kernel: no limit was raised by an earlier call
+    cases.sort(key=lambda c: -c[3])
+    out = subprocess.run([exe], input="".join(" ".join(map(str, c)) + "\n" for c in cases), capture_output=True, text=True, check=True).stdout
+    assert len(out.splitlines()) == len(cases)
+    for case, line in zip(cases, out.splitlines()):
+        *launches, rc = line.split()
+        assert rc == "0" and len(launches) == 3, (case, line)              # slot numbers, sort, sums
+        for x in launches:
+            lds, limit = map(int, x.split(":"))
+            assert lds <= limit <= 160 * 1024, (case, line)
