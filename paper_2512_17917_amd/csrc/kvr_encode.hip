@@ -97,7 +97,12 @@ constexpr int SORT_LDS_INTS = 15360;       // 60 KB of table: segs * w + w <= th
 // chunk (a volatile cursor), 51 without, 31.7 with the records in LDS; compressing 8 x 8 units of 32768 tokens 542 -> 517 us,
 // 128 units 1011 -> 944, 32 units of 45000, four rows 521 -> 491.  Longer lists go straight to memory (16 units of 131072
 // 899 -> 859 from the cursors alone).
+// From seven waves on only (slots up to 1920): they fill a CU by themselves.  Fewer waves need other workgroups beside them to
+// hide the latency of memory, and the records leave one workgroup per CU.  us an insert, in LDS and not, 20000 tokens, 86 and 128
+// units, three rows: 1500 slots (9 waves) 453 / 461 and 622 / 642, 2000 (6) 544 / 530 and 730 / 740, 2560 (5) 578 / 546 and 782 / 774,
+// 4000 (2) 869 / 739 and 1146 / 1033, 8000 (1) 1661 / 1379 and 2167 / 1892; 64 units, one workgroup per CU either way: within 1 %.
 constexpr size_t SORT_GATHER_LDS = 160 * 1024;
+constexpr int SORT_GATHER_WAVES = 7;
 
 static int sort_segments(int w) {
   int segs = (SORT_LDS_INTS - w) / w;
@@ -348,7 +353,7 @@ static hipError_t launch_t(const DevDesc& d, const void* k_src, const void* v_sr
                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     });
     if (attr_rc != hipSuccess) return attr_rc;
-    if (gather <= SORT_GATHER_LDS)
+    if (gather <= SORT_GATHER_LDS && segs >= SORT_GATHER_WAVES)
       hipLaunchKernelGGL(encode_sort_kernel<true>, dim3(units * d.r), dim3(segs * WAVE), gather, st, d, count, cap,
                          ws_bucket, src_slot, tok_pos, ws_order, ws_start);
     else

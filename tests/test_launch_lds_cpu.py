@@ -4,6 +4,8 @@ than 64 KB only where its limit was raised for it."""
 import os
 import subprocess
 
+import pytest
+
 from paper_2512_17917_amd import build as B
 
 PROBE = r"""
@@ -41,19 +43,36 @@ int main() {
 """
 
 
-def test_bulk_insert_stays_within_its_lds_limit(tmp_path):
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    tmp_path = tmp_path_factory.mktemp("launches")
     src, exe = str(tmp_path / "probe.hip"), str(tmp_path / "probe")
     open(src, "w").write(PROBE)
     subprocess.run([B._hipcc(), "--offload-host-only", "-std=c++17", "-I", B.CSRC, src, "-L", os.path.dirname(B.OUT),
                     "-l:" + os.path.basename(B.OUT), f"-Wl,-rpath,{os.path.dirname(B.OUT)}", "-o", exe], check=True, capture_output=True)
+
+    def ask(cases):
+        out = subprocess.run([exe], input="".join(" ".join(map(str, c)) + "\n" for c in cases), capture_output=True, text=True, check=True).stdout
+        assert len(out.splitlines()) == len(cases)
+        for case, line in zip(cases, out.splitlines()):
+            *launches, rc = line.split()
+            assert rc == "0" and len(launches) == 3, (case, line)          # slot numbers, sort, sums
+            yield case, [tuple(map(int, x.split(":"))) for x in launches]
+    return ask
+
+
+def test_bulk_insert_stays_within_its_lds_limit(launches):
     cases = [(2, 3, w, cap) for w in (1, 29, 273, 511, 4000, 5120, 7680, 8191, 8192) for cap in (65, 2000, 24575, 24576, 40000, 1 << 20)]
     # lists first that take the plain kernel: no limit was raised by an earlier call
     cases.sort(key=lambda c: -c[3])
-    out = subprocess.run([exe], input="".join(" ".join(map(str, c)) + "\n" for c in cases), capture_output=True, text=True, check=True).stdout
-    assert len(out.splitlines()) == len(cases)
-    for case, line in zip(cases, out.splitlines()):
-        *launches, rc = line.split()
-        assert rc == "0" and len(launches) == 3, (case, line)              # slot numbers, sort, sums
-        for x in launches:
-            lds, limit = map(int, x.split(":"))
-            assert lds <= limit <= 160 * 1024, (case, line)
+    for case, asked in launches(cases):
+        assert all(lds <= limit <= 160 * 1024 for lds, limit in asked), (case, asked)
+
+
+def test_sort_of_few_waves_leaves_a_cu_room(launches):
+    """The records of a list that fits go to LDS beside the table from seven waves on; with fewer, other workgroups have to find
+    room on the CU: the table alone, whatever the list's length."""
+    for (_, _, w, cap), asked in launches([(128, 3, w, cap) for w in (273, 1920, 1921, 2560, 4000, 8192) for cap in (1000, 20000)]):
+        waves = min(16, max(1, (15360 - w) // w))
+        table = (waves + 1) * w * 4
+        assert asked[1][0] == (table + 4 + 4 * cap if waves >= 7 else table), (w, cap, asked)
