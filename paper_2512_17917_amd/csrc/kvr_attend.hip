@@ -16,6 +16,7 @@
 #include "kvr_launch.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace kvr {
 
@@ -55,6 +56,74 @@ static int ret_slices(long long units, int ret_cap, int n_wgs, int n_col, int wa
   return slices;
 }
 
+// The plans below price the slots by their bytes.  A workgroup walks whole slices, one after another, and where it has several,
+// or the slots many CUs, that is too little: this is the estimate by turns of slices.  us, fitted to 644 calls of 20 .. 512 units x
+// 7 .. 9000 slots x 65 .. 8000 listed tokens, each measured in all the ways below, and checked on 52 of 8 .. 128 units, up to 131072 tokens, in 1800 splits: a
+// slice streams at 40 KB per us, less where many CUs share memory (128 of them 30, 256 17), and then ends (8 waves, of the 64- and
+// 16-channel kernels: 3.5 .. 5; 16 waves, of the streaming kernel: 10 .. 14).
+constexpr double RET_TURN_RATE = 40e3, RET_TURN_CHIP = 5.4e6;      // bytes per us of one CU, of all
+static double ret_turns(long long units, int ret_cap, int slices, int n_wgs, int n_col, int waves) {
+  const double shared = RET_TURN_RATE * (double)std::min<long long>(n_wgs, units * slices) / RET_TURN_CHIP;
+  const double end = waves == 8 ? 3.0 + 0.45 * n_col : 10.0 + 0.25 * n_col;
+  const int tiles = ((ret_cap + 15) / 16 + slices - 1) / slices;
+  return (double)((units * slices + n_wgs - 1) / n_wgs) * (tiles * 8192.0 / RET_TURN_RATE * std::sqrt(1.0 + shared * shared) + end);
+}
+
+// List workgroups per unit (each takes `wg` us), workgroups for the slots (256: all CUs, before the list) and slices of a unit's slots.
+struct RetChoice {
+  int n;
+  double wg;
+  int n_wgs, slices;
+  bool own;                 // the slots in a launch of their own
+};
+struct ListChoice {
+  int n;
+  double wg;
+};
+// The plan's choice c, or the slots ahead of the list, where that is better by turns of slices:
+//  * the slots first, on all CUs of the launch: eight heads, 246 units of 585 + 1755 tokens 446 us a call on the 8 CUs left, 71 first
+//    (as launches of their own 85), four heads, 246 units of 1441 + 4325 111 on 64, 100 first (125);
+//  * in a launch of their own, whose small workgroups share CUs, for hardly any slots of many units: 400 units of 4 + 220, eight
+//    heads 59.1 on 56 CUs, 50.8 own (72 + 300: 62.4, 56.1), four heads 47.8, 42.1; up to 64 slots, beside the streaming kernel 256
+//    (four heads, 512 units of 130 + 600 60.7 first, 64.1 own).
+// Only for a gain of 5 % by this estimate (streaming kernel 10 %): within it, and among the CUs that the list can leave (20 units
+// of 7000 + 1400, one head, 25.5 us; by this estimate 34), the plans' own figures are the better ones.
+static RetChoice ret_ahead(RetChoice c, const ListChoice* lists, int n_lists, long long units, int ret_cap, int n_col, int waves,
+                              int most, int own_slices) {
+  if (c.n_wgs == 0) return c;
+  const long long units8 = (units + 7) / 8;
+  const int tiles = (ret_cap + 15) / 16, biggest = ret_stream_most(n_col, waves), least = std::max(1, (tiles + biggest - 1) / biggest);
+  const long long left = 32 - c.n_wgs / 8;
+  double best = ret_turns(units, ret_cap, c.slices, c.n_wgs, n_col, waves);
+  best = left > 0 ? std::max((double)((units8 * c.n + left - 1) / left) * c.wg, best) : (double)((units8 * c.n + 31) / 32) * c.wg + best;
+  best *= waves == 8 ? 0.95 : 0.9;
+  // the slots' time on all CUs: as many slices as a number of turns holds
+  int slices = 1;
+  const auto slots = [&](int n) {
+    const int top = std::min(tiles, most - n);
+    const long long first = (units * least + 255) / 256;
+    double us = 1e30;
+    for (long long turns = first; turns < first + 3; ++turns) {
+      const int s = std::max(least, (int)std::min<long long>(turns * 256 / units, top));
+      const double t = ret_turns(units, ret_cap, s, 256, n_col, waves);
+      if (t < us) { us = t; slices = s; }
+      if (s >= top) break;
+    }
+    return us;
+  };
+  for (int i = 0; i < n_lists; ++i) {
+    const int n = lists[i].n;
+    const double wg = lists[i].wg;
+    const long long turns = (units8 * n + 31) / 32;
+    if ((double)turns * wg >= best || n + least > most) continue;
+    const double list = (double)turns * wg, t = list + slots(n);
+    if (t < best) { best = t; c = {n, wg, 256, slices, false}; }
+    const double own = list + (waves == 8 ? 5.0 : 10.0) + 512.0 * (double)units * ret_cap / 4.2e6;
+    if (own < best && ret_cap <= (waves == 8 ? 64 : 256) && n + own_slices <= most) { best = own; c = {n, wg, 0, own_slices, true}; }
+  }
+  return c;
+}
+
 // One launch for the retained slots and the Vague list (64- and 16-channel kernels): n_vslices workgroups per unit over the
 // list and n_ret_wgs workgroups over the slots, at most `most` slices of both kinds per unit (what callers' workspaces hold).
 // A workgroup of either kind has a CU to itself (its registers fill the SIMDs) and a unit's workgroups share an XCD of 32
@@ -79,15 +148,16 @@ static void plan_pair(AttendPlan& p, const DevDesc& d, long long units, int ret_
   const long long units8 = (units + 7) / 8;
   const double bytes = 512.0 * units * ret_cap;
   const int biggest = 16 * ret_stream_most(d.G, 8), least = (ret_cap + biggest - 1) / biggest;
-  double best = 1e30;
-  int best_n = 1, best_r = 0, last = 0;
+  double best = 1e30, best_wg = 0.0;
+  int best_n = 1, best_r = 0, last = 0, n_lists = 0;
+  ListChoice lists[std::max(STAGED64_KMAX, staged16_kmax(4))];
   for (int rho = 1; rho <= kmax; ++rho) {
     const int n = (wr + 8 * rho - 1) / (8 * rho);
-    if (n == last) continue;
+    if (n == last || (n + least > most && rho < kmax)) continue;
     last = n;
-    if (n + least > most && rho < kmax) continue;
     const double wg = fixed + round * ((wr + 8 * n - 1) / (8 * n));
     const long long per_xcd = units8 * n, turns = (per_xcd + 31) / 32;
+    lists[n_lists++] = {n, wg};
     for (long long k = turns; k <= turns + 2; ++k) {
       int r = ret_cap > 0 ? 8 * (32 - (int)((per_xcd + k - 1) / k)) : 0;
       double t = (double)k * wg;
@@ -97,15 +167,19 @@ static void plan_pair(AttendPlan& p, const DevDesc& d, long long units, int ret_
         r = 256;
         t += 2.0 + ret_time(bytes, r);
       }
-      if (t < best - 1e-9) { best = t; best_n = n; best_r = r; }
+      if (t < best - 1e-9) { best = t; best_n = n; best_r = r; best_wg = wg; }
     }
   }
-  p.n_vslices = best_n;
   const int slices = best_r > 0 ? ret_slices(units, ret_cap, best_r, d.G, 8, most - best_n) : 1;
-  p.rslice_tokens = std::max(1, ((ret_cap + 15) / 16 + slices - 1) / slices) * 16;
+  const RetChoice c = ret_ahead({best_n, best_wg, best_r, slices, false}, lists, n_lists, units, ret_cap, d.G, 8, most, p.n_rslices);
+  p.n_vslices = c.n;
+  p.ret_own = c.own;
+  p.pair_lds = p.lds_bytes;
+  if (c.own) return;                         // slices as that launch has them anyway
+  p.rslice_tokens = std::max(1, ((ret_cap + 15) / 16 + c.slices - 1) / c.slices) * 16;
   p.n_rslices = (ret_cap + p.rslice_tokens - 1) / p.rslice_tokens;
-  p.n_ret_wgs = (int)std::min<long long>(best_r, (units * p.n_rslices + 7) / 8 * 8);
-  p.pair_lds = std::max(p.lds_bytes, ret_cap > 0 ? ret_stream_lds(d.G, 8, p.rslice_tokens) : 0);
+  p.n_ret_wgs = (int)std::min<long long>(c.n_wgs, (units * p.n_rslices + 7) / 8 * 8);
+  if (ret_cap > 0) p.pair_lds = std::max(p.pair_lds, ret_stream_lds(d.G, 8, p.rslice_tokens));
 }
 
 // The streaming kernel's launch, likewise: one of its workgroups per CU (16 waves, 17 us and 17 ns per token of its part).  It
@@ -115,33 +189,45 @@ static void plan_pair(AttendPlan& p, const DevDesc& d, long long units, int ret_
 // 16 parts, the slots first: 65), 64 units 194 -> 167 (3 and 64; slots first 203), 8 of 900 34 -> 22.
 StreamPlan plan_stream(const DevDesc& d, int n_col, long long units, int ret_cap, int vague_cap, int most) {
   constexpr double FIXED = 17.0, TOKEN = 0.017;
-  StreamPlan p;
+  StreamPlan p = {};
   const long long units8 = (units + 7) / 8;
   const double bytes = 512.0 * units * ret_cap;
   const int full = multi_staged_part_tokens(vague_cap, units), n_full = (vague_cap + full - 1) / full;
-  double best = 1e30;
-  int best_r = 0;
+  double best = 1e30, best_wg = 0.0;
+  int best_r = 0, n_lists = 0;
+  constexpr int LISTS = 32;
+  ListChoice lists[LISTS];
+  int list_tokens[LISTS];
   p.vslice_tokens = full;
+  const auto parts = [&](int tokens) { return (vague_cap + tokens - 1) / tokens; };
   for (int n = n_full; n >= 1 && n >= n_full / 2; --n) {
     const int tokens = n == n_full ? full : (vague_cap + 16 * n - 1) / (16 * n) * 16;
-    const long long per_xcd = units8 * ((vague_cap + tokens - 1) / tokens), turns = (per_xcd + 31) / 32;
+    const long long per_xcd = units8 * parts(tokens), turns = (per_xcd + 31) / 32;
     int r = ret_cap > 0 ? 8 * (32 - (int)((per_xcd + turns - 1) / turns)) : 0;
-    double t = (double)turns * (FIXED + TOKEN * tokens);
+    const double wg = FIXED + TOKEN * tokens;
+    double t = (double)turns * wg;
+    if (n_lists < LISTS) { lists[n_lists] = {parts(tokens), wg}; list_tokens[n_lists++] = tokens; }
     if (r > 0) {
       t = std::max(t, ret_time(bytes, r));
     } else if (ret_cap > 0) {
       r = 256;
       t += 2.0 + ret_time(bytes, r);
     }
-    if (t < best - 1e-9) { best = t; best_r = r; p.vslice_tokens = tokens; }
+    if (t < best - 1e-9) { best = t; best_r = r; best_wg = wg; p.vslice_tokens = tokens; }
     if (ret_cap < 512) break;                // a few slots: first, on all CUs, they cost no more than a part less would
   }
-  p.n_vslices = (vague_cap + p.vslice_tokens - 1) / p.vslice_tokens;
-  int slices = best_r > 0 ? ret_slices(units, ret_cap, best_r, n_col, 16, most - p.n_vslices) : 1;
-  p.rslice_tokens = std::max(1, ((ret_cap + 15) / 16 + slices - 1) / slices) * 16;
+  const int best_parts = parts(p.vslice_tokens);
+  const int slices = best_r > 0 ? ret_slices(units, ret_cap, best_r, n_col, 16, most - best_parts) : 1;
+  const RetChoice c = ret_ahead({best_parts, best_wg, best_r, slices, false}, lists, n_lists, units, ret_cap, n_col, 16, most, 1);
+  for (int i = 0; c.n != best_parts && i < n_lists; ++i)
+    if (lists[i].n == c.n) p.vslice_tokens = list_tokens[i];
+  p.n_vslices = parts(p.vslice_tokens);
+  p.own = c.own;
+  p.lds = multi_staged_lds(d, n_col);
+  p.rslice_tokens = std::max(1, ((ret_cap + 15) / 16 + c.slices - 1) / c.slices) * 16;
   p.n_rslices = (ret_cap + p.rslice_tokens - 1) / p.rslice_tokens;
-  p.n_ret_wgs = (int)std::min<long long>(best_r, (units * p.n_rslices + 7) / 8 * 8);
-  p.lds = std::max(multi_staged_lds(d, n_col), ret_cap > 0 ? ret_stream_lds(n_col, 16, p.rslice_tokens) : 0);
+  p.n_ret_wgs = (int)std::min<long long>(c.n_wgs, (units * p.n_rslices + 7) / 8 * 8);
+  if (p.n_ret_wgs > 0) p.lds = std::max(p.lds, ret_stream_lds(n_col, 16, p.rslice_tokens));
   return p;
 }
 
@@ -149,7 +235,7 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
   AttendPlan p;
   const long long units = (long long)d.B * d.Hkv;
   const long long tot_cap = ret_cap + vague_cap;
-  p.staged = p.pair = false;
+  p.staged = p.pair = p.ret_own = false;
   p.n_vslices = 0;
   p.ch = 0;
   p.lds_bytes = 0;
@@ -701,7 +787,8 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
   const int side_lds = attend_side_lds(d, plan);
   const bool side = !plan.pair && sd.stream != nullptr && big && side_lds > 0;
   if (plan.pair) {
-    e = plan.ch == 64 ? launch_attend_pair64(d, a, plan, st) : launch_attend_pair16(d, a, plan, st);
+    if (plan.ret_own) e = launch_attend_retained(d, a, plan.n_rslices, 0, 0, st);
+    if (e == hipSuccess) e = plan.ch == 64 ? launch_attend_pair64(d, a, plan, st) : launch_attend_pair16(d, a, plan, st);
   } else if (side) {
     e = hipEventRecord(sd.fork, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(sd.stream, sd.fork, 0);

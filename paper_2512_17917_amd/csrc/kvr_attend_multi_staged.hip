@@ -119,6 +119,17 @@ __device__ __forceinline__ void stage_issue_pitch(const unsigned char* __restric
   }
 }
 
+// Parts of a retained slot's weight: three (as many bits as float32) but for 16 columns, where two take two products as well.
+constexpr int ret_parts(int n_col) { return n_col <= 8 ? 3 : 2; }
+
+// The retained slots alone, before the list's launch, in workgroups of four waves of which many share a CU (StreamPlan::own).
+constexpr int RA_WAVES = 4;
+template <int NCOL>
+__global__ __launch_bounds__(64 * RA_WAVES) void attend_slots_kernel(DevDesc d, RetStream a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  ret_stream_role<NCOL, ret_parts(NCOL), RA_WAVES>(d, a, blockIdx.x, gridDim.x, smem);
+}
+
 template <int NCOL>
 __global__ __launch_bounds__(MS_THREADS) void attend_multi_staged_kernel(DevDesc d, MultiStagedArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -127,8 +138,7 @@ __global__ __launch_bounds__(MS_THREADS) void attend_multi_staged_kernel(DevDesc
   const int units = d.B * d.Hkv;
   // workgroup ids go round-robin to the 8 XCDs: all parts of a unit get ids that are equal modulo 8
   if ((int)blockIdx.x < a.n_ret_wgs) {
-    // weights in three parts (as many bits as float32) but for 16 columns: two products as well
-    ret_stream_role<NCOL, (NCOL <= 8 ? 3 : 2), MS_WAVES>(d, a.ret, blockIdx.x, a.n_ret_wgs, smem);
+    ret_stream_role<NCOL, ret_parts(NCOL), MS_WAVES>(d, a.ret, blockIdx.x, a.n_ret_wgs, smem);
     return;
   }
   const int lin = blockIdx.x - a.n_ret_wgs;
@@ -455,7 +465,7 @@ int multi_staged_part_tokens(long long vague_cap, long long units) {
 }
 
 template <int NCOL>
-static hipError_t launch_n(const DevDesc& d, const MultiStagedArgs& a, int lds, hipStream_t st) {
+static hipError_t launch_n(const DevDesc& d, const MultiStagedArgs& a, int lds, bool own, hipStream_t st) {
   auto kern = attend_multi_staged_kernel<NCOL>;
   static std::once_flag once;
   static hipError_t attr_rc = hipSuccess;
@@ -467,6 +477,13 @@ static hipError_t launch_n(const DevDesc& d, const MultiStagedArgs& a, int lds, 
   if (lds < multi_staged_lds(d, NCOL) || lds > STAGED_LDS_LIMIT) return hipErrorInvalidValue;
   const int units = d.B * d.Hkv;
   const int units_pad = (units + 7) / 8 * 8;
+  if (own) {
+    const int slots_lds = ret_stream_lds(NCOL, RA_WAVES, a.ret.slice_tokens);
+    if (slots_lds > 64 * 1024) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(attend_slots_kernel<NCOL>, dim3(units * a.ret.n_rslices), dim3(64 * RA_WAVES), slots_lds, st, d, a.ret);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(kern, dim3(a.n_ret_wgs + units_pad * a.n_parts), dim3(MS_THREADS), lds, st, d, a);
   return hipGetLastError();
 }
@@ -499,11 +516,11 @@ hipError_t launch_attend_multi_staged(const DevDesc& d, const AttendArgs& a0, co
                     plan.rslice_tokens, plan.n_rslices, a.n_slices, a0.ret_cap, a0.part_o, a0.part_ml, a0.logits};
   a.n_ret_wgs = plan.n_ret_wgs;
   switch (n_q * d.G) {
-    case 1: return launch_n<1>(d, a, plan.lds, st);
-    case 2: return launch_n<2>(d, a, plan.lds, st);
-    case 4: return launch_n<4>(d, a, plan.lds, st);
-    case 8: return launch_n<8>(d, a, plan.lds, st);
-    case 16: return launch_n<16>(d, a, plan.lds, st);
+    case 1: return launch_n<1>(d, a, plan.lds, plan.own, st);
+    case 2: return launch_n<2>(d, a, plan.lds, plan.own, st);
+    case 4: return launch_n<4>(d, a, plan.lds, plan.own, st);
+    case 8: return launch_n<8>(d, a, plan.lds, plan.own, st);
+    case 16: return launch_n<16>(d, a, plan.lds, plan.own, st);
     default: return hipErrorInvalidValue;
   }
 }

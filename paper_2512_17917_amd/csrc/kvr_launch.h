@@ -14,6 +14,7 @@ namespace kvr {
 // slices of a unit.
 struct StreamPlan {
   int vslice_tokens, n_vslices, rslice_tokens, n_rslices, n_ret_wgs, lds;
+  bool own;             // the slots have a launch of their own before it
 };
 
 // How one kvr_attend_decode call is cut into workgroups.  Slices 0 .. n_rslices-1
@@ -31,7 +32,8 @@ struct AttendPlan {
   bool streamed;        // Vague tokens by the streaming LDS-staged kernel of kvr_attend_multi with one query
                         // (8 query heads per kv head; vslice_tokens / n_vslices are its parts)
   bool pair;            // staged, and its launch takes the retained slots along (64- and 16-channel kernels)
-  int n_ret_wgs;        // pair: workgroups for the retained slots
+  bool ret_own;         // pair: the slots have a launch of their own before it after all
+  int n_ret_wgs;        // pair: workgroups for the retained slots (0: none, or ret_own)
   int pair_lds;         // and its dynamic LDS (a workgroup of either kind)
   StreamPlan stream;    // streamed
   size_t off_part_o, off_part_ml, off_logits, off_rec, off_tiles, total_bytes;

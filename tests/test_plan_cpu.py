@@ -13,7 +13,7 @@ PROBE = r"""
 // by side), of the staged kernel, of the retained kernel alone,
 // parts of the Vague list, channels per phase of the staged kernel (0: the list is not staged); then slices of the retained
 // slots and their tokens, workgroups for them in the list's launch, LDS of that launch (0: a launch of their own), tokens that
-// the parts hold at most, bytes of workspace
+// the parts hold at most, bytes of workspace, 1 if the slots of a plan for one launch have one of their own after all
 int main() {
   int units, G, r, w, ret, vague;
   while (std::scanf("%d %d %d %d %d %d", &units, &G, &r, &w, &ret, &vague) == 6) {
@@ -21,10 +21,10 @@ int main() {
     d.B = 1; d.Hkv = units; d.Hq = units * G; d.G = G; d.r = r; d.w = w; d.sign_mask = 2;
     const kvr::AttendPlan p = kvr::attend_plan(d, KVR_BF16, ret, vague);
     const long long part = p.streamed ? p.vslice_tokens : p.ch == 64 ? 512 * kvr::STAGED64_KMAX : 512 * kvr::staged16_kmax(r);
-    std::printf("%d %d %d %d %d %d %d %d %d %lld %zu\n", kvr::attend_side_lds(d, p), p.lds_bytes,
+    std::printf("%d %d %d %d %d %d %d %d %d %lld %zu %d\n", kvr::attend_side_lds(d, p), p.lds_bytes,
                 kvr::retained_lds(G, p.rslice_tokens), p.n_vslices, p.staged ? p.ch : 0, p.n_rslices, p.rslice_tokens,
                 p.pair ? p.n_ret_wgs : p.streamed ? p.stream.n_ret_wgs : 0, p.pair ? p.pair_lds : p.streamed ? p.stream.lds : 0,
-                part * p.n_vslices, p.total_bytes);
+                part * p.n_vslices, p.total_bytes, p.pair ? p.ret_own : p.streamed ? p.stream.own : 0);
   }
 }
 """
@@ -126,7 +126,46 @@ def test_one_launch_up_to_the_largest_sizes(plan, G, r, w):
     cases = [(units, G, r, w, ret, vague) for units in (1, 9, 640, 4100, 65535) for ret in (1, 5000, 1 << 20, 1 << 30)
              for vague in (64, 40000, 1 << 22, 1 << 28, 1 << 30)]
     for (units, _, _, _, ret, vague), p in zip(cases, plan(*cases)):
-        parts, slices, tokens, wgs, lds, listed, size = p[3], *p[5:]
+        parts, slices, tokens, wgs, lds, listed, size, own = p[3], *p[5:]
         assert parts >= 1 and listed >= vague and slices * tokens >= ret > (slices - 1) * tokens, (units, ret, vague, p)
-        assert 8 <= wgs <= 256 and wgs % 8 == 0 and 0 < lds <= 160 * 1024, (units, ret, vague, p)
+        assert (wgs == 0 if own else 8 <= wgs <= 256) and wgs % 8 == 0 and 0 < lds <= 160 * 1024, (units, ret, vague, p)
         assert size >= units * G * ((slices + parts) * 130 * 4 + (ret if G == 8 else ret + vague) * 4), (units, ret, vague, p)
+
+
+@pytest.mark.parametrize("G,r,w", [(8, 3, 21), (4, 3, 53), (1, 3, 1), (4, 4, 20)])
+def test_slots_are_not_left_a_few_cus(plan, G, r, w):
+    """Lists that leave hardly a CU (246 units fill 31 of an XCD's 32): the slots of all units would be walked there one after
+    another.  The slots of a launch take less than twice as many turns as on all CUs, or no longer than the list's workgroups."""
+    cases = [(units, G, r, w, ret, vague) for units in (192, 224, 246, 300, 400, 512) for ret, vague in
+             ((7, 220), (72, 216), (585, 1755), (1441, 4325), (3000, 800), (7000, 1400))]
+    for (units, _, _, _, ret, vague), p in zip(cases, plan(*cases)):
+        slices, tokens, wgs, own = p[5], p[6], p[7], p[11]
+        if own:
+            assert wgs == 0 and ret <= (256 if G == 8 else 64)
+            continue
+        turns = -(-units * slices // wgs)
+        assert wgs >= 32 and turns * tokens <= 8 * 1024 + 16 * vague, (units, ret, vague, p)
+
+
+SLOTS_AHEAD = [                              # units, heads, rows, slots per row, retained, listed
+    (246, 4, 3, 21, 585, 1755, "first"),
+    (128, 1, 3, 18, 507, 5108, "first"),
+    (128, 4, 4, 20, 2025, 6975, "first"),
+    (400, 4, 3, 1, 7, 220, "own"),
+    (400, 2, 3, 2, 64, 300, "own"),
+    (200, 4, 3, 6, 10112, 300, "lds"),       # one slice of all that LDS holds
+    (200, 4, 3, 6, 10113, 300, "lds"),
+    (246, 8, 3, 21, 585, 1755, "first"),
+    (400, 8, 3, 1, 30, 220, "own"),
+    (512, 8, 3, 4, 250, 1000, "own"),
+]
+
+
+@pytest.mark.parametrize("units,G,r,w,ret,vague,how", SLOTS_AHEAD)
+def test_slots_ahead_of_the_list(plan, units, G, r, w, ret, vague, how):
+    """first: workgroups for the slots on all CUs (at most one per slice, in whole eights); own: none in the list's launch."""
+    p = plan((units, G, r, w, ret, vague))[0]
+    slices, wgs, lds, own = p[5], p[7], p[8], p[11]
+    assert own == (how == "own") and (wgs == 0) == (how == "own")
+    assert how != "first" or wgs == min(256, -(-units * slices // 8) * 8)
+    assert how != "lds" or (slices == 1 and lds > 155 * 1024) == (ret <= 10112)
