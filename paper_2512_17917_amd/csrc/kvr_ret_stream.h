@@ -70,9 +70,9 @@ __device__ __forceinline__ uint32_t rs_finite(uint32_t x) {
 template <int NCOL, int PARTS>
 struct RsShape {
   static constexpr int NC = NCOL < 4 ? 4 : NCOL, REP = 16 / NC, OPS = (PARTS + REP - 1) / REP;
-  // Three parts in two products share accumulators: an infinite value would give the sums of the first part a NaN where the
-  // third part is zero, so the second product leaves what is not finite out.
-  static constexpr bool GUARD = OPS > 1 && PARTS == 3;
+  // Parts in two products share accumulators: an infinite value would give the sums of the first part a NaN where the part of
+  // the second product is zero, so that one leaves what is not finite out.
+  static constexpr bool GUARD = OPS > 1;
 };
 
 template <int NCOL, int PARTS>
