@@ -784,8 +784,8 @@ static hipError_t launch_g(const DevDesc& d, int dtype, const AttendArgs& a0, co
   const int cus = cu_count();
   const bool big = (long long)units * plan.n_vslices >= 2ll * cus;
   // And only where a CU holds a workgroup of each.
-  const int side_lds = attend_side_lds(d, plan);
-  const bool side = !plan.pair && sd.stream != nullptr && big && side_lds > 0;
+  const int side_lds = !plan.pair && sd.stream != nullptr && big ? attend_side_lds(d, plan) : 0;
+  const bool side = side_lds > 0;
   if (plan.pair) {
     if (plan.ret_own) e = launch_attend_retained(d, a, plan.n_rslices, 0, 0, st);
     if (e == hipSuccess) e = plan.ch == 64 ? launch_attend_pair64(d, a, plan, st) : launch_attend_pair16(d, a, plan, st);

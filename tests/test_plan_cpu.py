@@ -169,3 +169,22 @@ def test_slots_ahead_of_the_list(plan, units, G, r, w, ret, vague, how):
     assert own == (how == "own") and (wgs == 0) == (how == "own")
     assert how != "first" or wgs == min(256, -(-units * slices // 8) * 8)
     assert how != "lds" or (slices == 1 and lds > 155 * 1024) == (ret <= 10112)
+
+
+SIDE_BY_SIDE = [                             # units, heads, rows, slots per row, retained, listed
+    (128, 4, 3, 1400, 9500, 9400, "whole"),  # the retained kernel's capped form keeps the logits of a slice of 960 tokens
+    (129, 4, 3, 1550, 6001, 9400, "whole"),  # 640, the last one 241
+    (128, 2, 4, 1200, 9500, 9400, "whole"),
+    (128, 4, 3, 1550, 9500, 9400, "parts"),  # of 512 tokens at a time
+    (128, 2, 4, 1230, 9500, 9400, "parts"),
+    (128, 1, 3, 1670, 9501, 9400, "parts"),
+]
+
+
+@pytest.mark.parametrize("units,G,r,w,ret,vague,how", SIDE_BY_SIDE)
+def test_calls_that_fork(plan, units, G, r, w, ret, vague, how):
+    """The general staged kernel, in more than two turns of the chip, with room for the retained kernel on a CU."""
+    p = plan((units, G, r, w, ret, vague))[0]
+    side, staged, alone, parts, ch, slices, tokens, wgs, lds = p[:9]
+    assert ch == 16 and wgs == 0 and lds == 0 and units * parts >= 512 and staged + side + 128 <= 160 * 1024
+    assert tokens > 512 and side == (alone if how == "whole" else 4 * G * 512) <= alone and (how == "whole") == (side == alone)
