@@ -37,13 +37,15 @@ static int slice_tokens_for(long long tokens, long long units) {
 
 int attend_slice_tokens(long long tokens, long long units) { return slice_tokens_for(tokens, units); }
 
+// The chip in these plans: 256 CUs, 32 on an XCD.  (Written in: plans are made without a GPU too, for the size of a workspace.)
 constexpr double RET_RATE = 38e3, RET_CHIP = 5.0e6, RET_SLICE = 6.0;   // bytes per us of a CU, of all; us a slice ends with
 // us for n_wgs workgroups, each on a CU of its own, to stream `bytes` of retained rows
 static double ret_time(double bytes, int n_wgs) {
   return RET_SLICE + std::max(bytes / (RET_RATE * n_wgs), bytes / RET_CHIP);
 }
 // Slices of a unit's retained slots for n_wgs workgroups of `waves` waves: a number that spreads evenly over them, of slices as
-// large as LDS allows and at most `most`.  40 units of 4104 slots, eight heads, 56 workgroups: one slice a unit (16 workgroups
+// large as LDS allows and at most `most`.  45 KB per us is what one CU gets with few others beside it (43 measured on 8, 41 on 32),
+// 38 what it gets in a launch (37 on 64).  40 units of 4104 slots, eight heads, 56 workgroups: one slice a unit (16 workgroups
 // with none) 51 us, four 57.
 static int ret_slices(long long units, int ret_cap, int n_wgs, int n_col, int waves, int most) {
   const int tiles = (ret_cap + 15) / 16, biggest = ret_stream_most(n_col, waves), least = std::max(1, (tiles + biggest - 1) / biggest);
@@ -80,14 +82,16 @@ struct ListChoice {
   int n;
   double wg;
 };
-// The plan's choice c, or the slots ahead of the list, where that is better by turns of slices:
+// The plan's choice c, or the slots ahead of the list or elsewhere, where that is better by turns of slices:
 //  * the slots first, on all CUs of the launch: eight heads, 246 units of 585 + 1755 tokens 446 us a call on the 8 CUs left, 71 first
 //    (as launches of their own 85), four heads, 246 units of 1441 + 4325 111 on 64, 100 first (125);
 //  * in a launch of their own, whose small workgroups share CUs, for hardly any slots of many units: 400 units of 4 + 220, eight
 //    heads 59.1 on 56 CUs, 50.8 own (72 + 300: 62.4, 56.1), four heads 47.8, 42.1; up to 64 slots, beside the streaming kernel 256
 //    (four heads, 512 units of 130 + 600 60.7 first, 64.1 own).
-// Only for a gain of 5 % by this estimate (streaming kernel 10 %): within it, and among the CUs that the list can leave (20 units
-// of 7000 + 1400, one head, 25.5 us; by this estimate 34), the plans' own figures are the better ones.
+//  * where the plan has workgroups walk six slices or more, on other CUs that the list can leave: 400 units of 1441 + 4325, four
+//    heads 201 on 56, 184 on 80, 512 units, one head 202 on 80, 174 on 128 (fewer slices each: 20 units of 7000 + 1400, one head
+//    25.5 us, by this estimate 34).
+// Only for a gain of 5 % by this estimate (streaming kernel 10 %): within it the plans' own figures are the better ones.
 static RetChoice ret_ahead(RetChoice c, const ListChoice* lists, int n_lists, long long units, int ret_cap, int n_col, int waves,
                               int most, int own_slices) {
   if (c.n_wgs == 0) return c;
@@ -97,15 +101,16 @@ static RetChoice ret_ahead(RetChoice c, const ListChoice* lists, int n_lists, lo
   double best = ret_turns(units, ret_cap, c.slices, c.n_wgs, n_col, waves);
   best = left > 0 ? std::max((double)((units8 * c.n + left - 1) / left) * c.wg, best) : (double)((units8 * c.n + 31) / 32) * c.wg + best;
   best *= waves == 8 ? 0.95 : 0.9;
-  // the slots' time on all CUs: as many slices as a number of turns holds
+  // the slots' time on n_wgs workgroups: as many slices as a number of turns holds
   int slices = 1;
-  const auto slots = [&](int n) {
+  const bool many = units * c.slices >= 6ll * c.n_wgs;
+  const auto slots = [&](int n, int n_wgs) {
     const int top = std::min(tiles, most - n);
-    const long long first = (units * least + 255) / 256;
+    const long long first = (units * least + n_wgs - 1) / n_wgs;
     double us = 1e30;
     for (long long turns = first; turns < first + 3; ++turns) {
-      const int s = std::max(least, (int)std::min<long long>(turns * 256 / units, top));
-      const double t = ret_turns(units, ret_cap, s, 256, n_col, waves);
+      const int s = std::max(least, (int)std::min<long long>(turns * n_wgs / units, top));
+      const double t = ret_turns(units, ret_cap, s, n_wgs, n_col, waves);
       if (t < us) { us = t; slices = s; }
       if (s >= top) break;
     }
@@ -116,7 +121,13 @@ static RetChoice ret_ahead(RetChoice c, const ListChoice* lists, int n_lists, lo
     const double wg = lists[i].wg;
     const long long turns = (units8 * n + 31) / 32;
     if ((double)turns * wg >= best || n + least > most) continue;
-    const double list = (double)turns * wg, t = list + slots(n);
+    for (long long k = turns; many && k <= turns + 2 && (double)k * wg < best; ++k) {
+      const int n_wgs = 8 * (32 - (int)((units8 * n + k - 1) / k));
+      if (n_wgs <= 0) continue;
+      const double t = std::max((double)k * wg, slots(n, n_wgs));
+      if (t < best) { best = t; c = {n, wg, n_wgs, slices, false}; }
+    }
+    const double list = (double)turns * wg, t = list + slots(n, 256);
     if (t < best) { best = t; c = {n, wg, 256, slices, false}; }
     const double own = list + (waves == 8 ? 5.0 : 10.0) + 512.0 * (double)units * ret_cap / 4.2e6;
     if (own < best && ret_cap <= (waves == 8 ? 64 : 256) && n + own_slices <= most) { best = own; c = {n, wg, 0, own_slices, true}; }
@@ -266,7 +277,7 @@ AttendPlan attend_plan(const DevDesc& d, int dtype, long long ret_cap, long long
       // rounds of 64 tokens takes about (fixed + rho) round times (fixed part: staging the sketch chunks,
       // hashes, softmax, reductions), and the launch runs ceil(workgroups / 256)
       // such workgroups one after another on each CU.  It decides for the general kernel; for the other two it only bounds
-      // the number of slices (plan_pair).
+      // the number of slices (plan_pair), so that no call needs a larger workspace than it did when it decided for them.
       const int kmax = s16 ? 13 : STAGED_KMAX;
       const double fixed_rounds = s16 ? 7.5 : 2.8;
       double best = 1e30;
@@ -336,7 +347,7 @@ int attend_side_lds(const DevDesc& d, const AttendPlan& p) {
   // Registers: two waves of a staged kernel of up to 192 and one of the retained kernel's capped form (128) share a SIMD's
   // 512.  Four rows and four heads take more in the general kernel, four rows always in the 16-channel kernel, and the retained
   // kernel only finds room where a workgroup has just ended: 4400 rows in four, four heads 1105 us side by side, 1087 back to
-  // back.  Where they fit: three rows of 1500 slots (general kernel), 32 units 907 / 947.
+  // back.  (The 16-channel kernel's launch holds the slots: there the answer decides nothing.)  Where they fit: three rows of 1500 slots (general kernel), 32 units 907 / 947.
   if (d.r != 3 && (staged16_applies(d) || d.G == 4)) return 0;
   // LDS: room for a slice's logits, or for 512 tokens' and the sums.
   constexpr int UNIT = 1280;                   // LDS is handed out in these

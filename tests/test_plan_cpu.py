@@ -196,3 +196,9 @@ def test_parts_of_a_streamed_list_leave_the_slots_room(plan, units):
     for ret, vague in ((300, 3000), (400, 12000), (510, 9000)):
         parts = plan((units, 8, 3, ret // 30, ret, vague))[0][3]
         assert -(-units // 8) * parts <= 32, (units, ret, vague, parts)
+
+
+def test_slots_of_many_units_have_more_cus(plan):
+    """Where workgroups would walk six slices or more (80 and 56 of them), more CUs are taken from the list."""
+    for case, least in (((512, 1, 3, 53, 1441, 4325), 128), ((400, 4, 3, 53, 1441, 4325), 80), ((400, 8, 3, 21, 585, 1755), 120)):
+        assert plan(case)[0][7] >= least, case
