@@ -165,7 +165,8 @@ def parse_args():
                          "slack + 1 tokens leave each unit at once (0, the headline configuration: one token in, "
                          "one out per step)")
     ap.add_argument("--no-side-stream", action="store_true",
-                    help="do not lend kvr_attend_decode a second stream: its two main kernels run back to back")
+                    help="do not lend kvr_attend_decode a second stream (the named workloads make one launch for "
+                         "retained slots and Vague list and do not use it)")
     ap.add_argument("--skip-cpu-baseline", action="store_true")
     ap.add_argument("--cpu-units", type=int, default=8)
     ap.add_argument("--calibrate-copy", action="store_true",
@@ -385,7 +386,7 @@ def run_workload(args):
             "traffic_note": off.get("traffic_note", "not measured for this workload"),
             "algorithmic_bytes_per_launch": bytes_launch,
             "algorithmic_bytes_note": "retained K,V + sketch K,V + Vague index list + scores read and written + q, out: "
-                                      "all of it moved by the two kernels inside the timed region",
+                                      "all of it moved by the call's kernels inside the timed region",
             "avg_launch_ms": avg_kern_s * 1e3,
             "launches_timed": len(kern_ms),
             "launch_sampling": f"HIP events on every {ev_every}. call of the timed region",

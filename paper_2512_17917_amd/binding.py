@@ -99,7 +99,9 @@ def event_elapsed_ms(a, b) -> float:
 
 class SideStream:
     """A second stream (default priority) and the fork / join events that a caller
-    lends to kvr_attend_decode so that its two main kernels can run side by side.
+    lends to kvr_attend_decode.  Used where retained slots and Vague list are separate
+    kernels (bf16, a sketch that only the general staged kernel holds) and the list
+    fills the chip twice over; other calls make one launch for both and leave it alone.
     Plumbing only.  One object serves any number of calls that are ordered on one
     stream."""
 

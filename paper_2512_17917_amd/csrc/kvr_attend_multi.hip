@@ -5,16 +5,16 @@
 // rebuilt cache; with n_q queries per sequence the rebuild is shared by all of
 // them, which is the point of batching them.
 //
-//   1. the dense kernel below runs over the retained slots,
-//   2. the Vague index list goes through the LDS-staged kernel of
-//      kvr_attend_multi_staged.hip when the sketch allows it (three rows, values
-//      signed only, a 64-channel chunk fits LDS); else the dense kernel runs again
-//      over the list: with three sketch rows it rebuilds each 16-token tile itself
-//      (sketch rows gathered from L2, median by selection; a rebuilt piece serves
-//      all columns and never reaches memory); otherwise
-//      kvr_reconstruct's kernel first writes the rebuilt tokens to workspace (one
-//      layer's worth) and the dense kernel reads them like retained rows,
-//   3. the merge kernel of kvr_attend_decode combines the slice partials, writes
+//   1. retained slots and Vague index list go through one launch of the LDS-staged
+//      kernel of kvr_attend_multi_staged.hip when the sketch allows it (three rows,
+//      values signed only, a 64-channel chunk fits LDS); else the dense kernel below
+//      runs over the retained slots and again over the list: with three sketch rows
+//      it rebuilds each 16-token tile itself (sketch rows gathered from L2, median
+//      by selection; a rebuilt piece serves all columns and never reaches memory);
+//      otherwise kvr_reconstruct's kernel first writes the rebuilt tokens to
+//      workspace (one layer's worth) and the dense kernel reads them like retained
+//      rows,
+//   2. the merge kernel of kvr_attend_decode combines the slice partials, writes
 //      `out` and adds the probabilities to the cumulative scores.
 //
 // The dense kernel is the retained-slot kernel of kvr_attend_decode with the

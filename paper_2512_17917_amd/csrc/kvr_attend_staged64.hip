@@ -165,10 +165,6 @@ __device__ __forceinline__ int opaque_s(int v) {
 // other).  Left alone, the older wave wins every arbitration, finishes a phase
 // far ahead of the younger one and idles at the barrier while the younger one
 // runs alone, with nobody to cover its latencies.
-// Both levels are above the default 0, at which the retained-slot kernel runs
-// when it shares the CU: its waves stream from HBM and need few issue slots, and
-// every slot they win from a wave of this kernel delays a whole workgroup at the
-// next barrier.
 __device__ __forceinline__ void take_turn(int t) {
   if (t & 1) __builtin_amdgcn_s_setprio(2);
   else __builtin_amdgcn_s_setprio(1);

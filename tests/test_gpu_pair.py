@@ -24,12 +24,12 @@ def kvr():
     (120, 1, 3, 341, 1000, 12800),   # two turns or more; slices of several items per workgroup
     (8, 4, 3, 333, 3000, 6000),      # few rounds, many workgroups; slices that end inside a tile
     (9, 4, 3, 6, 1, 64),             # the smallest list that is staged
-    (3, 1, 3, 6, 9300, 700),         # more slots than LDS holds logits of with four heads
+    (3, 1, 3, 6, 9300, 700),         # many slots and few units: short slices
     (1, 4, 3, 40, 9300, 3000),
     (200, 4, 3, 400, 100, 8704),     # 16 channels, three rows: 17 rounds
     (8, 2, 3, 1365, 2000, 3000),
     (200, 1, 4, 50, 100, 12288),     # four rows: 24 rounds
-    (32, 4, 4, 300, 150, 700),       # no CU left by the list: the slots first
+    (32, 4, 4, 300, 150, 700),       # lists of two rounds and a few slots each
     (9, 2, 4, 6, 1, 64),
 ])
 def test_rounds_and_slices(kvr, units, G, r, w, ret_cap, cap):
