@@ -90,7 +90,8 @@ struct ListChoice {
 //    (four heads, 512 units of 130 + 600 60.7 first, 64.1 own).
 //  * where the plan has workgroups walk six slices or more, on other CUs that the list can leave: 400 units of 1441 + 4325, four
 //    heads 201 on 56, 184 on 80, 512 units, one head 202 on 80, 174 on 128 (fewer slices each: 20 units of 7000 + 1400, one head
-//    25.5 us, by this estimate 34).
+//    25.5 us, by this estimate 34).  Beside the streaming kernel from three on: eight heads, 320 units of 3000 + 900 219 -> 154, 144 of
+//    11000 + 2800 307 -> 250; not with 16 columns, whose slices LDS keeps short (100 units of 11000 + 2800 219, by this 260).
 // Only for a gain of 5 % by this estimate (streaming kernel 10 %): within it the plans' own figures are the better ones.
 static RetChoice ret_ahead(RetChoice c, const ListChoice* lists, int n_lists, long long units, int ret_cap, int n_col, int waves,
                               int most, int own_slices) {
@@ -103,7 +104,7 @@ static RetChoice ret_ahead(RetChoice c, const ListChoice* lists, int n_lists, lo
   best *= waves == 8 ? 0.95 : 0.9;
   // the slots' time on n_wgs workgroups: as many slices as a number of turns holds
   int slices = 1;
-  const bool many = units * c.slices >= 6ll * c.n_wgs;
+  const bool many = units * c.slices >= (waves == 16 && n_col <= 8 ? 3ll : 6ll) * c.n_wgs;
   const auto slots = [&](int n, int n_wgs) {
     const int top = std::min(tiles, most - n);
     const long long first = (units * least + n_wgs - 1) / n_wgs;

@@ -25,6 +25,7 @@ def test_staged_list(kvr, units, G, r, w, ret_cap, cap, how):
     (246, 4, 4, 21, 585, 300),       # and 16
     (400, 1, 2, 1, 7, 220),          # a launch of their own, two columns
     (400, 4, 4, 1, 256, 220),        # 16, the longest slice
+    (144, 8, 1, 341, 11000, 2800),   # more CUs for the slots than the list's turns leave, slices near what LDS holds
 ])
 def test_streamed_list(kvr, units, G, n_q, w, ret_cap, cap):
     P.test_streamed_list(kvr, units, G, n_q, w, ret_cap, cap)

@@ -199,6 +199,8 @@ def test_parts_of_a_streamed_list_leave_the_slots_room(plan, units):
 
 
 def test_slots_of_many_units_have_more_cus(plan):
-    """Where workgroups would walk six slices or more (80 and 56 of them), more CUs are taken from the list."""
-    for case, least in (((512, 1, 3, 53, 1441, 4325), 128), ((400, 4, 3, 53, 1441, 4325), 80), ((400, 8, 3, 21, 585, 1755), 120)):
+    """Where workgroups would walk six slices or more (80 and 56 of them), beside the streaming kernel three, more CUs are taken
+    from the list."""
+    for case, least in (((512, 1, 3, 53, 1441, 4325), 128), ((400, 4, 3, 53, 1441, 4325), 80), ((400, 8, 3, 21, 585, 1755), 120),
+                        ((320, 8, 3, 111, 3000, 900), 160), ((144, 8, 3, 341, 11000, 2800), 160)):
         assert plan(case)[0][7] >= least, case
